@@ -253,6 +253,22 @@ __device__ __forceinline__ void wave_write_meta(const WavePlan& wp, const int32_
     }
 }
 
+// The share of a row's n partial results that one of the kWaves waves of a merge workgroup sums.  With few
+// of them (`alone`) the first wave takes all: a second round trip costs less than meeting in LDS.
+struct MergeShare {
+    int first, end;
+    bool alone;
+};
+template <int kWaves>
+__device__ __forceinline__ MergeShare merge_share(int n, int wave) {
+    MergeShare s;
+    s.alone = kWaves == 1 || n <= kMergeAlone;
+    const int per = s.alone ? n : (n + kWaves - 1) / kWaves;
+    s.first = s.alone ? 0 : wave * per;
+    s.end = s.first + per < n ? s.first + per : n;
+    return s;
+}
+
 }  // namespace
 }  // namespace xattn
 #endif

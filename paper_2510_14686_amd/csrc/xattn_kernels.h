@@ -57,6 +57,12 @@ int rows_per_tile(int rows_total, int path);
 // holds three events, recorded before the decode kernel, between the kernels and after the merge.
 hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t* events);
 
+// Waves per output row of the merge kernels: as many as keep the launch within what the chip holds at once
+// (256 compute units of 32 waves).  Few rows mean few sequences, whose keys may be split into hundreds of
+// slots; rows of up to kMergeAlone slots are summed by their first wave alone whatever this says.
+constexpr int kMergeAlone = 8;
+inline int merge_waves(long rows) { return rows <= 512 ? 16 : rows <= 2048 ? 4 : 1; }
+
 // Latent-KV (MLA-shaped) decode: every head reads the same cached row of 576 bf16 per token.
 struct MlaParams {
     const uint16_t* q;               // bf16 [batch, q_len, n_heads, 576]

@@ -590,19 +590,26 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
 // ---------------------------------------------------------------------------------- merge kernel
 // Aggregation of the partial results of split sequences (section 4.4.3, "Layer 2"):
 //   M = max_s m_s;  l = sum_s l_s 2^(m_s - M);  out = sum_s o_s 2^(m_s - M) / l;  lse = (M + log2 l) ln 2
-// One wave per output row (b, t, h); lane holds columns 2*lane, 2*lane+1.  Sequences with a single
+// kWaves waves per output row (b, t, h); lane holds columns 2*lane, 2*lane+1.  Sequences with a single
 // segment were finished by the decode kernel and are skipped; sequences without keys get out = 0 and
 // lse = -inf here.  All loads of a round are issued before any is used.
-__global__ __launch_bounds__(256) void merge_kernel(DecodeParams prm) {
+// Bound by its dependent round trips (table, records and partial rows, every further 8 partial rows), not by
+// bytes: one wave per row took 21.4 us for one sequence of 30001 tokens (32 rows of 256 slots); sixteen
+// waves that each sum a share of the slots and meet once in LDS take 5.2 us.
+template <int kWaves>
+__global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(DecodeParams prm) {
     const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
     const long stride_rows = (long)prm.q_len * prm.n_q_heads;
-    const long row = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const long row = kWaves == 1 ? (long)blockIdx.x * 4 + wave : (long)blockIdx.x;
     if (row >= (long)prm.batch * stride_rows) return;
     const int b = (int)(row / stride_rows);
     const int th = (int)(row - (long)b * stride_rows);
     const int2 fs = reinterpret_cast<const int2*>(prm.meta)[b];
     const int n = fs.y;
     if (n == 1) return;
+    const MergeShare sh = merge_share<kWaves>(n, wave);
+    if (sh.alone && kWaves > 1 && wave > 0) return;       // few slots: the first wave does the row
     uint32_t* outp = reinterpret_cast<uint32_t*>(prm.out + row * kHeadDim) + lane;
     if (n == 0) {
         *outp = 0u;
@@ -611,33 +618,56 @@ __global__ __launch_bounds__(256) void merge_kernel(DecodeParams prm) {
     }
     const float2* ml = reinterpret_cast<const float2*>(prm.part_ml) + (long)fs.x * stride_rows + th;
     const float2* po = reinterpret_cast<const float2*>(prm.part_o + ((long)fs.x * stride_rows + th) * kHeadDim) + lane;
-    // Lane s holds (m_s, l_s) of slot s of the current group of 64 slots; the first 8 slots' partial
+    // Lane i holds (m, l) of slot first + i of the current group of 64 slots; the first 8 slots' partial
     // rows are requested in the same breath, so a typical row (up to 8 segments) costs one round trip.
-    float2 mine = make_float2(kNegInf, 0.0f);
-    if (lane < n) mine = ml[lane * stride_rows];
-    float2 o[8];
+    float M = kNegInf, l = 0.0f, o0 = 0.0f, o1 = 0.0f;
+    if (sh.first < sh.end) {
+        float2 mine = make_float2(kNegInf, 0.0f);
+        if (sh.first + lane < sh.end) mine = ml[(sh.first + lane) * stride_rows];
+        float2 o[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) o[u] = po[(u < n ? u : n - 1) * stride_rows * (kHeadDim / 2)];
-    float M = mine.x;
-    for (int base = 64; base < n; base += 64)
-        if (base + lane < n) M = fmaxf(M, ml[(base + lane) * stride_rows].x);
+        for (int u = 0; u < 8; ++u) o[u] = po[(sh.first + u < sh.end ? sh.first + u : sh.end - 1) * stride_rows * (kHeadDim / 2)];
+        M = mine.x;
+        for (int base = sh.first + 64; base < sh.end; base += 64)
+            if (base + lane < sh.end) M = fmaxf(M, ml[(base + lane) * stride_rows].x);
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
-    const float m_use = (M == kNegInf) ? 0.0f : M;
-    float l = 0.0f, o0 = 0.0f, o1 = 0.0f;
-    for (int s0 = 0; s0 < n; s0 += 8) {
-        if (s0 > 0) {
-            if ((s0 & 63) == 0) mine = (s0 + lane < n) ? ml[(s0 + lane) * stride_rows] : make_float2(kNegInf, 0.0f);
+        for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+        const float m_use = (M == kNegInf) ? 0.0f : M;
+        for (int i0 = 0; sh.first + i0 < sh.end; i0 += 8) {
+            const int s0 = sh.first + i0;
+            if (i0 > 0) {
+                if ((i0 & 63) == 0) mine = (s0 + lane < sh.end) ? ml[(s0 + lane) * stride_rows] : make_float2(kNegInf, 0.0f);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) o[u] = po[(s0 + u < n ? s0 + u : n - 1) * stride_rows * (kHeadDim / 2)];
+                for (int u = 0; u < 8; ++u) o[u] = po[(s0 + u < sh.end ? s0 + u : sh.end - 1) * stride_rows * (kHeadDim / 2)];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float m_s = __shfl(mine.x, (i0 + u) & 63, 64), l_s = __shfl(mine.y, (i0 + u) & 63, 64);
+                const float w = s0 + u < sh.end ? fast_exp2(m_s - m_use) : 0.0f;      // past the end: weight 0
+                l = __builtin_fmaf(l_s, w, l);
+                o0 = __builtin_fmaf(o[u].x, w, o0);
+                o1 = __builtin_fmaf(o[u].y, w, o1);
+            }
         }
+    }
+    if constexpr (kWaves > 1) {
+        if (!sh.alone) {                                  // the waves' sums, each against its own maximum, meet in LDS
+            __shared__ float2 part[kWaves][64], part_ml[kWaves];
+            part[wave][lane] = make_float2(o0, o1);
+            if (lane == 0) part_ml[wave] = make_float2(M, l);
+            __syncthreads();
+            if (wave > 0) return;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float m_s = __shfl(mine.x, (s0 + u) & 63, 64), l_s = __shfl(mine.y, (s0 + u) & 63, 64);
-            const float w = s0 + u < n ? fast_exp2(m_s - m_use) : 0.0f;      // past the end: weight 0
-            l = __builtin_fmaf(l_s, w, l);
-            o0 = __builtin_fmaf(o[u].x, w, o0);
-            o1 = __builtin_fmaf(o[u].y, w, o1);
+            for (int w = 1; w < kWaves; ++w) M = fmaxf(M, part_ml[w].x);
+            const float m_use = (M == kNegInf) ? 0.0f : M;
+            l = o0 = o1 = 0.0f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const float f = fast_exp2(part_ml[w].x - m_use);
+                l = __builtin_fmaf(part_ml[w].y, f, l);
+                o0 = __builtin_fmaf(part[w][lane].x, f, o0);
+                o1 = __builtin_fmaf(part[w][lane].y, f, o1);
+            }
         }
     }
     const float inv = l > 0.0f ? 1.0f / l : 0.0f;
@@ -721,7 +751,11 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
     if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[1], stream)) != hipSuccess) return e;
     const long rows = (long)prm.batch * prm.q_len * prm.n_q_heads;
-    hipLaunchKernelGGL(merge_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, prm);
+    switch (merge_waves(rows)) {
+        case 16: hipLaunchKernelGGL(merge_kernel<16>, dim3((unsigned)rows), dim3(1024), 0, stream, prm); break;
+        case 4: hipLaunchKernelGGL(merge_kernel<4>, dim3((unsigned)rows), dim3(256), 0, stream, prm); break;
+        default: hipLaunchKernelGGL(merge_kernel<1>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, prm); break;
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[2], stream)) != hipSuccess) return e;
     return hipSuccess;

@@ -938,18 +938,22 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     }
 }
 
-// One wave per output row of 512 columns; lane holds columns 8*lane .. 8*lane+7.  A partial row is 512
+// kWaves waves per output row of 512 columns; lane holds columns 8*lane .. 8*lane+7.  A partial row is 512
 // fp16 values times its own scale (the fourth value of its (m, l, lq, 1 / scale) record).
-__global__ __launch_bounds__(256) void mla_merge_kernel(MlaParams prm) {
+template <int kWaves>
+__global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_kernel(MlaParams prm) {
     const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
     const long rows_total = (long)prm.q_len * prm.n_heads;
-    const long row = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const long row = kWaves == 1 ? (long)blockIdx.x * 4 + wave : (long)blockIdx.x;
     if (row >= (long)prm.batch * rows_total) return;
     const int b = (int)(row / rows_total);
     const long th = row - (long)b * rows_total;
     const int2 fs = reinterpret_cast<const int2*>(prm.meta)[b];
     const int n = fs.y;
     if (n == 1) return;
+    const MergeShare sh = merge_share<kWaves>(n, wave);
+    if (sh.alone && kWaves > 1 && wave > 0) return;       // few slots: the first wave does the row
     uint4* outp = reinterpret_cast<uint4*>(prm.out + row * kDv) + lane;
     if (n == 0) {
         *outp = make_uint4(0u, 0u, 0u, 0u);
@@ -960,26 +964,26 @@ __global__ __launch_bounds__(256) void mla_merge_kernel(MlaParams prm) {
     const uint4* po = reinterpret_cast<const uint4*>(prm.part_o + ((long)fs.x * rows_total + th) * kDv) + lane;
     const long po_stride = rows_total * (kDv / 8);
     float M = kNegInf;
-    for (int base = 0; base < n; base += 64)
-        if (base + lane < n) M = fmaxf(M, ml[(base + lane) * rows_total].x);
+    for (int base = sh.first; base < sh.end; base += 64)
+        if (base + lane < sh.end) M = fmaxf(M, ml[(base + lane) * rows_total].x);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
     const float m_use = (M == kNegInf) ? 0.0f : M;
     float l = 0.0f, lq = 0.0f;
     float acc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    for (int s0 = 0; s0 < n; s0 += 4) {
+    for (int s0 = sh.first; s0 < sh.end; s0 += 4) {
         float4 a[4];
         uint4 o[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int s = s0 + u < n ? s0 + u : n - 1;
+            const int s = s0 + u < sh.end ? s0 + u : sh.end - 1;
             a[u] = ml[s * rows_total];
             const u32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(&po[s * po_stride]));   // read once
             o[u] = make_uint4(t.x, t.y, t.z, t.w);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const float w = s0 + u < n ? fast_exp2(a[u].x - m_use) : 0.0f;
+            const float w = s0 + u < sh.end ? fast_exp2(a[u].x - m_use) : 0.0f;
             l = __builtin_fmaf(a[u].y, w, l);
             lq = __builtin_fmaf(a[u].z, w, lq);
             const float ws = w * a[u].w;             // weight times the inverse of the row's scale
@@ -989,6 +993,31 @@ __global__ __launch_bounds__(256) void mla_merge_kernel(MlaParams prm) {
                 const f32x2_t v = __builtin_convertvector(__builtin_bit_cast(f16x2_t, q[c]), f32x2_t);
                 acc[2 * c] = __builtin_fmaf(v[0], ws, acc[2 * c]);
                 acc[2 * c + 1] = __builtin_fmaf(v[1], ws, acc[2 * c + 1]);
+            }
+        }
+    }
+    if constexpr (kWaves > 1) {
+        if (!sh.alone) {                                  // the waves' sums, each against its own maximum, meet in LDS
+            __shared__ f32x4_t part[kWaves][2][64];
+            __shared__ f32x4_t part_ml[kWaves];
+            part[wave][0][lane] = f32x4_t{acc[0], acc[1], acc[2], acc[3]};
+            part[wave][1][lane] = f32x4_t{acc[4], acc[5], acc[6], acc[7]};
+            if (lane == 0) part_ml[wave] = f32x4_t{M, l, lq, 0.0f};
+            __syncthreads();
+            if (wave > 0) return;
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) M = fmaxf(M, part_ml[w][0]);
+            const float m_all = (M == kNegInf) ? 0.0f : M;
+            l = lq = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[c] = 0.0f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const float f = fast_exp2(part_ml[w][0] - m_all);
+                l = __builtin_fmaf(part_ml[w][1], f, l);
+                lq = __builtin_fmaf(part_ml[w][2], f, lq);
+#pragma unroll
+                for (int c = 0; c < 8; ++c) acc[c] = __builtin_fmaf(part[w][c >> 2][lane][c & 3], f, acc[c]);
             }
         }
     }
@@ -1037,7 +1066,11 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[1], stream)) != hipSuccess) return e;
     const long rows = (long)prm.batch * rows_total;
-    hipLaunchKernelGGL(mla_merge_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, prm);
+    switch (merge_waves(rows)) {
+        case 16: hipLaunchKernelGGL(mla_merge_kernel<16>, dim3((unsigned)rows), dim3(1024), 0, stream, prm); break;
+        case 4: hipLaunchKernelGGL(mla_merge_kernel<4>, dim3((unsigned)rows), dim3(256), 0, stream, prm); break;
+        default: hipLaunchKernelGGL(mla_merge_kernel<1>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, prm); break;
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[2], stream)) != hipSuccess) return e;
     return hipSuccess;
