@@ -159,10 +159,12 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
 /*
  * Tuning knobs of the partition (section 4.4.3 Layer 3), for sweeps and for tests that show the
  * result does not depend on the partition.  key:
- *   XATTN_CFG_PIECES            number of equal-token pieces the batch's keys are cut into
- *                               (= workgroups launched); 0 = automatic (the CU count; xattn_mla_decode,
- *                               where a piece is worked on by one workgroup per 128 query rows of a
- *                               sequence: the CU count divided by that number)
+ *   XATTN_CFG_PIECES            number of equal-token pieces the batch's keys are cut into;
+ *                               0 = automatic: the CU count; divided by the number of workgroups that
+ *                               work on a piece (xattn_decode: one per 32 query rows of a KV head;
+ *                               xattn_mla_decode: one per 128 query rows of a sequence); and, with fewer
+ *                               than 8 KV heads, times 8 / n_kv_heads (a workgroup then holds that many
+ *                               pieces) as far as the partial results fit XATTN_NOALLOC_SCRATCH_BYTES
  *   XATTN_CFG_MIN_PIECE_TOKENS  lower bound on a piece's tokens; 0 = default (64); values below 16
  *                               count as 16
  *   XATTN_CFG_TIMING            1 = record per-kernel events (see xattn_timing_read); 0 = off

@@ -57,11 +57,38 @@ int g_timed_calls = 0;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-int pieces_for(int n_cu) { return g_cfg_pieces > 0 ? g_cfg_pieces : n_cu; }
-
 struct WorkspaceLayout {
     size_t meta_off, ml_off, o_off, total;
 };
+WorkspaceLayout layout_for(int batch, int q_len, int n_q_heads, int n_pieces);
+
+// How a GQA call's keys are cut: the number of pieces, and how many of them a workgroup holds.
+struct DecodeSplit {
+    int pieces, parts;
+    size_t bytes;         // of workspace: for one piece per compute unit at least
+};
+// One workgroup per compute unit.  A wave streams one KV head, so with fewer than eight KV heads a
+// workgroup takes several pieces to keep eight waves' loads in flight (two KV heads, 138468 tokens: 46.6 us
+// with one piece per workgroup, 32.5 us with four), as long as the partial results stay within the fixed scratch array, which also bounds what the merge
+// has to read back.  Several workgroups share a piece when a wave cannot hold all query rows of its KV
+// head: fewer pieces then, as in mla_pieces_for.
+DecodeSplit decode_split(int n_cu, int batch, int q_len, int n_q_heads, int n_kv_heads) {
+    const int rows = n_q_heads / n_kv_heads * q_len;
+    auto bytes_for = [&](int pieces) { return layout_for(batch, q_len, n_q_heads, pieces).total; };
+    DecodeSplit s{g_cfg_pieces > 0 ? g_cfg_pieces : n_cu, 1, bytes_for(g_cfg_pieces > 0 ? g_cfg_pieces : n_cu)};
+    const int per_wave = rows_per_wave(rows, g_cfg_path), groups = (rows + per_wave - 1) / per_wave;
+    if (g_cfg_pieces == 0 && groups > 1) s.pieces = n_cu / groups / 8 * 8 < 8 ? 8 : n_cu / groups / 8 * 8;
+    const int most = n_kv_heads < kMaxWavesPerBlock ? kMaxWavesPerBlock / n_kv_heads : 1;
+    if (g_cfg_pieces > 0) {
+        s.parts = most;
+        return s;
+    }
+    for (int parts = most; parts > 1; --parts) {
+        const size_t bytes = bytes_for(s.pieces * parts);
+        if (bytes <= XATTN_NOALLOC_SCRATCH_BYTES) return DecodeSplit{s.pieces * parts, parts, bytes > s.bytes ? bytes : s.bytes};
+    }
+    return s;
+}
 
 // Pieces of a latent-KV call: as many as give one workgroup per compute unit when a piece is worked
 // on by several workgroups (one per group of query rows; they sit side by side on one XCD and share
@@ -219,12 +246,19 @@ int decode_call(const char* who, FixedWorkspaceFn fixed_workspace, const void* q
     st = device_state(&d, &dev);
     if (st != XATTN_OK) return st;
 
-    const int n_pieces = pieces_for(d->n_cu);
-    const WorkspaceLayout w = layout_for(batch, q_len, n_q_heads, n_pieces);
+    DecodeSplit split = decode_split(d->n_cu, batch, q_len, n_q_heads, n_kv_heads);
     char* ws = nullptr;
-    st = fixed_workspace ? fixed_workspace(who, dev, w.total, &ws)
-                         : acquire_workspace(d, w.total, static_cast<hipStream_t>(stream), who, &ws);
+    auto acquire = [&] {
+        return fixed_workspace ? fixed_workspace(who, dev, split.bytes, &ws)
+                               : acquire_workspace(d, split.bytes, static_cast<hipStream_t>(stream), who, &ws);
+    };
+    st = acquire();
+    if (st != XATTN_OK && g_cfg_pieces == 0 && split.parts > 1) {      // a workspace for one piece per compute unit will do
+        split = {split.pieces / split.parts, 1, layout_for(batch, q_len, n_q_heads, d->n_cu).total};
+        st = acquire();
+    }
     if (st != XATTN_OK) return st;
+    const WorkspaceLayout w = layout_for(batch, q_len, n_q_heads, split.pieces);
 
     DecodeParams prm;
     prm.q = static_cast<const uint16_t*>(q);
@@ -236,13 +270,15 @@ int decode_call(const char* who, FixedWorkspaceFn fixed_workspace, const void* q
     prm.n_q_heads = n_q_heads;
     prm.n_kv_heads = n_kv_heads;
     prm.group = n_q_heads / n_kv_heads;
+    prm.inv_group = 1.0f / (float)prm.group;
     prm.scale_log2 = (float)((double)scale * 1.4426950408889634074);
     prm.out = static_cast<uint16_t*>(out);
     prm.lse = lse;
     prm.meta = reinterpret_cast<int32_t*>(ws + w.meta_off);
     prm.part_ml = reinterpret_cast<float*>(ws + w.ml_off);
     prm.part_o = reinterpret_cast<float*>(ws + w.o_off);
-    prm.n_pieces = n_pieces;
+    prm.n_pieces = split.pieces;
+    prm.parts = split.parts;
     prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : kDefaultMinPieceTokens;
     if (prm.min_piece_tokens < 16) prm.min_piece_tokens = 16;      // one 16-key block at least
     prm.xcd_skew = g_cfg_xcd_skew > 0 ? g_cfg_xcd_skew - 1 : kDefaultXcdSkewGqa;
@@ -296,10 +332,9 @@ int xattn_configure(int key, int value) {
 size_t xattn_workspace_bytes(int batch, int q_len, int n_q_heads, int n_kv_heads, int head_dim) {
     if (check_shape(batch, q_len, n_q_heads, n_kv_heads, head_dim) != XATTN_OK) return 0;
     // Upper bound over the automatic piece count of any supported device and the configured one.
-    int pieces = g_cfg_pieces > 0 ? g_cfg_pieces : 256;
     DeviceState* d = nullptr;
-    if (g_cfg_pieces == 0 && device_state(&d, nullptr) == XATTN_OK) pieces = pieces_for(d->n_cu);
-    return layout_for(batch, q_len, n_q_heads, pieces).total;
+    const int n_cu = g_cfg_pieces == 0 && device_state(&d, nullptr) == XATTN_OK ? d->n_cu : 256;
+    return decode_split(n_cu, batch, q_len, n_q_heads, n_kv_heads).bytes;
 }
 
 size_t xattn_mla_workspace_bytes(int batch, int q_len, int n_heads, int d_latent, int d_rope) {

@@ -15,10 +15,11 @@ namespace {
 constexpr int kU = 4;                 // key rows per 16-lane group per block
 constexpr int kBlockKeys = 4 * kU;    // key rows per wave per block
 constexpr int kRowBytes = kHeadDim * 2;
-// Wave-private LDS of the matrix path: a 16-key K block (4 KiB) during the key loop, a 16-row fp32
+// Wave-private LDS of the matrix path: a 16-key K block (4.5 KiB) during the key loop, a 16-row fp32
 // output tile with padded rows (16 x 528 bytes) when a segment is stored.
 constexpr int kLdsPerWave = 16 * (kHeadDim * 4 + 16);
 constexpr float kNegInf = -__builtin_inff();
+constexpr float kLazyLog2 = 8.0f;                // slack of the softmax reference maximum, in powers of two
 constexpr float kLn2 = 0.6931471805599453f;
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
@@ -30,6 +31,11 @@ typedef __attribute__((ext_vector_type(2))) float f32x2_t;
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 
 // ---------------------------------------------------------------------------------- lane helpers
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ const void* uniform(const void* ptr) {
+    const uint64_t a = (uint64_t)(uintptr_t)ptr;
+    return reinterpret_cast<const void*>((uintptr_t)((uint32_t)uniform((int)(uint32_t)a) | ((uint64_t)(uint32_t)uniform((int)(uint32_t)(a >> 32)) << 32)));
+}
 template <int kCtrl>
 __device__ __forceinline__ float dpp_f(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xf, 0xf, true));
@@ -61,16 +67,48 @@ __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
 }
 __device__ __forceinline__ float bf16_lo(uint32_t x) { return __uint_as_float(x << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t x) { return __uint_as_float(x & 0xffff0000u); }
-// fp32 -> bf16 bits, round to nearest even (finite inputs and infinities; NaN keeps a quiet NaN).
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+// Two values rounded to bf16 (nearest even) and packed: the conversion instruction.
+__device__ __forceinline__ uint32_t cvt_bf16(float a, float b) {
+    const f32x2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-    return f32_to_bf16_bits(lo) | (f32_to_bf16_bits(hi) << 16);
-}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// max / sum over the four lanes (kb = 0..3) that hold the same row: lane-swap instructions, no LDS.
+// The swap exchanges, between its two register operands, lane group 1 (3) of the first with lane
+// group 0 (2) of the second (16-lane form), or the upper half of the first with the lower half of
+// the second (32-lane form): called on (x, x), the two results together hold both partners' values.
+// (The results are copied to scalars before the bit cast: a bit cast applied directly to an element
+// of the result vector read element 0 for both.)
+__device__ __forceinline__ void swap16(float x, float& r0, float& r1) {
+    const uint32_t a = __builtin_bit_cast(uint32_t, x);
+    const u32x2_t t = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const uint32_t t0 = t.x, t1 = t.y;
+    r0 = __builtin_bit_cast(float, t0);
+    r1 = __builtin_bit_cast(float, t1);
+}
+__device__ __forceinline__ void swap32(float x, float& r0, float& r1) {
+    const uint32_t a = __builtin_bit_cast(uint32_t, x);
+    const u32x2_t t = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    const uint32_t t0 = t.x, t1 = t.y;
+    r0 = __builtin_bit_cast(float, t0);
+    r1 = __builtin_bit_cast(float, t1);
+}
+__device__ __forceinline__ float kb_max(float x) {
+    float a, b;
+    swap16(x, a, b);
+    x = fmaxf(a, b);
+    swap32(x, a, b);
+    return fmaxf(a, b);
+}
+__device__ __forceinline__ float kb_sum(float x) {
+    float a, b;
+    swap16(x, a, b);
+    x = a + b;
+    swap32(x, a, b);
+    return a + b;
+}
 
 // Raw buffer descriptor over [base, base + bytes): loads past the end return 0.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {

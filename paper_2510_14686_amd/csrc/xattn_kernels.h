@@ -25,6 +25,7 @@ struct DecodeParams {
     const void* const* v_ptrs;
     const int32_t* kv_lens;          // device int32[batch]
     int batch, q_len, n_q_heads, n_kv_heads, group;
+    float inv_group;                 // 1 / group
     float scale_log2;                // scale * log2(e)
     uint16_t* out;                   // bf16 [batch, q_len, n_q_heads, 128]
     float* lse;                      // fp32 [batch, q_len, n_q_heads] or null
@@ -32,6 +33,7 @@ struct DecodeParams {
     float* part_ml;                  // fp32 [slots, q_len * n_q_heads, 2]  (max, sum)
     int32_t* meta;                   // int32 [batch, 2]
     int n_pieces;                    // pieces the token stream is cut into (upper bound on active ones)
+    int parts;                       // pieces per workgroup: waves per workgroup / KV heads per workgroup
     int min_piece_tokens;
     int xcd_skew;                    // per mille: share taken from the odd XCDs' parts of the stream and given to the even ones
     int path;                        // kPathAuto, kPathVector or kPathMatrix
@@ -50,8 +52,9 @@ constexpr int kPathMatrix = 2;
 
 bool use_matrix_path(int rows_total, int path);
 
-// Query rows one workgroup pass handles for a KV head with rows_total = group * q_len rows.
-int rows_per_tile(int rows_total, int path);
+// Query rows one wave handles for a KV head with rows_total = group * q_len rows; more rows than that
+// make row groups, workgroups that read the same pieces.
+int rows_per_wave(int rows_total, int path);
 
 // Enqueues the split-KV decode kernel and the merge kernel on `stream`.  If `events` is not null it
 // holds three events, recorded before the decode kernel, between the kernels and after the merge.

@@ -2,10 +2,10 @@
 //
 // Work decomposition (paper section 4.4.3, "Layer 3": balance compute units by token count, split
 // long sequences, let short ones share a unit).  The keys of the whole batch form one stream of
-// N = sum_b kv_lens[b] tokens, cut into P pieces of N / P tokens (to within one 16-key block);
-// workgroup p owns one piece of that stream, whatever sequences it falls in.  Inside a workgroup wave w owns
-// KV head w, so a workgroup streams one contiguous byte range of K and one of V (no block table:
-// section 4.3, "Operator Adaptation").  Each (piece, sequence) intersection is a segment.  A segment
+// N = sum_b kv_lens[b] tokens, cut into P pieces of N / P tokens (to within one 16-key block); a workgroup
+// owns one piece of that stream, whatever sequences it falls in (several with fewer than 8 KV heads).  Inside
+// a workgroup wave w owns KV head w, so a workgroup streams one contiguous byte range of K and one of V (no
+// block table: section 4.3, "Operator Adaptation").  Each (piece, sequence) intersection is a segment.  A segment
 // that covers its whole sequence writes the final result; any other writes an un-normalised partial
 // (o, m, l) to slot piece + sequence_index, and the merge kernel combines a sequence's slots (the
 // aggregation step of section 4.4.3, "Layer 2").  Combining inside the decode kernel by the last wave
@@ -20,7 +20,9 @@
 // registers.  Two inner loops:
 //   * vector path (up to 8 rows): q.k by bf16 dot2 into fp32, reduced over the 16 lanes with DPP;
 //     online softmax in fp32 (log2 domain); p.v by fp32 FMA.
-//   * matrix path (tiles of 16 rows, the multi-token verification case): the K block is transposed
+//   * matrix path (one or two tiles of 16 rows per wave; beyond 32 rows several workgroups share a piece.
+//     verify, 32 rows per KV head, 165109 tokens: one tile per wave, every piece read twice, 238.6 us; two
+//     tiles 145.4 us, of which about 30 are fixed: 38 MB of partial results): the K block is transposed
 //     through wave-private LDS into the MFMA operand layout, S^T = K Q^T by bf16 MFMA 16x16x32;
 //     softmax on the accumulator layout (a lane holds 4 keys of one row); O^T += V^T P^T by bf16 MFMA
 //     16x16x16 straight from the V registers (V never touches LDS), with p fed as hi + lo bf16 parts
@@ -223,10 +225,10 @@ __device__ __forceinline__ void vector_segment(const DecodeParams& prm, const Se
             const long orow = row_index(r);
             const float inv = st.l[r] > 0.0f ? 1.0f / st.l[r] : 0.0f;
             uint4 w;
-            w.x = pack_bf16(st.o[r][0] * inv, st.o[r][1] * inv);
-            w.y = pack_bf16(st.o[r][2] * inv, st.o[r][3] * inv);
-            w.z = pack_bf16(st.o[r][4] * inv, st.o[r][5] * inv);
-            w.w = pack_bf16(st.o[r][6] * inv, st.o[r][7] * inv);
+            w.x = cvt_bf16(st.o[r][0] * inv, st.o[r][1] * inv);
+            w.y = cvt_bf16(st.o[r][2] * inv, st.o[r][3] * inv);
+            w.z = cvt_bf16(st.o[r][4] * inv, st.o[r][5] * inv);
+            w.w = cvt_bf16(st.o[r][6] * inv, st.o[r][7] * inv);
             *reinterpret_cast<uint4*>(prm.out + orow * kHeadDim + ds * 8) = w;
             if (prm.lse && ds == 0)
                 prm.lse[orow] = st.l[r] > 0.0f ? (st.m[r] + __log2f(st.l[r])) * kLn2 : kNegInf;
@@ -243,79 +245,117 @@ __device__ __forceinline__ void vector_segment(const DecodeParams& prm, const Se
 
 // ---------------------------------------------------------------------------------- matrix path
 // Lane (kb, n) = (lane / 16, lane % 16).  Loads: lane holds 16 bytes (chunk n of 16) of key rows
-// 4*kb + i, i = 0..3, of the 16-key block.  MFMA index maps (any consistent map of the 128 columns
-// to the contraction index, and of output columns to physical columns, is allowed):
+// 4*i + kb, i = 0..3, of the 16-key block, so that a load instruction reads four consecutive 256-byte rows.
+// Below, "key 4*kb + i" of a block is the one that lane group kb holds in register i.  (K loaded as the MFMA
+// takes it, 64 bytes of each of 16 rows per instruction, needs no LDS and costs 5 to 8 % of the large calls.)  MFMA index maps (any consistent map of the 128 columns to the contraction index, and
+// of output columns to physical columns, is allowed):
 //   S^T[key][row] = sum_c K[key][c] Q[row][c]: 16x16x32 step s, lane (kb, x) contracts chunk 4*s + kb
 //   O^T_e[x][row] += V[key][8*x + e] P[row][key]: 16x16x4 call (i, e) contracts keys 4*kb + i
+// Pitch of a K row in LDS: 2 * odd chunks modulo 16, conflict-free for writes of whole rows and for the
+// operand reads, and every access is one address plus a constant.
+constexpr int kKPitch = kRowBytes + 32;
 struct KvRegs {
     u32x4_t k[4];
     u32x4_t v[4];
 };
 
-__device__ __forceinline__ void load_regs(KvRegs& r, __amdgpu_buffer_rsrc_t rk, __amdgpu_buffer_rsrc_t rv,
-                                          uint32_t voffset, uint32_t row_stride, int j_block) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t so = (uint32_t)(j_block + i) * row_stride;
-        r.k[i] = load_b128_nt(rk, voffset, so);
-        r.v[i] = load_b128_nt(rv, voffset, so);
+// The loads of the next block, issued two at a time at four points of the block in hand: eight at once
+// ahead of the block cost 2 % of the large calls (long_context 260.8 us all at once, 257.2 us K first and V
+// behind the scores, 255.5 us in four pairs).
+struct NextLoad {
+    KvRegs& r;
+    __amdgpu_buffer_rsrc_t rk, rv;
+    uint32_t voffset, row_stride;
+    int j_block;
+    bool on;
+    __device__ __forceinline__ void k(int i) const { r.k[i] = load_b128_nt(rk, voffset, (uint32_t)(j_block + 4 * i) * row_stride); }
+    __device__ __forceinline__ void v(int i) const { r.v[i] = load_b128_nt(rv, voffset, (uint32_t)(j_block + 4 * i) * row_stride); }
+    template <int kPoint>
+    __device__ __forceinline__ void at() const {
+        if (!on) return;
+        if constexpr (kPoint < 2) {
+            k(2 * kPoint);
+            k(2 * kPoint + 1);
+        } else {
+            v(2 * kPoint - 4);
+            v(2 * kPoint - 3);
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
-}
+    __device__ __forceinline__ void all() const {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) k(i);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v(i);
+    }
+};
+struct NoLoad {
+    template <int kPoint>
+    __device__ __forceinline__ void at() const {}
+};
 
 struct MatrixState {
     f32x4_t o[8];     // O^T tiles: o[e][j] = column 8*(4*kb + j) + e of row n
     float m, l;       // row n: running max (all kb groups agree), this lane's share of the running sum
 };
 
-template <int kPv>
-__device__ __forceinline__ void matrix_block(MatrixState& st, const KvRegs& r, const bf16x8_t (&qop)[4],
-                                             char* lds_wave, float scale_log2, int j_block, int lim, int kb,
-                                             int n) {
-    // K block -> LDS as [key][chunk ^ (key & 7)] (16-byte chunks), then back as the MFMA A operand.
+// One 16-key block against kTiles tiles of 16 rows: every K register and every V operand permuted from
+// registers feeds the MFMAs of all tiles.
+template <int kPv, int kTiles, typename Next>
+__device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const KvRegs& r, const bf16x8_t (&qop)[kTiles][4],
+                                             char* lds_wave, float scale_log2, int j_block, const int (&lim)[kTiles], int kb,
+                                             int n, Next next) {
+    next.template at<0>();
+    // K block -> wave-private LDS, then back as the MFMA A operand.
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int key = 4 * kb + i;
-        *reinterpret_cast<u32x4_t*>(lds_wave + key * kRowBytes + ((n ^ (key & 7)) << 4)) = r.k[i];
-    }
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4_t*>(lds_wave + (4 * kb + i) * kKPitch + n * 16) = r.k[i];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    f32x4_t s = {0.0f, 0.0f, 0.0f, 0.0f};
+    next.template at<1>();
+    f32x4_t s[kTiles];
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) s[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int step = 0; step < 4; ++step) {
-        const int c = 4 * step + kb;
-        const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(lds_wave + n * kRowBytes + ((c ^ (n & 7)) << 4));
-        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qop[step], s, 0, 0, 0);
+        const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(lds_wave + n * kKPitch + (4 * step + kb) * 16);
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qop[t][step], s[t], 0, 0, 0);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-    // s[i] = score of key j_block + 4*kb + i for row n
-    float p[4];
-    float mx = kNegInf;
+    next.template at<2>();
+    // s[t][i] = score of key j_block + 4*kb + i for row n of tile t
+    float p[kTiles][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        p[i] = (j_block + 4 * kb + i < lim) ? s[i] * scale_log2 : kNegInf;
-        mx = fmaxf(mx, p[i]);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(st.m, mx);
-    const float m_use = (m_new == kNegInf) ? 0.0f : m_new;
-    const float alpha = fast_exp2(st.m - m_use);
-    float sum = 0.0f;
+    for (int t = 0; t < kTiles; ++t) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        p[i] = fast_exp2(p[i] - m_use);
-        sum += p[i];
-    }
-    st.l = st.l * alpha + sum;
-    st.m = m_new;
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+        for (int i = 0; i < 4; ++i) p[t][i] = s[t][i] * scale_log2;
+        if (__builtin_amdgcn_ballot_w64(j_block + kBlockKeys > lim[t]) != 0) {      // only blocks that reach a limit
 #pragma unroll
-        for (int e = 0; e < 8; ++e) st.o[e] *= alpha;
+            for (int i = 0; i < 4; ++i) p[t][i] = (j_block + 4 * i + kb < lim[t]) ? p[t][i] : kNegInf;
+        }
+        const float mx = kb_max(fmaxf(fmaxf(p[t][0], p[t][1]), fmaxf(p[t][2], p[t][3])));
+        // The reference maximum moves only when a block exceeds it by more than 2^kLazyLog2 (weights reach
+        // that at most, which costs fp32 sums and bf16's relative precision nothing), so the rescaling of
+        // the accumulators runs about once per segment and not whenever one of 16 rows sees a new maximum.
+        const bool moves = mx > st[t].m + kLazyLog2;
+        if (__builtin_amdgcn_ballot_w64(moves) != 0) {
+            const float m_new = moves ? mx : st[t].m;
+            const float alpha = moves ? fast_exp2(st[t].m - m_new) : 1.0f;
+            st[t].m = m_new;
+            st[t].l *= alpha;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) st[t].o[e] *= alpha;
+        }
+        const float m_use = (st[t].m == kNegInf) ? 0.0f : st[t].m;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[t][i] = fast_exp2(p[t][i] - m_use);
+        st[t].l += (p[t][0] + p[t][1]) + (p[t][2] + p[t][3]);
     }
+    next.template at<3>();
     if (kPv == kPvFp32) {
         // O^T_e += V_i[e] (x) p_i over the 4 key groups: fp32 MFMA, p exact.
 #pragma unroll
@@ -326,21 +366,28 @@ __device__ __forceinline__ void matrix_block(MatrixState& st, const KvRegs& r, c
             v[4] = bf16_lo(r.v[i].z); v[5] = bf16_hi(r.v[i].z);
             v[6] = bf16_lo(r.v[i].w); v[7] = bf16_hi(r.v[i].w);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) st.o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e], p[i], st.o[e], 0, 0, 0);
+            for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e], p[t][i], st[t].o[e], 0, 0, 0);
         }
     } else {
         // bf16 MFMA 16x16x16 contracts the block's 16 keys at once: lane (kb, x) supplies keys 4*kb + i,
         // i = 0..3, of column 8*x + e (the e-th bf16 of its four V registers) and of row n (its four p).
         // kPvBf16x2 feeds p as hi + lo bf16 parts in two MFMAs, which keeps p to 16 significant bits.
-        const f32x2_t p01 = {p[0], p[1]}, p23 = {p[2], p[3]};
-        const bf16x2_t h01 = __builtin_convertvector(p01, bf16x2_t), h23 = __builtin_convertvector(p23, bf16x2_t);
-        const u32x2_t ph = {__builtin_bit_cast(uint32_t, h01), __builtin_bit_cast(uint32_t, h23)};
-        u32x2_t pl = {0u, 0u};
-        if (kPv == kPvBf16x2) {
-            const f32x2_t r01 = p01 - __builtin_convertvector(h01, f32x2_t);
-            const f32x2_t r23 = p23 - __builtin_convertvector(h23, f32x2_t);
-            pl.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(r01, bf16x2_t));
-            pl.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(r23, bf16x2_t));
+        u32x2_t ph[kTiles], pl[kTiles];
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t) {
+            const f32x2_t p01 = {p[t][0], p[t][1]}, p23 = {p[t][2], p[t][3]};
+            const bf16x2_t h01 = __builtin_convertvector(p01, bf16x2_t), h23 = __builtin_convertvector(p23, bf16x2_t);
+            ph[t] = u32x2_t{__builtin_bit_cast(uint32_t, h01), __builtin_bit_cast(uint32_t, h23)};
+            pl[t] = u32x2_t{0u, 0u};
+            if (kPv == kPvBf16x2) {
+                const f32x2_t r01 = p01 - __builtin_convertvector(h01, f32x2_t);
+                const f32x2_t r23 = p23 - __builtin_convertvector(h23, f32x2_t);
+                pl[t].x = __builtin_bit_cast(uint32_t, __builtin_convertvector(r01, bf16x2_t));
+                pl[t].y = __builtin_bit_cast(uint32_t, __builtin_convertvector(r23, bf16x2_t));
+            }
         }
         const uint32_t vw[4][4] = {{r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w}, {r.v[1].x, r.v[1].y, r.v[1].z, r.v[1].w},
                                    {r.v[2].x, r.v[2].y, r.v[2].z, r.v[2].w}, {r.v[3].x, r.v[3].y, r.v[3].z, r.v[3].w}};
@@ -349,11 +396,14 @@ __device__ __forceinline__ void matrix_block(MatrixState& st, const KvRegs& r, c
             const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;      // high or low halves of both words
             const u32x2_t a = {__builtin_amdgcn_perm(vw[1][e >> 1], vw[0][e >> 1], sel),
                                __builtin_amdgcn_perm(vw[3][e >> 1], vw[2][e >> 1], sel)};
-            st.o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
-                                                                __builtin_bit_cast(s16x4_t, ph), st.o[e], 0, 0, 0);
-            if (kPv == kPvBf16x2)
-                st.o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
-                                                                    __builtin_bit_cast(s16x4_t, pl), st.o[e], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < kTiles; ++t) {
+                st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
+                                                                       __builtin_bit_cast(s16x4_t, ph[t]), st[t].o[e], 0, 0, 0);
+                if (kPv == kPvBf16x2)
+                    st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
+                                                                           __builtin_bit_cast(s16x4_t, pl[t]), st[t].o[e], 0, 0, 0);
+            }
         }
     }
 }
@@ -364,77 +414,88 @@ __device__ __forceinline__ void matrix_block(MatrixState& st, const KvRegs& r, c
 // segment's first loads are not queued behind the old segment's stores (a wave's memory operations
 // complete in order, and a store's completion takes several microseconds under a saturated read
 // stream) and the read stream does not drain at a segment boundary.
+template <int kTiles>
 struct MatrixCtx {
     Segment seg;
     __amdgpu_buffer_rsrc_t rk, rv;
     uint32_t voffset;
-    bf16x8_t qop[4];
-    int lim;          // first key index row n may not see
-    bool row_ok;      // row n of the tile exists
-    int t, g;         // row n <-> (token, head within the group)
-    long orow;        // output row of row n
+    bf16x8_t qop[kTiles][4];
+    int lim[kTiles];  // first key index row n of the tile may not see
     KvRegs first;     // block 0
 };
 
-__device__ __forceinline__ void matrix_begin(MatrixCtx& c, const DecodeParams& prm, const Segment& seg, int lane) {
+// Row r of the segment's rows <-> (token t, head kvh*G + g).  r / G as a product with 1 / G: (r + 1/2) / G is
+// at least 1 / (2 G) >= 2^-7 away from an integer (G <= 64), far more than the product's rounding.
+__device__ __forceinline__ int row_token(const DecodeParams& prm, int r) { return (int)(((float)r + 0.5f) * prm.inv_group); }
+__device__ __forceinline__ int seq_row(const DecodeParams& prm, const Segment& seg, int r) {      // row within the sequence
+    const int rr = seg.row0 + r;
+    const int t = row_token(prm, rr);
+    return t * prm.n_q_heads + seg.kvh * prm.group + (rr - t * prm.group);
+}
+
+template <int kTiles>
+__device__ __forceinline__ void matrix_begin(MatrixCtx<kTiles>& c, const DecodeParams& prm, const Segment& seg, int lane) {
     const int kb = lane >> 4, n = lane & 15;
-    const int G = prm.group, T = prm.q_len, Hq = prm.n_q_heads;
     const uint32_t row_stride = (uint32_t)prm.n_kv_heads * kRowBytes;
     c.seg = seg;
     c.rk = make_rsrc(seg.kp, seq_bytes(prm, seg.L));
     c.rv = make_rsrc(seg.vp, seq_bytes(prm, seg.L));
-    c.voffset = (uint32_t)(4 * kb) * row_stride + (uint32_t)seg.kvh * kRowBytes + n * 16;
-    load_regs(c.first, c.rk, c.rv, c.voffset, row_stride, seg.j0);
-    // Row n of the tile <-> (token t, head kvh*G + g); rows past n_rows are zero padding.
-    c.row_ok = n < seg.n_rows;
-    const int rr = seg.row0 + (c.row_ok ? n : 0);
-    c.t = rr / G;
-    c.g = rr - c.t * G;
-    c.orow = (long)(seg.b * T + c.t) * Hq + seg.kvh * G + c.g;
+    c.voffset = (uint32_t)kb * row_stride + (uint32_t)seg.kvh * kRowBytes + n * 16;
+    NextLoad{c.first, c.rk, c.rv, c.voffset, row_stride, seg.j0, true}.all();
+    // Q through a descriptor over the sequence's rows: rows past n_rows lie past its end and read as zero.
+    const int seq_rows = prm.q_len * prm.n_q_heads;
+    const __amdgpu_buffer_rsrc_t rq = make_rsrc(prm.q + (long)seg.b * seq_rows * kHeadDim, (uint32_t)(seq_rows * kRowBytes));
 #pragma unroll
-    for (int step = 0; step < 4; ++step) {
-        u32x4_t qv = {0u, 0u, 0u, 0u};
-        if (c.row_ok) qv = *reinterpret_cast<const u32x4_t*>(prm.q + c.orow * kHeadDim + (4 * step + kb) * 8);
-        c.qop[step] = __builtin_bit_cast(bf16x8_t, qv);
+    for (int t = 0; t < kTiles; ++t) {
+        const bool row_ok = 16 * t + n < seg.n_rows;
+        const int r = row_ok ? 16 * t + n : 0;
+        const int qoff = (row_ok ? seq_row(prm, seg, r) : seq_rows) * kRowBytes + kb * 16;
+#pragma unroll
+        for (int step = 0; step < 4; ++step)
+            c.qop[t][step] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(rq, qoff + 64 * step, 0, 0));
+        const int causal = seg.L - prm.q_len + row_token(prm, seg.row0 + r) + 1;
+        c.lim[t] = causal < seg.j1 ? causal : seg.j1;
     }
-    const int causal = seg.L - T + c.t + 1;
-    c.lim = causal < seg.j1 ? causal : seg.j1;
 }
 
-template <int kPv>
-__device__ __forceinline__ void matrix_run(MatrixState& st, MatrixCtx& c, const DecodeParams& prm, int lane,
+template <int kPv, int kTiles>
+__device__ __forceinline__ void matrix_run(MatrixState (&st)[kTiles], MatrixCtx<kTiles>& c, const DecodeParams& prm, int lane,
                                            char* lds_wave) {
     const int kb = lane >> 4, n = lane & 15;
     const uint32_t row_stride = (uint32_t)prm.n_kv_heads * kRowBytes;
     const Segment& seg = c.seg;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) st.o[e] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    st.m = kNegInf;
-    st.l = 0.0f;
-    // Two register buffers: the next block's 8 loads per lane are issued before the current block's
-    // arithmetic.
+    for (int t = 0; t < kTiles; ++t) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) st[t].o[e] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        st[t].m = kNegInf;
+        st[t].l = 0.0f;
+    }
+    // Two register buffers: the next block's 8 loads per lane go out during the current block's arithmetic.
     const int n_blocks = (seg.j1 - seg.j0 + kBlockKeys - 1) / kBlockKeys;
     auto key0 = [&](int blk) { return seg.j0 + blk * kBlockKeys; };
     KvRegs Bk;
     int blk = 0;
-    for (; blk + 2 <= n_blocks; blk += 2) {
-        load_regs(Bk, c.rk, c.rv, c.voffset, row_stride, key0(blk + 1));
-        matrix_block<kPv>(st, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n);
-        if (blk + 2 < n_blocks) load_regs(c.first, c.rk, c.rv, c.voffset, row_stride, key0(blk + 2));
-        matrix_block<kPv>(st, Bk, c.qop, lds_wave, prm.scale_log2, key0(blk + 1), c.lim, kb, n);
+        for (; blk + 2 <= n_blocks; blk += 2) {
+        matrix_block<kPv, kTiles>(st, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n,
+                                  NextLoad{Bk, c.rk, c.rv, c.voffset, row_stride, key0(blk + 1), true});
+        matrix_block<kPv, kTiles>(st, Bk, c.qop, lds_wave, prm.scale_log2, key0(blk + 1), c.lim, kb, n,
+                                  NextLoad{c.first, c.rk, c.rv, c.voffset, row_stride, key0(blk + 2), blk + 2 < n_blocks});
     }
-    if (blk < n_blocks) matrix_block<kPv>(st, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n);
+    if (blk < n_blocks)
+        matrix_block<kPv, kTiles>(st, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n, NoLoad());
 }
 
+// Stores the 16 rows of tile t of the segment; rows past the last get an offset past the descriptor's end,
+// and their stores are dropped.
+constexpr uint32_t kPastTheEnd = 0x40000000u;
 template <bool kWriteThrough>
-__device__ __forceinline__ void matrix_finish(const MatrixState& st, const MatrixCtx& c, const DecodeParams& prm,
+__device__ __forceinline__ void matrix_finish(const MatrixState& st, const Segment& seg, int tile, const DecodeParams& prm,
                                               int lane, char* lds_wave) {
     const int kb = lane >> 4, n = lane & 15;
-    const int G = prm.group, T = prm.q_len, Hq = prm.n_q_heads;
-    const Segment& seg = c.seg;
-    float l = st.l;
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
+    const int seq_rows = prm.q_len * prm.n_q_heads;
+    const int n_rows = seg.n_rows - 16 * tile;
+    const float l = kb_sum(st.l);
     // Store through LDS so that every store instruction writes whole contiguous rows (a lane's own
     // accumulators are 16-byte pieces of 16 different rows).
     auto fence = [] {
@@ -442,39 +503,29 @@ __device__ __forceinline__ void matrix_finish(const MatrixState& st, const Matri
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    auto row_of = [&](int r, long* out_row, int* seq_row) {      // tile row r -> output row, row within the sequence
-        const int rr2 = seg.row0 + r;
-        const int t2 = rr2 / G, g2 = rr2 - t2 * G;
-        *seq_row = t2 * Hq + seg.kvh * G + g2;
-        *out_row = (long)seg.b * T * Hq + *seq_row;
-    };
-    fence();      // the last block's LDS reads are done
     if (seg.whole) {
         constexpr int kPitch = kRowBytes + 16;                   // bf16 rows, padded against bank conflicts
         const float inv = l > 0.0f ? 1.0f / l : 0.0f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             uint4 w;
-            w.x = pack_bf16(st.o[0][j] * inv, st.o[1][j] * inv);
-            w.y = pack_bf16(st.o[2][j] * inv, st.o[3][j] * inv);
-            w.z = pack_bf16(st.o[4][j] * inv, st.o[5][j] * inv);
-            w.w = pack_bf16(st.o[6][j] * inv, st.o[7][j] * inv);
+            w.x = cvt_bf16(st.o[0][j] * inv, st.o[1][j] * inv);
+            w.y = cvt_bf16(st.o[2][j] * inv, st.o[3][j] * inv);
+            w.z = cvt_bf16(st.o[4][j] * inv, st.o[5][j] * inv);
+            w.w = cvt_bf16(st.o[6][j] * inv, st.o[7][j] * inv);
             *reinterpret_cast<uint4*>(lds_wave + n * kPitch + (4 * kb + j) * 16) = w;
         }
         fence();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {                             // 4 rows of 256 bytes per store instruction
             const int r = 4 * i + (lane >> 4);
-            if (r < seg.n_rows) {
-                long orow2;
-                int th2;
-                row_of(r, &orow2, &th2);
-                const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lds_wave + r * kPitch + (lane & 15) * 16);
-                store_b128<kWriteThrough>(prm.out + (long)seg.b * T * Hq * kHeadDim, (uint32_t)(T * Hq * kRowBytes),
-                              (uint32_t)(th2 * kRowBytes + (lane & 15) * 16), w);
-            }
+            const uint32_t off = (uint32_t)seq_row(prm, seg, 16 * tile + r) * kRowBytes + (lane & 15) * 16;
+            const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lds_wave + r * kPitch + (lane & 15) * 16);
+            store_b128<kWriteThrough>(prm.out + (long)seg.b * seq_rows * kHeadDim, (uint32_t)(seq_rows * kRowBytes),
+                          off | (r < n_rows ? 0u : kPastTheEnd), w);
         }
-        if (c.row_ok && prm.lse && kb == 0) prm.lse[c.orow] = l > 0.0f ? (st.m + __log2f(l)) * kLn2 : kNegInf;
+        if (n < n_rows && prm.lse && kb == 0)
+            prm.lse[(long)seg.b * seq_rows + seq_row(prm, seg, 16 * tile + n)] = l > 0.0f ? (st.m + __log2f(l)) * kLn2 : kNegInf;
     } else {
         constexpr int kPitch = kHeadDim * 4 + 16;                // fp32 rows, padded
 #pragma unroll
@@ -487,64 +538,73 @@ __device__ __forceinline__ void matrix_finish(const MatrixState& st, const Matri
 #pragma unroll
         for (int i = 0; i < 8; ++i) {                             // 2 rows of 512 bytes per store instruction
             const int r = 2 * i + (lane >> 5);
-            if (r < seg.n_rows) {
-                long orow2;
-                int th2;
-                row_of(r, &orow2, &th2);
-                const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lds_wave + r * kPitch + (lane & 31) * 16);
-                store_b128<kWriteThrough>(prm.part_o + (long)seg.slot * (T * Hq) * kHeadDim, (uint32_t)(T * Hq * kHeadDim * 4),
-                              (uint32_t)(th2 * kHeadDim * 4 + (lane & 31) * 16), w);
-            }
+            const uint32_t off = (uint32_t)seq_row(prm, seg, 16 * tile + r) * (kHeadDim * 4) + (lane & 31) * 16;
+            const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lds_wave + r * kPitch + (lane & 31) * 16);
+            store_b128<kWriteThrough>(prm.part_o + (long)seg.slot * seq_rows * kHeadDim, (uint32_t)(seq_rows * kHeadDim * 4),
+                          off | (r < n_rows ? 0u : kPastTheEnd), w);
         }
-        if (c.row_ok && kb == 0) {
-            const long prow = (long)seg.slot * (T * Hq) + c.t * Hq + seg.kvh * G + c.g;
+        if (n < n_rows && kb == 0) {
+            const long prow = (long)seg.slot * seq_rows + seq_row(prm, seg, 16 * tile + n);
             reinterpret_cast<float2*>(prm.part_ml)[prow] = make_float2(st.m, l);
         }
     }
-    fence();      // the next segment's K blocks reuse this LDS
+    fence();      // the next tile, or the next segment's K blocks, reuse this LDS
 }
 
 // ---------------------------------------------------------------------------------- decode kernel
-// grid.x = pieces, grid.y = row tiles of R rows, grid.z = groups of up to 8 KV heads; block = 64 * heads.
-// kMatrix selects the matrix path (R must be 16 then).
+// grid.x = workgroups of pieces times groups of R query rows, grid.z = groups of up to 8 KV heads;
+// block = 64 * heads * parts: a workgroup holds `parts` pieces, one wave per KV head and piece.
+// kMatrix selects the matrix path (R must be 16 * kTiles then).
 // Fixed work of a (piece, sequence) segment in token units for the partition (0 = pieces of equal token
 // count; 16 measured best of 0 / 16 / 48: 0.2 to 1 % on the four large workloads).
 constexpr int kGqaSegCost = 16;
 
 template <int R, bool kMatrix, int kPv>
 __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
+    constexpr int kTiles = kMatrix ? R / 16 : 1;
     __shared__ __attribute__((aligned(16))) char lds[kMatrix ? kMaxWavesPerBlock * kLdsPerWave : 16];
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int kvh = blockIdx.z * kMaxWavesPerBlock + wave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int heads = prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;      // per workgroup
+    const int part = prm.parts == 1 ? 0 : wave / heads;
+    const int kvh = blockIdx.z * kMaxWavesPerBlock + wave - part * heads;
     if (kvh >= prm.n_kv_heads) return;
     const WavePlan wp = wave_plan(prm.kv_lens, nullptr, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kGqaSegCost,
                                   prm.xcd_skew, lane, nullptr);
     const Plan& pl = wp.pl;
 
-    // Piece index: consecutive workgroups go to different XCDs, so give each XCD one contiguous
-    // eighth of the token stream.
+    // Piece index: consecutive workgroups go to different XCDs, so give each XCD one contiguous eighth of
+    // the token stream.  Of an XCD's workgroups, consecutive ones are the row groups of the same pieces:
+    // they run at the same time and share the pieces' K and V in that XCD's L2.  A workgroup's parts are
+    // far apart in the XCD's eighth, so that a short stream's few pieces spread over the compute units.
     const int per_xcd = (pl.n_pieces + 7) >> 3;
     const int bid = blockIdx.x;
-    const int p = (bid & 7) * per_xcd + (bid >> 3);
+    const int rows_total = prm.group * prm.q_len;
+    const int n_groups = (rows_total + R - 1) / R;
+    const int slot_in_xcd = bid >> 3;
+    const int set = n_groups == 1 ? slot_in_xcd : slot_in_xcd / n_groups;
+    const int row_group = slot_in_xcd - set * n_groups;
+    const int sets = (int)(gridDim.x >> 3) / n_groups;       // workgroups of different pieces per XCD
+    const int p_local = part * sets + set;
+    const int p = (bid & 7) * per_xcd + p_local;
     const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
-    const bool active = (bid >> 3) < per_xcd && p < pl.n_pieces && s0 < s1;
+    const bool active = p_local < per_xcd && p < pl.n_pieces && s0 < s1;
 
-    if (blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 64) {
+    if (blockIdx.z == 0 && threadIdx.x < 64) {
         // For the merge kernel: first partial slot and number of segments of every sequence, 64
-        // sequences per wave, the groups of 64 dealt out over the workgroups.
-        for (int g = bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
+        // sequences per wave, the groups of 64 dealt out over the workgroups from the last one, which
+        // has no piece of its own when the stream is short.
+        for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
     }
     if (!active) return;
 
     Walk walk;
     wave_locate(wp, prm.kv_lens, nullptr, nullptr, prm.batch, s0, lane, nullptr, walk.b, walk.j);
-    walk.remaining = s1 - s0;
+    walk.remaining = uniform(s1 - s0);
 
-    const int rows_total = prm.group * prm.q_len;
     Segment seg;
     seg.kvh = kvh;
-    seg.row0 = blockIdx.y * R;
+    seg.row0 = row_group * R;
     seg.n_rows = rows_total - seg.row0 < R ? rows_total - seg.row0 : R;
     // Next (piece, sequence) intersection of this piece, in stream order; false when the piece is done.
     auto next_seg = [&](Segment& out) {
@@ -552,32 +612,37 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
         if (!next_segment(walk, prm.batch, pl.seg_cost,
                           [&](int b) { return __builtin_amdgcn_readfirstlane(clamp_len(prm.kv_lens[b])); }, ps))
             return false;
+        // Everything about a segment is wave-uniform; said so, it lives in scalar registers, and the loads
+        // through its descriptors need no loop over the lanes' values.
         out = seg;
-        out.b = ps.b;
-        out.kp = prm.k_ptrs[ps.b];
-        out.vp = prm.v_ptrs[ps.b];
-        out.L = ps.L;
-        out.j0 = ps.j0;
-        out.j1 = ps.j1;
-        out.slot = p + ps.b;
-        out.whole = ps.whole;
+        out.b = uniform(ps.b);
+        out.kp = uniform(prm.k_ptrs[out.b]);
+        out.vp = uniform(prm.v_ptrs[out.b]);
+        out.L = uniform(ps.L);
+        out.j0 = uniform(ps.j0);
+        out.j1 = uniform(ps.j1);
+        out.slot = uniform(p) + out.b;
+        out.whole = uniform(ps.whole);
         return true;
     };
-    if (kMatrix) {
+    if constexpr (kMatrix) {
         char* lds_wave = lds + wave * kLdsPerWave;
         Segment cur_seg;
-        if (!next_seg(cur_seg)) return;
-        MatrixCtx cur;
+        if (uniform(next_seg(cur_seg)) == 0) return;
+        MatrixCtx<kTiles> cur;
         matrix_begin(cur, prm, cur_seg, lane);
         for (;;) {
-            MatrixState st;
-            matrix_run<kPv>(st, cur, prm, lane, lds_wave);
+            MatrixState st[kTiles];
+            matrix_run<kPv, kTiles>(st, cur, prm, lane, lds_wave);
             Segment nxt_seg;
-            const bool more = next_seg(nxt_seg);
-            MatrixCtx nxt;
+            const bool more = uniform(next_seg(nxt_seg)) != 0;
+            MatrixCtx<kTiles> nxt;
             if (more) matrix_begin(nxt, prm, nxt_seg, lane);     // its loads go out before cur's stores
-            if (more) matrix_finish<true>(st, cur, prm, lane, lds_wave);
-            else matrix_finish<false>(st, cur, prm, lane, lds_wave);
+#pragma unroll
+            for (int t = 0; t < kTiles; ++t) {
+                if (more) matrix_finish<true>(st[t], cur.seg, t, prm, lane, lds_wave);
+                else matrix_finish<false>(st[t], cur.seg, t, prm, lane, lds_wave);
+            }
             if (!more) break;
             cur = nxt;
         }
@@ -671,7 +736,7 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(
         }
     }
     const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-    *outp = pack_bf16(o0 * inv, o1 * inv);
+    *outp = cvt_bf16(o0 * inv, o1 * inv);
     if (prm.lse && lane == 0) prm.lse[row] = l > 0.0f ? (M + __log2f(l)) * kLn2 : kNegInf;
 }
 
@@ -713,8 +778,8 @@ bool use_matrix_path(int rows_total, int path) {
     return path == kPathMatrix || (path == kPathAuto && rows_total >= 4);
 }
 
-int rows_per_tile(int rows_total, int path) {
-    if (use_matrix_path(rows_total, path)) return 16;
+int rows_per_wave(int rows_total, int path) {
+    if (use_matrix_path(rows_total, path)) return rows_total <= 16 ? 16 : 32;
     static const int kSizes[] = {1, 2, 3, 4, 5, 6, 8};
     for (int s : kSizes)
         if (rows_total <= s) return s;
@@ -724,14 +789,21 @@ int rows_per_tile(int rows_total, int path) {
 hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t* events) {
     const int rows_total = prm.group * prm.q_len;
     const bool matrix = use_matrix_path(rows_total, prm.path);
-    const int R = rows_per_tile(rows_total, prm.path);
+    const int R = rows_per_wave(rows_total, prm.path);
     const int heads_per_block = prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;
-    dim3 grid((prm.n_pieces + 7) / 8 * 8, (rows_total + R - 1) / R,
-              (prm.n_kv_heads + kMaxWavesPerBlock - 1) / kMaxWavesPerBlock);
-    dim3 block(64 * heads_per_block);
+    const int n_groups = (rows_total + R - 1) / R;
+    const int sets = (prm.n_pieces + prm.parts - 1) / prm.parts;
+    dim3 grid((sets + 7) / 8 * 8 * n_groups, 1, (prm.n_kv_heads + kMaxWavesPerBlock - 1) / kMaxWavesPerBlock);
+    dim3 block(64 * heads_per_block * prm.parts);
     hipError_t e;
     if (events && (e = hipEventRecord(events[0], stream)) != hipSuccess) return e;
-    if (matrix) {
+    if (matrix && R == 32) {
+        switch (prm.pv_mode) {
+            case kPvBf16: e = launch_decode_r<32, true, kPvBf16>(prm, grid, block, stream); break;
+            case kPvFp32: e = launch_decode_r<32, true, kPvFp32>(prm, grid, block, stream); break;
+            default: e = launch_decode_r<32, true, kPvBf16x2>(prm, grid, block, stream); break;
+        }
+    } else if (matrix) {
         switch (prm.pv_mode) {
             case kPvBf16: e = launch_decode_r<16, true, kPvBf16>(prm, grid, block, stream); break;
             case kPvFp32: e = launch_decode_r<16, true, kPvFp32>(prm, grid, block, stream); break;

@@ -82,7 +82,6 @@ constexpr int kStageWave = 16 * kStagePitch;     // 8448 bytes
 // with two segments finish 13 us later than their token count says) in units of one token's share of
 // the block loop (2.3 us per 32 tokens).
 constexpr int kMlaSegCost = 192;
-constexpr float kLazyLog2 = 8.0f;                // slack of the softmax reference maximum, in powers of two
 // Precision of the softmax weights in the value product (see the header comment).
 constexpr int kLoNever = 0;                      // one bf16 per weight everywhere
 constexpr int kLoAlways = 1;                     // hi + lo bf16 parts everywhere
@@ -214,52 +213,11 @@ __device__ __forceinline__ void block_to_lds(char* lds_block, u32x4_t rc, int j_
     }
 }
 
-// max / sum over the four lanes (kb = 0..3) that hold the same row: lane-swap instructions, no LDS.
-// The swap exchanges, between its two register operands, lane group 1 (3) of the first with lane
-// group 0 (2) of the second (16-lane form), or the upper half of the first with the lower half of
-// the second (32-lane form): called on (x, x), the two results together hold both partners' values.
-// (The results are copied to scalars before the bit cast: a bit cast applied directly to an element
-// of the result vector read element 0 for both.)
-__device__ __forceinline__ void swap16(float x, float& r0, float& r1) {
-    const uint32_t a = __builtin_bit_cast(uint32_t, x);
-    const u32x2_t t = __builtin_amdgcn_permlane16_swap(a, a, false, false);
-    const uint32_t t0 = t.x, t1 = t.y;
-    r0 = __builtin_bit_cast(float, t0);
-    r1 = __builtin_bit_cast(float, t1);
-}
-__device__ __forceinline__ void swap32(float x, float& r0, float& r1) {
-    const uint32_t a = __builtin_bit_cast(uint32_t, x);
-    const u32x2_t t = __builtin_amdgcn_permlane32_swap(a, a, false, false);
-    const uint32_t t0 = t.x, t1 = t.y;
-    r0 = __builtin_bit_cast(float, t0);
-    r1 = __builtin_bit_cast(float, t1);
-}
-__device__ __forceinline__ float kb_max(float x) {
-    float a, b;
-    swap16(x, a, b);
-    x = fmaxf(a, b);
-    swap32(x, a, b);
-    return fmaxf(a, b);
-}
-__device__ __forceinline__ float kb_sum(float x) {
-    float a, b;
-    swap16(x, a, b);
-    x = a + b;
-    swap32(x, a, b);
-    return a + b;
-}
-
 // Two values rounded to fp16 (nearest even) and packed.
 typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_f16(float a, float b) {
     const f32x2_t v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2_t));
-}
-
-// Two values rounded to bf16 (nearest even) and packed: the conversion instruction.
-__device__ __forceinline__ uint32_t cvt_bf16(float a, float b) {
-    const f32x2_t v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
 // Scheduling groups (the group sizes must be compile-time constants, hence the templates).
@@ -1023,10 +981,10 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_ker
     }
     const float inv = lq > 0.0f ? 1.0f / lq : 0.0f;
     uint4 w;
-    w.x = pack_bf16(acc[0] * inv, acc[1] * inv);
-    w.y = pack_bf16(acc[2] * inv, acc[3] * inv);
-    w.z = pack_bf16(acc[4] * inv, acc[5] * inv);
-    w.w = pack_bf16(acc[6] * inv, acc[7] * inv);
+    w.x = cvt_bf16(acc[0] * inv, acc[1] * inv);
+    w.y = cvt_bf16(acc[2] * inv, acc[3] * inv);
+    w.z = cvt_bf16(acc[4] * inv, acc[5] * inv);
+    w.w = cvt_bf16(acc[6] * inv, acc[7] * inv);
     *outp = w;
     if (prm.lse && lane == 0) prm.lse[row] = l > 0.0f ? (M + __log2f(l)) * kLn2 : kNegInf;
 }
