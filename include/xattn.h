@@ -175,7 +175,8 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *                               MFMA on hi + lo bf16 parts of the weights (16 significant bits);
  *                               1 = fp32 MFMA (weights exact, slower); 2 = one bf16 MFMA (weights
  *                               rounded to bf16)
- *                               (xattn_mla_decode: 0 = default, hi + lo bf16 parts for the first 128 keys
+ *                               (xattn_mla_decode: 0 = default, hi + lo bf16 parts throughout with up to 32
+ *                               query rows per sequence, else for the first 128 keys
  *                               of every segment and wherever a key carries 1/4 or more of its row's
  *                               running sum, one bf16 elsewhere; 1 = hi + lo parts everywhere;
  *                               2 = one bf16 per weight everywhere, less exact on peaked rows)

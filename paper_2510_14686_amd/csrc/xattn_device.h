@@ -36,6 +36,7 @@ __device__ __forceinline__ const void* uniform(const void* ptr) {
     const uint64_t a = (uint64_t)(uintptr_t)ptr;
     return reinterpret_cast<const void*>((uintptr_t)((uint32_t)uniform((int)(uint32_t)a) | ((uint64_t)(uint32_t)uniform((int)(uint32_t)(a >> 32)) << 32)));
 }
+__device__ __forceinline__ void* uniform(void* ptr) { return const_cast<void*>(uniform(static_cast<const void*>(ptr))); }
 template <int kCtrl>
 __device__ __forceinline__ float dpp_f(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xf, 0xf, true));

@@ -896,6 +896,228 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     }
 }
 
+// ----------------------------------------------------------------------- few query rows: 32 at most
+// With 16 rows (heads split over several GPUs) a cached byte meets 30 flop: bound by HBM, and what matters
+// is that a compute unit keeps its loads in flight.  One wave per 16 rows does not: it issues 38 loads per
+// block, then works through the block alone (2.7 TB/s at 16 rows).  Here four waves share a
+// 16-row tile: of a block's scores wave q computes key tile q % 2 over half q / 2 of the key width (9 MFMAs,
+// 36 registers of Q), the four partial tiles meet in LDS, every wave does the (small) softmax of the whole
+// tile for itself, and accumulates 128 of the 512 value columns (8 MFMAs, 32 accumulators).  No operand
+// is read from LDS twice per tile, and nothing has to be combined at the end of a segment but the rows'
+// largest magnitudes.  Two barriers per block, two blocks in flight behind the one in use.
+// The weights enter the value product as hi + lo bf16 parts throughout (the matrix cores are idle
+// anyway), or as one bf16 where the caller asked for that.
+// Measured, 64 sequences of 1024 to 8192 tokens, 16 heads: call 135.1 -> 61.3 us
+// (5.4 TB/s); 32 sequences of 16384 tokens: 16 rows 221 -> 104 us, 32 rows 165 -> 107. At 64 rows this layout
+// (two tiles per wave) takes 154 us where one wave per tile takes 134: the line lies at 32.
+constexpr int kRowsSegCost = 96;                 // a segment's fixed work in tokens (48: +2 %, 160: +0.7 %)
+constexpr int kRowsSteps = kQSteps / 2;          // score steps per wave
+constexpr int kRowsCols = kColTiles / 4;         // value column tiles per wave
+constexpr int kRowsStagePitch = kRowsCols * 32 + 16;
+
+template <int RT, bool kLo>
+__global__ __launch_bounds__(256 * RT) void mla_rows_kernel(MlaParams prm) {
+    constexpr int NW = 4 * RT;
+    __shared__ __attribute__((aligned(16))) char lds_c[kStages * kLdsBlock];
+    __shared__ f32x4_t lds_x[RT][4][64];    // partial scores: [rt][key tile + 2 * half][lane]
+    __shared__ float lds_amax[RT][4][16];
+    static_assert(NW * 16 * kRowsStagePitch <= kStages * kLdsBlock, "output staging must fit the block buffers");
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int kb = lane >> 4, n = lane & 15;
+    const int rt = wave >> 2, quarter = wave & 3, kt = quarter & 1, half = quarter >> 1;
+    const int T = prm.q_len, H = prm.n_heads, rows_total = T * H;
+    SeqWindow win;
+    const WavePlan wp = wave_plan(prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kRowsSegCost,
+                                  prm.xcd_skew, lane, &win);
+    const Plan& pl = wp.pl;
+    const int per_xcd = (pl.n_pieces + 7) >> 3;
+    const int bid = blockIdx.x;
+    const int p = (bid & 7) * per_xcd + (bid >> 3);
+    const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
+    const bool active = (bid >> 3) < per_xcd && p < pl.n_pieces && s0 < s1;
+    if (tid < 64)
+        for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
+    if (!active) return;       // the whole workgroup: every wave computed the same plan
+
+    Walk walk;
+    wave_locate(wp, prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, s0, lane, &win, walk.b, walk.j);
+    walk.remaining = uniform(s1 - s0);
+
+    const DmaLane dma = dma_lane(lane);
+    const int my_loads = (kDmaPerBlock - wave + NW - 1) / NW;
+    // Step t of the wave's half: MFMA step 9 * half + t; steps 16 and 17 lie in the tail area.
+    const int qk_off = (16 * kt + n) * kPitch + kb * 16 + half * kRowsSteps * 64;
+    const int qt_off = kTailOff + (16 * kt + n) * kTailPitch + kb * 16;
+    const int pv_off = (4 * kb + (n >> 2)) * kPitch + (n & 3) * 8 + quarter * kRowsCols * 32;
+    char* stage = lds_c + wave * (16 * kRowsStagePitch);
+    auto fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+
+    PieceSeg ps;
+    while (uniform(next_segment(walk, prm.batch, pl.seg_cost,
+                                [&](int bb) { return window_len(win, prm.kv_lens, bb); }, ps))) {
+        const int b = uniform(ps.b), L = uniform(ps.L), j0 = uniform(ps.j0), j1 = uniform(ps.j1);
+        const bool whole = uniform(ps.whole) != 0;
+        const long slot = (long)uniform(p) + b;
+        const unsigned long long cbytes = (unsigned long long)L * kRowB;
+        const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, prm.c_ptrs, b);
+        const u32x4_t rc = {(uint32_t)uniform((int)(uint32_t)caddr), (uint32_t)uniform((int)((uint32_t)(caddr >> 32) & 0xffffu)),
+                            cbytes > 0xffffffffull ? 0xffffffffu : (uint32_t)cbytes, 0x00020000u};
+        const int n_blocks = (j1 - j0 + kMlaKeys - 1) / kMlaKeys;
+        // Q operand: lane (kb, n) holds columns 32 step + 8 kb .. + 7 of row n; rows past the last read as zero.
+        const __amdgpu_buffer_rsrc_t rq = make_rsrc(prm.q + (long)b * rows_total * kDqk, (uint32_t)rows_total * kRowB);
+        const int row = 16 * rt + n;             // of the sequence's T * H rows
+        bf16x8_t qop[kRowsSteps];
+#pragma unroll
+        for (int t = 0; t < kRowsSteps; ++t)
+            qop[t] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                                      rq, row * kRowB + (half * kRowsSteps + t) * 64 + kb * 16, 0, 0));
+        const int causal = L - T + (row < rows_total ? row : 0) / H + 1;
+        const int lim = causal < j1 ? causal : j1;
+        block_to_lds<NW>(lds_c, rc, j0, wave, dma);
+        // Q is used here so that the wait for its loads sits outside the loop (see mla_decode_kernel).
+#pragma unroll
+        for (int t = 0; t < kRowsSteps; ++t) asm volatile("" : "+v"(qop[t]));
+        if (n_blocks > 1) block_to_lds<NW>(lds_c + kLdsBlock, rc, j0 + kMlaKeys, wave, dma);
+
+        f32x4_t o[kRowsCols];
+        float m = kNegInf, l = 0.0f, lq = 0.0f;
+#pragma unroll
+        for (int c = 0; c < kRowsCols; ++c) o[c] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        int cur_buf = 0, next_buf = 2;
+        for (int blk = 0; blk < n_blocks; ++blk) {
+            const char* cur = lds_c + cur_buf * kLdsBlock;
+            // every wave waits for its own loads of block blk; behind the barrier the block is in LDS and
+            // everyone is done with block blk - 1 and its partial scores
+            dma_wait(blk + 1 < n_blocks ? my_loads : 0);
+            __syncthreads();
+            if (blk + 2 < n_blocks) block_to_lds<NW>(lds_c + next_buf * kLdsBlock, rc, j0 + (blk + 2) * kMlaKeys, wave, dma);
+            f32x4_t s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int t = 0; t < kRowsSteps; ++t) {
+                // the wave's half decides (uniformly) whether its last two steps read the tail area
+                const bool tail = t >= kMainSteps - kRowsSteps && half == 1;
+                const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(
+                    cur + (tail ? qt_off + (t - (kMainSteps - kRowsSteps)) * 64 : qk_off + t * 64));
+                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qop[t], s, 0, 0, 0);
+            }
+            lds_x[rt][quarter][lane] = s;
+            __syncthreads();
+            float q[8];                          // scores, then weights: key 16 kt + 4 kb + i at index 4 kt + i
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const f32x4_t sum = lds_x[rt][k][lane] + lds_x[rt][k + 2][lane];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) q[4 * k + i] = sum[i];
+            }
+            bf16x8_t va[kRowsCols];              // value fragments: see mla_block for the transposing read
+#pragma unroll
+            for (int c = 0; c < kRowsCols; ++c) {
+                const s16x4v_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4v_t*)(cur + pv_off + c * 32));
+                const s16x4v_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4v_t*)(cur + pv_off + kTileB + c * 32));
+                const u32x2_t w0 = __builtin_bit_cast(u32x2_t, v0), w1 = __builtin_bit_cast(u32x2_t, v1);
+                va[c] = __builtin_bit_cast(bf16x8_t, u32x4_t{w0.x, w0.y, w1.x, w1.y});
+            }
+            const int j_block = j0 + blk * kMlaKeys;
+            if (__builtin_amdgcn_ballot_w64(j_block + kMlaKeys > lim) != 0) {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) q[t] = j_block + 16 * (t >> 2) + 4 * kb + (t & 3) < lim ? q[t] : kNegInf;
+            }
+            float mx = max_num(max_num(max_num(q[0], q[1]), max_num(q[2], q[3])), max_num(max_num(q[4], q[5]), max_num(q[6], q[7])));
+            mx = kb_max(mx) * prm.scale_log2;
+            const bool moves = mx > m + kLazyLog2;          // the reference maximum follows lazily, see mla_block
+            if (__builtin_amdgcn_ballot_w64(moves) != 0) {
+                const float m_new = moves ? mx : m;
+                const float alpha = moves ? fast_exp2(m - m_new) : 1.0f;
+                m = m_new;
+                l *= alpha;
+                lq *= alpha;
+#pragma unroll
+                for (int c = 0; c < kRowsCols; ++c) o[c] *= alpha;
+            }
+            const float m_use = m == kNegInf ? 0.0f : m;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) q[t] = fast_exp2(__builtin_fmaf(q[t], prm.scale_log2, -m_use));
+            const float sum = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+            l += sum;                            // this lane's share of the row's sums, both
+            uint32_t hi[4], lo[4] = {0u, 0u, 0u, 0u};
+            float sum_q = 0.0f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                hi[u] = cvt_bf16(q[2 * u], q[2 * u + 1]);
+                const f32x2_t back = __builtin_convertvector(__builtin_bit_cast(bf16x2_t, hi[u]), f32x2_t);
+                if (kLo) lo[u] = cvt_bf16(q[2 * u] - back[0], q[2 * u + 1] - back[1]);
+                else sum_q += back[0] + back[1];
+            }
+            lq += kLo ? sum : sum_q;             // one bf16 per weight: normalised by the rounded weights, see mla_block
+            const bf16x8_t ph = __builtin_bit_cast(bf16x8_t, u32x4_t{hi[0], hi[1], hi[2], hi[3]});
+            const bf16x8_t plo = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[0], lo[1], lo[2], lo[3]});
+#pragma unroll
+            for (int c = 0; c < kRowsCols; ++c)
+                o[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c], ph, o[c], 0, 0, 0);
+            if constexpr (kLo) {
+#pragma unroll
+                for (int c = 0; c < kRowsCols; ++c)
+                    o[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c], plo, o[c], 0, 0, 0);
+            }
+            cur_buf = cur_buf == kStages - 1 ? 0 : cur_buf + 1;
+            next_buf = next_buf == kStages - 1 ? 0 : next_buf + 1;
+        }
+        // The wave's rows x 128 columns, rounded as in mla_decode_kernel (bf16 results; partial rows fp16
+        // scaled to the largest magnitude of the whole row, which the tile's four waves agree on in LDS).
+        if (!whole) {
+            float amax = 0.0f;
+#pragma unroll
+            for (int c = 0; c < kRowsCols; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) amax = fmaxf(amax, __builtin_fabsf(o[c][i]));
+            amax = kb_max(amax);
+            if (kb == 0) lds_amax[rt][quarter][n] = amax;
+        }
+        __syncthreads();                         // everyone is done with the block buffers: they stage the output now
+        uint16_t* dst = whole ? prm.out + (long)b * rows_total * kDv : prm.part_o + slot * rows_total * kDv;
+        const __amdgpu_buffer_rsrc_t rd = make_rsrc(uniform(static_cast<void*>(dst)), (uint32_t)rows_total * (kDv * 2));
+        const float l_row = kb_sum(l), lq_row = kb_sum(lq);
+        float sc, inv_scale = 0.0f;
+        if (whole) {
+            sc = lq_row > 0.0f ? 1.0f / lq_row : 0.0f;
+        } else {
+            const float amax = fmaxf(fmaxf(lds_amax[rt][0][n], lds_amax[rt][1][n]), fmaxf(lds_amax[rt][2][n], lds_amax[rt][3][n]));
+            sc = amax > 0.0f ? fminf(32768.0f / amax, 0x1.0p100f) : 0.0f;
+            inv_scale = amax > 0.0f ? 1.0f / sc : 0.0f;
+        }
+#pragma unroll
+        for (int c = 0; c < kRowsCols; ++c) {
+            const f32x4_t v = o[c] * sc;
+            uint2 d;
+            d.x = whole ? cvt_bf16(v[0], v[1]) : pack_f16(v[0], v[1]);
+            d.y = whole ? cvt_bf16(v[2], v[3]) : pack_f16(v[2], v[3]);
+            *reinterpret_cast<uint2*>(stage + n * kRowsStagePitch + (16 * c + 4 * kb) * 2) = d;
+        }
+        fence();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {        // rows 4 i .. 4 i + 3, 256 bytes each; rows past the last are dropped
+            const int r = 4 * i + kb;
+            const u32x4_t d = *reinterpret_cast<const u32x4_t*>(stage + r * kRowsStagePitch + n * 16);
+            __builtin_amdgcn_raw_buffer_store_b128(d, rd, (16 * rt + r) * (kDv * 2) + quarter * (kRowsCols * 32) + n * 16, 0, 0);
+        }
+        fence();
+        if (row < rows_total && kb == 0 && quarter == 0) {
+            if (whole) {
+                if (prm.lse) prm.lse[(long)b * rows_total + row] = l_row > 0.0f ? (m + __log2f(l_row)) * kLn2 : kNegInf;
+            } else {
+                reinterpret_cast<float4*>(prm.part_ml)[slot * rows_total + row] = make_float4(m, l_row, lq_row, inv_scale);
+            }
+        }
+        __syncthreads();          // the next segment's first block goes to buffer 0, which staged output until here
+    }
+}
+
 // kWaves waves per output row of 512 columns; lane holds columns 8*lane .. 8*lane+7.  A partial row is 512
 // fp16 values times its own scale (the fourth value of its (m, l, lq, 1 / scale) record).
 template <int kWaves>
@@ -997,12 +1219,19 @@ hipError_t launch_mla_cfg(const MlaParams& prm, dim3 grid, hipStream_t stream) {
     return hipGetLastError();
 }
 
+template <int RT>
+hipError_t launch_mla_rows(const MlaParams& prm, dim3 grid, hipStream_t stream) {
+    if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_rows_kernel<RT, false>), grid, dim3(256 * RT), 0, stream, prm);
+    else hipLaunchKernelGGL((mla_rows_kernel<RT, true>), grid, dim3(256 * RT), 0, stream, prm);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 // Workgroup shape for rows_total = q_len * n_heads query rows per sequence: (waves, 16-row tiles per
-// wave).  Automatic: one tile per wave, 8 waves from 65 rows on (two waves per SIMD, 256 registers
-// each).  layout 1: at most 4 waves of one tile (64 rows per workgroup); layout 2: 4 waves of two
-// tiles from 65 rows on (one wave per SIMD, 512 registers).
+// wave).  Automatic: up to 32 rows mla_rows_kernel (one row group, as the shape given here); then one tile per
+// wave, 8 waves from 65 rows on (two waves per SIMD, 256 registers each).  layout 1: at most 4 waves of one tile
+// (64 rows per workgroup); layout 2: 4 waves of two tiles from 65 rows on (one wave per SIMD, 512 registers).
 void mla_block_shape(int rows_total, int layout, int* waves, int* tiles_per_wave) {
     const int tiles = (rows_total + 15) / 16;
     *tiles_per_wave = (tiles > 4 && layout == 2) ? 2 : 1;
@@ -1016,7 +1245,9 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     dim3 grid((unsigned)((prm.n_pieces + 7) / 8 * 8 * ((rows_total + 16 * rt * nw - 1) / (16 * rt * nw))));
     hipError_t e;
     if (events && (e = hipEventRecord(events[0], stream)) != hipSuccess) return e;
-    if (rt == 2) e = launch_mla_cfg<4, 2>(prm, grid, stream);
+    if (prm.layout == 0 && rows_total <= 16) e = launch_mla_rows<1>(prm, grid, stream);
+    else if (prm.layout == 0 && rows_total <= 32) e = launch_mla_rows<2>(prm, grid, stream);
+    else if (rt == 2) e = launch_mla_cfg<4, 2>(prm, grid, stream);
     else if (nw == 8) e = launch_mla_cfg<8, 1>(prm, grid, stream);
     else if (nw == 4) e = launch_mla_cfg<4, 1>(prm, grid, stream);
     else if (nw == 2) e = launch_mla_cfg<2, 1>(prm, grid, stream);
