@@ -165,7 +165,9 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *                               xattn_mla_decode: one per 128 query rows of a sequence); and, with fewer
  *                               than 8 KV heads, times 8 / n_kv_heads (a workgroup then holds that many
  *                               pieces) as far as the partial results fit XATTN_NOALLOC_SCRATCH_BYTES
- *   XATTN_CFG_MIN_PIECE_TOKENS  lower bound on a piece's tokens; 0 = default (64); values below 16
+ *   XATTN_CFG_MIN_PIECE_TOKENS  lower bound on a piece's tokens; 0 = default (64, and 16 as long as no
+ *                               compute unit gets more than one piece; xattn_mla_decode: 32 for the
+ *                               first 32 pieces); values below 16
  *                               count as 16
  *   XATTN_CFG_TIMING            1 = record per-kernel events (see xattn_timing_read); 0 = off
  *   XATTN_CFG_PATH              inner loop of the decode kernel: 0 = automatic (vector path below 4

@@ -212,7 +212,7 @@ __device__ __forceinline__ int chunk_positions(__amdgpu_buffer_rsrc_t rl, int fi
 // of a segment; the GQA kernel's independent waves hide those two loads and only lose registers to it.)
 __device__ __forceinline__ WavePlan wave_plan(const int32_t* __restrict__ kv_lens, const void* const* k_ptrs,
                                               const void* const* v_ptrs, int batch, int n_pieces, int min_piece,
-                                              int seg_cost, int xcd_skew, int lane, SeqWindow* win) {
+                                              int seg_cost, int xcd_skew, FewPieces few, int lane, SeqWindow* win) {
     WavePlan wp;
     int lg = 0;
     while ((64 << lg) < batch) ++lg;                       // wave-uniform: batch is a kernel argument
@@ -241,7 +241,7 @@ __device__ __forceinline__ WavePlan wave_plan(const int32_t* __restrict__ kv_len
     const int incl = wave_incl_scan_i(mine, lane);
     wp.mine = mine;
     wp.excl = incl - mine;
-    wp.pl = plan_for_total(__builtin_amdgcn_readlane(incl, 63), n_pieces, min_piece, seg_cost, xcd_skew);
+    wp.pl = plan_for_total(__builtin_amdgcn_readlane(incl, 63), n_pieces, min_piece, seg_cost, xcd_skew, few);
     return wp;
 }
 

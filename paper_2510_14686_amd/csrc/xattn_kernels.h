@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "xattn_plan.h"
+
 namespace xattn {
 
 constexpr int kHeadDim = 128;
@@ -35,6 +37,7 @@ struct DecodeParams {
     int n_pieces;                    // pieces the token stream is cut into (upper bound on active ones)
     int parts;                       // pieces per workgroup: waves per workgroup / KV heads per workgroup
     int min_piece_tokens;
+    FewPieces few;                   // see plan_for_total
     int xcd_skew;                    // per mille: share taken from the odd XCDs' parts of the stream and given to the even ones
     int path;                        // kPathAuto, kPathVector or kPathMatrix
     int pv_mode;                     // matrix path: kPvBf16x2, kPvFp32 or kPvBf16
@@ -79,6 +82,7 @@ struct MlaParams {
     float* part_ml;                  // fp32 [slots, q_len * n_heads, 4]: (max, sum, sum of rounded weights, 1 / scale)
     int32_t* meta;                   // int32 [batch, 2]
     int n_pieces, min_piece_tokens;
+    FewPieces few;
     int xcd_skew;                    // as in DecodeParams
     int layout;                      // 0 automatic, 1 one 16-row tile per wave, 2 two tiles per wave
     int weight_mode;                 // softmax weights in the value product: 0 default (hi + lo bf16 parts where a key

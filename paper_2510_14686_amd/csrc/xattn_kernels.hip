@@ -22,13 +22,15 @@
 //     online softmax in fp32 (log2 domain); p.v by fp32 FMA.
 //   * matrix path (one or two tiles of 16 rows per wave; beyond 32 rows several workgroups share a piece.
 //     verify, 32 rows per KV head, 165109 tokens: one tile per wave, every piece read twice, 238.6 us; two
-//     tiles 145.4 us, of which about 30 are fixed: 38 MB of partial results): the K block is transposed
+//     tiles 129.7 us, of which about 20 are fixed: 38 MB of partial results): the K block is transposed
 //     through wave-private LDS into the MFMA operand layout, S^T = K Q^T by bf16 MFMA 16x16x32;
 //     softmax on the accumulator layout (a lane holds 4 keys of one row); O^T += V^T P^T by bf16 MFMA
 //     16x16x16 straight from the V registers (V never touches LDS), with p fed as hi + lo bf16 parts
 //     so that it keeps 16 significant bits.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "xattn_device.h"
 #include "xattn_kernels.h"
@@ -341,9 +343,12 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
         // The reference maximum moves only when a block exceeds it by more than 2^kLazyLog2 (weights reach
         // that at most, which costs fp32 sums and bf16's relative precision nothing), so the rescaling of
         // the accumulators runs about once per segment and not whenever one of 16 rows sees a new maximum.
+        // It is a whole number, so that another cut of the keys scales a weight by a power of two, which
+        // leaves its hi + lo parts as they are; with one bf16 per weight it is the maximum itself, so that a
+        // row's only key has the exact weight 1.
         const bool moves = mx > st[t].m + kLazyLog2;
         if (__builtin_amdgcn_ballot_w64(moves) != 0) {
-            const float m_new = moves ? mx : st[t].m;
+            const float m_new = moves ? (kPv == kPvBf16 ? mx : __builtin_ceilf(mx)) : st[t].m;
             const float alpha = moves ? fast_exp2(st[t].m - m_new) : 1.0f;
             st[t].m = m_new;
             st[t].l *= alpha;
@@ -570,7 +575,7 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     const int kvh = blockIdx.z * kMaxWavesPerBlock + wave - part * heads;
     if (kvh >= prm.n_kv_heads) return;
     const WavePlan wp = wave_plan(prm.kv_lens, nullptr, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kGqaSegCost,
-                                  prm.xcd_skew, lane, nullptr);
+                                  prm.xcd_skew, prm.few, lane, nullptr);
     const Plan& pl = wp.pl;
 
     // Piece index: consecutive workgroups go to different XCDs, so give each XCD one contiguous eighth of
@@ -580,15 +585,22 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     const int per_xcd = (pl.n_pieces + 7) >> 3;
     const int bid = blockIdx.x;
     const int rows_total = prm.group * prm.q_len;
-    const int n_groups = (rows_total + R - 1) / R;
+    const int slots_per_xcd = gridDim.x >> 3;
+    int rows = R;                                            // per wave
+    if constexpr (kTiles == 2) {
+        // When the pieces in use leave enough workgroups idle, every tile gets one of its own (35 rows, 53
+        // sequences of 6 to 100 tokens: 17.5 us in pairs, 10.0 us apart).
+        if (prm.parts * (slots_per_xcd / ((rows_total + 15) / 16)) >= per_xcd) rows = 16;
+    }
+    const int n_groups = (rows_total + rows - 1) / rows;
     const int slot_in_xcd = bid >> 3;
     const int set = n_groups == 1 ? slot_in_xcd : slot_in_xcd / n_groups;
     const int row_group = slot_in_xcd - set * n_groups;
-    const int sets = (int)(gridDim.x >> 3) / n_groups;       // workgroups of different pieces per XCD
+    const int sets = slots_per_xcd / n_groups;               // workgroups of different pieces per XCD
     const int p_local = part * sets + set;
     const int p = (bid & 7) * per_xcd + p_local;
     const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
-    const bool active = p_local < per_xcd && p < pl.n_pieces && s0 < s1;
+    const bool active = set < sets && p_local < per_xcd && p < pl.n_pieces && s0 < s1;
 
     if (blockIdx.z == 0 && threadIdx.x < 64) {
         // For the merge kernel: first partial slot and number of segments of every sequence, 64
@@ -604,8 +616,8 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
 
     Segment seg;
     seg.kvh = kvh;
-    seg.row0 = row_group * R;
-    seg.n_rows = rows_total - seg.row0 < R ? rows_total - seg.row0 : R;
+    seg.row0 = row_group * rows;
+    seg.n_rows = rows_total - seg.row0 < rows ? rows_total - seg.row0 : rows;
     // Next (piece, sequence) intersection of this piece, in stream order; false when the piece is done.
     auto next_seg = [&](Segment& out) {
         PieceSeg ps;
@@ -627,25 +639,30 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     };
     if constexpr (kMatrix) {
         char* lds_wave = lds + wave * kLdsPerWave;
-        Segment cur_seg;
-        if (uniform(next_seg(cur_seg)) == 0) return;
-        MatrixCtx<kTiles> cur;
-        matrix_begin(cur, prm, cur_seg, lane);
-        for (;;) {
-            MatrixState st[kTiles];
-            matrix_run<kPv, kTiles>(st, cur, prm, lane, lds_wave);
-            Segment nxt_seg;
-            const bool more = uniform(next_seg(nxt_seg)) != 0;
-            MatrixCtx<kTiles> nxt;
-            if (more) matrix_begin(nxt, prm, nxt_seg, lane);     // its loads go out before cur's stores
+        auto run_piece = [&](auto tiles) {
+            constexpr int kT = decltype(tiles)::value;
+            Segment cur_seg;
+            if (uniform(next_seg(cur_seg)) == 0) return;
+            MatrixCtx<kT> cur;
+            matrix_begin(cur, prm, cur_seg, lane);
+            for (;;) {
+                MatrixState st[kT];
+                matrix_run<kPv, kT>(st, cur, prm, lane, lds_wave);
+                Segment nxt_seg;
+                const bool more = uniform(next_seg(nxt_seg)) != 0;
+                MatrixCtx<kT> nxt;
+                if (more) matrix_begin(nxt, prm, nxt_seg, lane);     // its loads go out before cur's stores
 #pragma unroll
-            for (int t = 0; t < kTiles; ++t) {
-                if (more) matrix_finish<true>(st[t], cur.seg, t, prm, lane, lds_wave);
-                else matrix_finish<false>(st[t], cur.seg, t, prm, lane, lds_wave);
+                for (int t = 0; t < kT; ++t) {
+                    if (more) matrix_finish<true>(st[t], cur.seg, t, prm, lane, lds_wave);
+                    else matrix_finish<false>(st[t], cur.seg, t, prm, lane, lds_wave);
+                }
+                if (!more) break;
+                cur = nxt;
             }
-            if (!more) break;
-            cur = nxt;
-        }
+        };
+        if (kTiles == 2 && rows == 16) run_piece(std::integral_constant<int, 1>());
+        else run_piece(std::integral_constant<int, kTiles>());
     } else {
         Segment s2;
         while (next_seg(s2)) vector_segment<R>(prm, s2, lane);

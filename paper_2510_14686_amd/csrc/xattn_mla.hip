@@ -677,7 +677,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     const int T = prm.q_len, H = prm.n_heads, rows_total = T * H;
     SeqWindow win;
     const WavePlan wp = wave_plan(prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kMlaSegCost,
-                                  prm.xcd_skew, lane, &win);
+                                  prm.xcd_skew, prm.few, lane, &win);
     const Plan& pl = wp.pl;
     const int per_xcd = (pl.n_pieces + 7) >> 3;
     // Workgroup ids go round-robin over the 8 XCDs.  Of an XCD's workgroups, consecutive ones are the
@@ -928,7 +928,7 @@ __global__ __launch_bounds__(256 * RT) void mla_rows_kernel(MlaParams prm) {
     const int T = prm.q_len, H = prm.n_heads, rows_total = T * H;
     SeqWindow win;
     const WavePlan wp = wave_plan(prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kRowsSegCost,
-                                  prm.xcd_skew, lane, &win);
+                                  prm.xcd_skew, prm.few, lane, &win);
     const Plan& pl = wp.pl;
     const int per_xcd = (pl.n_pieces + 7) >> 3;
     const int bid = blockIdx.x;

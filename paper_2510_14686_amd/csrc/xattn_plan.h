@@ -31,7 +31,7 @@ constexpr int kMaxPieces = 65536;
 
 struct Plan {
     int total;      // N: positions of the whole stream
-    int n_pieces;   // pieces in use: min(launched pieces, N / minimum piece size), at least 1
+    int n_pieces;   // pieces in use: see plan_for_total
     int seg_cost;
     int xcd_skew;   // per mille; see piece_bound
 };
@@ -42,8 +42,16 @@ XATTN_HD int clamp_len(int v) { return v > 0 ? v : 0; }
 // Stream positions of a sequence of `len` tokens (any sign).
 XATTN_HD int stream_len(int len, int seg_cost) { return len > 0 ? len + seg_cost : 0; }
 
-XATTN_HD Plan plan_for_total(int total, int n_pieces, int min_piece, int seg_cost, int xcd_skew = 0) {
+// A short stream is cut finer than min_piece, down to few_min positions, into up to few_pieces pieces: as
+// long as that only spreads it over idle compute units, shorter pieces finish earlier.
+struct FewPieces {
+    int pieces, min_piece;
+};
+XATTN_HD Plan plan_for_total(int total, int n_pieces, int min_piece, int seg_cost, int xcd_skew = 0, FewPieces few = {0, 1}) {
     int n = total / (min_piece > 0 ? min_piece : 1);
+    int n_few = total / few.min_piece;
+    n_few = n_few < few.pieces ? n_few : few.pieces;
+    n = n < n_few ? n_few : n;
     n = n < 1 ? 1 : n;
     Plan pl;
     pl.total = total;

@@ -33,10 +33,14 @@ def _case(lens, T, Hq, Hkv):
 # rows per KV head: 1 and 3 (vector path), 4, 16, 17, 32 (one and two tiles), 33 and 64 (two workgroups per piece)
 @pytest.mark.parametrize("T,group", [(1, 1), (3, 1), (1, 4), (4, 4), (1, 17), (4, 8), (3, 11), (16, 4)])
 @pytest.mark.parametrize("Hkv", [1, 2, 3, 8])
-def test_pieces_and_rows_per_workgroup(T, group, Hkv):
-    """More pieces than compute units, so that every wave of a workgroup has a piece of its own."""
+@pytest.mark.parametrize("lens", [(5000, 16, 37, 3333), (700, 16, 37, 300), (17,)])
+def test_pieces_and_rows_per_workgroup(T, group, Hkv, lens):
+    """More pieces than compute units, so that every wave of a workgroup has a piece of its own; and short
+    streams in the default partition: pieces of 16 keys, a workgroup for every 16 query rows."""
+    import paper_2510_14686_amd as xa
     from gpu_util import check_against_oracle
-    lens = [5000, T, 37, 3333]
+    if sum(lens) < 2000:
+        xa.xattn_configure(xa.XATTN_CFG_MIN_PIECE_TOKENS, 0)
     q, ks, vs = _case(lens, T, group * Hkv, Hkv)
     check_against_oracle(q, ks, vs, lens, SCALE, what="T=%d group=%d Hkv=%d" % (T, group, Hkv))
 
