@@ -49,17 +49,19 @@ __device__ __forceinline__ float row16_sum(float x) {
     x += dpp_f<0x140>(x);   // row_mirror
     return x;
 }
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+// Inclusive sum over the lanes: within rows of 16 by row shifts (lanes shifted in from outside read 0), then
+// the rows' totals by the row broadcasts.  No LDS round trips, of which six would be in every prologue.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int dpp_add_i(int v) {
+    return v + __builtin_amdgcn_update_dpp(0, v, kCtrl, kRows, 0xf, true);
 }
-__device__ __forceinline__ int wave_incl_scan_i(int v, int lane) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int n = __shfl_up(v, o, 64);
-        if (lane >= o) v += n;
-    }
+__device__ __forceinline__ int wave_incl_scan_i(int v) {
+    v = dpp_add_i<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_add_i<0x112, 0xf>(v);   // row_shr:2
+    v = dpp_add_i<0x114, 0xf>(v);   // row_shr:4
+    v = dpp_add_i<0x118, 0xf>(v);   // row_shr:8
+    v = dpp_add_i<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add_i<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
     return v;
 }
 __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
@@ -238,7 +240,7 @@ __device__ __forceinline__ WavePlan wave_plan(const int32_t* __restrict__ kv_len
         case 5: mine = chunk_positions<8>(rl, first, seg_cost); break;
         default: mine = chunk_positions<16>(rl, first, seg_cost); break;   // batch <= 4096 (checked by the host)
     }
-    const int incl = wave_incl_scan_i(mine, lane);
+    const int incl = wave_incl_scan_i(mine);
     wp.mine = mine;
     wp.excl = incl - mine;
     wp.pl = plan_for_total(__builtin_amdgcn_readlane(incl, 63), n_pieces, min_piece, seg_cost, xcd_skew, few);
@@ -267,7 +269,7 @@ __device__ __forceinline__ void wave_locate(const WavePlan& wp, const int32_t* _
         const __amdgpu_buffer_rsrc_t rl = make_rsrc(kv_lens, (uint32_t)batch * 4u);
         v = lane < wp.chunk ? stream_len(__builtin_amdgcn_raw_buffer_load_b32(rl, (base + lane) * 4, 0, 0), wp.pl.seg_cost) : 0;
     }
-    const int incl = wave_incl_scan_i(v, lane);
+    const int incl = wave_incl_scan_i(v);
     const unsigned long long hit2 = __ballot(off >= incl - v && off < incl);
     const int ln2 = hit2 ? __builtin_ctzll(hit2) : 0;
     b = __builtin_amdgcn_readfirstlane(base + ln2);
@@ -283,7 +285,7 @@ __device__ __forceinline__ void wave_write_meta(const WavePlan& wp, const int32_
     const __amdgpu_buffer_rsrc_t rl = make_rsrc(kv_lens, (uint32_t)batch * 4u);
     const int len = clamp_len(__builtin_amdgcn_raw_buffer_load_b32(rl, seq * 4, 0, 0));
     const int v = stream_len(len, wp.pl.seg_cost);
-    const int before = wave_incl_scan_i(v, lane) - v;                       // within the group
+    const int before = wave_incl_scan_i(v) - v;                       // within the group
     const int chunk_first = __shfl(wp.excl, (seq >> wp.chunk_log2) & 63, 64);
     const int start = chunk_first + before - __shfl(before, lane & ~(wp.chunk - 1), 64);
     if (seq < batch) {

@@ -700,7 +700,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
 
     Walk walk;
     wave_locate(wp, prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, s0, lane, &win, walk.b, walk.j);
-    walk.remaining = s1 - s0;
+    walk.remaining = uniform(s1 - s0);
 
     // Row n of tile rt of this wave: row index within the sequence's T * H rows.
     const int wave_row0 = row_group * (16 * RT * NW) + wave * (16 * RT);
@@ -718,11 +718,11 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     };
 
     PieceSeg ps;
-    while (next_segment(walk, prm.batch, pl.seg_cost,
-                        [&](int bb) { return window_len(win, prm.kv_lens, bb); }, ps)) {
-        const int b = ps.b, L = ps.L, j0 = ps.j0, j1 = ps.j1;
-        const bool whole = ps.whole;
-        const long slot = (long)p + b;
+    while (uniform(next_segment(walk, prm.batch, pl.seg_cost,
+                                [&](int bb) { return window_len(win, prm.kv_lens, bb); }, ps))) {
+        const int b = uniform(ps.b), L = uniform(ps.L), j0 = uniform(ps.j0), j1 = uniform(ps.j1);
+        const bool whole = uniform(ps.whole) != 0;
+        const long slot = (long)uniform(p) + b;
         const unsigned long long cbytes = (unsigned long long)L * kRowB;
         const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, prm.c_ptrs, b);
         // raw buffer descriptor: base, no stride, bytes, 32-bit raw format
@@ -730,7 +730,9 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
                             (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(caddr >> 32) & 0xffffu)),
                             cbytes > 0xffffffffull ? 0xffffffffu : (uint32_t)cbytes, 0x00020000u};
 
-        // Q operand: lane (kb, n) holds columns 32 step + 8 kb .. + 7 of row n of each tile.
+        // Q operand: lane (kb, n) holds columns 32 step + 8 kb .. + 7 of row n of each tile; rows past the last
+        // lie past the end of the descriptor and read as zero.
+        const __amdgpu_buffer_rsrc_t rq = make_rsrc(prm.q + (long)b * rows_total * kDqk, (uint32_t)rows_total * kRowB);
         bf16x8_t qop[RT][kQRegSteps];
         int lim[RT];
         MlaTile st[RT];
@@ -738,11 +740,9 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
         for (int rt = 0; rt < RT; ++rt) {
             const int row = wave_row0 + 16 * rt + n;
             const bool row_ok = row < rows_total;
-            const long qrow = (long)b * rows_total + (row_ok ? row : 0);
 #pragma unroll
             for (int step = 0; step < kQSteps; ++step) {
-                u32x4_t qv = {0u, 0u, 0u, 0u};
-                if (row_ok) qv = *reinterpret_cast<const u32x4_t*>(prm.q + qrow * kDqk + (4 * step + kb) * 8);
+                const u32x4_t qv = __builtin_amdgcn_raw_buffer_load_b128(rq, row * kRowB + kb * 16 + 64 * step, 0, 0);
                 if (step < kQRegSteps) qop[rt][step < kQRegSteps ? step : 0] = __builtin_bit_cast(bf16x8_t, qv);
                 else *reinterpret_cast<u32x4_t*>(q_lds + rt * kQLdsWave + (step - kQRegSteps) * 1024) = qv;
             }
@@ -858,11 +858,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
             // The stores go through a buffer descriptor over the sequence's (or slot's) rows: 32-bit
             // offsets, and rows past rows_total fall outside and are dropped, so the loop has no branch.
             uint16_t* dst = whole ? prm.out + (long)b * rows_total * kDv : prm.part_o + slot * rows_total * kDv;
-            const uint64_t daddr = (uint64_t)(uintptr_t)dst;
-            const __amdgpu_buffer_rsrc_t rd = make_rsrc(
-                reinterpret_cast<void*>(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(daddr >> 32)) << 32) |
-                                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)daddr)),
-                (uint32_t)rows_total * (kDv * 2));
+            const __amdgpu_buffer_rsrc_t rd = make_rsrc(uniform(static_cast<void*>(dst)), (uint32_t)rows_total * (kDv * 2));
             const uint32_t lane_dst = (uint32_t)((tile_row0 + (lane >> 5)) * (kDv * 2) + (lane & 31) * 16);
             const char* lane_stage = stage + (lane >> 5) * kStagePitch + (lane & 31) * 16;
 #pragma unroll
