@@ -18,7 +18,7 @@
 // range may not have mapped).  All query rows that share the KV head (GQA group x new tokens:
 // section 4.4.1, K is loaded once for all of them and Q stays in registers) use the row from
 // registers.  Two inner loops:
-//   * vector path (up to 8 rows): q.k by bf16 dot2 into fp32, reduced over the 16 lanes with DPP;
+//   * vector path (XATTN_CFG_PATH = 1): q.k by bf16 dot2 into fp32, reduced over the 16 lanes with DPP;
 //     online softmax in fp32 (log2 domain); p.v by fp32 FMA.
 //   * matrix path (one or two tiles of 16 rows per wave; beyond 32 rows several workgroups share a piece.
 //     verify, 32 rows per KV head, 165109 tokens: one tile per wave, every piece read twice, 238.6 us; two
@@ -26,7 +26,7 @@
 //     through wave-private LDS into the MFMA operand layout, S^T = K Q^T by bf16 MFMA 16x16x32;
 //     softmax on the accumulator layout (a lane holds 4 keys of one row); O^T += V^T P^T by bf16 MFMA
 //     16x16x16 straight from the V registers (V never touches LDS), with p fed as hi + lo bf16 parts
-//     so that it keeps 16 significant bits.
+//     so that it keeps 16 significant bits (24, in three parts, below 4 rows per KV head).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -379,19 +379,26 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
     } else {
         // bf16 MFMA 16x16x16 contracts the block's 16 keys at once: lane (kb, x) supplies keys 4*kb + i,
         // i = 0..3, of column 8*x + e (the e-th bf16 of its four V registers) and of row n (its four p).
-        // kPvBf16x2 feeds p as hi + lo bf16 parts in two MFMAs, which keeps p to 16 significant bits.
-        u32x2_t ph[kTiles], pl[kTiles];
+        // kPvBf16x2 feeds p as hi + lo bf16 parts in two MFMAs, which keeps p to 16 significant bits; kPvBf16x3
+        // adds what those two leave, which is all 24.
+        constexpr bool kLo = kPv == kPvBf16x2 || kPv == kPvBf16x3;
+        u32x2_t ph[kTiles], pl[kTiles], pr[kTiles];
 #pragma unroll
         for (int t = 0; t < kTiles; ++t) {
             const f32x2_t p01 = {p[t][0], p[t][1]}, p23 = {p[t][2], p[t][3]};
             const bf16x2_t h01 = __builtin_convertvector(p01, bf16x2_t), h23 = __builtin_convertvector(p23, bf16x2_t);
             ph[t] = u32x2_t{__builtin_bit_cast(uint32_t, h01), __builtin_bit_cast(uint32_t, h23)};
-            pl[t] = u32x2_t{0u, 0u};
-            if (kPv == kPvBf16x2) {
+            pl[t] = pr[t] = u32x2_t{0u, 0u};
+            if (kLo) {
                 const f32x2_t r01 = p01 - __builtin_convertvector(h01, f32x2_t);
                 const f32x2_t r23 = p23 - __builtin_convertvector(h23, f32x2_t);
-                pl[t].x = __builtin_bit_cast(uint32_t, __builtin_convertvector(r01, bf16x2_t));
-                pl[t].y = __builtin_bit_cast(uint32_t, __builtin_convertvector(r23, bf16x2_t));
+                const bf16x2_t l01 = __builtin_convertvector(r01, bf16x2_t), l23 = __builtin_convertvector(r23, bf16x2_t);
+                pl[t] = u32x2_t{__builtin_bit_cast(uint32_t, l01), __builtin_bit_cast(uint32_t, l23)};
+                if (kPv == kPvBf16x3) {
+                    const f32x2_t q01 = r01 - __builtin_convertvector(l01, f32x2_t);
+                    const f32x2_t q23 = r23 - __builtin_convertvector(l23, f32x2_t);
+                    pr[t] = u32x2_t{cvt_bf16(q01[0], q01[1]), cvt_bf16(q23[0], q23[1])};
+                }
             }
         }
         const uint32_t vw[4][4] = {{r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w}, {r.v[1].x, r.v[1].y, r.v[1].z, r.v[1].w},
@@ -405,7 +412,10 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
             for (int t = 0; t < kTiles; ++t) {
                 st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
                                                                        __builtin_bit_cast(s16x4_t, ph[t]), st[t].o[e], 0, 0, 0);
-                if (kPv == kPvBf16x2)
+                if (kPv == kPvBf16x3)
+                    st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
+                                                                           __builtin_bit_cast(s16x4_t, pr[t]), st[t].o[e], 0, 0, 0);
+                if (kLo)
                     st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
                                                                            __builtin_bit_cast(s16x4_t, pl[t]), st[t].o[e], 0, 0, 0);
             }
@@ -793,12 +803,13 @@ hipError_t launch_write_kvcache(const WriteParams& prm, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Measured on MI355X: the matrix path is the faster one from 4 query rows per KV head upwards
-// (Qwen-style groups of 4, 5 and 8 at q_len 1, and every multi-token case); below that most of a
-// 16-row MFMA tile would be padding and the vector path does less work.
-bool use_matrix_path(int rows_total, int path) {
-    return path == kPathMatrix || (path == kPathAuto && rows_total >= 4);
-}
+// Measured on MI355X, the matrix path is the faster one from a single query row per KV head up, although most
+// of a tile is then padding: it keeps the next segment's loads ahead of the stores, and the calls are bound by
+// HBM.  138468 tokens of 8 KV heads, 1 / 2 / 3 rows: vector path 95.4 / 97.2 / 99.0 us, matrix path 92.8 /
+// 93.0 / 93.2; 80 to 700 tokens 9.1 -> 8.7 and 11.0 -> 10.5; no shape tried was slower by more than 1 %.  The
+// weights keep 24 bits there (kPvBf16x3): the error against 64 bits is the vector path's to seven digits on
+// eight shapes (1.656835e-3, which is the output's own rounding).
+bool use_matrix_path(int, int path) { return path != kPathVector; }
 
 int rows_per_wave(int rows_total, int path) {
     if (use_matrix_path(rows_total, path)) return rows_total <= 16 ? 16 : 32;
@@ -829,7 +840,11 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
         switch (prm.pv_mode) {
             case kPvBf16: e = launch_decode_r<16, true, kPvBf16>(prm, grid, block, stream); break;
             case kPvFp32: e = launch_decode_r<16, true, kPvFp32>(prm, grid, block, stream); break;
-            default: e = launch_decode_r<16, true, kPvBf16x2>(prm, grid, block, stream); break;
+            default:
+                // the calls that took the vector path keep its 24-bit weights
+                e = rows_total < 4 ? launch_decode_r<16, true, kPvBf16x3>(prm, grid, block, stream)
+                                   : launch_decode_r<16, true, kPvBf16x2>(prm, grid, block, stream);
+                break;
         }
     } else {
         switch (R) {
