@@ -20,6 +20,7 @@ constexpr int kMaxBatch = 4096;
 constexpr int kMaxQLen = 16;
 constexpr int kMaxRows = 64;
 constexpr int kDefaultMinPieceTokens = 64;
+constexpr size_t kFewBytes = 8 << 20;      // partial results up to which a short GQA call is cut into one-block pieces
 
 // The library's own workspaces: one per (device, stream), so that calls on different streams of a
 // device may overlap.  A buffer that has become too small is RETIRED, not freed: a HIP graph recorded
@@ -282,8 +283,11 @@ int decode_call(const char* who, FixedWorkspaceFn fixed_workspace, const void* q
     prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : kDefaultMinPieceTokens;
     if (prm.min_piece_tokens < 16) prm.min_piece_tokens = 16;      // one 16-key block at least
     // One block per piece as long as every piece gets a compute unit of its own: 695 tokens 11.4 -> 8.9 us,
-    // 207 tokens of 16 KV heads 13.7 -> 11.8; 64-token pieces beyond that (smaller ones only add merge work).
-    prm.few = g_cfg_min_piece > 0 ? FewPieces{0, 1} : FewPieces{d->n_cu, 16};
+    // 207 tokens of 16 KV heads 13.7 -> 11.8; 64-token pieces beyond that (smaller ones only add merge work), and
+    // where the partial results of many query rows would come to more than kFewBytes (62 sequences of 42 to
+    // 84 tokens, 24 rows of 8 KV heads: 24.1 us in 64-token pieces, 28.1 in 32 MB of one-block pieces).
+    const int few_slots = (int)(kFewBytes / ((size_t)q_len * n_q_heads * (kHeadDim + 2) * sizeof(float))) - batch;
+    prm.few = g_cfg_min_piece > 0 || few_slots < 1 ? FewPieces{0, 1} : FewPieces{few_slots < d->n_cu ? few_slots : d->n_cu, 16};
     prm.xcd_skew = g_cfg_xcd_skew > 0 ? g_cfg_xcd_skew - 1 : kDefaultXcdSkewGqa;
     prm.path = g_cfg_path;
     prm.pv_mode = g_cfg_pv_mode;
