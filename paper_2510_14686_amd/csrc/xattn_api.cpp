@@ -70,9 +70,9 @@ struct DecodeSplit {
 };
 // One workgroup per compute unit.  A wave streams one KV head, so with fewer than eight KV heads a
 // workgroup takes several pieces to keep eight waves' loads in flight (two KV heads, 138468 tokens: 46.6 us
-// with one piece per workgroup, 32.5 us with four), as long as the partial results stay within the fixed scratch array, which also bounds what the merge
-// has to read back.  Several workgroups share a piece when a wave cannot hold all query rows of its KV
-// head: fewer pieces then, as in mla_pieces_for.
+// with one piece per workgroup, 32.0 us with four), as long as the partial results stay within the fixed
+// scratch array, which also bounds what the merge has to read back.  Several workgroups share a piece when a
+// wave cannot hold all query rows of its KV head: fewer pieces then, as in mla_pieces_for.
 DecodeSplit decode_split(int n_cu, int batch, int q_len, int n_q_heads, int n_kv_heads) {
     const int rows = n_q_heads / n_kv_heads * q_len;
     auto bytes_for = [&](int pieces) { return layout_for(batch, q_len, n_q_heads, pieces).total; };
