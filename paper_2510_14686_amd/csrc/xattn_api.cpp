@@ -202,7 +202,10 @@ int acquire_workspace(DeviceState* d, size_t total, hipStream_t stream, const ch
         const size_t want = total + total / 4;
         void* fresh = nullptr;
         const hipError_t e = hipMalloc(&fresh, want);
-        if (e != hipSuccess) return fail_hip(e, "hipMalloc(workspace)");
+        if (e != hipSuccess) {
+            (void)hipGetLastError();      // reported here: the next launch must not find it recorded
+            return fail_hip(e, "hipMalloc(workspace)");
+        }
         // Work already enqueued, and graphs already recorded, keep using the old buffer.
         if (w->ptr) d->retired.push_back(w->ptr);
         w->ptr = fresh;
