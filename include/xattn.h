@@ -93,7 +93,8 @@ int xattn_decode(const void* q, const void* const* k_ptrs, const void* const* v_
 /*
  * xattn_decode for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels, partition and results
- * (bit for bit) as xattn_decode; the partial results of split sequences go to a device array of
+ * (bit for bit) as xattn_decode on a library-owned workspace of the usual size or on a caller's of
+ * xattn_workspace_bytes; the partial results of split sequences go to a device array of
  * XATTN_NOALLOC_SCRATCH_BYTES that is part of the library's code object (every GPU the library runs
  * on holds its copy until the process ends) instead of a workspace from hipMalloc.  The call
  * allocates nothing: no hipMalloc, hipFree or event creation; xattn_set_workspace and
@@ -145,9 +146,13 @@ int xattn_mla_decode(const void* q, const void* const* c_ptrs, const int32_t* kv
  * xattn_set_workspace:       hand the library a DEVICE buffer (256-byte aligned) for the current
  *                            device, used by calls on every stream; the caller keeps ownership and
  *                            keeps it alive while calls are in flight or graphs that recorded them
- *                            exist.  (NULL, 0) returns to the library-owned workspaces: one per
+ *                            exist.  xattn_decode with fewer than 8 KV heads also takes a buffer that
+ *                            is smaller than xattn_workspace_bytes but holds one piece per compute unit,
+ *                            and then cuts the keys into fewer pieces (slower; the result differs by
+ *                            the order of the fp32 sums).  (NULL, 0) returns to the library-owned workspaces: one per
  *                            stream (up to 64 streams per device), allocated with hipMalloc by the
- *                            first call on the stream that needs more than it has.  An outgrown
+ *                            first call on the stream that needs more than it has, 32 MiB at least
+ *                            (or, where that much cannot be had, what the call needs).  An outgrown
  *                            buffer is not freed before the process ends, because work in flight and
  *                            recorded graphs may still use it; growth is geometric, so the outgrown
  *                            buffers of a stream add up to less than four times its live one.

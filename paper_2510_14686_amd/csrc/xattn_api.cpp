@@ -26,13 +26,16 @@ constexpr size_t kFewBytes = 8 << 20;      // partial results up to which a shor
 // device may overlap.  A buffer that has become too small is RETIRED, not freed: a HIP graph recorded
 // earlier may hold its address in the arguments of its kernel nodes, and replaying such a graph must
 // stay valid.  Buffers grow geometrically, so the retired ones add up to less than the live one
-// times four; all of them are released when the process ends.
+// times four; all of them are released when the process ends.  None is smaller than kLeastWorkspace: any
+// split that decode_split may choose then fits the workspace a stream has, whichever call made it, so a
+// call's partition (and the bits of its result) do not depend on what ran before it.
 struct StreamWorkspace {
     hipStream_t stream = nullptr;
     void* ptr = nullptr;
     size_t bytes = 0;
 };
 constexpr int kMaxStreamWorkspaces = 64;
+constexpr size_t kLeastWorkspace = XATTN_NOALLOC_SCRATCH_BYTES;
 
 struct DeviceState {
     int n_cu = 0;
@@ -66,29 +69,28 @@ WorkspaceLayout layout_for(int batch, int q_len, int n_q_heads, int n_pieces);
 // How a GQA call's keys are cut: the number of pieces, and how many of them a workgroup holds.
 struct DecodeSplit {
     int pieces, parts;
-    size_t bytes;         // of workspace: for one piece per compute unit at least
 };
+// What every GQA call needs of workspace: one piece per compute unit (or the configured pieces).
+size_t decode_least_bytes(int n_cu, int batch, int q_len, int n_q_heads) {
+    return layout_for(batch, q_len, n_q_heads, g_cfg_pieces > 0 ? g_cfg_pieces : n_cu).total;
+}
 // One workgroup per compute unit.  A wave streams one KV head, so with fewer than eight KV heads a
 // workgroup takes several pieces to keep eight waves' loads in flight (two KV heads, 138468 tokens: 46.6 us
-// with one piece per workgroup, 32.0 us with four), as long as the partial results stay within the fixed
-// scratch array, which also bounds what the merge has to read back.  Several workgroups share a piece when a
-// wave cannot hold all query rows of its KV head: fewer pieces then, as in mla_pieces_for.
-DecodeSplit decode_split(int n_cu, int batch, int q_len, int n_q_heads, int n_kv_heads) {
+// with one piece per workgroup, 32.0 us with four), as long as the partial results stay within the workspace
+// and within the size of the fixed scratch array, which also bounds what the merge has to read back.  Several
+// workgroups share a piece when a wave cannot hold all query rows of its KV head: fewer pieces then, as in
+// mla_pieces_for.  `have` bytes of workspace: decode_least_bytes at least.
+DecodeSplit decode_split(int n_cu, int batch, int q_len, int n_q_heads, int n_kv_heads, size_t have) {
     const int rows = n_q_heads / n_kv_heads * q_len;
-    auto bytes_for = [&](int pieces) { return layout_for(batch, q_len, n_q_heads, pieces).total; };
-    DecodeSplit s{g_cfg_pieces > 0 ? g_cfg_pieces : n_cu, 1, bytes_for(g_cfg_pieces > 0 ? g_cfg_pieces : n_cu)};
-    const int per_wave = rows_per_wave(rows, g_cfg_path), groups = (rows + per_wave - 1) / per_wave;
-    if (g_cfg_pieces == 0 && groups > 1) s.pieces = n_cu / groups / 8 * 8 < 8 ? 8 : n_cu / groups / 8 * 8;
     const int most = n_kv_heads < kMaxWavesPerBlock ? kMaxWavesPerBlock / n_kv_heads : 1;
-    if (g_cfg_pieces > 0) {
-        s.parts = most;
-        return s;
-    }
-    for (int parts = most; parts > 1; --parts) {
-        const size_t bytes = bytes_for(s.pieces * parts);
-        if (bytes <= XATTN_NOALLOC_SCRATCH_BYTES) return DecodeSplit{s.pieces * parts, parts, bytes > s.bytes ? bytes : s.bytes};
-    }
-    return s;
+    if (g_cfg_pieces > 0) return DecodeSplit{g_cfg_pieces, most};
+    const int per_wave = rows_per_wave(rows, g_cfg_path), groups = (rows + per_wave - 1) / per_wave;
+    const int shared = n_cu / groups / 8 * 8;
+    const int pieces = groups == 1 ? n_cu : shared < 8 ? 8 : shared;
+    if (have > XATTN_NOALLOC_SCRATCH_BYTES) have = XATTN_NOALLOC_SCRATCH_BYTES;
+    int parts = most;
+    while (parts > 1 && layout_for(batch, q_len, n_q_heads, pieces * parts).total > have) --parts;
+    return DecodeSplit{pieces * parts, parts};
 }
 
 // Pieces of a latent-KV call: as many as give one workgroup per compute unit when a piece is worked
@@ -174,12 +176,13 @@ int device_state(DeviceState** out, int* dev_out) {
 
 // A workspace of at least `total` bytes for a call on `stream`: the caller's if one was handed
 // over, else the library's own for that stream, grown when needed (never while `stream` is being
-// captured: growing allocates).
-int acquire_workspace(DeviceState* d, size_t total, hipStream_t stream, const char* who, char** ws_out) {
+// captured: growing allocates).  have_out: the bytes it holds.
+int acquire_workspace(DeviceState* d, size_t total, hipStream_t stream, const char* who, char** ws_out, size_t* have_out) {
     if (d->user_ws) {
         if (d->user_bytes < total)
             return fail(XATTN_ENOMEM, "%s: caller workspace has %zu bytes, this call needs %zu", who, d->user_bytes, total);
         *ws_out = static_cast<char*>(d->user_ws);
+        *have_out = d->user_bytes;
         return XATTN_OK;
     }
     StreamWorkspace* w = nullptr;
@@ -199,9 +202,15 @@ int acquire_workspace(DeviceState* d, size_t total, hipStream_t stream, const ch
             d->owned.push_back(StreamWorkspace{stream, nullptr, 0});
             w = &d->owned.back();
         }
-        const size_t want = total + total / 4;
+        const size_t grown = total + total / 4;
+        size_t want = grown > kLeastWorkspace ? grown : kLeastWorkspace;
         void* fresh = nullptr;
-        const hipError_t e = hipMalloc(&fresh, want);
+        hipError_t e = hipMalloc(&fresh, want);
+        if (e != hipSuccess && want > grown) {      // device memory is short: what this call needs will do
+            (void)hipGetLastError();
+            want = grown;
+            e = hipMalloc(&fresh, want);
+        }
         if (e != hipSuccess) {
             (void)hipGetLastError();      // reported here: the next launch must not find it recorded
             return fail_hip(e, "hipMalloc(workspace)");
@@ -212,6 +221,7 @@ int acquire_workspace(DeviceState* d, size_t total, hipStream_t stream, const ch
         w->bytes = want;
     }
     *ws_out = static_cast<char*>(w->ptr);
+    *have_out = w->bytes;
     return XATTN_OK;
 }
 
@@ -250,18 +260,13 @@ int decode_call(const char* who, FixedWorkspaceFn fixed_workspace, const void* q
     st = device_state(&d, &dev);
     if (st != XATTN_OK) return st;
 
-    DecodeSplit split = decode_split(d->n_cu, batch, q_len, n_q_heads, n_kv_heads);
+    const size_t least = decode_least_bytes(d->n_cu, batch, q_len, n_q_heads);
     char* ws = nullptr;
-    auto acquire = [&] {
-        return fixed_workspace ? fixed_workspace(who, dev, split.bytes, &ws)
-                               : acquire_workspace(d, split.bytes, static_cast<hipStream_t>(stream), who, &ws);
-    };
-    st = acquire();
-    if (st != XATTN_OK && g_cfg_pieces == 0 && split.parts > 1) {      // a workspace for one piece per compute unit will do
-        split = {split.pieces / split.parts, 1, layout_for(batch, q_len, n_q_heads, d->n_cu).total};
-        st = acquire();
-    }
+    size_t have = XATTN_NOALLOC_SCRATCH_BYTES;
+    st = fixed_workspace ? fixed_workspace(who, dev, least, &ws)
+                         : acquire_workspace(d, least, static_cast<hipStream_t>(stream), who, &ws, &have);
     if (st != XATTN_OK) return st;
+    const DecodeSplit split = decode_split(d->n_cu, batch, q_len, n_q_heads, n_kv_heads, have);
     const WorkspaceLayout w = layout_for(batch, q_len, n_q_heads, split.pieces);
 
     DecodeParams prm;
@@ -344,7 +349,9 @@ size_t xattn_workspace_bytes(int batch, int q_len, int n_q_heads, int n_kv_heads
     // Upper bound over the automatic piece count of any supported device and the configured one.
     DeviceState* d = nullptr;
     const int n_cu = g_cfg_pieces == 0 && device_state(&d, nullptr) == XATTN_OK ? d->n_cu : 256;
-    return decode_split(n_cu, batch, q_len, n_q_heads, n_kv_heads).bytes;
+    const size_t least = decode_least_bytes(n_cu, batch, q_len, n_q_heads);
+    const size_t split = layout_for(batch, q_len, n_q_heads, decode_split(n_cu, batch, q_len, n_q_heads, n_kv_heads, SIZE_MAX).pieces).total;
+    return split > least ? split : least;
 }
 
 size_t xattn_mla_workspace_bytes(int batch, int q_len, int n_heads, int d_latent, int d_rope) {
@@ -413,7 +420,8 @@ int xattn_mla_decode(const void* q, const void* const* c_ptrs, const int32_t* kv
     const int n_pieces = mla_pieces_for(d->n_cu, q_len, n_heads);
     const MlaWorkspaceLayout w = mla_layout_for(batch, q_len, n_heads, n_pieces);
     char* ws = nullptr;
-    st = acquire_workspace(d, w.total, static_cast<hipStream_t>(stream), "xattn_mla_decode", &ws);
+    size_t have = 0;
+    st = acquire_workspace(d, w.total, static_cast<hipStream_t>(stream), "xattn_mla_decode", &ws, &have);
     if (st != XATTN_OK) return st;
 
     MlaParams prm;

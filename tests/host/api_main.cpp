@@ -5,7 +5,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
-#include <cstring>
+#include <string>
 #include <vector>
 
 #include "../../include/xattn.h"
@@ -94,6 +94,13 @@ static bool fits(size_t bytes) {
            reinterpret_cast<const char*>(p.part_o) + slots * rows * 512 <= base + bytes;
 }
 
+template <typename Fn>
+static bool fail_text_stays(Fn fn) {
+    const std::string before = xattn_last_error();
+    fn();
+    return before == xattn_last_error();
+}
+
 // A call whose allocation fails reports it and leaves nothing recorded: the next call works.
 static void a_failed_allocation_fails_one_call() {
     g_free = 0;
@@ -120,9 +127,82 @@ static void a_call_runs_on_what_can_be_allocated() {
     g_free = (size_t)1 << 40;
 }
 
+// The split of a call follows from its shape alone on the library's workspaces: whatever ran on the stream
+// before, eager or captured, and the same as in xattn_decode_noalloc's fixed array.
+static size_t g_fixed_asked;
+static int fixed_workspace(const char*, int, size_t bytes, char** ws) {
+    g_fixed_asked = bytes;
+    *ws = reinterpret_cast<char*>((uintptr_t)1 << 60);
+    return XATTN_OK;
+}
+static void the_split_does_not_depend_on_earlier_calls() {
+    static int dummy __attribute__((aligned(16)));
+    void** const ptrs = reinterpret_cast<void**>(&dummy);
+    CHECK(xattn::decode_call("noalloc", fixed_workspace, &dummy, ptrs, ptrs, &dummy, 64, 1, 8, 2, 128, 0.125f, &dummy, nullptr, nullptr) == XATTN_OK);
+    const int pieces = xattn::g_prm.n_pieces, parts = xattn::g_prm.parts;
+    CHECK(parts == 4 && pieces == 1024 && fits(XATTN_NOALLOC_SCRATCH_BYTES));
+    CHECK(fail_text_stays([&] {
+        // first call of a stream; a latent-KV call, a small call or a large one before it; captured or not
+        for (int first = 0; first < 4; ++first)
+            for (int captured = 0; captured < (first == 0 ? 1 : 2); ++captured) {
+                const intptr_t stream = 100 + 2 * first + captured;
+                if (first == 1) CHECK(mla_decode(stream, 1, 1, 1) == XATTN_OK);
+                if (first == 2) CHECK(decode(stream, 1, 1, 8, 8) == XATTN_OK);
+                if (first == 3) CHECK(decode(stream, 512, 8, 64, 8) == XATTN_OK);
+                const size_t allocs = g_allocs.size();
+                g_capturing = captured != 0;
+                CHECK(decode(stream, 64, 1, 8, 2) == XATTN_OK);
+                g_capturing = false;
+                CHECK(xattn::g_prm.parts == parts && xattn::g_prm.n_pieces == pieces);
+                CHECK(!captured || g_allocs.size() == allocs);
+                CHECK(fits(g_allocs.back()));
+            }
+    }));
+    // a stream without a workspace: a capture cannot make one, and records nothing
+    g_capturing = true;
+    const int before = xattn::g_decodes;
+    CHECK(decode(200, 64, 1, 8, 2) == XATTN_ENOMEM);
+    CHECK(mla_decode(200, 64, 1, 16) == XATTN_ENOMEM);
+    CHECK(xattn::g_decodes == before);
+    g_capturing = false;
+    // nor can it enlarge one
+    CHECK(decode(201, 1, 1, 8, 8) == XATTN_OK);
+    g_capturing = true;
+    CHECK(decode(201, 4096, 8, 64, 8) == XATTN_ENOMEM);
+    g_capturing = false;
+}
+
+// A caller's workspace: anything from one piece per compute unit on is used, as far as it goes, and a call that
+// succeeds leaves the last failure's message alone.
+static void a_caller_workspace_is_used_as_far_as_it_goes() {
+    const int shapes[][4] = {{64, 1, 8, 2}, {7, 2, 5, 1}, {30, 16, 12, 3}, {200, 1, 32, 8}, {3, 4, 64, 4}};
+    for (const auto& s : shapes) {
+        CHECK(xattn_configure(XATTN_CFG_PIECES, 256) == XATTN_OK);
+        const size_t least = xattn_workspace_bytes(s[0], s[1], s[2], s[3], 128);
+        CHECK(xattn_configure(XATTN_CFG_PIECES, 0) == XATTN_OK);
+        const size_t most = xattn_workspace_bytes(s[0], s[1], s[2], s[3], 128);
+        CHECK(least <= most);
+        int last_parts = 0;
+        for (int step = 0; step <= 8; ++step) {
+            const size_t bytes = least + (most - least) / 8 * step + (step == 8 ? (most - least) % 8 : 0);
+            CHECK(xattn_set_workspace(reinterpret_cast<void*>((uintptr_t)1 << 61), bytes) == XATTN_OK);
+            CHECK(fail_text_stays([&] { CHECK(decode(1, s[0], s[1], s[2], s[3]) == XATTN_OK); }));
+            CHECK(fits(bytes) && xattn::g_prm.parts >= last_parts);
+            last_parts = xattn::g_prm.parts;
+        }
+        CHECK(xattn_set_workspace(reinterpret_cast<void*>((uintptr_t)1 << 61), least - 1) == XATTN_OK);
+        CHECK(decode(1, s[0], s[1], s[2], s[3]) == XATTN_ENOMEM);
+        CHECK(xattn_set_workspace(nullptr, 0) == XATTN_OK);
+        CHECK(decode(1, s[0], s[1], s[2], s[3]) == XATTN_OK);
+        CHECK(xattn::g_prm.parts == last_parts);           // xattn_workspace_bytes is enough for the library's split
+    }
+}
+
 int main() {
     a_failed_allocation_fails_one_call();
     a_call_runs_on_what_can_be_allocated();
+    the_split_does_not_depend_on_earlier_calls();
+    a_caller_workspace_is_used_as_far_as_it_goes();
     CHECK(g_recorded == hipSuccess);
     if (g_failures) return 1;
     std::puts("all scenarios ran");

@@ -153,14 +153,16 @@ def test_recorded_graph_stays_valid_after_the_workspace_has_grown():
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=side):
             xa.xattn_decode(qd, store.k_ptrs, store.v_ptrs, lens_d, B, T, Hq, Hkv, D, SCALE, out, lse, side)
-        # a larger shape on the same stream: 16 times the query rows, the workspace must be replaced
-        T2, Hq2, Hkv2 = 4, 32, 8
+        # a larger shape on the same stream: 64 times the query rows and more than the least workspace, which must
+        # be replaced
+        T2, Hq2, Hkv2 = 16, 32, 8
         ks2 = [normal_bf16(98, 1 + b, 2000 * Hkv2 * D).reshape(2000, Hkv2, D) for b in range(B)]
         with xa.KVStore(ks2, ks2) as store2:
             q2 = torch.zeros((B, T2, Hq2, D), dtype=torch.int16, device="cuda")
             lens2 = torch.full((B,), 2000, dtype=torch.int32, device="cuda")
             out2 = torch.zeros((B, T2, Hq2, D), dtype=torch.int16, device="cuda")
             assert xa.xattn_workspace_bytes(B, T2, Hq2, Hkv2, D) > 2 * xa.xattn_workspace_bytes(B, T, Hq, Hkv, D)
+            assert xa.xattn_workspace_bytes(B, T2, Hq2, Hkv2, D) > xa.binding.XATTN_NOALLOC_SCRATCH_BYTES
             xa.xattn_decode(q2, store2.k_ptrs, store2.v_ptrs, lens2, B, T2, Hq2, Hkv2, D, SCALE, out2, None, side)
             side.synchronize()
         # allocations that would land in memory the library had freed
