@@ -19,7 +19,6 @@ constexpr int kRowBytes = kHeadDim * 2;
 // output tile with padded rows (16 x 528 bytes) when a segment is stored.
 constexpr int kLdsPerWave = 16 * (kHeadDim * 4 + 16);
 constexpr float kNegInf = -__builtin_inff();
-constexpr float kLazyLog2 = 8.0f;                // slack of the softmax reference maximum, in powers of two
 constexpr float kLn2 = 0.6931471805599453f;
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;

@@ -340,15 +340,11 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
             for (int i = 0; i < 4; ++i) p[t][i] = (j_block + 4 * i + kb < lim[t]) ? p[t][i] : kNegInf;
         }
         const float mx = kb_max(fmaxf(fmaxf(p[t][0], p[t][1]), fmaxf(p[t][2], p[t][3])));
-        // The reference maximum moves only when a block exceeds it by more than 2^kLazyLog2 (weights reach
-        // that at most, which costs fp32 sums and bf16's relative precision nothing), so the rescaling of
-        // the accumulators runs about once per segment and not whenever one of 16 rows sees a new maximum.
-        // It is a whole number, so that another cut of the keys scales a weight by a power of two, which
-        // leaves its hi + lo parts as they are; with one bf16 per weight it is the maximum itself, so that a
-        // row's only key has the exact weight 1.
-        const bool moves = mx > st[t].m + kLazyLog2;
+        // The reference is the exact running maximum: no weight exceeds 1, so a sum stays as far inside the fp32
+        // range as its values allow, and the largest key's weight is exactly 1 in any number of bf16 parts.
+        const bool moves = mx > st[t].m;
         if (__builtin_amdgcn_ballot_w64(moves) != 0) {
-            const float m_new = moves ? (kPv == kPvBf16 ? mx : __builtin_ceilf(mx)) : st[t].m;
+            const float m_new = moves ? mx : st[t].m;
             const float alpha = moves ? fast_exp2(st[t].m - m_new) : 1.0f;
             st[t].m = m_new;
             st[t].l *= alpha;

@@ -82,6 +82,7 @@ constexpr int kStageWave = 16 * kStagePitch;     // 8448 bytes
 // with two segments finish 13 us later than their token count says) in units of one token's share of
 // the block loop (2.3 us per 32 tokens).
 constexpr int kMlaSegCost = 192;
+constexpr float kLazyLog2 = 8.0f;                // slack of the softmax reference maximum, in powers of two
 // Precision of the softmax weights in the value product (see the header comment).
 constexpr int kLoNever = 0;                      // one bf16 per weight everywhere
 constexpr int kLoAlways = 1;                     // hi + lo bf16 parts everywhere
