@@ -497,6 +497,19 @@ __device__ __forceinline__ void matrix_run(MatrixState (&st)[kTiles], MatrixCtx<
         matrix_block<kPv, kTiles>(st, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n, NoLoad());
 }
 
+// Whether any lane's sums hold an infinity or NaN (times 0 gives NaN, which no later term removes).
+template <int kTiles>
+__device__ __forceinline__ bool any_not_finite(const MatrixState (&st)[kTiles]) {
+    float z = 0.0f;
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z = __builtin_fmaf(st[t].o[e][j], 0.0f, z);
+    return __builtin_amdgcn_ballot_w64(z != z) != 0;
+}
+
 // Stores the 16 rows of tile t of the segment; rows past the last get an offset past the descriptor's end,
 // and their stores are dropped.
 constexpr uint32_t kPastTheEnd = 0x40000000u;
@@ -656,6 +669,14 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
             for (;;) {
                 MatrixState st[kT];
                 matrix_run<kPv, kT>(st, cur, prm, lane, lds_wave);
+                if constexpr (kPv == kPvBf16x3) {
+                    // An infinite value times a weight's second or third part, which may be zero or negative, is NaN
+                    // where the sum is infinite: such a segment once more with the weights in one piece.
+                    if (__builtin_expect(any_not_finite(st), 0)) {
+                        NextLoad{cur.first, cur.rk, cur.rv, cur.voffset, (uint32_t)prm.n_kv_heads * kRowBytes, cur.seg.j0, true}.all();
+                        matrix_run<kPvFp32, kT>(st, cur, prm, lane, lds_wave);
+                    }
+                }
                 Segment nxt_seg;
                 const bool more = uniform(next_seg(nxt_seg)) != 0;
                 MatrixCtx<kT> nxt;

@@ -87,3 +87,30 @@ def test_the_largest_key_has_an_exact_weight(configure, T, group):
         worst = max(worst, float(np.max(np.abs(np.sum(got * ref, -1) / np.sum(ref * ref, -1) - 1.0))))
     # 4.5 standard deviations for the output, and the smaller key's weight: 2^-5.8 of the row, off by 2^-8 of itself
     assert worst <= 4.5 * 2.5e-4 + 2.0 ** -13.8, worst
+
+
+# rows 1 to 3 per KV head, one segment
+@pytest.mark.parametrize("T,group,Hkv", [(1, 1, 2), (1, 2, 8), (3, 1, 3), (1, 1, 600), (1, 3, 700)])
+@pytest.mark.parametrize("pieces", [1])
+def test_infinite_values_below_four_rows(configure, T, group, Hkv, pieces):
+    """An infinity or NaN among the values reaches its own column of the rows that see its key, as what the sum
+    makes of it, and nothing else."""
+    from gpu_util import TOL_LSE, TOL_MAX_ABS, gpu_attn
+    configure(pieces, 16)
+    L, Hq = 16 * 20 - 16, group * Hkv         # a sequence counts as its keys + 16: pieces end at whole blocks
+    q = normal_bf16(61, 0, T * Hq * D).reshape(1, T, Hq, D)
+    k = normal_bf16(61, 1, L * Hkv * D).reshape(L, Hkv, D)
+    v = normal_bf16(61, 2, L * Hkv * D).reshape(L, Hkv, D).copy()
+    inf, minus_inf, nan = 0x7F80, 0xFF80, 0x7FC0
+    for col, (key, value) in enumerate([(0, inf), (5, minus_inf), (16, inf), (47, inf), (100, minus_inf), (163, inf), (200, nan),
+                                        (299, inf)]):
+        v[key, :, 3 + 11 * col] = value
+    v[20, :, 127] = inf
+    v[220, :, 127] = minus_inf                # in different segments, or in one
+    out_bits, lse = gpu_attn(q, [k], [v], [L], SCALE)
+    ref_out, ref_lse = oracle.attn(q, [k], [v], [L], SCALE)
+    got = bf16_to_f32(out_bits).astype(np.float64).reshape(ref_out.shape)
+    assert np.array_equal(np.isnan(got), np.isnan(ref_out))
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref_out)) and np.array_equal(np.isneginf(got), np.isneginf(ref_out))
+    finite = np.isfinite(ref_out)
+    assert np.max(np.abs(got[finite] - ref_out[finite])) <= TOL_MAX_ABS and np.max(np.abs(lse - ref_lse)) <= TOL_LSE
