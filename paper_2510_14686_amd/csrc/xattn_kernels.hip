@@ -754,10 +754,11 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const float m_s = __shfl(mine.x, (i0 + u) & 63, 64), l_s = __shfl(mine.y, (i0 + u) & 63, 64);
-                const float w = s0 + u < sh.end ? fast_exp2(m_s - m_use) : 0.0f;      // past the end: weight 0
-                l = __builtin_fmaf(l_s, w, l);
-                o0 = __builtin_fmaf(o[u].x, w, o0);
-                o1 = __builtin_fmaf(o[u].y, w, o1);
+                const bool in = s0 + u < sh.end;          // past the end: nothing, also where the row read is infinite
+                const float w = in ? fast_exp2(m_s - m_use) : 0.0f;
+                l = __builtin_fmaf(in ? l_s : 0.0f, w, l);
+                o0 = __builtin_fmaf(in ? o[u].x : 0.0f, w, o0);
+                o1 = __builtin_fmaf(in ? o[u].y : 0.0f, w, o1);
             }
         }
     }

@@ -89,9 +89,9 @@ def test_the_largest_key_has_an_exact_weight(configure, T, group):
     assert worst <= 4.5 * 2.5e-4 + 2.0 ** -13.8, worst
 
 
-# rows 1 to 3 per KV head, one segment
+# rows 1 to 3 per KV head; merges of 16, 4 and 1 waves per row; segments from one to 64
 @pytest.mark.parametrize("T,group,Hkv", [(1, 1, 2), (1, 2, 8), (3, 1, 3), (1, 1, 600), (1, 3, 700)])
-@pytest.mark.parametrize("pieces", [1])
+@pytest.mark.parametrize("pieces", [1, 3, 20, 64])
 def test_infinite_values_below_four_rows(configure, T, group, Hkv, pieces):
     """An infinity or NaN among the values reaches its own column of the rows that see its key, as what the sum
     makes of it, and nothing else."""
