@@ -178,8 +178,7 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *   XATTN_CFG_PATH              inner loop of the decode kernel: 0 = automatic (the matrix-core path),
  *                               1 = vector path, 2 = matrix-core path (section 4.4.1)
  *   XATTN_CFG_PV_MODE           matrix-core path, product of softmax weights and V: 0 = default, bf16
- *                               MFMA on hi + lo bf16 parts of the weights (16 significant bits; three
- *                               parts, 24 bits, below 4 query rows per KV head);
+ *                               MFMA on three bf16 parts of the weights (all 24 significant bits);
  *                               1 = fp32 MFMA (weights exact, slower); 2 = one bf16 MFMA (weights
  *                               rounded to bf16)
  *                               (xattn_mla_decode: 0 = default, hi + lo bf16 parts throughout with up to 32

@@ -40,14 +40,13 @@ struct DecodeParams {
     FewPieces few;                   // see plan_for_total
     int xcd_skew;                    // per mille: share taken from the odd XCDs' parts of the stream and given to the even ones
     int path;                        // kPathAuto, kPathVector or kPathMatrix
-    int pv_mode;                     // matrix path: kPvBf16x2 (kPvBf16x3 below 4 rows per KV head), kPvFp32 or kPvBf16
+    int pv_mode;                     // matrix path: kPvBf16x3, kPvFp32 or kPvBf16
 };
 
 // How the matrix path multiplies the softmax weights p with V.
-constexpr int kPvBf16x2 = 0;   // default: bf16 MFMA 16x16x16 twice, p as hi + lo bf16 parts (16 significant bits)
+constexpr int kPvBf16x3 = 0;   // default: bf16 MFMA 16x16x16 three times, p as three bf16 parts (24 significant bits)
 constexpr int kPvFp32 = 1;     // fp32 MFMA 16x16x4, p exact; 4x the matrix-core time, measurably slower
 constexpr int kPvBf16 = 2;     // bf16 MFMA 16x16x16 once, p rounded to bf16; same speed as the default, less exact
-constexpr int kPvBf16x3 = 3;   // p as three bf16 parts (24 significant bits): the default below 4 rows per KV head
 
 // Inner-loop choice: automatic = matrix path (see use_matrix_path).
 constexpr int kPathAuto = 0;

@@ -375,9 +375,11 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
     } else {
         // bf16 MFMA 16x16x16 contracts the block's 16 keys at once: lane (kb, x) supplies keys 4*kb + i,
         // i = 0..3, of column 8*x + e (the e-th bf16 of its four V registers) and of row n (its four p).
-        // kPvBf16x2 feeds p as hi + lo bf16 parts in two MFMAs, which keeps p to 16 significant bits; kPvBf16x3
-        // adds what those two leave, which is all 24.
-        constexpr bool kLo = kPv == kPvBf16x2 || kPv == kPvBf16x3;
+        // kPvBf16x3 feeds p as three bf16 parts in three MFMAs, which keeps all of its 24 significant bits.  (Two
+        // parts keep 16 of them, and the 2^-17 of the largest weight is then the error of a row that one key
+        // carries, ahead of the output's rounding.  The third costs 0 to 0.3 % of the large calls, 1 % with two
+        // tiles, 2 % of 64 sequences of two KV heads.)
+        constexpr bool kLo = kPv == kPvBf16x3;
         u32x2_t ph[kTiles], pl[kTiles], pr[kTiles];
 #pragma unroll
         for (int t = 0; t < kTiles; ++t) {
@@ -390,11 +392,9 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
                 const f32x2_t r23 = p23 - __builtin_convertvector(h23, f32x2_t);
                 const bf16x2_t l01 = __builtin_convertvector(r01, bf16x2_t), l23 = __builtin_convertvector(r23, bf16x2_t);
                 pl[t] = u32x2_t{__builtin_bit_cast(uint32_t, l01), __builtin_bit_cast(uint32_t, l23)};
-                if (kPv == kPvBf16x3) {
-                    const f32x2_t q01 = r01 - __builtin_convertvector(l01, f32x2_t);
-                    const f32x2_t q23 = r23 - __builtin_convertvector(l23, f32x2_t);
-                    pr[t] = u32x2_t{cvt_bf16(q01[0], q01[1]), cvt_bf16(q23[0], q23[1])};
-                }
+                const f32x2_t q01 = r01 - __builtin_convertvector(l01, f32x2_t);
+                const f32x2_t q23 = r23 - __builtin_convertvector(l23, f32x2_t);
+                pr[t] = u32x2_t{cvt_bf16(q01[0], q01[1]), cvt_bf16(q23[0], q23[1])};
             }
         }
         const uint32_t vw[4][4] = {{r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w}, {r.v[1].x, r.v[1].y, r.v[1].z, r.v[1].w},
@@ -408,12 +408,12 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
             for (int t = 0; t < kTiles; ++t) {
                 st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
                                                                        __builtin_bit_cast(s16x4_t, ph[t]), st[t].o[e], 0, 0, 0);
-                if (kPv == kPvBf16x3)
+                if (kLo) {
                     st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
                                                                            __builtin_bit_cast(s16x4_t, pr[t]), st[t].o[e], 0, 0, 0);
-                if (kLo)
                     st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
                                                                            __builtin_bit_cast(s16x4_t, pl[t]), st[t].o[e], 0, 0, 0);
+                }
             }
         }
     }
@@ -669,10 +669,11 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
             for (;;) {
                 MatrixState st[kT];
                 matrix_run<kPv, kT>(st, cur, prm, lane, lds_wave);
-                if constexpr (kPv == kPvBf16x3) {
+                if constexpr (kPv == kPvBf16x3 && kTiles == 1) {
                     // An infinite value times a weight's second or third part, which may be zero or negative, is NaN
-                    // where the sum is infinite: such a segment once more with the weights in one piece.
-                    if (__builtin_expect(any_not_finite(st), 0)) {
+                    // where the sum is infinite: such a segment once more with the weights in one piece.  Below 4
+                    // rows, which the vector path's fp32 products served before.
+                    if (rows_total < 4 && __builtin_expect(any_not_finite(st), 0)) {
                         NextLoad{cur.first, cur.rk, cur.rv, cur.voffset, (uint32_t)prm.n_kv_heads * kRowBytes, cur.seg.j0, true}.all();
                         matrix_run<kPvFp32, kT>(st, cur, prm, lane, lds_wave);
                     }
@@ -808,7 +809,7 @@ __global__ __launch_bounds__(256) void write_kvcache_kernel(WriteParams prm) {
     }
 }
 
-template <int R, bool kMatrix, int kPv = kPvBf16x2>
+template <int R, bool kMatrix, int kPv = kPvBf16x3>
 hipError_t launch_decode_r(const DecodeParams& prm, dim3 grid, dim3 block, hipStream_t stream) {
     hipLaunchKernelGGL((split_decode_kernel<R, kMatrix, kPv>), grid, block, 0, stream, prm);
     return hipGetLastError();
@@ -852,17 +853,13 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
         switch (prm.pv_mode) {
             case kPvBf16: e = launch_decode_r<32, true, kPvBf16>(prm, grid, block, stream); break;
             case kPvFp32: e = launch_decode_r<32, true, kPvFp32>(prm, grid, block, stream); break;
-            default: e = launch_decode_r<32, true, kPvBf16x2>(prm, grid, block, stream); break;
+            default: e = launch_decode_r<32, true, kPvBf16x3>(prm, grid, block, stream); break;
         }
     } else if (matrix) {
         switch (prm.pv_mode) {
             case kPvBf16: e = launch_decode_r<16, true, kPvBf16>(prm, grid, block, stream); break;
             case kPvFp32: e = launch_decode_r<16, true, kPvFp32>(prm, grid, block, stream); break;
-            default:
-                // the calls that took the vector path keep its 24-bit weights
-                e = rows_total < 4 ? launch_decode_r<16, true, kPvBf16x3>(prm, grid, block, stream)
-                                   : launch_decode_r<16, true, kPvBf16x2>(prm, grid, block, stream);
-                break;
+            default: e = launch_decode_r<16, true, kPvBf16x3>(prm, grid, block, stream); break;
         }
     } else {
         switch (R) {
