@@ -180,7 +180,8 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *   XATTN_CFG_PV_MODE           matrix-core path, product of softmax weights and V: 0 = default, bf16
  *                               MFMA on three bf16 parts of the weights (all 24 significant bits);
  *                               1 = fp32 MFMA (weights exact, slower); 2 = one bf16 MFMA (weights
- *                               rounded to bf16)
+ *                               rounded to bf16).  Below 4 query rows per KV head 1 and 2 apply only
+ *                               with XATTN_CFG_PATH = 2
  *                               (xattn_mla_decode: 0 = default, hi + lo bf16 parts throughout with up to 32
  *                               query rows per sequence, else for the first 128 keys
  *                               of every segment and wherever a key carries 1/4 or more of its row's

@@ -856,7 +856,9 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
             default: e = launch_decode_r<32, true, kPvBf16x3>(prm, grid, block, stream); break;
         }
     } else if (matrix) {
-        switch (prm.pv_mode) {
+        // The weight modes are the matrix path's from 4 rows per KV head on; below, where a call comes here by
+        // default, its weights have 24 bits in every mode, as on the vector path it would take otherwise.
+        switch (rows_total < 4 && prm.path != kPathMatrix ? kPvBf16x3 : prm.pv_mode) {
             case kPvBf16: e = launch_decode_r<16, true, kPvBf16>(prm, grid, block, stream); break;
             case kPvFp32: e = launch_decode_r<16, true, kPvFp32>(prm, grid, block, stream); break;
             default: e = launch_decode_r<16, true, kPvBf16x3>(prm, grid, block, stream); break;

@@ -114,3 +114,18 @@ def test_infinite_values_below_four_rows(configure, T, group, Hkv, pieces):
     assert np.array_equal(np.isposinf(got), np.isposinf(ref_out)) and np.array_equal(np.isneginf(got), np.isneginf(ref_out))
     finite = np.isfinite(ref_out)
     assert np.max(np.abs(got[finite] - ref_out[finite])) <= TOL_MAX_ABS and np.max(np.abs(lse - ref_lse)) <= TOL_LSE
+
+
+@pytest.mark.parametrize("T,group", [(1, 1), (1, 3), (3, 1)])
+def test_weight_modes_do_not_apply_below_four_rows(configure, T, group):
+    from gpu_util import gpu_attn
+    L, Hkv = 700, 2
+    Hq = group * Hkv
+    q = normal_bf16(62, 0, T * Hq * D).reshape(1, T, Hq, D)
+    kv = [normal_bf16(62, 1 + i, L * Hkv * D).reshape(L, Hkv, D) for i in range(2)]
+    want = gpu_attn(q, [kv[0]], [kv[1]], [L], SCALE)
+    for pv_mode in (1, 2):
+        configure(0, 0, 0, pv_mode)
+        got = gpu_attn(q, [kv[0]], [kv[1]], [L], SCALE)
+        np.testing.assert_array_equal(got[0], want[0])
+        np.testing.assert_array_equal(got[1], want[1])
