@@ -47,6 +47,7 @@ struct DecodeParams {
 constexpr int kPvBf16x3 = 0;   // default: bf16 MFMA 16x16x16 three times, p as three bf16 parts (24 significant bits)
 constexpr int kPvFp32 = 1;     // fp32 MFMA 16x16x4, p exact; 4x the matrix-core time, measurably slower
 constexpr int kPvBf16 = 2;     // bf16 MFMA 16x16x16 once, p rounded to bf16; same speed as the default, less exact
+constexpr int kPvBf16x3Apart = 3;      // internal, below 4 rows per KV head: as 0, and infinite values keep their sums
 
 // Inner-loop choice: automatic = matrix path (see use_matrix_path).
 constexpr int kPathAuto = 0;

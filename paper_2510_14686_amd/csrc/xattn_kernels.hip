@@ -301,10 +301,21 @@ struct MatrixState {
     float m, l;       // row n: running max (all kb groups agree), this lane's share of the running sum
 };
 
+// kPvBf16x3Apart sums the products of the weights' second and third parts apart from the first part's: a part that
+// is zero or negative makes NaN of an infinite value, and is dropped at the segment's end where the first part's
+// sum is not finite.  (The 32 registers and their rescaling cost 0.3 us of a call; running such a segment once more
+// with fp32 products, in a branch that is not taken otherwise, costs 0.5.)
+template <int kPv>
+constexpr bool kLowApart = kPv == kPvBf16x3Apart;
+template <int kPv>
+struct LowSums {
+    f32x4_t o[kLowApart<kPv> ? 8 : 1];
+};
+
 // One 16-key block against kTiles tiles of 16 rows: every K register and every V operand permuted from
 // registers feeds the MFMAs of all tiles.
 template <int kPv, int kTiles, typename Next>
-__device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const KvRegs& r, const bf16x8_t (&qop)[kTiles][4],
+__device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], LowSums<kPv>& low, const KvRegs& r, const bf16x8_t (&qop)[kTiles][4],
                                              char* lds_wave, float scale_log2, int j_block, const int (&lim)[kTiles], int kb,
                                              int n, Next next) {
     next.template at<0>();
@@ -349,7 +360,10 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
             st[t].m = m_new;
             st[t].l *= alpha;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) st[t].o[e] *= alpha;
+            for (int e = 0; e < 8; ++e) {
+                st[t].o[e] *= alpha;
+                if constexpr (kLowApart<kPv>) low.o[e] *= alpha;
+            }
         }
         const float m_use = (st[t].m == kNegInf) ? 0.0f : st[t].m;
 #pragma unroll
@@ -379,7 +393,7 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
         // parts keep 16 of them, and the 2^-17 of the largest weight is then the error of a row that one key
         // carries, ahead of the output's rounding.  The third costs 0 to 0.3 % of the large calls, 1 % with two
         // tiles, 2 % of 64 sequences of two KV heads.)
-        constexpr bool kLo = kPv == kPvBf16x3;
+        constexpr bool kLo = kPv == kPvBf16x3 || kPv == kPvBf16x3Apart;
         u32x2_t ph[kTiles], pl[kTiles], pr[kTiles];
 #pragma unroll
         for (int t = 0; t < kTiles; ++t) {
@@ -409,10 +423,11 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], const Kv
                 st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
                                                                        __builtin_bit_cast(s16x4_t, ph[t]), st[t].o[e], 0, 0, 0);
                 if (kLo) {
-                    st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
-                                                                           __builtin_bit_cast(s16x4_t, pr[t]), st[t].o[e], 0, 0, 0);
-                    st[t].o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
-                                                                           __builtin_bit_cast(s16x4_t, pl[t]), st[t].o[e], 0, 0, 0);
+                    f32x4_t& lo = kLowApart<kPv> ? low.o[kLowApart<kPv> ? e : 0] : st[t].o[e];
+                    lo = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
+                                                                   __builtin_bit_cast(s16x4_t, pr[t]), lo, 0, 0, 0);
+                    lo = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a),
+                                                                   __builtin_bit_cast(s16x4_t, pl[t]), lo, 0, 0, 0);
                 }
             }
         }
@@ -482,32 +497,30 @@ __device__ __forceinline__ void matrix_run(MatrixState (&st)[kTiles], MatrixCtx<
         st[t].m = kNegInf;
         st[t].l = 0.0f;
     }
+    static_assert(!kLowApart<kPv> || kTiles == 1, "one tile's registers");
+    LowSums<kPv> low;
+    if constexpr (kLowApart<kPv>)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) low.o[e] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     // Two register buffers: the next block's 8 loads per lane go out during the current block's arithmetic.
     const int n_blocks = (seg.j1 - seg.j0 + kBlockKeys - 1) / kBlockKeys;
     auto key0 = [&](int blk) { return seg.j0 + blk * kBlockKeys; };
     KvRegs Bk;
     int blk = 0;
         for (; blk + 2 <= n_blocks; blk += 2) {
-        matrix_block<kPv, kTiles>(st, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n,
+        matrix_block<kPv, kTiles>(st, low, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n,
                                   NextLoad{Bk, c.rk, c.rv, c.voffset, row_stride, key0(blk + 1), true});
-        matrix_block<kPv, kTiles>(st, Bk, c.qop, lds_wave, prm.scale_log2, key0(blk + 1), c.lim, kb, n,
+        matrix_block<kPv, kTiles>(st, low, Bk, c.qop, lds_wave, prm.scale_log2, key0(blk + 1), c.lim, kb, n,
                                   NextLoad{c.first, c.rk, c.rv, c.voffset, row_stride, key0(blk + 2), blk + 2 < n_blocks});
     }
     if (blk < n_blocks)
-        matrix_block<kPv, kTiles>(st, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n, NoLoad());
-}
-
-// Whether any lane's sums hold an infinity or NaN (times 0 gives NaN, which no later term removes).
-template <int kTiles>
-__device__ __forceinline__ bool any_not_finite(const MatrixState (&st)[kTiles]) {
-    float z = 0.0f;
-#pragma unroll
-    for (int t = 0; t < kTiles; ++t)
+        matrix_block<kPv, kTiles>(st, low, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n, NoLoad());
+    if constexpr (kLowApart<kPv>) {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) z = __builtin_fmaf(st[t].o[e][j], 0.0f, z);
-    return __builtin_amdgcn_ballot_w64(z != z) != 0;
+            for (int j = 0; j < 4; ++j) st[0].o[e][j] += __builtin_isfinite(st[0].o[e][j]) ? low.o[e][j] : 0.0f;
+    }
 }
 
 // Stores the 16 rows of tile t of the segment; rows past the last get an offset past the descriptor's end,
@@ -669,15 +682,6 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
             for (;;) {
                 MatrixState st[kT];
                 matrix_run<kPv, kT>(st, cur, prm, lane, lds_wave);
-                if constexpr (kPv == kPvBf16x3 && kTiles == 1) {
-                    // An infinite value times a weight's second or third part, which may be zero or negative, is NaN
-                    // where the sum is infinite: such a segment once more with the weights in one piece.  Below 4
-                    // rows, which the vector path's fp32 products served before.
-                    if (rows_total < 4 && __builtin_expect(any_not_finite(st), 0)) {
-                        NextLoad{cur.first, cur.rk, cur.rv, cur.voffset, (uint32_t)prm.n_kv_heads * kRowBytes, cur.seg.j0, true}.all();
-                        matrix_run<kPvFp32, kT>(st, cur, prm, lane, lds_wave);
-                    }
-                }
                 Segment nxt_seg;
                 const bool more = uniform(next_seg(nxt_seg)) != 0;
                 MatrixCtx<kT> nxt;
@@ -857,8 +861,9 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
         }
     } else if (matrix) {
         // The weight modes are the matrix path's from 4 rows per KV head on; below, where a call comes here by
-        // default, its weights have 24 bits in every mode, as on the vector path it would take otherwise.
-        switch (rows_total < 4 && prm.path != kPathMatrix ? kPvBf16x3 : prm.pv_mode) {
+        // default, its weights have 24 bits in every mode and its sums take infinite values, as on the vector path.
+        switch (rows_total < 4 && (prm.path != kPathMatrix || prm.pv_mode == kPvBf16x3) ? kPvBf16x3Apart : prm.pv_mode) {
+            case kPvBf16x3Apart: e = launch_decode_r<16, true, kPvBf16x3Apart>(prm, grid, block, stream); break;
             case kPvBf16: e = launch_decode_r<16, true, kPvBf16>(prm, grid, block, stream); break;
             case kPvFp32: e = launch_decode_r<16, true, kPvFp32>(prm, grid, block, stream); break;
             default: e = launch_decode_r<16, true, kPvBf16x3>(prm, grid, block, stream); break;
