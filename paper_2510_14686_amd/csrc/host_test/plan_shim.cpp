@@ -1,5 +1,6 @@
 // Host test library only: the partition of xattn_plan.h (the same code the kernels run) behind C entry
 // points, with the wave-parallel steps of the device front end (total, locate) replaced by plain loops.
+#include <cstddef>
 #include <cstdint>
 
 #include "../xattn_plan.h"
@@ -8,11 +9,11 @@ using namespace xattn;
 
 namespace {
 
-Plan plan_of(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew) {
+Plan plan_of(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min) {
     int64_t total = 0;
     for (int b = 0; b < batch; ++b) total += stream_len(kv_lens[b], seg_cost);
     if (total > INT32_MAX) total = -1;          // outside the documented limit: reported, not wrapped
-    return plan_for_total((int)total, n_pieces, min_piece, seg_cost, xcd_skew);
+    return plan_for_total((int)total, n_pieces, min_piece, seg_cost, xcd_skew, FewPieces{few_pieces, few_min});
 }
 
 }  // namespace
@@ -20,32 +21,32 @@ Plan plan_of(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int
 extern "C" {
 
 // total_out: stream positions N (-1 when N would exceed 2^31 - 1); returns the number of pieces in use.
-int xattn_test_plan(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int32_t* total_out) {
-    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew);
+int xattn_test_plan(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int32_t* total_out) {
+    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew, few_pieces, few_min);
     if (total_out) *total_out = pl.total;
     return pl.total < 0 ? -1 : pl.n_pieces;
 }
 
 // bounds_out[0 .. n_used]: piece_bound(p) for p = 0 .. n_used.
-int xattn_test_piece_bounds(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew,
+int xattn_test_piece_bounds(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min,
                             int32_t* bounds_out) {
-    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew);
+    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew, few_pieces, few_min);
     if (pl.total < 0) return -1;
     for (int p = 0; p <= pl.n_pieces; ++p) bounds_out[p] = piece_bound(pl, p);
     return pl.n_pieces;
 }
 
-int xattn_test_piece_of(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int position) {
-    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew);
+int xattn_test_piece_of(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int position) {
+    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew, few_pieces, few_min);
     if (pl.total < 0 || position < 0 || position >= pl.total) return -1;
     return piece_of(pl, position);
 }
 
 // The segments of piece p as the kernels walk them: rows of (b, j0, j1, slot, whole) in segs_out
 // (up to max_segs rows); returns their number.
-int xattn_test_piece_segments(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int p,
+int xattn_test_piece_segments(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int p,
                               int32_t* segs_out, int max_segs) {
-    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew);
+    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew, few_pieces, few_min);
     if (pl.total < 0 || p < 0 || p >= pl.n_pieces) return -1;
     const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
     // locate: the sequence that holds position s0 and the offset within its positions
@@ -69,9 +70,28 @@ int xattn_test_piece_segments(const int32_t* kv_lens, int batch, int n_pieces, i
     return n;
 }
 
+// How xattn_decode's workgroups share a plan of `total` positions out: count_out[piece in use * rows_total + row] =
+// the number of workgroup parts that compute it.  Returns the rows a wave holds in this launch; -1 where a part
+// works on a piece that is not in use, or on no row.
+int xattn_test_decode_work(int total, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int parts,
+                           int rows_total, int rows_max, int32_t* count_out) {
+    const Plan pl = plan_for_total(total, n_pieces, min_piece, seg_cost, xcd_skew, FewPieces{few_pieces, few_min});
+    const int grid_x = decode_grid_x(n_pieces, parts, rows_total, rows_max);
+    int rows = -1;
+    for (int bid = 0; bid < grid_x; ++bid)
+        for (int part = 0; part < parts; ++part) {
+            const DecodeWork w = decode_work(pl, grid_x, parts, rows_total, rows_max, bid, part);
+            if (!w.any) continue;
+            if (w.piece < 0 || w.piece >= pl.n_pieces || w.row0 < 0 || w.row0 >= rows_total || (rows >= 0 && w.rows != rows)) return -1;
+            rows = w.rows;
+            for (int r = w.row0; r < rows_total && r < w.row0 + w.rows; ++r) ++count_out[(size_t)w.piece * rows_total + r];
+        }
+    return rows;
+}
+
 // meta_out[2 b], meta_out[2 b + 1]: (first partial slot, number of segments) of sequence b.
-int xattn_test_meta(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int32_t* meta_out) {
-    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew);
+int xattn_test_meta(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int32_t* meta_out) {
+    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew, few_pieces, few_min);
     if (pl.total < 0) return -1;
     int start = 0;
     for (int b = 0; b < batch; ++b) {

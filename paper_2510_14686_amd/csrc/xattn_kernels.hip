@@ -612,29 +612,12 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
                                   prm.xcd_skew, prm.few, lane, nullptr);
     const Plan& pl = wp.pl;
 
-    // Piece index: consecutive workgroups go to different XCDs, so give each XCD one contiguous eighth of
-    // the token stream.  Of an XCD's workgroups, consecutive ones are the row groups of the same pieces:
-    // they run at the same time and share the pieces' K and V in that XCD's L2.  A workgroup's parts are
-    // far apart in the XCD's eighth, so that a short stream's few pieces spread over the compute units.
-    const int per_xcd = (pl.n_pieces + 7) >> 3;
     const int bid = blockIdx.x;
     const int rows_total = prm.group * prm.q_len;
-    const int slots_per_xcd = gridDim.x >> 3;
-    int rows = R;                                            // per wave
-    if constexpr (kTiles == 2) {
-        // When the pieces in use leave enough workgroups idle, every tile gets one of its own (35 rows, 53
-        // sequences of 6 to 100 tokens: 17.5 us in pairs, 10.0 us apart).
-        if (prm.parts * (slots_per_xcd / ((rows_total + 15) / 16)) >= per_xcd) rows = 16;
-    }
-    const int n_groups = (rows_total + rows - 1) / rows;
-    const int slot_in_xcd = bid >> 3;
-    const int set = n_groups == 1 ? slot_in_xcd : slot_in_xcd / n_groups;
-    const int row_group = slot_in_xcd - set * n_groups;
-    const int sets = slots_per_xcd / n_groups;               // workgroups of different pieces per XCD
-    const int p_local = part * sets + set;
-    const int p = (bid & 7) * per_xcd + p_local;
+    const DecodeWork work = decode_work(pl, gridDim.x, prm.parts, rows_total, R, bid, part);
+    const int p = work.piece, rows = work.rows;
     const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
-    const bool active = set < sets && p_local < per_xcd && p < pl.n_pieces && s0 < s1;
+    const bool active = work.any && s0 < s1;
 
     if (blockIdx.z == 0 && threadIdx.x < 64) {
         // For the merge kernel: first partial slot and number of segments of every sequence, 64
@@ -650,7 +633,7 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
 
     Segment seg;
     seg.kvh = kvh;
-    seg.row0 = row_group * rows;
+    seg.row0 = work.row0;
     seg.n_rows = rows_total - seg.row0 < rows ? rows_total - seg.row0 : rows;
     // Next (piece, sequence) intersection of this piece, in stream order; false when the piece is done.
     auto next_seg = [&](Segment& out) {
@@ -847,9 +830,7 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
     const bool matrix = use_matrix_path(rows_total, prm.path);
     const int R = rows_per_wave(rows_total, prm.path);
     const int heads_per_block = prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;
-    const int n_groups = (rows_total + R - 1) / R;
-    const int sets = (prm.n_pieces + prm.parts - 1) / prm.parts;
-    dim3 grid((sets + 7) / 8 * 8 * n_groups, 1, (prm.n_kv_heads + kMaxWavesPerBlock - 1) / kMaxWavesPerBlock);
+    dim3 grid(decode_grid_x(prm.n_pieces, prm.parts, rows_total, R), 1, (prm.n_kv_heads + kMaxWavesPerBlock - 1) / kMaxWavesPerBlock);
     dim3 block(64 * heads_per_block * prm.parts);
     hipError_t e;
     if (events && (e = hipEventRecord(events[0], stream)) != hipSuccess) return e;

@@ -42,8 +42,8 @@ XATTN_HD int clamp_len(int v) { return v > 0 ? v : 0; }
 // Stream positions of a sequence of `len` tokens (any sign).
 XATTN_HD int stream_len(int len, int seg_cost) { return len > 0 ? len + seg_cost : 0; }
 
-// A short stream is cut finer than min_piece, down to few_min positions, into up to few_pieces pieces: as
-// long as that only spreads it over idle compute units, shorter pieces finish earlier.
+// A short stream is cut finer than n_pieces' min_piece, down to few.min_piece positions, into up to few.pieces
+// pieces: as long as that only spreads it over idle compute units, shorter pieces finish earlier.
 struct FewPieces {
     int pieces, min_piece;
 };
@@ -114,6 +114,37 @@ XATTN_HD int piece_of(const Plan& pl, int x) {
     while (p + 1 < pl.n_pieces && piece_bound(pl, p + 1) <= x) ++p;
     while (p > 0 && piece_bound(pl, p) > x) --p;
     return p;
+}
+
+// xattn_decode's workgroups.  grid.x = decode_grid_x(...) of them work on the pieces: a workgroup holds `parts`
+// pieces, and the query rows of a KV head that a wave cannot hold (rows_max) go to further workgroups.
+XATTN_HD int decode_grid_x(int n_pieces, int parts, int rows_total, int rows_max) {
+    const int sets = (n_pieces + parts - 1) / parts;         // workgroups of different pieces
+    return (sets + 7) / 8 * 8 * ((rows_total + rows_max - 1) / rows_max);
+}
+struct DecodeWork {
+    int piece, row0;      // rows [row0, row0 + rows) of the rows_total
+    int rows;             // per wave: rows_max or fewer, the same in the whole launch
+    bool any;             // false: nothing to do
+};
+// What part `part` of workgroup `bid` works on.  Consecutive workgroups go to different XCDs, so each XCD gets
+// one contiguous eighth of the token stream.  Of an XCD's workgroups, consecutive ones are the row groups of the
+// same pieces: they run at the same time and share the pieces' K and V in that XCD's L2.  A workgroup's parts are
+// far apart in the XCD's eighth, so that a short stream's few pieces spread over the compute units.
+XATTN_HD DecodeWork decode_work(const Plan& pl, int grid_x, int parts, int rows_total, int rows_max, int bid, int part) {
+    const int per_xcd = (pl.n_pieces + 7) >> 3, slots_per_xcd = grid_x >> 3;
+    DecodeWork w;
+    w.rows = rows_max;
+    // When the pieces in use leave enough workgroups idle, every tile of 16 rows gets one of its own (35 rows, 53
+    // sequences of 6 to 100 tokens: 17.5 us in pairs, 10.0 us apart).
+    if (rows_max == 32 && parts * (slots_per_xcd / ((rows_total + 15) / 16)) >= per_xcd) w.rows = 16;
+    const int n_groups = (rows_total + w.rows - 1) / w.rows, slot = bid >> 3;
+    const int set = n_groups == 1 ? slot : slot / n_groups;
+    const int sets = slots_per_xcd / n_groups, local = part * sets + set;
+    w.row0 = (slot - set * n_groups) * w.rows;
+    w.piece = (bid & 7) * per_xcd + local;
+    w.any = set < sets && local < per_xcd && w.piece < pl.n_pieces;
+    return w;
 }
 
 // What the merge kernel needs to know of a sequence that starts at stream position `start` and has

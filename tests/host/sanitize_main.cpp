@@ -28,11 +28,11 @@ int oracle_mla(const uint16_t* q, const uint16_t* const* c_ptrs, const int32_t* 
 void oracle_page_of(uint64_t va, uint64_t va_start, uint64_t page_size, uint64_t* page_idx, uint64_t* offset);
 void wl_normal_bf16(uint64_t seed, uint64_t stream, uint64_t offset, uint64_t n, uint16_t* out);
 void wl_uniform_u64(uint64_t seed, uint64_t stream, uint64_t offset, uint64_t n, uint64_t* out);
-int xattn_test_plan(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int32_t* total_out);
-int xattn_test_piece_bounds(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int32_t* bounds_out);
-int xattn_test_piece_segments(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int p,
+int xattn_test_plan(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int32_t* total_out);
+int xattn_test_piece_bounds(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int32_t* bounds_out);
+int xattn_test_piece_segments(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int p,
                               int32_t* segs_out, int max_segs);
-int xattn_test_meta(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int32_t* meta_out);
+int xattn_test_meta(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int32_t* meta_out);
 }
 
 static int g_failures = 0;
@@ -181,16 +181,16 @@ static void plan_scenarios() {
         for (int pieces : pieces_list) {
             for (int skew : {0, 32, 200}) {
                 int32_t total = 0;
-                const int used = xattn_test_plan(lens.data(), batch, pieces, 16, 16, skew, &total);
+                const int used = xattn_test_plan(lens.data(), batch, pieces, 16, 16, skew, 0, 1, &total);
                 CHECK(used >= 1 && used <= pieces);
                 std::vector<int32_t> bounds(pieces + 2), meta(2 * (size_t)batch), segs(5 * 4200);
-                CHECK(xattn_test_piece_bounds(lens.data(), batch, pieces, 16, 16, skew, bounds.data()) == used);
+                CHECK(xattn_test_piece_bounds(lens.data(), batch, pieces, 16, 16, skew, 0, 1, bounds.data()) == used);
                 CHECK(bounds[0] == 0 && bounds[used] == total);
-                CHECK(xattn_test_meta(lens.data(), batch, pieces, 16, 16, skew, meta.data()) == 0);
+                CHECK(xattn_test_meta(lens.data(), batch, pieces, 16, 16, skew, 0, 1, meta.data()) == 0);
                 long tokens = 0, want = 0;
                 for (int b = 0; b < batch; ++b) want += lens[b] > 0 ? lens[b] : 0;
                 for (int p = 0; p < used; ++p) {
-                    const int n = xattn_test_piece_segments(lens.data(), batch, pieces, 16, 16, skew, p, segs.data(), 4200);
+                    const int n = xattn_test_piece_segments(lens.data(), batch, pieces, 16, 16, skew, 0, 1, p, segs.data(), 4200);
                     CHECK(n >= 0 && n <= 4200);
                     for (int i = 0; i < n && i < 4200; ++i) tokens += segs[5 * i + 2] - segs[5 * i + 1];
                 }

@@ -163,3 +163,79 @@ def test_stream_positions_up_to_the_32_bit_limit():
     assert segs[-1][0] == 4095 and segs[-1][2] == lens[-1]
     too_many = np.full(4096, 524288, np.int64)                   # N = 2^31 + ...: outside the limit
     assert host_lib.plan(too_many, 256, 64, GQA_COST) == (-1, -1)
+
+
+# ----------------------------------------------------------------------------- short streams, the kernels' defaults
+FEW_GQA, FEW_MLA = (256, 16), (32, 32)
+
+
+def _short_streams():
+    """Streams around the totals where the finer cut of short streams starts, is full and ends."""
+    for total in (17, 31, 32, 33, 511, 512, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 16383, 16384, 16385, 40000):
+        yield "one of %d" % total, [total]
+    rng = np.random.RandomState(12)
+    for n, hi in ((4, 300), (53, 100), (256, 16), (62, 84), (700, 5)):
+        yield "%d of up to %d" % (n, hi), 1 + rng.randint(0, hi, size=n)
+    yield "with empty ones", [0, 5, -2, 300, 0, 0, 17]
+
+
+SHORT = list(_short_streams())
+
+
+@pytest.mark.parametrize("cost,few,n_pieces,min_piece", [(GQA_COST, FEW_GQA, 256, 64), (GQA_COST, FEW_GQA, 1024, 64), (GQA_COST, FEW_GQA, 128, 64),
+                                                         (GQA_COST, (37, 16), 256, 64), (MLA_COST, FEW_MLA, 256, 64), (96, FEW_MLA, 128, 64)])
+@pytest.mark.parametrize("name,lens", SHORT, ids=[c[0] for c in SHORT])
+def test_short_streams_are_cut_finer(name, lens, cost, few, n_pieces, min_piece):
+    lens = np.asarray(lens, np.int64)
+    B, skew = len(lens), 32
+    N = int(sum(L + cost for L in lens if L > 0))
+    total, used = host_lib.plan(lens, n_pieces, min_piece, cost, skew, few)
+    assert total == N
+    assert used == max(1, min(n_pieces, max(N // min_piece, min(few[0], N // few[1]))))
+    bounds = host_lib.piece_bounds(lens, n_pieces, min_piece, cost, skew, few).astype(np.int64)
+    assert bounds[0] == 0 and bounds[-1] == N and len(bounds) == used + 1
+    sizes = np.diff(bounds)
+    assert np.all(sizes > 0) and np.all(bounds[:-1] % 16 == 0)
+    for x in range(0, N, max(1, N // 997)):
+        assert host_lib.piece_of(lens, n_pieces, min_piece, cost, x, skew, few) == int(np.searchsorted(bounds, x, side="right")) - 1
+    # every key in one segment, slots unique, and the merge's table equal to the walk
+    meta = host_lib.meta(lens, n_pieces, min_piece, cost, skew, few)
+    seen = {b: [] for b in range(B)}
+    slots = set()
+    for p in range(used):
+        for b, j0, j1, slot, whole in host_lib.piece_segments(lens, n_pieces, min_piece, cost, p, skew=skew, few=few):
+            assert slot == p + b and slot < n_pieces + B and slot not in slots
+            slots.add(slot)
+            seen[b].append((j0, j1, slot, whole))
+    for b in range(B):
+        segs = seen[b]
+        assert int(meta[b, 1]) == len(segs)
+        if not segs:
+            assert lens[b] <= 0
+            continue
+        assert segs[0][0] == 0 and segs[-1][1] == lens[b] and all(u[1] == v[0] for u, v in zip(segs, segs[1:]))
+        assert [s[2] for s in segs] == list(range(int(meta[b, 0]), int(meta[b, 0]) + len(segs)))
+        assert bool(segs[0][3]) == (len(segs) == 1)
+
+
+@pytest.mark.parametrize("parts", [1, 2, 4, 8])
+@pytest.mark.parametrize("n_pieces", [8, 37, 128, 256, 512, 1000, 2048])
+def test_every_piece_and_row_has_one_workgroup_part(n_pieces, parts):
+    """xattn_decode's map from workgroups to pieces and query rows, for every number of pieces that a stream may
+    bring into use and 1 to 64 rows: each row of each piece in use is computed once, on the matrix path (16 or 32
+    rows per wave; a tile per workgroup where enough of them are idle) and on the vector path (up to 8)."""
+    used_counts = sorted({1, 2, 7, 8, 9, 15, 16, 17, n_pieces // 3 + 1, n_pieces // 2, n_pieces // 2 + 1, n_pieces - 1, n_pieces})
+    narrow = wide = 0
+    for used in used_counts:
+        if not 1 <= used <= n_pieces:
+            continue
+        for rows in (1, 2, 3, 4, 8, 9, 15, 16, 17, 24, 31, 32, 33, 47, 48, 49, 63, 64):
+            for rows_max in {8, 16 if rows <= 16 else 32}:
+                total = 16 * used + 5
+                got_rows, count = host_lib.decode_work(total, n_pieces, 64, GQA_COST, used, parts, rows, rows_max, few=(used, 16))
+                assert np.all(count == 1), (used, rows, rows_max)
+                assert got_rows == rows_max or (rows_max == 32 and got_rows == 16)
+                if rows_max == 32:
+                    narrow += got_rows == 16
+                    wide += got_rows == 32
+    assert n_pieces < 128 or (narrow and wide)          # both ways were taken
