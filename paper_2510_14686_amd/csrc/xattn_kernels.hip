@@ -357,12 +357,15 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], LowSums<
         if (__builtin_amdgcn_ballot_w64(moves) != 0) {
             const float m_new = moves ? mx : st[t].m;
             const float alpha = moves ? fast_exp2(st[t].m - m_new) : 1.0f;
+            const bool first = __builtin_amdgcn_ballot_w64(moves && st[t].m != kNegInf) == 0;      // all sums are still 0
             st[t].m = m_new;
             st[t].l *= alpha;
+            if (!first) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                st[t].o[e] *= alpha;
-                if constexpr (kLowApart<kPv>) low.o[e] *= alpha;
+                for (int e = 0; e < 8; ++e) {
+                    st[t].o[e] *= alpha;
+                    if constexpr (kLowApart<kPv>) low.o[e] *= alpha;
+                }
             }
         }
         const float m_use = (st[t].m == kNegInf) ? 0.0f : st[t].m;
@@ -519,7 +522,10 @@ __device__ __forceinline__ void matrix_run(MatrixState (&st)[kTiles], MatrixCtx<
 #pragma unroll
         for (int e = 0; e < 8; ++e)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) st[0].o[e][j] += __builtin_isfinite(st[0].o[e][j]) ? low.o[e][j] : 0.0f;
+            for (int j = 0; j < 4; ++j) {
+                const float sum = st[0].o[e][j] + low.o[e][j];
+                st[0].o[e][j] = __builtin_amdgcn_fmed3f(sum, sum, st[0].o[e][j]);      // of a NaN and o: o
+            }
     }
 }
 
