@@ -21,6 +21,7 @@ def small_pieces():
     yield
     xa.xattn_configure(xa.XATTN_CFG_PIECES, 0)
     xa.xattn_configure(xa.XATTN_CFG_MIN_PIECE_TOKENS, 0)
+    xa.xattn_configure(xa.XATTN_CFG_PATH, 0)
 
 
 def _case(lens, T, Hq, Hkv):
@@ -30,17 +31,31 @@ def _case(lens, T, Hq, Hkv):
     return q, ks, vs
 
 
-# rows per KV head: 1 and 3 (vector path), 4, 16, 17, 32 (one and two tiles), 33 and 64 (two workgroups per piece)
+# rows per KV head: 1, 3, 4 and 16 (one tile), 17 and 32 (two), 33 and 64 (two workgroups per piece); the vector path
+# with 1 to 8 rows per wave and up to eight workgroups per piece
+@pytest.mark.parametrize("path", [0, 1])
 @pytest.mark.parametrize("T,group", [(1, 1), (3, 1), (1, 4), (4, 4), (1, 17), (4, 8), (3, 11), (16, 4)])
 @pytest.mark.parametrize("Hkv", [1, 2, 3, 8])
 @pytest.mark.parametrize("lens", [(5000, 16, 37, 3333), (700, 16, 37, 300), (17,)])
-def test_pieces_and_rows_per_workgroup(T, group, Hkv, lens):
-    """More pieces than compute units, so that every wave of a workgroup has a piece of its own; and short
+def test_pieces_and_rows_per_workgroup(T, group, Hkv, lens, path):
+    """More pieces than workgroups with few KV heads, so that several waves of one have a piece of their own; and short
     streams in the default partition: pieces of 16 keys, a workgroup for every 16 query rows."""
     import paper_2510_14686_amd as xa
     from gpu_util import check_against_oracle
+    xa.xattn_configure(xa.XATTN_CFG_PATH, path)
     if sum(lens) < 2000:
         xa.xattn_configure(xa.XATTN_CFG_MIN_PIECE_TOKENS, 0)
+    q, ks, vs = _case(lens, T, group * Hkv, Hkv)
+    check_against_oracle(q, ks, vs, lens, SCALE, what="T=%d group=%d Hkv=%d" % (T, group, Hkv))
+
+
+@pytest.mark.parametrize("T,group", [(1, 3), (1, 8), (4, 8), (3, 11)])
+@pytest.mark.parametrize("Hkv", [1, 2, 3])
+def test_every_part_of_every_workgroup_has_a_piece(T, group, Hkv):
+    """256 workgroups of 8, 4 and 2 parts, half as many where two share a piece: 2048 pieces of 16 keys at most, which
+    the stream fills."""
+    from gpu_util import check_against_oracle
+    lens = (33000, 5, 1000)
     q, ks, vs = _case(lens, T, group * Hkv, Hkv)
     check_against_oracle(q, ks, vs, lens, SCALE, what="T=%d group=%d Hkv=%d" % (T, group, Hkv))
 

@@ -89,6 +89,37 @@ def test_the_largest_key_has_an_exact_weight(configure, T, group):
     assert worst <= 4.5 * 2.5e-4 + 2.0 ** -13.8, worst
 
 
+@pytest.mark.parametrize("pv_mode", [0, 1])
+@pytest.mark.parametrize("pieces", [1, 2])
+@pytest.mark.parametrize("T,group", ROWS)
+def test_weights_have_more_than_sixteen_bits(configure, T, group, pieces, pv_mode):
+    """Two keys whose values cancel to about 2^-15 of themselves, in one segment and in two: 16-bit weights are off by
+    up to 2^-17, a sixteenth of the result on average."""
+    from gpu_util import gpu_attn
+    configure(pieces, 16, 0, pv_mode)
+    L, Hkv = 32, 8
+    delta = 0.25 + np.arange(Hkv) / 16.0                      # second key's score below the first's, per KV head
+    Hq = group * Hkv
+    q = np.zeros((1, T, Hq, D), np.float32)
+    q[..., 0] = 1.0
+    k = np.zeros((L, Hkv, D), np.float32)
+    k[:, :, 0] = -200.0                                       # no weight
+    k[3, :, 0] = 0.0
+    k[20, :, 0] = -delta
+    v = np.zeros((L, Hkv, D), np.float32)
+    a, b = np.meshgrid(np.arange(128, 256), np.arange(128, 256), indexing="ij")
+    for h in range(Hkv):
+        diff = np.abs(a - b * math.exp(-delta[h])).ravel()
+        best = np.argsort(diff)[:D]                           # the 128 closest pairs of 8-bit values
+        v[3, h], v[20, h] = a.ravel()[best], -b.ravel()[best]
+    out_bits, _ = gpu_attn(_bf16(q), [_bf16(k)], [_bf16(v)], [L], 1.0)
+    ref, _ = oracle.attn(_bf16(q), [_bf16(k)], [_bf16(v)], [L], 1.0)
+    got = bf16_to_f32(out_bits).astype(np.float64).reshape(ref.shape)
+    # the output's rounding; and of the summands, below 256: exp2 (2^-23), its argument (up to 1: twice 2^-24), the
+    # weights of a merge (2^-23) and the sums (2^-24)
+    assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 256 * 2.0 ** -21)
+
+
 # rows 1 to 3 per KV head; merges of 16, 4 and 1 waves per row; segments from one to 64
 @pytest.mark.parametrize("T,group,Hkv", [(1, 1, 2), (1, 2, 8), (3, 1, 3), (1, 1, 600), (1, 3, 700)])
 @pytest.mark.parametrize("pieces", [1, 3, 20, 64])
