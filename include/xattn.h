@@ -170,9 +170,9 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *                               xattn_mla_decode: one per 128 query rows of a sequence); and, with fewer
  *                               than 8 KV heads, times 8 / n_kv_heads (a workgroup then holds that many
  *                               pieces) as far as the partial results fit XATTN_NOALLOC_SCRATCH_BYTES
- *   XATTN_CFG_MIN_PIECE_TOKENS  lower bound on a piece's tokens; 0 = default (64, and 16 as long as no
- *                               compute unit gets more than one piece; xattn_mla_decode: 32 for the
- *                               first 32 pieces); values below 16
+ *   XATTN_CFG_MIN_PIECE_TOKENS  lower bound on a piece's tokens; 0 = default (64; 16 for up to as many
+ *                               pieces as compute units and 8 MiB of partial results;
+ *                               xattn_mla_decode: 64, and 32 for up to 32 pieces); values below 16
  *                               count as 16
  *   XATTN_CFG_TIMING            1 = record per-kernel events (see xattn_timing_read); 0 = off
  *   XATTN_CFG_PATH              inner loop of the decode kernel: 0 = automatic (the matrix-core path),
@@ -187,9 +187,11 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *                               of every segment and wherever a key carries 1/4 or more of its row's
  *                               running sum, one bf16 elsewhere; 1 = hi + lo parts everywhere;
  *                               2 = one bf16 per weight everywhere, less exact on peaked rows)
- *   XATTN_CFG_MLA_LAYOUT        xattn_mla_decode workgroup shape for more than 64 query rows per sequence:
- *                               0 = automatic (8 waves of one 16-row tile), 1 = 4 waves of one tile,
- *                               2 = 4 waves of two tiles; for experiments, results do not depend on it
+ *   XATTN_CFG_MLA_LAYOUT        xattn_mla_decode workgroup shape: 0 = automatic (up to 32 query rows per
+ *                               sequence four waves share a 16-row tile; then one tile per wave, up to
+ *                               8 waves), 1 = one tile per wave, up to 4 waves, for any number of rows,
+ *                               2 = as 1 up to 64 rows, then 4 waves of two tiles; for experiments,
+ *                               results agree within their rounding
  *   XATTN_CFG_XCD_SKEW          the chip's eight XCDs do not stream at the same rate (the odd-numbered ones
  *                               are slower), so the stream is cut into eight XCD parts of unequal length
  *                               before each part is cut into equal pieces: 0 = the kernel's default,

@@ -290,10 +290,13 @@ int decode_call(const char* who, FixedWorkspaceFn fixed_workspace, const void* q
     prm.parts = split.parts;
     prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : kDefaultMinPieceTokens;
     if (prm.min_piece_tokens < 16) prm.min_piece_tokens = 16;      // one 16-key block at least
-    // One block per piece as long as every piece gets a compute unit of its own: 695 tokens 11.4 -> 8.9 us,
-    // 207 tokens of 16 KV heads 13.7 -> 11.8; 64-token pieces beyond that (smaller ones only add merge work), and
-    // where the partial results of many query rows would come to more than kFewBytes (62 sequences of 42 to
-    // 84 tokens, 24 rows of 8 KV heads: 24.1 us in 64-token pieces, 28.1 in 32 MB of one-block pieces).
+    // One block per piece up to one piece per compute unit (with more than 8 KV heads, per group of 8 heads): 695
+    // tokens 11.4 -> 8.9 us, 207 tokens of 16 KV heads 13.7 -> 11.8; 64-token pieces beyond that (smaller ones only
+    // add merge work), and where the partial results of many query rows would come to more than kFewBytes.
+    // 0 / 2 / 4 / 8 / 16 / 32 MiB of them, us: 62 sequences of 42 to 84 tokens, 8 KV heads, 24 rows 21.5 / 21.6 /
+    // 21.6 / 21.6 / 22.7 / 26.4, 4 rows 14.3 / 14.0 / 12.3 / 12.3 / 12.3 / 12.3; 8 of 100 to 300, 32 rows 15.2 /
+    // 15.2 / 15.2 / 15.5 / 17.9 / 17.9, 8 rows 13.1 / 13.3 / 11.7 / 11.7 / 11.7 / 11.7; on seven more shapes 8 is
+    // within 3 % of the best but for 20 sequences of 60 to 120 with 8 rows of 16 KV heads (7 %).
     const int few_slots = (int)(kFewBytes / ((size_t)q_len * n_q_heads * (kHeadDim + 2) * sizeof(float))) - batch;
     prm.few = g_cfg_min_piece > 0 || few_slots < 1 ? FewPieces{0, 1} : FewPieces{few_slots < d->n_cu ? few_slots : d->n_cu, 16};
     prm.xcd_skew = g_cfg_xcd_skew > 0 ? g_cfg_xcd_skew - 1 : kDefaultXcdSkewGqa;
@@ -440,8 +443,11 @@ int xattn_mla_decode(const void* q, const void* const* c_ptrs, const int32_t* kv
     prm.n_pieces = n_pieces;
     prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : kDefaultMinPieceTokens;
     if (prm.min_piece_tokens < 16) prm.min_piece_tokens = 16;
-    // A block is 32 keys and a segment's fixed work larger here: 72 rows, 182 tokens 19.2 -> 17.7 us; more
-    // short pieces than this cost more in the merge than they gain.
+    // A block is 32 keys and a segment's fixed work larger here.  Up to 0 / 16 / 32 / 64 / 128 / 256 short pieces,
+    // us: 171 tokens, 72 rows 18.8 / 16.9 / 15.0 / 15.0 / 15.0 / 15.0; 113 tokens, 128 rows 20.4 / 16.3 from 16 on; 469
+    // tokens, 16 rows 10.9 / 10.9 / 10.8 / 10.7 / 10.7 / 10.7.  Longer streams gain up to 8 % from 128 (2194 tokens,
+    // 16 rows 13.4 / 13.4 / 13.4 / 12.7 / 12.3 / 12.3) or lose from 64 (1298 tokens, 128 rows 20.4 / 20.4 / 20.4 /
+    // 21.4 / 19.9 / 19.9); 32 changes none of them.
     prm.few = g_cfg_min_piece > 0 ? FewPieces{0, 1} : FewPieces{32, 32};
     prm.xcd_skew = g_cfg_xcd_skew > 0 ? g_cfg_xcd_skew - 1 : kDefaultXcdSkewMla;
     prm.layout = g_cfg_mla_layout;

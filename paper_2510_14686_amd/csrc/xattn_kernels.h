@@ -49,12 +49,13 @@ constexpr int kPvFp32 = 1;     // fp32 MFMA 16x16x4, p exact; 4x the matrix-core
 constexpr int kPvBf16 = 2;     // bf16 MFMA 16x16x16 once, p rounded to bf16; same speed as the default, less exact
 constexpr int kPvBf16x3Apart = 3;      // internal, below 4 rows per KV head: as 0, and infinite values keep their sums
 
-// Inner-loop choice: automatic = matrix path (see use_matrix_path).
+// Inner-loop choice: automatic = matrix path (see use_matrix_path); kPathMatrix also opens the weight modes to
+// calls below 4 rows per KV head.
 constexpr int kPathAuto = 0;
 constexpr int kPathVector = 1;
 constexpr int kPathMatrix = 2;
 
-bool use_matrix_path(int rows_total, int path);
+bool use_matrix_path(int path);
 
 // Query rows one wave handles for a KV head with rows_total = group * q_len rows; more rows than that
 // make row groups, workgroups that read the same pieces.

@@ -25,8 +25,8 @@
 //     tiles 129.7 us, of which about 20 are fixed: 38 MB of partial results): the K block is transposed
 //     through wave-private LDS into the MFMA operand layout, S^T = K Q^T by bf16 MFMA 16x16x32;
 //     softmax on the accumulator layout (a lane holds 4 keys of one row); O^T += V^T P^T by bf16 MFMA
-//     16x16x16 straight from the V registers (V never touches LDS), with p fed as hi + lo bf16 parts
-//     so that it keeps 16 significant bits (24, in three parts, below 4 rows per KV head).
+//     16x16x16 straight from the V registers (V never touches LDS), with p fed as three bf16 parts
+//     so that it keeps its 24 significant bits.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -249,8 +249,9 @@ __device__ __forceinline__ void vector_segment(const DecodeParams& prm, const Se
 // Lane (kb, n) = (lane / 16, lane % 16).  Loads: lane holds 16 bytes (chunk n of 16) of key rows
 // 4*i + kb, i = 0..3, of the 16-key block, so that a load instruction reads four consecutive 256-byte rows.
 // Below, "key 4*kb + i" of a block is the one that lane group kb holds in register i.  (K loaded as the MFMA
-// takes it, 64 bytes of each of 16 rows per instruction, needs no LDS and costs 5 to 8 % of the large calls.)  MFMA index maps (any consistent map of the 128 columns to the contraction index, and
-// of output columns to physical columns, is allowed):
+// takes it, 64 bytes of each of 16 rows per instruction, needs no LDS and costs 5 to 8 % of the large calls.)
+// MFMA index maps (any consistent map of the 128 columns to the contraction index, and of output columns to
+// physical columns, is allowed):
 //   S^T[key][row] = sum_c K[key][c] Q[row][c]: 16x16x32 step s, lane (kb, x) contracts chunk 4*s + kb
 //   O^T_e[x][row] += V[key][8*x + e] P[row][key]: 16x16x4 call (i, e) contracts keys 4*kb + i
 // Pitch of a K row in LDS: 2 * odd chunks modulo 16, conflict-free for writes of whole rows and for the
@@ -340,7 +341,7 @@ __device__ __forceinline__ void matrix_block(MatrixState (&st)[kTiles], LowSums<
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
     next.template at<2>();
-    // s[t][i] = score of key j_block + 4*kb + i for row n of tile t
+    // s[t][i] = score of the key in register i, row 4*i + kb of the block, for row n of tile t
     float p[kTiles][4];
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) {
@@ -510,7 +511,7 @@ __device__ __forceinline__ void matrix_run(MatrixState (&st)[kTiles], MatrixCtx<
     auto key0 = [&](int blk) { return seg.j0 + blk * kBlockKeys; };
     KvRegs Bk;
     int blk = 0;
-        for (; blk + 2 <= n_blocks; blk += 2) {
+    for (; blk + 2 <= n_blocks; blk += 2) {
         matrix_block<kPv, kTiles>(st, low, c.first, c.qop, lds_wave, prm.scale_log2, key0(blk), c.lim, kb, n,
                                   NextLoad{Bk, c.rk, c.rv, c.voffset, row_stride, key0(blk + 1), true});
         matrix_block<kPv, kTiles>(st, low, Bk, c.qop, lds_wave, prm.scale_log2, key0(blk + 1), c.lim, kb, n,
@@ -819,12 +820,13 @@ hipError_t launch_write_kvcache(const WriteParams& prm, hipStream_t stream) {
 // of a tile is then padding: it keeps the next segment's loads ahead of the stores, and the calls are bound by
 // HBM.  138468 tokens of 8 KV heads, 1 / 2 / 3 rows: vector path 95.4 / 97.2 / 99.0 us, matrix path 92.8 /
 // 93.0 / 93.2; 80 to 700 tokens 9.1 -> 8.7 and 11.0 -> 10.5; no shape tried was slower by more than 1 %.  The
-// weights keep 24 bits there (kPvBf16x3): the error against 64 bits is the vector path's to seven digits on
-// eight shapes (1.656835e-3, which is the output's own rounding).
-bool use_matrix_path(int, int path) { return path != kPathVector; }
+// weights keep 24 bits there: the error against 64 bits is the vector path's to seven digits on eight shapes
+// (1.656835e-3, which is the output's own rounding).  The vector path stays as a second computation of the same
+// function that shares none of the matrix path's layouts, for cross-checks.
+bool use_matrix_path(int path) { return path != kPathVector; }
 
 int rows_per_wave(int rows_total, int path) {
-    if (use_matrix_path(rows_total, path)) return rows_total <= 16 ? 16 : 32;
+    if (use_matrix_path(path)) return rows_total <= 16 ? 16 : 32;
     static const int kSizes[] = {1, 2, 3, 4, 5, 6, 8};
     for (int s : kSizes)
         if (rows_total <= s) return s;
@@ -833,7 +835,7 @@ int rows_per_wave(int rows_total, int path) {
 
 hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t* events) {
     const int rows_total = prm.group * prm.q_len;
-    const bool matrix = use_matrix_path(rows_total, prm.path);
+    const bool matrix = use_matrix_path(prm.path);
     const int R = rows_per_wave(rows_total, prm.path);
     const int heads_per_block = prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;
     dim3 grid(decode_grid_x(prm.n_pieces, prm.parts, rows_total, R), 1, (prm.n_kv_heads + kMaxWavesPerBlock - 1) / kMaxWavesPerBlock);

@@ -896,7 +896,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
 // ----------------------------------------------------------------------- few query rows: 32 at most
 // With 16 rows (heads split over several GPUs) a cached byte meets 30 flop: bound by HBM, and what matters
 // is that a compute unit keeps its loads in flight.  One wave per 16 rows does not: it issues 38 loads per
-// block, then works through the block alone (2.7 TB/s at 16 rows).  Here four waves share a
+// block, then works through the block alone (2.4 TB/s at 16 rows).  Here four waves share a
 // 16-row tile: of a block's scores wave q computes key tile q % 2 over half q / 2 of the key width (9 MFMAs,
 // 36 registers of Q), the four partial tiles meet in LDS, every wave does the (small) softmax of the whole
 // tile for itself, and accumulates 128 of the 512 value columns (8 MFMAs, 32 accumulators).  No operand

@@ -2,7 +2,8 @@
 // HIP graph capture, tight serving loops, harnesses that forbid it).  The partial results of split
 // sequences, which xattn_decode keeps in a workspace from hipMalloc, live here in a device array of
 // fixed size that is part of the library's code object; every GPU holds its own copy until the
-// process ends.  Same kernels, same partition and therefore the same bits as xattn_decode.
+// process ends.  Same kernels, same partition and therefore the same bits as xattn_decode on a workspace that
+// holds the call's whole split.
 #include <hip/hip_runtime.h>
 
 #include <mutex>

@@ -58,7 +58,8 @@ XATTN_HD Plan plan_for_total(int total, int n_pieces, int min_piece, int seg_cos
     pl.n_pieces = n < n_pieces ? n : n_pieces;
     pl.seg_cost = seg_cost;
     // the skew needs the eight XCD parts to hold the same number of pieces, and pieces long enough for a
-    // few per cent of them to be a block or more
+    // few per cent of them to be a block or more (pieces, not workgroups: calls with several pieces per
+    // workgroup reach it at that many times the tokens; the skew was not measured for them)
     const bool can_skew = xcd_skew > 0 && pl.n_pieces % 8 == 0 && total / pl.n_pieces >= kMinSkewPiece;
     pl.xcd_skew = can_skew ? (xcd_skew < kMaxXcdSkew ? xcd_skew : kMaxXcdSkew) : 0;
     return pl;

@@ -49,7 +49,7 @@ static int g_decodes = 0, g_merges = 0;
 static DecodeParams g_prm;
 static MlaParams g_mla;
 
-bool use_matrix_path(int, int path) { return path != kPathVector; }
+bool use_matrix_path(int path) { return path != kPathVector; }
 int rows_per_wave(int rows_total, int) { return rows_total <= 16 ? 16 : 32; }
 void mla_block_shape(int, int, int* waves, int* tiles) { *waves = 8; *tiles = 1; }
 static hipError_t launch() {
