@@ -126,6 +126,43 @@ def test_capture_refuses_to_grow_the_workspace():
         assert float(marker[0]) == 1.0                             # the capture recorded the rest and replays
 
 
+def test_capture_after_a_smaller_call_gives_the_eager_bits():
+    """With fewer than 8 KV heads the partition takes several pieces per workgroup: the same ones in a graph, on a
+    stream whose workspace a smaller call of another shape made, as eagerly and in the fixed scratch array."""
+    import torch
+
+    import paper_2510_14686_amd as xa
+    xa.xattn_configure(xa.XATTN_CFG_PIECES, 0)
+    B, T, Hq, Hkv = 8, 1, 8, 2
+    lens = np.array([3000, 2000, 50, 4000, 9000, 1, 700, 5000], np.int32)
+    q = normal_bf16(99, 0, B * T * Hq * D).reshape(B, T, Hq, D)
+    ks = [normal_bf16(99, 1 + 2 * b, int(L) * Hkv * D).reshape(int(L), Hkv, D) for b, L in enumerate(lens)]
+    vs = [normal_bf16(99, 2 + 2 * b, int(L) * Hkv * D).reshape(int(L), Hkv, D) for b, L in enumerate(lens)]
+    side = torch.cuda.Stream()                                  # a fresh stream: its workspace starts empty
+    with xa.KVStore(ks, vs) as store:
+        qd = torch.from_numpy(q.view(np.int16)).cuda()
+        lens_d = torch.from_numpy(lens).cuda()
+        outs = [torch.zeros((B, T, Hq, D), dtype=torch.int16, device="cuda") for _ in range(3)]
+        lses = [torch.zeros((B, T, Hq), dtype=torch.float32, device="cuda") for _ in range(3)]
+        torch.cuda.synchronize()
+        xa.xattn_decode(qd, store.k_ptrs, store.v_ptrs, lens_d, 1, T, Hkv, Hkv, D, SCALE, outs[0], lses[0], side)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            xa.xattn_decode(qd, store.k_ptrs, store.v_ptrs, lens_d, B, T, Hq, Hkv, D, SCALE, outs[0], lses[0], side)
+        main = torch.cuda.current_stream()
+        for r in range(3):
+            outs[0].fill_(0x7FC0)
+            lses[0].fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for fn, i in ((xa.xattn_decode, 1), (xa.xattn_decode_noalloc, 2)):
+                fn(qd, store.k_ptrs, store.v_ptrs, lens_d, B, T, Hq, Hkv, D, SCALE, outs[i], lses[i], main)
+                torch.cuda.synchronize()
+                assert torch.equal(outs[i], outs[0]) and torch.equal(lses[i], lses[0]), (r, i)
+
+
 def test_recorded_graph_stays_valid_after_the_workspace_has_grown():
     """A graph records the address of its stream's workspace.  A later, larger eager call on the same
     stream has to replace that workspace; the buffer the graph uses is retired, not freed, so replaying
