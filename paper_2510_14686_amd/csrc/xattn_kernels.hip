@@ -22,7 +22,7 @@
 //     online softmax in fp32 (log2 domain); p.v by fp32 FMA.
 //   * matrix path (one or two tiles of 16 rows per wave; beyond 32 rows several workgroups share a piece.
 //     verify, 32 rows per KV head, 165109 tokens: one tile per wave, every piece read twice, 238.6 us; two
-//     tiles 129.7 us, of which about 20 are fixed: 38 MB of partial results): the K block is transposed
+//     tiles 130.9 us, of which about 20 are fixed: 38 MB of partial results): the K block is transposed
 //     through wave-private LDS into the MFMA operand layout, S^T = K Q^T by bf16 MFMA 16x16x32;
 //     softmax on the accumulator layout (a lane holds 4 keys of one row); O^T += V^T P^T by bf16 MFMA
 //     16x16x16 straight from the V registers (V never touches LDS), with p fed as three bf16 parts
