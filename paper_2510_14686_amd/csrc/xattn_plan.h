@@ -42,7 +42,7 @@ XATTN_HD int clamp_len(int v) { return v > 0 ? v : 0; }
 // Stream positions of a sequence of `len` tokens (any sign).
 XATTN_HD int stream_len(int len, int seg_cost) { return len > 0 ? len + seg_cost : 0; }
 
-// A short stream is cut finer than n_pieces' min_piece, down to few.min_piece positions, into up to few.pieces
+// A short stream is cut finer than min_piece, down to few.min_piece positions, into up to few.pieces
 // pieces: as long as that only spreads it over idle compute units, shorter pieces finish earlier.
 struct FewPieces {
     int pieces, min_piece;
