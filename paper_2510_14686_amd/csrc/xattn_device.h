@@ -111,6 +111,17 @@ __device__ __forceinline__ float kb_sum(float x) {
     swap32(x, a, b);
     return a + b;
 }
+// The same over all lanes; no LDS round trips either.
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, dpp_f<0xB1>(x));
+    x = fmaxf(x, dpp_f<0x4E>(x));
+    x = fmaxf(x, dpp_f<0x141>(x));
+    return kb_max(fmaxf(x, dpp_f<0x140>(x)));
+}
+__device__ __forceinline__ float wave_sum(float x) { return kb_sum(row16_sum(x)); }
+__device__ __forceinline__ float lane_value(float x, int lane) {      // lane: wave-uniform
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
 
 // Raw buffer descriptor over [base, base + bytes): loads past the end return 0.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {

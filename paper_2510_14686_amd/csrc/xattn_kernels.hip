@@ -698,32 +698,35 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
 //   M = max_s m_s;  l = sum_s l_s 2^(m_s - M);  out = sum_s o_s 2^(m_s - M) / l;  lse = (M + log2 l) ln 2
 // kWaves waves per output row (b, t, h); lane holds columns 2*lane, 2*lane+1.  Sequences with a single
 // segment were finished by the decode kernel and are skipped; sequences without keys get out = 0 and
-// lse = -inf here.  All loads of a round are issued before any is used.
-// Bound by its dependent round trips (table, records and partial rows, every further 8 partial rows), not by
-// bytes: one wave per row took 21.4 us for one sequence of 30001 tokens (32 rows of 256 slots); sixteen
-// waves that each sum a share of the slots and meet once in LDS take 5.2 us.
+// lse = -inf here.
+// Bound by its dependent steps (table; records and partial rows; every further 8 partial rows), not by bytes: one wave
+// per row took 21.4 us for one sequence of 30001 tokens (32 rows of 256 slots); sixteen waves that each sum a share of
+// the slots and meet once in LDS take 5.2 us.  For the same reason a lane fetches one slot's record and takes its
+// weight while the first 8 partial rows are on their way, weights pass by lane reads, and the row's sequence comes
+// from a 32-bit division (the whole call, with a shuffle per weight and a 64-bit division before: 695 tokens of 2 KV
+// heads 8.8 -> 8.5 us; 138468 tokens 32.3 -> 31.8).
 template <int kWaves>
 __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(DecodeParams prm) {
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const long stride_rows = (long)prm.q_len * prm.n_q_heads;
-    const long row = kWaves == 1 ? (long)blockIdx.x * 4 + wave : (long)blockIdx.x;
-    if (row >= (long)prm.batch * stride_rows) return;
-    const int b = (int)(row / stride_rows);
-    const int th = (int)(row - (long)b * stride_rows);
+    const int wave = uniform(threadIdx.x >> 6);
+    const uint32_t seq_rows = (uint32_t)(prm.q_len * prm.n_q_heads);
+    const uint32_t row = kWaves == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
+    const uint32_t b = row / seq_rows;
+    if (b >= (uint32_t)prm.batch) return;
     const int2 fs = reinterpret_cast<const int2*>(prm.meta)[b];
     const int n = fs.y;
     if (n == 1) return;
     const MergeShare sh = merge_share<kWaves>(n, wave);
     if (sh.alone && kWaves > 1 && wave > 0) return;       // few slots: the first wave does the row
-    uint32_t* outp = reinterpret_cast<uint32_t*>(prm.out + row * kHeadDim) + lane;
+    uint32_t* outp = reinterpret_cast<uint32_t*>(prm.out + (long)row * kHeadDim) + lane;
     if (n == 0) {
         *outp = 0u;
         if (prm.lse && lane == 0) prm.lse[row] = kNegInf;
         return;
     }
-    const float2* ml = reinterpret_cast<const float2*>(prm.part_ml) + (long)fs.x * stride_rows + th;
-    const float2* po = reinterpret_cast<const float2*>(prm.part_o + ((long)fs.x * stride_rows + th) * kHeadDim) + lane;
+    const long stride_rows = seq_rows, first_row = (long)fs.x * stride_rows + (row - b * seq_rows);
+    const float2* ml = reinterpret_cast<const float2*>(prm.part_ml) + first_row;
+    const float2* po = reinterpret_cast<const float2*>(prm.part_o + first_row * kHeadDim) + lane;
     // Lane i holds (m, l) of slot first + i of the current group of 64 slots; the first 8 slots' partial
     // rows are requested in the same breath, so a typical row (up to 8 segments) costs one round trip.
     float M = kNegInf, l = 0.0f, o0 = 0.0f, o1 = 0.0f;
@@ -736,26 +739,30 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(
         M = mine.x;
         for (int base = sh.first + 64; base < sh.end; base += 64)
             if (base + lane < sh.end) M = fmaxf(M, ml[(base + lane) * stride_rows].x);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+        M = wave_max(M);
         const float m_use = (M == kNegInf) ? 0.0f : M;
+        float w = fast_exp2(mine.x - m_use);               // lanes past the end: 0
+        l = mine.y * w;
         for (int i0 = 0; sh.first + i0 < sh.end; i0 += 8) {
             const int s0 = sh.first + i0;
             if (i0 > 0) {
-                if ((i0 & 63) == 0) mine = (s0 + lane < sh.end) ? ml[(s0 + lane) * stride_rows] : make_float2(kNegInf, 0.0f);
+                if ((i0 & 63) == 0) {
+                    mine = (s0 + lane < sh.end) ? ml[(s0 + lane) * stride_rows] : make_float2(kNegInf, 0.0f);
+                    w = fast_exp2(mine.x - m_use);
+                    l = __builtin_fmaf(mine.y, w, l);
+                }
 #pragma unroll
                 for (int u = 0; u < 8; ++u) o[u] = po[(s0 + u < sh.end ? s0 + u : sh.end - 1) * stride_rows * (kHeadDim / 2)];
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const float m_s = __shfl(mine.x, (i0 + u) & 63, 64), l_s = __shfl(mine.y, (i0 + u) & 63, 64);
+                const float w_s = lane_value(w, (i0 + u) & 63);
                 const bool in = s0 + u < sh.end;          // past the end: nothing, also where the row read is infinite
-                const float w = in ? fast_exp2(m_s - m_use) : 0.0f;
-                l = __builtin_fmaf(in ? l_s : 0.0f, w, l);
-                o0 = __builtin_fmaf(in ? o[u].x : 0.0f, w, o0);
-                o1 = __builtin_fmaf(in ? o[u].y : 0.0f, w, o1);
+                o0 = __builtin_fmaf(in ? o[u].x : 0.0f, w_s, o0);
+                o1 = __builtin_fmaf(in ? o[u].y : 0.0f, w_s, o1);
             }
         }
+        l = wave_sum(l);
     }
     if constexpr (kWaves > 1) {
         if (!sh.alone) {                                  // the waves' sums, each against its own maximum, meet in LDS
