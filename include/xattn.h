@@ -62,7 +62,7 @@ const char* xattn_last_error(void);
  *                  tokens' K/V are already written).  Read on the device only.  A value < q_len
  *                  leaves the tokens without visible keys with out = 0 and lse = -inf.  The device
  *                  adds the lengths up in 32 bits: the sum over the batch of (kv_lens[b] + 16) must
- *                  stay below 2^31 (for xattn_mla_decode: kv_lens[b] + 192).  The host cannot check
+ *                  stay below 2^31 (for xattn_mla_decode: kv_lens[b] + 256).  The host cannot check
  *                  it and results are undefined beyond, but lengths whose caches fit one GPU's
  *                  memory cannot reach it (2^31 rows of the smallest K/V row pair are 1 TiB).
  * batch    1..4096;  q_len 1..16;  head_dim must be 128;  n_q_heads a multiple of n_kv_heads;
@@ -188,9 +188,9 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *                               running sum, one bf16 elsewhere; 1 = hi + lo parts everywhere;
  *                               2 = one bf16 per weight everywhere, less exact on peaked rows)
  *   XATTN_CFG_MLA_LAYOUT        xattn_mla_decode workgroup shape: 0 = automatic (up to 32 query rows per
- *                               sequence four waves share a 16-row tile; then one tile per wave, up to
- *                               8 waves), 1 = one tile per wave, up to 4 waves, for any number of rows,
- *                               2 = as 1 up to 64 rows, then 4 waves of two tiles; for experiments,
+ *                               sequence four waves share a 16-row tile; then one 32-row tile per wave,
+ *                               4 waves), 1 = one 16-row tile per wave, up to 4 waves, for any number of
+ *                               rows, 2 = as 1 up to 64 rows, then 32-row tiles; for experiments,
  *                               results agree within their rounding
  *   XATTN_CFG_XCD_SKEW          the chip's eight XCDs do not stream at the same rate (the odd-numbered ones
  *                               are slower), so the stream is cut into eight XCD parts of unequal length

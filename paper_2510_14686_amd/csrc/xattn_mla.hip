@@ -5,40 +5,36 @@
 // heads are multiplied with the same cached rows, K is loaded once for all of them and Q stays
 // resident).  Per token the cache holds one row of 576 bf16 (512 latent + 64 rope) that is the key of
 // every head, and whose first 512 values are every head's value.  With 128 heads that is 242 flop per
-// cached byte: the path is bound by the matrix cores and by the LDS that feeds them, not by HBM.
+// cached byte: the path is bound by the matrix cores and what feeds them, with 16 rows by HBM.
 //
-// Partition: the same token-stream pieces as the GQA kernel (section 4.4.3, "Layer 3").  A workgroup
-// owns one piece and up to 128 query rows (row = token * n_heads + head): eight waves, two per SIMD
-// (256 registers each), a wave owning one tile of 16 rows whose output accumulators (16 x 512 fp32 =
-// 128 registers) stay resident for the whole piece.  Of the tile's Q, 13 of the 18 MFMA steps stay in
-// registers (52); each lane parks its chunks of the other 5 in LDS and reads them back per block,
-// which leaves the registers for fetching operands ahead of the MFMAs.  (Workgroups of four waves,
-// one per SIMD with 512 registers and two tiles each, read every LDS operand half as often: built
-// below as mla_block_pp and selectable, but a lone wave per SIMD has nobody to cover its softmax and
-// its longer prologue and epilogue, and it measures about 10 % slower.)
-// All waves share each 32-key block of the cache through LDS:
-//   * the block (32 x 1152 bytes, contiguous in memory) goes from HBM straight into LDS (buffer loads
+// Partition: the same token-stream pieces as the GQA kernel (section 4.4.3, "Layer 3").  A workgroup owns one piece and
+// up to 128 query rows (row = token * n_heads + head), and walks the piece in 32-key blocks that all its waves share
+// through LDS.  Three kernels by the number of rows per sequence:
+//   * up to 32: mla_rows_kernel, four waves per tile of 16 rows;
+//   * more: mla_tile_kernel, one wave per tile of 32 rows;
+//   * mla_decode_kernel, one wave per tile of 16 rows, four tiles at most (XATTN_CFG_MLA_LAYOUT = 1): a second computation
+//     of the same function that shares neither the layouts nor the MFMA shape of the others, for cross-checks.
+// Common to them (the figures are mla_decode_kernel's):
+//   * a block (32 x 1152 bytes, contiguous in memory) goes from HBM straight into LDS (buffer loads
 //     with the LDS destination, 1 KiB per wave instruction, no staging registers), once per
-//     workgroup; three LDS buffers, one barrier per block, two blocks in flight during the
-//     arithmetic.  In LDS the latent and the rope part of the rows sit in two areas with padded
-//     pitches chosen against bank conflicts (the LDS side of such a load is fixed to lane order, so
+//     workgroup, two blocks in flight during the arithmetic.  In LDS the latent and the rope part of the rows sit in two
+//     areas laid out against bank conflicts (the LDS side of such a load is fixed to lane order, so
 //     the layout is made through the global address each lane fetches);
 //   * S^T = C Q^T: per 16-key tile 18 bf16 MFMA 16x16x32, the A operand (keys) read from LDS;
 //   * softmax on the accumulator layout: lane (kb, n) holds, of row n, the keys 4 kb + i of both key
 //     tiles, which is exactly the B operand (8 keys per lane) of the next product, so the weights
-//     never leave the lane; row maxima cross the four lane groups with lane-swap instructions; the
-//     reference maximum of a row moves only when a block exceeds it by more than 2^8, so the 128
+//     never leave the lane; row maxima cross the lane groups with lane-swap instructions; the
+//     reference maximum of a row moves only when a block exceeds it by more than 2^8, so the
 //     accumulators are rescaled about once per segment instead of in most blocks;
-//   * O^T += C[:, 0:512]^T P^T: bf16 MFMA 16x16x32 over the 32 keys, the A operand (16 value columns x
+//   * O^T += C[:, 0:512]^T P^T: bf16 MFMA over the 32 keys, the A operand (value columns x
 //     8 keys per lane) fetched with LDS transposing reads.  A weight enters the product as one bf16
 //     where it is small against the row's sum, and as hi + lo bf16 parts (two MFMAs, 16 significant
 //     bits) where it is not: in the first kExactBlocks blocks of every segment, whose keys' share of
 //     the final sum is not yet known, and in any later block that holds a key with at least 1/4 of
-//     the row's running sum.  The output is normalised by the sum of the weights as they entered
-//     the product.  (Rounding every weight to one bf16 costs nothing on diffuse rows, where the
+//     the row's running sum (of any row of the tile).  The output is normalised by the sum of the weights as they
+//     entered the product.  (Rounding every weight to one bf16 costs nothing on diffuse rows, where the
 //     errors average out; where a few keys carry the row, outputs are large enough for bf16 output
 //     rounding to use up most of the tolerance, and the weights' own 2^-9 no longer fits beside it.)
-// LDS reads are issued a few steps ahead of the MFMAs that use them, pinned with scheduling groups.
 // A segment that is not a whole sequence leaves its rows in the workspace as fp16, scaled by the
 // row's largest magnitude, with (m, l, lq, 1 / scale) in fp32; the merge kernel combines them.
 #include <hip/hip_runtime.h>
@@ -78,10 +74,11 @@ constexpr int kVAhead = 2;                       // value fragments in flight ah
 constexpr int kColTiles = kDv / 16;              // 32 tiles of 16 value columns
 constexpr int kStagePitch = (kDv / 2) * 2 + 16;  // epilogue: 16 rows x 256 16-bit columns at a time per wave, padded rows
 constexpr int kStageWave = 16 * kStagePitch;     // 8448 bytes
-// A segment's fixed work (first block's latency, Q, output staging and stores; measured: workgroups
-// with two segments finish 13 us later than their token count says) in units of one token's share of
-// the block loop (2.3 us per 32 tokens).
-constexpr int kMlaSegCost = 192;
+// A segment's fixed work (Q, the first block's latency and scores, the rounding and stores of the output) in units of
+// one token's share of the block loop.  Calls with 192 / 224 / 256 / 320, us: 64 sequences of 1024 to 8192 tokens, 128
+// rows 98.9 / 98.0 / 97.1 / -, 256 rows 165.9 / 165.0 / 163.5 / -, 64 rows 74.6 / 73.9 / 73.3 / -; 64 of 64 to 256, 128
+// rows 28.8 / 29.4 / 29.6 / -; 320 was level with 256.
+constexpr int kMlaSegCost = 256;
 constexpr float kLazyLog2 = 8.0f;                // slack of the softmax reference maximum, in powers of two
 // Precision of the softmax weights in the value product (see the header comment).
 constexpr int kLoNever = 0;                      // one bf16 per weight everywhere
@@ -89,10 +86,6 @@ constexpr int kLoAlways = 1;                     // hi + lo bf16 parts everywher
 constexpr int kLoDynamic = 2;                    // hi + lo parts only in blocks with a dominant key
 constexpr int kExactBlocks = 4;                  // default mode: the first blocks of a segment run as kLoAlways
 constexpr float kDominantShare = 4.0f;           // a key is dominant from 1 / 4 of the row's running sum
-// Eight waves: the first wave of each SIMD issues its loads of the block after next behind the block's
-// arithmetic, the second one ahead of it, so the two run a fraction of a phase apart and one's vector
-// work falls on the other's MFMAs more often (measured: 3-4 % of the kernel).
-constexpr bool kSkewWaves = true;
 constexpr int kStages = 3;                       // LDS block buffers: two blocks in flight behind the one in use
 
 typedef short s16x4v_t __attribute__((ext_vector_type(4)));
@@ -115,12 +108,11 @@ __device__ __forceinline__ void static_for(F&& f) { static_for(f, std::make_inte
 // cannot tell the two halves of the double buffer apart and would wait for every outstanding load
 // before each read.  dma_wait() before the workgroup barrier is what makes a block visible.
 __device__ __forceinline__ void dma16(u32x4_t rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
-    // m0 carries the LDS address of the load.  The compiler keeps values of its own in m0 (lane
-    // indices, LDS-DMA bases) and does not accept m0 in a clobber list, so the statement saves and
-    // restores it; the load has read m0 by the time it is issued.
-    uint32_t saved_m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 1\n\tbuffer_load_dwordx4 %2, %3, %4 offen nt lds\n\ts_mov_b32 m0, %0"
-                 : "=&s"(saved_m0) : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    // m0 carries the LDS address of the load.  It is not saved: the compiler uses it for indexed register moves,
+    // messages and LDS loads of its own, of which these kernels have none (and it takes no m0 in a clobber list).
+    // Saving and restoring it costs as much as the load: a wave issues an instruction every four cycles or so.
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 : : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 // Waits until at most n of this wave's loads are outstanding (they complete in order): n = the number
 // of loads of the newest block leaves the block before it complete.
@@ -169,7 +161,7 @@ __device__ __forceinline__ void block_load(char* lds_block, u32x4_t rc, int j_bl
                   (uint32_t)(j_block + p * kTailRowsPerLoad) * kRowB);
     }
 }
-// The same for workgroups of four or eight waves with as few scalar instructions as possible: which
+// The same for workgroups of four or eight waves (mla_rows_kernel) with as few scalar instructions as possible: which
 // loads fill the tail area is then known from q alone, and the tail loads run with all lanes.  The
 // lanes that "fetch nothing" above then fetch bytes that do no harm: chunks 72 and 73 of a row (the
 // start of the next row) land in the padding of the tail pitch, lanes 60-63 fetch what the next tail
@@ -412,259 +404,6 @@ __device__ __forceinline__ void mla_block(MlaTile (&st)[RT], const char* qk_base
     }
 }
 
-// ----------------------------------------------------------------------- two row tiles per wave
-// One wave per SIMD with 512 registers: the output accumulators of two 16-row tiles (256) in the
-// accumulation registers, everything else in the ordinary ones.  Every operand fragment read from LDS
-// feeds the MFMAs of both tiles where the order of the work allows it: with one tile per wave each
-// MFMA needs a fragment of its own, 1 KiB per 16 cycles and SIMD, which is all the LDS delivers.
-// A block runs as scores of both tiles (every key fragment feeds two MFMAs), the two softmaxes slice
-// by slice in turn (two independent chains of dependent instructions), values of both tiles (every
-// value fragment feeds two MFMAs).
-// The MFMAs are assembly statements: their accumulators can then be named (scores in ordinary
-// registers, outputs in accumulation registers; through the builtin the compiler puts every MFMA
-// result into the accumulation registers, which the outputs fill alone), and such statements keep
-// their order among themselves and against memory operations, so LDS reads stay where they are
-// written, a fixed number of MFMAs ahead of their use.  Vector instructions do move across them;
-// the softmax is therefore cut into slices of a few instructions whose results pass through an empty
-// statement of the same kind (pin): a slice cannot start before the pin its inputs came through nor
-// end after its own.
-//
-// What the compiler cannot see of an MFMA inside a statement: a vector instruction may read a result
-// register only once the MFMA has left the pipe, so a few idle cycles (mfma_drain) stand between the
-// last score MFMA and the softmax, and between the last value MFMA of a segment and the epilogue; a
-// rescaling reads accumulators a phase or more after the MFMA that wrote them.
-constexpr int kFrags = 2 * kQSteps;              // key fragments per block, ordered (step, key tile)
-constexpr int kPpKAhead = 6;                     // key fragments in flight ahead of their MFMAs
-constexpr int kPpVAhead = 6;                     // value fragments (two reads each) in flight ahead of theirs
-constexpr int kPpDmaEvery = 3;                   // key fragments between two loads of the block after next
-constexpr int kSoftSlices = 27;
-
-__device__ __forceinline__ void mfma_first_v(f32x4_t& acc, bf16x8_t a, bf16x8_t b) {      // acc = a b
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma_v(f32x4_t& acc, bf16x8_t a, bf16x8_t b) {            // acc += a b
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma_a(f32x4_t& acc, bf16x8_t a, bf16x8_t b) {            // the same on accumulation registers
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-// Between the last MFMA statements and the first vector instructions that read their results: the 16
-// cycles an MFMA spends in the pipe and the write-back behind them, with a margin.  The results pass
-// through the statement, so their readers stay behind it.
-__device__ __forceinline__ void mfma_drain(f32x4_t& a, f32x4_t& b, f32x4_t& c, f32x4_t& d) {
-    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
-}
-__device__ __forceinline__ void mfma_drain_acc(f32x4_t& a, f32x4_t& b, f32x4_t& c, f32x4_t& d) {
-    asm volatile("s_nop 15\n\ts_nop 7" : "+a"(a), "+a"(b), "+a"(c), "+a"(d));
-}
-template <typename A> __device__ __forceinline__ void pin(A& a) { asm volatile("" : "+v"(a)); }
-template <typename A, typename B> __device__ __forceinline__ void pin(A& a, B& b) { asm volatile("" : "+v"(a), "+v"(b)); }
-template <typename A, typename B, typename C> __device__ __forceinline__ void pin(A& a, B& b, C& c) {
-    asm volatile("" : "+v"(a), "+v"(b), "+v"(c));
-}
-// max(a, b) of two scores (finite or -inf, no NaNs) as one instruction, the median of (a, b, largest
-// finite float): fmaxf() first quiets each operand it cannot prove to be the result of arithmetic
-// (matrix results, swapped lanes), an instruction apiece.
-__device__ __forceinline__ float max_num(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0x1.fffffep+127f); }
-
-// o *= alpha for a tile whose accumulators live in the accumulation registers: each passes through
-// ordinary registers, one after the other (the pins keep the compiler from fetching all 128 first,
-// which would evict everything else that lives in ordinary registers).
-__device__ __forceinline__ void rescale_acc(MlaTile& st, float alpha) {
-#pragma unroll
-    for (int ct = 0; ct < kColTiles; ++ct) {
-        if (ct > 0) asm volatile("" : "+a"(st.o[ct]), "+a"(st.o[ct - 1]));
-        st.o[ct] *= alpha;
-    }
-}
-
-// The softmax of one row tile over one block, between slices.
-struct SoftRow {
-    float p[8];                      // scores, then weights: keys 16 kt + 4 kb + i at index 4 kt + i
-    float t0, t1, t2, t3, sw0, sw1;
-    float mx, m_new, m_use, alpha, sum, sum_q, dom;
-    uint32_t h[4], lo[4];            // the weights as bf16 pairs, and what the rounding left
-    bool with_lo;
-};
-// Slice K of kSoftSlices.  s: the tile's scores (per key tile); st: its running state.
-template <int K, int kLo, bool kMasked, bool kPinned>
-__device__ __forceinline__ void soft_slice(SoftRow& r, MlaTile& st, const f32x4_t (&s)[2], float scale_log2, int j_block,
-                                           int lim, int kb) {
-    if constexpr (K == 0) {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) r.p[t] = s[t >> 2][t & 3];
-        if (kMasked) {               // keys at or past lim (end of the segment, causal limit of the row) count as -inf
-#pragma unroll
-            for (int t = 0; t < 8; ++t) r.p[t] = (j_block + 16 * (t >> 2) + 4 * kb + (t & 3) < lim) ? r.p[t] : kNegInf;
-        }
-        r.t0 = max_num(r.p[0], r.p[1]);
-        r.t1 = max_num(r.p[2], r.p[3]);
-        if (kPinned) pin(r.t0, r.t1);
-    } else if constexpr (K == 1) {
-        r.t2 = max_num(r.p[4], r.p[5]);
-        r.t3 = max_num(r.p[6], r.p[7]);
-        if (kPinned) pin(r.t2, r.t3);
-    } else if constexpr (K == 2) {
-        r.t0 = max_num(r.t0, r.t1);
-        r.t2 = max_num(r.t2, r.t3);
-        if (kPinned) pin(r.t0, r.t2);
-    } else if constexpr (K == 3) {
-        swap16(max_num(r.t0, r.t2), r.sw0, r.sw1);
-        if (kPinned) pin(r.sw0, r.sw1);
-    } else if constexpr (K == 4) {
-        swap32(max_num(r.sw0, r.sw1), r.sw0, r.sw1);
-        if (kPinned) pin(r.sw0, r.sw1);
-    } else if constexpr (K == 5) {   // the reference maximum follows lazily, see mla_block
-        r.mx = max_num(r.sw0, r.sw1) * scale_log2;
-        r.m_new = r.mx > st.m + kLazyLog2 ? r.mx : st.m;
-        if (kPinned) pin(r.mx, r.m_new);
-    } else if constexpr (K == 6) {
-        r.m_use = (r.m_new == kNegInf) ? 0.0f : r.m_new;
-        r.alpha = fast_exp2(st.m - r.m_use);
-        if (kPinned) pin(r.m_use, r.alpha);
-    } else if constexpr (K >= 7 && K <= 14) {
-        r.p[K - 7] = fast_exp2(__builtin_fmaf(r.p[K - 7], scale_log2, -r.m_use));
-        if (kPinned) pin(r.p[K - 7], r.m_use);
-    } else if constexpr (K == 15) {
-        r.t0 = r.p[0] + r.p[1];
-        r.t1 = r.p[2] + r.p[3];
-        if (kPinned) pin(r.t0, r.t1);
-    } else if constexpr (K == 16) {
-        r.t2 = r.p[4] + r.p[5];
-        r.t3 = r.p[6] + r.p[7];
-        if (kPinned) pin(r.t2, r.t3);
-    } else if constexpr (K == 17) {
-        r.sum = (r.t0 + r.t1) + (r.t2 + r.t3);
-        swap16(r.sum, r.sw0, r.sw1);
-        if (kPinned) pin(r.sum, r.sw0, r.sw1);
-    } else if constexpr (K == 18) {
-        swap32(r.sw0 + r.sw1, r.sw0, r.sw1);
-        if (kPinned) pin(r.sw0, r.sw1);
-    } else if constexpr (K == 19) {
-        st.l = st.l * r.alpha + (r.sw0 + r.sw1);
-        st.m = r.m_new;
-        if (kPinned) pin(st.l, st.m);
-    } else if constexpr (K == 20) {  // a key with at least 1 / kDominantShare of the row's sum so far
-        if (kLo == kLoDynamic) {
-            r.dom = fast_exp2(r.mx - r.m_use) * kDominantShare >= st.l ? 1.0f : 0.0f;
-            if (kPinned) pin(r.dom);
-        }
-    } else if constexpr (K == 21 || K == 22) {
-#pragma unroll
-        for (int u = 2 * (K - 21); u < 2 * (K - 21) + 2; ++u) {
-            const f32x2_t pp = {r.p[2 * u], r.p[2 * u + 1]};
-            r.h[u] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2_t));
-        }
-        if (kPinned) pin(r.h[2 * (K - 21)], r.h[2 * (K - 21) + 1]);
-    } else if constexpr (K == 23) {  // the sum of the rounded weights: each pair times (1, 1), added in fp32
-        r.sum_q = 0.0f;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) r.sum_q = dot2_bf16(r.h[u], 0x3f803f80u, r.sum_q);
-        if (kPinned) pin(r.sum_q);
-    } else if constexpr (K == 24 || K == 25) {
-        if (kLo != kLoNever) {
-#pragma unroll
-            for (int u = 2 * (K - 24); u < 2 * (K - 24) + 2; ++u) {
-                const f32x2_t pp = {r.p[2 * u], r.p[2 * u + 1]};
-                const f32x2_t back = __builtin_convertvector(__builtin_bit_cast(bf16x2_t, r.h[u]), f32x2_t);
-                r.lo[u] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pp - back, bf16x2_t));
-            }
-            if (kPinned) pin(r.lo[2 * (K - 24)], r.lo[2 * (K - 24) + 1]);
-        }
-    } else if constexpr (K == 26) {
-        r.with_lo = kLo == kLoAlways || (kLo == kLoDynamic && __builtin_amdgcn_ballot_w64(r.dom != 0.0f) != 0);
-        st.lq = st.lq * r.alpha + (r.with_lo ? r.sum : r.sum_q);
-        if (kPinned) pin(st.lq);
-    }
-}
-
-// issue(q): the caller's load q of the block after next (a wave-wide load into LDS); they are spread
-// over the score phase, one every kPpDmaEvery fragments: issued together behind the barrier they queue
-// up in front of the memory pipeline and hold every wave until the last one is accepted.
-template <int kLo, bool kMasked, typename Issue>
-__device__ __forceinline__ void mla_block_pp(MlaTile (&st)[2], const char* qk_base, const char* qt_base, const char* pv_base,
-                                             const bf16x8_t (&qop)[2][kQRegSteps], const char* q_lds, float scale_log2,
-                                             int j_block, const int (&lim)[2], int kb, Issue issue) {
-    f32x4_t s[2][2];                 // [row tile][key tile]
-    bf16x8_t ka[kFrags], ql[2][kQSteps - kQRegSteps], va[kColTiles];
-    SoftRow sr[2];
-    // Key fragment F = (step, key tile); with key tile 0 of a step from kQRegSteps on come the lane's
-    // parked chunks of Q for both row tiles.
-    auto load_k = [&](auto f_c) {
-        constexpr int F = decltype(f_c)::value, step = F >> 1, kt = F & 1;
-        if constexpr (step < kMainSteps) ka[F] = *reinterpret_cast<const bf16x8_t*>(qk_base + kt * kTileB + step * 64);
-        else ka[F] = *reinterpret_cast<const bf16x8_t*>(qt_base + kt * kTailTileB + (step - kMainSteps) * 64);
-        if constexpr (kt == 0 && step >= kQRegSteps) {
-#pragma unroll
-            for (int rt = 0; rt < 2; ++rt)
-                ql[rt][step - kQRegSteps] =
-                    *reinterpret_cast<const bf16x8_t*>(q_lds + rt * kQLdsWave + (step - kQRegSteps) * 1024);
-        }
-    };
-    // Value fragment of column tile ct: see mla_block for the layout.
-    auto read_v = [&](int ct) {
-        const s16x4v_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) s16x4v_t*)(pv_base + ct * 32));
-        const s16x4v_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) s16x4v_t*)(pv_base + kTileB + ct * 32));
-        const u32x2_t w0 = __builtin_bit_cast(u32x2_t, v0), w1 = __builtin_bit_cast(u32x2_t, v1);
-        return __builtin_bit_cast(bf16x8_t, u32x4_t{w0.x, w0.y, w1.x, w1.y});
-    };
-    auto load_v = [&](auto i_c) { va[decltype(i_c)::value] = read_v(decltype(i_c)::value); };
-
-    // Scores of both tiles: every key fragment feeds two MFMAs (four independent accumulators).
-    static_for<kPpKAhead>(load_k);
-    static_for<kFrags>([&](auto f_c) {
-        constexpr int F = decltype(f_c)::value, step = F >> 1, kt = F & 1;
-        if constexpr (F + kPpKAhead < kFrags) load_k(std::integral_constant<int, F + kPpKAhead>());
-        else if constexpr (F + kPpKAhead - kFrags < kPpVAhead) load_v(std::integral_constant<int, F + kPpKAhead - kFrags>());
-        if constexpr (F % kPpDmaEvery == kPpDmaEvery - 1) issue(std::integral_constant<int, F / kPpDmaEvery>());
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-            bf16x8_t qv;
-            if constexpr (step < kQRegSteps) qv = qop[rt][step];
-            else qv = ql[rt][step - kQRegSteps];
-            if constexpr (step == 0) mfma_first_v(s[rt][kt], ka[F], qv);
-            else mfma_v(s[rt][kt], ka[F], qv);
-        }
-    });
-    static_assert(kPpVAhead <= kPpKAhead, "the first value fragments are fetched in the last score steps");
-    mfma_drain(s[0][0], s[0][1], s[1][0], s[1][1]);
-    // Softmax of both tiles, slice by slice in turn: two independent chains of dependent instructions.
-    static_for<kSoftSlices>([&](auto k_c) {
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
-            soft_slice<decltype(k_c)::value, kLo, kMasked, false>(sr[rt], st[rt], s[rt], scale_log2, j_block, lim[rt], kb);
-    });
-    bf16x8_t ph[2], pl[2];
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-        if (__builtin_amdgcn_ballot_w64(sr[rt].alpha != 1.0f) != 0) rescale_acc(st[rt], sr[rt].alpha);       // about once per segment
-        ph[rt] = __builtin_bit_cast(bf16x8_t, u32x4_t{sr[rt].h[0], sr[rt].h[1], sr[rt].h[2], sr[rt].h[3]});
-        if (kLo != kLoNever) pl[rt] = __builtin_bit_cast(bf16x8_t, u32x4_t{sr[rt].lo[0], sr[rt].lo[1], sr[rt].lo[2], sr[rt].lo[3]});
-    }
-    // Values of both tiles: every value fragment feeds two MFMAs (four with the lo parts).
-    static_for<kColTiles>([&](auto i_c) {
-        constexpr int I = decltype(i_c)::value;
-        if constexpr (I + kPpVAhead < kColTiles) load_v(std::integral_constant<int, I + kPpVAhead>());
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) mfma_a(st[rt].o[I], va[I], ph[rt]);
-        if (kLo == kLoAlways) {
-#pragma unroll
-            for (int rt = 0; rt < 2; ++rt) mfma_a(st[rt].o[I], va[I], pl[rt]);
-        }
-    });
-    if (kLo == kLoDynamic) {
-        // The rare block with a dominant key: a second pass over the value fragments with the lo parts.
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-            if (!sr[rt].with_lo) continue;
-#pragma unroll
-            for (int ct = 0; ct < kColTiles; ++ct) mfma_a(st[rt].o[ct], read_v(ct), pl[rt]);
-        }
-    }
-}
-
 // kMode: 0 = default (hi + lo weights in the first kExactBlocks blocks of a segment and wherever a key
 // dominates its row), 1 = hi + lo weights everywhere, 2 = one bf16 per weight everywhere.
 template <int NW, int RT, int kMode>
@@ -768,66 +507,28 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
         fence();                  // the Q chunks in LDS are read back by the lane that wrote them
 
         const int n_blocks = (j1 - j0 + kMlaKeys - 1) / kMlaKeys;
-        if constexpr (RT == 2) {
-            // block 1 -> buffer 1; with two tiles per wave every block has its loads, past the segment's
-            // end against an empty buffer (see the block loop), so that the waits need no case.
-            u32x4_t rc1 = rc;
-            if (n_blocks <= 1) rc1[2] = 0u;
-            block_to_lds<NW>(lds_c + kLdsBlock, rc1, j0 + kMlaKeys, wave, dma);
-        } else {
-            if (n_blocks > 1) block_to_lds<NW>(lds_c + kLdsBlock, rc, j0 + kMlaKeys, wave, dma);   // block 1 -> buffer 1
-        }
+        if (n_blocks > 1) block_to_lds<NW>(lds_c + kLdsBlock, rc, j0 + kMlaKeys, wave, dma);   // block 1 -> buffer 1
         int cur_buf = 0, next_buf = 2;         // block blk sits in buffer blk % 3, block blk + 2 goes to next_buf
         // One block: every wave waits for its own loads of block blk (those of block blk + 1 may stay
         // in flight), then the barrier: block blk is in LDS and everyone is done reading block
         // blk - 1, whose buffer the loads of block blk + 2 may overwrite.
-        auto step = [&](int blk, auto lo_mode, auto masked) {
+        auto step = [&](int blk, auto lo_mode) {
             const char* cur = lds_c + cur_buf * kLdsBlock;
-            dma_wait(RT == 2 || blk + 1 < n_blocks ? my_loads : 0);
+            dma_wait(blk + 1 < n_blocks ? my_loads : 0);
             __syncthreads();
-            if constexpr (RT == 2) {
-                static_assert(RT != 2 || (kDmaPerBlock + NW - 1) / NW <= kFrags / kPpDmaEvery, "a slot for every load");
-                // The loads of block blk + 2, spread over the score phase.  Past the segment's end they
-                // run against an empty buffer (nothing is fetched, zeros land in the free LDS buffer),
-                // so that every block issues the same number of loads and the slots need no branch.
-                u32x4_t rc_next = rc;
-                if (blk + 2 >= n_blocks) rc_next[2] = 0u;
-                const DmaWave d4 = dma_wave_for(lds_c + next_buf * kLdsBlock, j0 + (blk + 2) * kMlaKeys, wave);
-                mla_block_pp<decltype(lo_mode)::value, decltype(masked)::value>(
-                    st, cur + qk_off, cur + qt_off, cur + pv_off, qop, q_lds, prm.scale_log2, j0 + blk * kMlaKeys, lim, kb,
-                    [&](auto q_c) { block_load_static<NW, decltype(q_c)::value>(d4, rc_next, dma, wave); });
-            } else {
-                const bool late = kSkewWaves && NW == 8 && wave < 4;
-                if (blk + 2 < n_blocks && !late)
-                    block_to_lds<NW>(lds_c + next_buf * kLdsBlock, rc, j0 + (blk + 2) * kMlaKeys, wave, dma);
-                mla_block<RT, decltype(lo_mode)::value>(st, cur + qk_off, cur + qt_off, cur + pv_off, qop, q_lds, prm.scale_log2,
-                                                        j0 + blk * kMlaKeys, lim, kb);
-                if (blk + 2 < n_blocks && late)
-                    block_to_lds<NW>(lds_c + next_buf * kLdsBlock, rc, j0 + (blk + 2) * kMlaKeys, wave, dma);
-            }
+            if (blk + 2 < n_blocks) block_to_lds<NW>(lds_c + next_buf * kLdsBlock, rc, j0 + (blk + 2) * kMlaKeys, wave, dma);
+            mla_block<RT, decltype(lo_mode)::value>(st, cur + qk_off, cur + qt_off, cur + pv_off, qop, q_lds, prm.scale_log2,
+                                                    j0 + blk * kMlaKeys, lim, kb);
             cur_buf = cur_buf == kStages - 1 ? 0 : cur_buf + 1;
             next_buf = next_buf == kStages - 1 ? 0 : next_buf + 1;
         };
         // Default mode: the first blocks of a segment with hi + lo weights, the others with hi + lo
         // only where a key dominates.
         const int n_exact = kMode == 1 ? n_blocks : kMode == 2 ? 0 : (n_blocks < kExactBlocks ? n_blocks : kExactBlocks);
-        // Two tiles per wave: blocks that end at or below every row's limit (the end of the segment, the
-        // causal limit of the wave's first row) run without masking, the few others in the masked form.
-        int first_masked = n_blocks;
-        if constexpr (RT == 2) {
-            const int causal_min = L - T + wave_row0 / H + 1;
-            const int clear = ((causal_min < j1 ? causal_min : j1) - j0) / kMlaKeys;
-            first_masked = clear < 0 ? 0 : (clear < n_blocks ? clear : n_blocks);
-        }
-        const int n_exact_clear = n_exact < first_masked ? n_exact : first_masked;
         int blk = 0;
-        for (; blk < n_exact_clear; ++blk) step(blk, std::integral_constant<int, kLoAlways>(), std::false_type());
-        for (; blk < first_masked; ++blk)
-            step(blk, std::integral_constant<int, kMode == 0 ? kLoDynamic : (kMode == 1 ? kLoAlways : kLoNever)>(), std::false_type());
-        for (; blk < n_blocks; ++blk) step(blk, std::integral_constant<int, kMode == 2 ? kLoNever : kLoAlways>(), std::true_type());
-        if constexpr (RT == 2) dma_wait(0);      // the empty loads behind the last block: they write (zeros) to the buffers
-        if constexpr (RT == 2)        // the accumulators are read below; all but the last were written long ago
-            mfma_drain_acc(st[0].o[kColTiles - 2], st[0].o[kColTiles - 1], st[1].o[kColTiles - 2], st[1].o[kColTiles - 1]);
+        for (; blk < n_exact; ++blk) step(blk, std::integral_constant<int, kLoAlways>());
+        for (; blk < n_blocks; ++blk)
+            step(blk, std::integral_constant<int, kMode == 0 ? kLoDynamic : (kMode == 1 ? kLoAlways : kLoNever)>());
         __syncthreads();          // everyone is done with the block buffers: they stage the output now
 
 #pragma unroll
@@ -892,6 +593,675 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
         __syncthreads();          // the next segment's first block goes to buffer 0, which staged output until here
     }
 }
+
+// ----------------------------------------------------------------------- tiles of 32 query rows
+// More than 32 query rows: a wave owns 32 rows, one wave per SIMD with 512 registers: the 32 x 512 fp32 output
+// accumulators in the 256 accumulation registers, Q (33 of its 36 MFMA steps) and two blocks' scores in the
+// ordinary ones.  With 32x32x16 MFMAs an operand fragment read from LDS (1 KiB) feeds 32 cycles of the matrix
+// pipe; with 16x16x32 it is 16, as fast as the LDS delivers fragments, and a loop with a wave per 16 rows (eight of
+// them) was bound by both in turn, 4600 cycles per block against 2900 here.
+// A block's 32 keys run through two phases, the work of two blocks interleaved so that the matrix pipe has
+// work while the vector unit does the softmax:
+//   A: scores of block i + 1 (36 MFMAs), and between them the weights of block i from its scores;
+//   B: values of block i (32 MFMAs), and between them the maximum of block i + 1's scores.
+// What bounds it: a lone wave issues an instruction every four cycles or so, and the 68 MFMAs (2176 cycles) leave room for
+// most of the others but not all: against MFMAs alone the loads into LDS cost 290 cycles of a block, the softmax 300, the
+// operand reads 120.  And power: on random data the clock falls from 2.4 to 1.8 GHz (all-zero data: 256 rows 130 us
+// instead of 164).  Whole calls, eight waves of 16 rows -> here, 64 sequences of 1024 to 8192 tokens: 128 rows
+// 106.4 -> 97.1 us, 256 rows 179.6 -> 163.5, 72 rows 97.0 -> 81.7, 33 rows 76.9 -> 67.4 (four waves of 16 before).
+// Tried without gain: operands 3, 5 or 6 fragments ahead; one wait for two fragments (2 % slower); a block's last
+// MFMAs behind the next barrier; its first weights ahead of its first MFMA (1 % slower).
+// Four LDS buffers: block i (values), i + 1 (scores), i + 2 and i + 3 on their way; one barrier per block.
+// A block's image in LDS: row r's latent part at r * kPitch, 16 bytes further from row 16 on, and the rope parts
+// as 128-byte rows whose 16-byte chunks are permuted by row (through the global address each lane fetches).
+// Key row x of the score MFMA is row tile_key(x) of the block.  With that, the lanes that one pass of an
+// LDS read serves (0-3, 12-15, 20-27 and so on for 128 bits; 0-31 for the transposing read) hit different banks.
+// The MFMAs are assembly statements: their accumulators can then be named (scores in ordinary registers, outputs
+// in accumulation registers; through the builtin the compiler puts every MFMA result into the accumulation
+// registers, which the outputs fill alone), and such statements keep their order among themselves and against
+// memory operations, so LDS reads stay where they are written, a fixed number of MFMAs ahead of their use.  Vector
+// instructions do move across them; the softmax is therefore cut into slices of a few instructions whose results
+// pass through an empty statement of the same kind (pin): a slice cannot start before the pin its inputs came
+// through nor end after its own.
+// What the compiler cannot see of an MFMA inside a statement: a vector instruction may read a result register only
+// once the MFMA has left the pipe (mfma_drain where no later MFMAs stand in between), and an MFMA may read a
+// register two instructions after a vector instruction wrote it (mfma_operands).
+constexpr int kTileRows = 32;
+constexpr int kTileWaves = 4;
+constexpr int kTileSteps = kDqk / 16;            // 36 MFMA steps of 16 columns
+constexpr int kTileQRegs = 33;                   // Q steps in registers, the rest parked in LDS
+constexpr int kTileQLds = (kTileSteps - kTileQRegs) * 1024;      // per wave
+constexpr int kTileCols = kDv / 32;              // 16 tiles of 32 value columns
+constexpr int kTileFrags = 2 * kTileCols;        // value fragments (16 keys x 32 columns) of a block
+constexpr int kTileStages = 4;
+constexpr int kTileHalf = 16 * kPitch + 16;      // rows 16..31
+constexpr int kTileTailOff = kTileHalf + 15 * kPitch + 1024;
+constexpr int kTileBlock = kTileTailOff + kMlaKeys * 128;
+constexpr int kTileLoads = kMlaKeys / kTileWaves + 1;            // loads per wave and block: 8 rows, and 8 rows' rope parts
+constexpr int kTileKAhead = 4, kTileVAhead = 4;  // fragments in flight ahead of their MFMAs
+constexpr int kTileLoadEvery = 7, kTileLoadsA = 5;       // a load every so many MFMAs, this many of them in phase A
+constexpr int kTileStagePitch = kDv * 2 + 16;    // epilogue: whole rows, padded
+
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+
+__device__ __forceinline__ void mfma_first_v(f32x16_t& acc, bf16x8_t a, bf16x8_t b) {      // acc = a b
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_v(f32x16_t& acc, bf16x8_t a, bf16x8_t b) {            // acc += a b
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+// 24 wait states between an MFMA (8 passes) and vector instructions that read its result; the result passes
+// through the statement, so its readers stay behind it.
+__device__ __forceinline__ void mfma_drain(f32x16_t& s) { asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s)); }
+
+// The output accumulators: column tile ct is a[16 ct : 16 ct + 15] wherever it is used, all 256 accumulation
+// registers together.  Every access is a statement that names those registers: left to choose, the compiler moves
+// tiles through ordinary registers, where it cannot know when an MFMA inside a statement has written its result.
+struct TileAcc {
+    f32x16_t t[kTileCols];
+};
+#define XATTN_ACC_EACH(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
+#define XATTN_ACC_REG(ct, i) "a[16*" #ct "+" #i "]"
+#define XATTN_ACC_TILE(ct) XATTN_ACC_TILE_##ct
+#define XATTN_ACC_TILE_0 "{a[0:15]}"
+#define XATTN_ACC_TILE_1 "{a[16:31]}"
+#define XATTN_ACC_TILE_2 "{a[32:47]}"
+#define XATTN_ACC_TILE_3 "{a[48:63]}"
+#define XATTN_ACC_TILE_4 "{a[64:79]}"
+#define XATTN_ACC_TILE_5 "{a[80:95]}"
+#define XATTN_ACC_TILE_6 "{a[96:111]}"
+#define XATTN_ACC_TILE_7 "{a[112:127]}"
+#define XATTN_ACC_TILE_8 "{a[128:143]}"
+#define XATTN_ACC_TILE_9 "{a[144:159]}"
+#define XATTN_ACC_TILE_10 "{a[160:175]}"
+#define XATTN_ACC_TILE_11 "{a[176:191]}"
+#define XATTN_ACC_TILE_12 "{a[192:207]}"
+#define XATTN_ACC_TILE_13 "{a[208:223]}"
+#define XATTN_ACC_TILE_14 "{a[224:239]}"
+#define XATTN_ACC_TILE_15 "{a[240:255]}"
+template <int kCt>
+__device__ __forceinline__ void acc_mfma(TileAcc& o, bf16x8_t a, bf16x8_t b) {            // tile kCt += a b
+#define X(ct) if constexpr (kCt == ct) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+" XATTN_ACC_TILE(ct)(o.t[ct]) : "v"(a), "v"(b));
+    XATTN_ACC_EACH(X)
+#undef X
+}
+__device__ __forceinline__ void acc_zero(TileAcc& o) {
+#define Z(ct, i) "v_accvgpr_write_b32 " XATTN_ACC_REG(ct, i) ", 0\n\t"
+#define X(ct)                                                                                                              \
+    asm volatile(Z(ct, 0) Z(ct, 1) Z(ct, 2) Z(ct, 3) Z(ct, 4) Z(ct, 5) Z(ct, 6) Z(ct, 7) Z(ct, 8) Z(ct, 9) Z(ct, 10)        \
+                 Z(ct, 11) Z(ct, 12) Z(ct, 13) Z(ct, 14) Z(ct, 15) : "=" XATTN_ACC_TILE(ct)(o.t[ct]));
+    XATTN_ACC_EACH(X)
+#undef X
+#undef Z
+}
+// Before the first vector instruction that reads the accumulators; all but the last were written long ago.
+__device__ __forceinline__ void acc_drain(TileAcc& o) {
+    asm volatile("s_nop 15\n\ts_nop 7" : "+" XATTN_ACC_TILE(14)(o.t[14]), "+" XATTN_ACC_TILE(15)(o.t[15]));
+}
+__device__ __forceinline__ void acc_scale(TileAcc& o, float f) {                           // behind acc_drain
+    float t0, t1, t2, t3;
+#define R(ct, i, t) "v_accvgpr_read_b32 %" #t ", " XATTN_ACC_REG(ct, i) "\n\t"
+#define M(t) "v_mul_f32 %" #t ", %" #t ", %5\n\t"
+#define W(ct, i, t) "v_accvgpr_write_b32 " XATTN_ACC_REG(ct, i) ", %" #t "\n\t"
+#define Q(ct, a, b, c, d) R(ct, a, 1) R(ct, b, 2) R(ct, c, 3) R(ct, d, 4) M(1) M(2) M(3) M(4) W(ct, a, 1) W(ct, b, 2) W(ct, c, 3) W(ct, d, 4)
+#define X(ct)                                                                                          \
+    asm volatile(Q(ct, 0, 1, 2, 3) Q(ct, 4, 5, 6, 7) Q(ct, 8, 9, 10, 11) Q(ct, 12, 13, 14, 15)         \
+                 : "+" XATTN_ACC_TILE(ct)(o.t[ct]), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3) : "v"(f));
+    XATTN_ACC_EACH(X)
+#undef X
+#undef Q
+#undef W
+#undef M
+#undef R
+}
+template <int kCt>
+__device__ __forceinline__ void acc_read(const TileAcc& o, float (&v)[16]) {              // behind acc_drain
+#define R(ct, i) "v_accvgpr_read_b32 %" #i ", " XATTN_ACC_REG(ct, i) "\n\t"
+#define X(ct)                                                                                                              \
+    if constexpr (kCt == ct)                                                                                               \
+        asm volatile(R(ct, 0) R(ct, 1) R(ct, 2) R(ct, 3) R(ct, 4) R(ct, 5) R(ct, 6) R(ct, 7) R(ct, 8) R(ct, 9) R(ct, 10)   \
+                     R(ct, 11) R(ct, 12) R(ct, 13) R(ct, 14) R(ct, 15)                                                     \
+                     : "=v"(v[0]), "=v"(v[1]), "=v"(v[2]), "=v"(v[3]), "=v"(v[4]), "=v"(v[5]), "=v"(v[6]), "=v"(v[7]),     \
+                       "=v"(v[8]), "=v"(v[9]), "=v"(v[10]), "=v"(v[11]), "=v"(v[12]), "=v"(v[13]), "=v"(v[14]), "=v"(v[15]) \
+                     : XATTN_ACC_TILE(ct)(o.t[ct]));
+    XATTN_ACC_EACH(X)
+#undef X
+#undef R
+}
+#undef XATTN_ACC_EACH
+__device__ __forceinline__ void mfma_operands(bf16x8_t& a, bf16x8_t& b) { asm volatile("s_nop 1" : "+v"(a), "+v"(b)); }
+template <typename A> __device__ __forceinline__ void pin(A& a) { asm volatile("" : "+v"(a)); }
+template <typename A, typename B> __device__ __forceinline__ void pin(A& a, B& b) { asm volatile("" : "+v"(a), "+v"(b)); }
+// max(a, b) of two scores (finite or -inf, no NaNs) as one instruction, the median of (a, b, largest
+// finite float): fmaxf() first quiets each operand it cannot prove to be the result of arithmetic
+// (matrix results, swapped lanes), an instruction apiece.
+__device__ __forceinline__ float max_num(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0x1.fffffep+127f); }
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float d;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ void max3_abs(float& m, float a, float b) {      // m = max(m, |a|, |b|)
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+}
+template <int N>
+__device__ __forceinline__ void dma_wait_for() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
+// The same for all of them, in a form that the compiler reads: a load of its own that it still counts as outstanding
+// would otherwise make it wait inside the block loop, and there for the blocks on their way as well.
+__device__ __forceinline__ void dma_wait_all() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0)
+    asm volatile("" ::: "memory");
+}
+
+// Row of the block that is key x of the score MFMAs; x = 8 g + 4 h + j gives 8 g + 2 j + h, so lane half h holds,
+// as accumulator 4 g + j, key 8 g + 2 j + h.
+__device__ __forceinline__ int tile_key(int x) { return (x & 24) + 2 * (x & 3) + ((x >> 2) & 1); }
+// Chunk of a rope part as stored: chunk c of row r sits at c ^ tile_tail_swap(r).
+__device__ __forceinline__ int tile_tail_swap(int row) { return ((row >> 1) & 3) | ((row >> 4) << 2); }
+
+// This wave's loads of a block: rows wave + 4 q (q < 8), and the rope parts of rows 8 wave .. 8 wave + 7.  Rows past the
+// end of the descriptor read as zero.
+struct TileDma {
+    uint32_t row_off, tail_off;      // per lane
+};
+__device__ __forceinline__ TileDma tile_dma(int wave, int lane) {
+    const int i = lane >> 3;
+    return TileDma{(uint32_t)lane * 16, (uint32_t)(i * kRowB + 1024 + ((lane & 7) ^ tile_tail_swap(8 * wave + i)) * 16)};
+}
+struct TileLoad {                    // a block's loads by this wave
+    u32x4_t rc;
+    uint32_t lds, mem;               // the wave's first row
+    uint32_t lds_tail, mem_tail;
+};
+__device__ __forceinline__ TileLoad tile_load_for(const char* lds_block, u32x4_t rc, int j_block, int wave) {
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)lds_block;
+    return TileLoad{rc, lds0 + (uint32_t)wave * kPitch, (uint32_t)(j_block + wave) * kRowB, lds0 + kTileTailOff + (uint32_t)wave * 1024,
+                    (uint32_t)(j_block + 8 * wave) * kRowB};
+}
+template <int Q>
+__device__ __forceinline__ void tile_load(const TileLoad& b, const TileDma& d) {
+    if constexpr (Q < kTileLoads - 1)
+        dma16(b.rc, b.lds + Q * kTileWaves * kPitch + (Q >= 4 ? 16 : 0), d.row_off, b.mem + Q * kTileWaves * kRowB);
+    else
+        dma16(b.rc, b.lds_tail, d.tail_off, b.mem_tail);
+}
+
+// A wave's Q on its way to the registers: whole rows by loads into LDS (a lane's own chunks straight from memory are 64
+// separate lines per load: 5.7 us of a segment's start), in two rounds of half of the latent and half of the rope part,
+// with chunks permuted by row so that the reads below meet different banks.  `first`: the workgroups of a sequence begin at
+// different rows, or all of them ask for the same lines at the same time.
+constexpr int kTileQStage = kTileRows * (512 + 64);
+__device__ __forceinline__ void tile_q_load(char* stage, u32x4_t rq, int wave_row0, int lane, int round, int first) {
+    uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)stage;
+    asm volatile("" : "+s"(lds0), "+s"(wave_row0), "+s"(first));
+    const int up = lane >> 5, c0 = (lane & 31) ^ up;
+#pragma unroll
+    for (int k = 0; k < kTileRows / 2; ++k) {
+        const int i = (k + first) & (kTileRows / 2 - 1);         // rows 2 i and 2 i + 1
+        dma16(rq, lds0 + i * 1024, (uint32_t)(up * kRowB + (c0 ^ (2 * i & 15)) * 16), (uint32_t)(wave_row0 + 2 * i) * kRowB + round * 512);
+    }
+#pragma unroll
+    for (int i = 0; i < kTileRows / 16; ++i)     // half of the rope parts of rows 16 i .. 16 i + 15
+        dma16(rq, lds0 + kTileRows * 512 + i * 1024, (uint32_t)((lane >> 2) * kRowB + 1024 + (((lane & 3) ^ (lane >> 4)) * 16)),
+              (uint32_t)(wave_row0 + 16 * i) * kRowB + round * 64);
+}
+// Steps 16 round .. + 15 (latent part) and 32 + 2 round, + 1 (rope part) of the round in the stage.
+__device__ __forceinline__ bf16x8_t tile_q_frag(const char* stage, int lane, int step) {
+    const int n = lane & 31, h = lane >> 5;
+    const char* p = step < 32 ? stage + n * 512 + ((2 * (step & 15) + h) ^ (n & 15)) * 16
+                              : stage + kTileRows * 512 + n * 64 + ((2 * (step & 1) + h) ^ ((n >> 2) & 3)) * 16;
+    return *reinterpret_cast<const bf16x8_t*>(p);
+}
+
+// What a lane keeps of its row (both halves of the wave hold the same rows).
+struct TileRow {
+    float m, l;          // reference maximum (log2 domain) and the running sum over the row's keys
+    float lq;            // this lane's share of the sum over the weights as they entered the value product
+    float mx;            // scaled maximum of the block whose weights come next
+};
+// Where a lane reads a block's operands: keys at k + 32 * step (steps 0..31) and, for the rope part, t ^ 32 * step, at tail.
+struct TileReads {
+    int key, tail, tail_chunk;       // offsets within a block; tail_chunk: byte offset within the 128-byte row
+    int value;
+};
+__device__ __forceinline__ TileReads tile_reads(int lane) {
+    const int h = lane >> 5, row = tile_key(lane & 31), m = lane & 15;
+    TileReads r;
+    r.key = row * kPitch + (row >= 16 ? 16 : 0) + h * 16;
+    r.tail = kTileTailOff + row * 128;
+    r.tail_chunk = (h ^ tile_tail_swap(row)) * 16;
+    // value fragment (ct, s), read u: lanes of a 16-lane group point at 16 columns of keys 16 s + 8 u + 2 q + h, q = 0..3
+    r.value = (2 * (m >> 2) + h) * kPitch + ((lane >> 4) & 1) * 32 + (m & 3) * 8;
+    return r;
+}
+__device__ __forceinline__ bf16x8_t tile_key_frag(const char* block, const TileReads& rd, int step) {
+    const char* p = step < 32 ? block + rd.key + step * 32 : block + rd.tail + (rd.tail_chunk ^ ((step - 32) * 32));
+    return *reinterpret_cast<const bf16x8_t*>(p);
+}
+// Value fragment f = 2 * column tile + half of the keys: the transposing read gives lane n of a 16-lane group the n-th
+// column of its group's four keys.
+__device__ __forceinline__ bf16x8_t tile_value_frag(const char* block, const TileReads& rd, int f) {
+    const char* p = block + rd.value + (f >> 1) * 64 + (f & 1) * kTileHalf;
+    const s16x4v_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4v_t*)p);
+    const s16x4v_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4v_t*)(p + 8 * kPitch));
+    const u32x2_t w0 = __builtin_bit_cast(u32x2_t, v0), w1 = __builtin_bit_cast(u32x2_t, v1);
+    return __builtin_bit_cast(bf16x8_t, u32x4_t{w0.x, w0.y, w1.x, w1.y});
+}
+// Keys at or past lim (the end of the segment, or the causal limit of the row) count as -inf.
+__device__ __forceinline__ void tile_mask(f32x16_t& s, int j_block, int lim, int h) {
+#pragma unroll
+    for (int t = 0; t < 16; ++t) s[t] = j_block + 8 * (t >> 2) + 2 * (t & 3) + h < lim ? s[t] : kNegInf;
+}
+__device__ __forceinline__ float tile_max(float t) {
+    float a, b;
+    swap32(t, a, b);
+    return fmaxf(a, b);
+}
+
+// Block i: its scores s become weights while the scores s_next of the block at `next` are computed (not in a
+// segment's last block), then its values at `cur` are added to o.  issue(q): the caller's load q of a later block.
+template <int kLo, bool kLast, typename Issue>
+__device__ __forceinline__ void tile_block(TileAcc& o, TileRow& st, const f32x16_t& s, f32x16_t& s_next,
+                                           const bf16x8_t (&qop)[kTileQRegs], const char* q_lds, const TileReads& rd,
+                                           const char* cur, const char* next, float scale_log2, int j_next, int lim, int h,
+                                           bool exact, Issue issue) {
+    bf16x8_t ka[kTileSteps], ql[kTileSteps - kTileQRegs], va[kTileFrags];
+    auto load_k = [&](auto f_c) {
+        constexpr int F = decltype(f_c)::value;
+        ka[F] = tile_key_frag(next, rd, F);
+        if constexpr (F >= kTileQRegs) ql[F - kTileQRegs] = *reinterpret_cast<const bf16x8_t*>(q_lds + (F - kTileQRegs) * 1024);
+    };
+    if constexpr (!kLast) static_for<kTileKAhead>(load_k);
+    // The reference maximum follows the row's maximum lazily, see mla_block.
+    const bool moves = st.mx > st.m + kLazyLog2;
+    if (__builtin_amdgcn_ballot_w64(moves) != 0) {
+        const float m_new = moves ? st.mx : st.m;
+        const float alpha = moves ? fast_exp2(st.m - m_new) : 1.0f;
+        const bool first = __builtin_amdgcn_ballot_w64(moves && st.m != kNegInf) == 0;      // all sums are still 0
+        st.m = m_new;
+        st.l *= alpha;
+        st.lq *= alpha;
+        if (!first) {
+            acc_drain(o);
+            acc_scale(o, alpha);
+        }
+    }
+    const float m_use = st.m == kNegInf ? 0.0f : st.m;
+    // Phase A.
+    float p[16], t4[4], sum = 0.0f, sum_q = 0.0f, dom = 0.0f;
+    uint32_t hi[8], lo[8];
+    auto weights = [&](auto f_c) {
+        constexpr int F = decltype(f_c)::value;
+        if constexpr (F < 16) {
+            p[F] = fast_exp2(__builtin_fmaf(s[F], scale_log2, -m_use));
+            pin(p[F]);
+        } else if constexpr (F < 20) {
+            constexpr int k = 4 * (F - 16);
+            t4[F - 16] = (p[k] + p[k + 1]) + (p[k + 2] + p[k + 3]);
+            pin(t4[F - 16]);
+        } else if constexpr (F == 20) {
+            sum = (t4[0] + t4[1]) + (t4[2] + t4[3]);
+            pin(sum);
+        } else if constexpr (F == 21) {
+            float a, b;
+            swap32(sum, a, b);
+            st.l += a + b;
+            pin(st.l);
+        } else if constexpr (F == 22) {      // a key with at least 1 / kDominantShare of the row's sum so far
+            if (kLo == kLoDynamic) {
+                dom = fast_exp2(st.mx - m_use) * kDominantShare >= st.l ? 1.0f : 0.0f;
+                pin(dom);
+            }
+        } else if constexpr (F < 27) {
+            constexpr int u = 2 * (F - 23);
+            hi[u] = cvt_bf16(p[2 * u], p[2 * u + 1]);
+            hi[u + 1] = cvt_bf16(p[2 * u + 2], p[2 * u + 3]);
+            pin(hi[u], hi[u + 1]);
+        } else if constexpr (F < 31) {
+            constexpr int u = 2 * (F - 27);
+            if constexpr (kLo == kLoAlways) {
+#pragma unroll
+                for (int k = u; k < u + 2; ++k) lo[k] = cvt_bf16(p[2 * k] - bf16_lo(hi[k]), p[2 * k + 1] - bf16_hi(hi[k]));
+                pin(lo[u], lo[u + 1]);
+            } else {                         // the sum of the rounded weights: each pair times (1, 1), added in fp32
+                sum_q = dot2_bf16(hi[u], 0x3f803f80u, sum_q);
+                sum_q = dot2_bf16(hi[u + 1], 0x3f803f80u, sum_q);
+                pin(sum_q);
+            }
+        }
+    };
+    static_for<kTileSteps>([&](auto f_c) {
+        constexpr int F = decltype(f_c)::value;
+        if constexpr (!kLast) {
+            if constexpr (F + kTileKAhead < kTileSteps) load_k(std::integral_constant<int, F + kTileKAhead>());
+        }
+        if constexpr (F + kTileVAhead >= kTileSteps) va[F + kTileVAhead - kTileSteps] = tile_value_frag(cur, rd, F + kTileVAhead - kTileSteps);
+        if constexpr (!kLast) {
+            bf16x8_t qv;
+            if constexpr (F < kTileQRegs) qv = qop[F];
+            else qv = ql[F - kTileQRegs];
+            if constexpr (F == 0) mfma_first_v(s_next, ka[F], qv);
+            else mfma_v(s_next, ka[F], qv);
+            if constexpr (F % kTileLoadEvery == 3 && F / kTileLoadEvery < kTileLoadsA) issue(std::integral_constant<int, F / kTileLoadEvery>());
+        }
+        weights(f_c);
+    });
+    const bool with_lo = kLo == kLoAlways || (kLo == kLoDynamic && (exact || __builtin_amdgcn_ballot_w64(dom != 0.0f) != 0));
+    st.lq += with_lo ? sum : sum_q;
+    bf16x8_t ph[2], pl[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        ph[k] = __builtin_bit_cast(bf16x8_t, u32x4_t{hi[4 * k], hi[4 * k + 1], hi[4 * k + 2], hi[4 * k + 3]});
+        if (kLo == kLoAlways) pl[k] = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[4 * k], lo[4 * k + 1], lo[4 * k + 2], lo[4 * k + 3]});
+    }
+    if constexpr (!kLast) {
+        if (__builtin_amdgcn_ballot_w64(j_next + kMlaKeys > lim) != 0) {         // only blocks that reach a limit
+            mfma_drain(s_next);
+            tile_mask(s_next, j_next, lim, h);
+        }
+    }
+    // Phase B.
+    mfma_operands(ph[0], ph[1]);
+    if (kLo == kLoAlways) mfma_operands(pl[0], pl[1]);
+    float t0, t1;
+    static_for<kTileFrags>([&](auto c_c) {
+        constexpr int C = decltype(c_c)::value;
+        if constexpr (C + kTileVAhead < kTileFrags) va[C + kTileVAhead] = tile_value_frag(cur, rd, C + kTileVAhead);
+        acc_mfma<(C >> 1)>(o, va[C], ph[C & 1]);
+        if constexpr (kLo == kLoAlways) acc_mfma<(C >> 1)>(o, va[C], pl[C & 1]);
+        if constexpr (!kLast) {
+            // The maximum of the next block's scores, whose last MFMA left the pipe behind the second of these.
+            if constexpr (C == 3) pin(s_next);
+            if constexpr (C == 4) {
+                t0 = max3(s_next[0], s_next[1], s_next[2]);
+                t1 = max3(s_next[3], s_next[4], s_next[5]);
+                pin(t0, t1);
+            } else if constexpr (C >= 5 && C < 9) {
+                t0 = max3(t0, s_next[2 * C - 4], s_next[2 * C - 3]);
+                if constexpr (C == 8) t0 = max3(t0, s_next[14], s_next[15]);
+                pin(t0);
+            } else if constexpr (C == 9) {
+                t0 = max3(t0, t1, t1);
+                st.mx = tile_max(t0) * scale_log2;
+                pin(st.mx);
+            }
+            if constexpr (C % kTileLoadEvery == 3 && C / kTileLoadEvery + kTileLoadsA < kTileLoads) issue(std::integral_constant<int, C / kTileLoadEvery + kTileLoadsA>());
+        }
+    });
+    if (kLo == kLoDynamic && with_lo) {
+        // The rare block with a dominant key: a second pass over the value fragments with the lo parts.
+#pragma unroll
+        for (int k = 0; k < 8; ++k) lo[k] = cvt_bf16(p[2 * k] - bf16_lo(hi[k]), p[2 * k + 1] - bf16_hi(hi[k]));
+#pragma unroll
+        for (int k = 0; k < 2; ++k) pl[k] = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[4 * k], lo[4 * k + 1], lo[4 * k + 2], lo[4 * k + 3]});
+        mfma_operands(pl[0], pl[1]);
+        static_for<kTileFrags + kTileVAhead>([&](auto f_c) {
+            constexpr int F = decltype(f_c)::value, C = F - kTileVAhead;
+            if constexpr (F < kTileFrags) va[F] = tile_value_frag(cur, rd, F);
+            if constexpr (C >= 0) acc_mfma<(C >> 1)>(o, va[C], pl[C & 1]);
+        });
+    }
+}
+
+// kMode: as mla_decode_kernel.
+template <int kMode>
+__global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm) {
+    __shared__ __attribute__((aligned(16))) char lds_c[kTileStages * kTileBlock];
+    __shared__ __attribute__((aligned(16))) char lds_q[kTileWaves * kTileQLds];      // each lane reads back what it wrote
+    static_assert(kTileWaves * kTileRows * kTileStagePitch <= kTileStages * kTileBlock, "output staging must fit the block buffers");
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int n = lane & 31, h = lane >> 5;
+    const int T = prm.q_len, H = prm.n_heads, rows_total = T * H;
+    SeqWindow win;
+    const WavePlan wp = wave_plan(prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kMlaSegCost,
+                                  prm.xcd_skew, prm.few, lane, &win);
+    const Plan& pl = wp.pl;
+    const int per_xcd = (pl.n_pieces + 7) >> 3;
+    // Workgroups as in mla_decode_kernel: the row groups of a piece side by side on one XCD.
+    const int bid = blockIdx.x;
+    const int n_groups = (rows_total + kTileWaves * kTileRows - 1) / (kTileWaves * kTileRows);
+    const int slot_in_xcd = bid >> 3;
+    const int row_group = slot_in_xcd % n_groups;
+    const int p = (bid & 7) * per_xcd + slot_in_xcd / n_groups;
+    const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
+    const bool active = slot_in_xcd / n_groups < per_xcd && p < pl.n_pieces && s0 < s1;
+    if (tid < 64)
+        for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
+    if (!active) return;       // the whole workgroup: every wave computed the same plan
+
+    Walk walk;
+    wave_locate(wp, prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, s0, lane, &win, walk.b, walk.j);
+    walk.remaining = uniform(s1 - s0);
+    dma_wait_all();
+
+    const int wave_row0 = (row_group * kTileWaves + wave) * kTileRows;
+    const bool busy = wave_row0 < rows_total;          // a wave without rows only loads
+    const int row = wave_row0 + n;
+    char* q_lds = lds_q + wave * kTileQLds + lane * 16;
+    char* stage = lds_c + wave * (kTileRows * kTileStagePitch);
+    const TileDma dma = tile_dma(wave, lane);
+    const TileReads rd = tile_reads(lane);
+    auto fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+
+    PieceSeg ps;
+    while (uniform(next_segment(walk, prm.batch, pl.seg_cost,
+                                [&](int bb) { return window_len(win, prm.kv_lens, bb); }, ps))) {
+        const int b = uniform(ps.b), L = uniform(ps.L), j0 = uniform(ps.j0), j1 = uniform(ps.j1);
+        const bool whole = uniform(ps.whole) != 0;
+        const long slot = (long)uniform(p) + b;
+        const unsigned long long cbytes = (unsigned long long)L * kRowB;
+        const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, prm.c_ptrs, b);
+        const u32x4_t rc = {(uint32_t)uniform((int)(uint32_t)caddr), (uint32_t)uniform((int)((uint32_t)(caddr >> 32) & 0xffffu)),
+                            cbytes > 0xffffffffull ? 0xffffffffu : (uint32_t)cbytes, 0x00020000u};
+        const int n_blocks = (j1 - j0 + kMlaKeys - 1) / kMlaKeys;
+        // The loads of block blk.  Past the segment's end they run against an empty descriptor (zeros land in a free
+        // buffer), so that every block has its loads and the waits need no case.
+        auto load_for = [&](int blk) {
+            u32x4_t r = rc;
+            if (blk >= n_blocks) r[2] = 0u;
+            return tile_load_for(lds_c + (blk & 3) * kTileBlock, r, j0 + blk * kMlaKeys, wave);
+        };
+        auto load_block = [&](int blk) {
+            const TileLoad b = load_for(blk);
+            static_for<kTileLoads>([&](auto q_c) { tile_load<decltype(q_c)::value>(b, dma); });
+        };
+
+        // Q operand: lane (h, n) holds columns 16 step + 8 h .. + 7 of row n; rows past the last lie past the end of the
+        // descriptor and read as zero.
+        const uint64_t qaddr = (uint64_t)(uintptr_t)(prm.q + (long)b * rows_total * kDqk);
+        const u32x4_t rq = {(uint32_t)uniform((int)(uint32_t)qaddr), (uint32_t)uniform((int)((uint32_t)(qaddr >> 32) & 0xffffu)),
+                            (uint32_t)rows_total * kRowB, 0x00020000u};
+        bf16x8_t qop[kTileQRegs];
+        TileAcc o;
+        f32x16_t s_even, s_odd;
+        TileRow st{kNegInf, 0.0f, 0.0f, kNegInf};
+        const int causal = L - T + (row < rows_total ? row : 0) / H + 1;
+        const int lim = causal < j1 ? causal : j1;
+        acc_zero(o);
+        // Q goes through the buffers behind those of blocks 0 and 1, in the wave's own part of them.
+        static_assert(kTileWaves * kTileQStage <= 2 * kTileBlock && kTileQRegs == 33, "Q's stage; the steps that are parked");
+        char* q_stage = lds_c + 2 * kTileBlock + wave * kTileQStage;
+        int q_lane = lane;
+        pin(q_lane);              // the addresses are made here: kept from segment to segment they would be spilled
+        auto park = [&](int step) { *reinterpret_cast<bf16x8_t*>(q_lds + (step - kTileQRegs) * 1024) = tile_q_frag(q_stage, q_lane, step); };
+        if (busy) tile_q_load(q_stage, rq, wave_row0, q_lane, 0, bid >> 3);
+        load_block(0);
+        if (busy) {
+            dma_wait_for<kTileLoads>();
+#pragma unroll
+            for (int step = 0; step < 16; ++step) qop[step] = tile_q_frag(q_stage, q_lane, step);
+            qop[32] = tile_q_frag(q_stage, q_lane, 32);
+            park(33);
+#pragma unroll
+            for (int step = 0; step < 16; ++step) pin(qop[step]);      // read before the second round overwrites them
+            pin(qop[32]);
+            fence();
+            tile_q_load(q_stage, rq, wave_row0, q_lane, 1, bid >> 3);
+        }
+        load_block(1);
+        dma_wait_for<kTileLoads>();
+        if (busy) {
+#pragma unroll
+            for (int step = 16; step < 32; ++step) qop[step] = tile_q_frag(q_stage, q_lane, step);
+            park(34);
+            park(35);
+#pragma unroll
+            for (int step = 16; step < 32; ++step) pin(qop[step]);
+            fence();
+        }
+        __syncthreads();
+        load_block(2);
+        if (busy) {
+            // Scores of block 0.
+            bf16x8_t ka[kTileSteps], ql[kTileSteps - kTileQRegs];
+            auto load_k = [&](auto f_c) {
+                constexpr int F = decltype(f_c)::value;
+                ka[F] = tile_key_frag(lds_c, rd, F);
+                if constexpr (F >= kTileQRegs) ql[F - kTileQRegs] = *reinterpret_cast<const bf16x8_t*>(q_lds + (F - kTileQRegs) * 1024);
+            };
+            static_for<kTileKAhead>(load_k);
+            static_for<kTileSteps>([&](auto f_c) {
+                constexpr int F = decltype(f_c)::value;
+                if constexpr (F + kTileKAhead < kTileSteps) load_k(std::integral_constant<int, F + kTileKAhead>());
+                bf16x8_t qv;
+                if constexpr (F < kTileQRegs) qv = qop[F];
+                else qv = ql[F - kTileQRegs];
+                if constexpr (F == 0) mfma_first_v(s_even, ka[F], qv);
+                else mfma_v(s_even, ka[F], qv);
+            });
+            mfma_drain(s_even);
+            if (__builtin_amdgcn_ballot_w64(j0 + kMlaKeys > lim) != 0) tile_mask(s_even, j0, lim, h);
+            float mx = max3(s_even[0], s_even[1], s_even[2]);
+#pragma unroll
+            for (int t = 3; t < 15; t += 2) mx = max3(mx, s_even[t], s_even[t + 1]);
+            st.mx = tile_max(max3(mx, s_even[15], s_even[15])) * prm.scale_log2;
+        }
+        // Block blk while block blk + 1 is scored.  Every wave waits for its own loads of block blk + 1 (those of block
+        // blk + 2 may stay in flight), then the barrier: block blk + 1 is in LDS and everyone is done with block blk - 1,
+        // whose buffer the loads of block blk + 3 overwrite.
+        auto step = [&](int blk, f32x16_t& s, f32x16_t& s_next, auto lo_mode) {
+            dma_wait_for<kTileLoads>();
+            __syncthreads();
+            const TileLoad later = load_for(blk + 3);
+            tile_block<decltype(lo_mode)::value, false>(o, st, s, s_next, qop, q_lds, rd, lds_c + (blk & 3) * kTileBlock,
+                                                        lds_c + ((blk + 1) & 3) * kTileBlock, prm.scale_log2, j0 + (blk + 1) * kMlaKeys,
+                                                        lim, h, false, [&](auto q_c) { tile_load<decltype(q_c)::value>(later, dma); });
+        };
+        auto last = [&](f32x16_t& s, auto lo_mode) {
+            tile_block<decltype(lo_mode)::value, true>(o, st, s, s, qop, q_lds, rd, lds_c + ((n_blocks - 1) & 3) * kTileBlock, nullptr,
+                                                       prm.scale_log2, 0, lim, h, n_blocks <= kExactBlocks, [](auto) {});
+        };
+        // Default mode: the first blocks of a segment with hi + lo weights, the others with hi + lo only where a
+        // key dominates.
+        constexpr auto kFirstMode = std::integral_constant<int, kMode == 2 ? kLoNever : kLoAlways>();
+        constexpr auto kThenMode = std::integral_constant<int, kMode == 0 ? kLoDynamic : kMode == 1 ? kLoAlways : kLoNever>();
+        if (busy) {
+            int blk = 0;
+            for (; blk + 1 < n_blocks && blk < kExactBlocks; ++blk) {
+                step(blk, s_even, s_odd, kFirstMode);
+                s_even = s_odd;
+            }
+            for (; blk + 2 < n_blocks; blk += 2) {
+                step(blk, s_even, s_odd, kThenMode);
+                step(blk + 1, s_odd, s_even, kThenMode);
+            }
+            if (blk + 1 < n_blocks) {
+                step(blk, s_even, s_odd, kThenMode);
+                s_even = s_odd;
+                ++blk;
+            }
+            last(s_even, kThenMode);
+            acc_drain(o);
+        } else {
+            for (int blk = 0; blk + 1 < n_blocks; ++blk) {
+                dma_wait_for<kTileLoads>();
+                __syncthreads();
+                load_block(blk + 3);
+            }
+        }
+        dma_wait_for<0>();        // the empty loads behind the last block: they write (zeros) to the buffers
+        __syncthreads();          // everyone is done with the block buffers: they stage the output now
+        if (busy) {
+            const float l = st.l;
+            float lq, lq_b;
+            swap32(st.lq, lq, lq_b);
+            lq += lq_b;
+            // Rounded as in mla_decode_kernel: bf16 results; partial rows fp16, scaled to the row's largest magnitude.
+            float sc, inv_scale = 0.0f;
+            if (whole) {
+                sc = lq > 0.0f ? 1.0f / lq : 0.0f;
+            } else {
+                float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                static_for<kTileCols>([&](auto ct_c) {
+                    float v[16];
+                    acc_read<decltype(ct_c)::value>(o, v);
+#pragma unroll
+                    for (int i = 0; i < 16; i += 2) max3_abs(part[(i / 2) & 3], v[i], v[i + 1]);
+                });
+                const float amax = tile_max(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3])));
+                sc = amax > 0.0f ? fminf(32768.0f / amax, 0x1.0p100f) : 0.0f;
+                inv_scale = amax > 0.0f ? 1.0f / sc : 0.0f;
+            }
+            uint16_t* dst = whole ? prm.out + (long)b * rows_total * kDv : prm.part_o + slot * rows_total * kDv;
+            const __amdgpu_buffer_rsrc_t rd_out = make_rsrc(uniform(static_cast<void*>(dst)), (uint32_t)rows_total * (kDv * 2));
+            // A quarter of the columns at a time through the stage, its rows stored behind the rounding of the quarter
+            // after it; four rows of 256 bytes per store, rows past the last are dropped.
+            int lane_out = lane;
+            pin(lane_out);        // as q_lane
+            char* lane_stage = stage + (lane_out & 31) * kTileStagePitch + 8 * (lane_out >> 5);
+            const char* lane_rows = stage + (lane_out >> 4) * kTileStagePitch + (lane_out & 15) * 16;
+            const int lane_dst = (wave_row0 + (lane_out >> 4)) * (kDv * 2) + (lane_out & 15) * 16;
+            auto round_quarter = [&](auto q_c, auto whole_c) {
+                static_for<kTileCols / 4>([&](auto t_c) {
+                    constexpr int ct = decltype(q_c)::value * (kTileCols / 4) + decltype(t_c)::value;
+                    float v[16];
+                    acc_read<ct>(o, v);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) v[i] *= sc;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)      // columns 32 ct + 8 g + 4 h .. + 3 of row n
+                        *reinterpret_cast<uint2*>(lane_stage + (32 * ct + 8 * g) * 2) =
+                            decltype(whole_c)::value ? make_uint2(cvt_bf16(v[4 * g], v[4 * g + 1]), cvt_bf16(v[4 * g + 2], v[4 * g + 3]))
+                                                     : make_uint2(pack_f16(v[4 * g], v[4 * g + 1]), pack_f16(v[4 * g + 2], v[4 * g + 3]));
+                });
+                fence();
+            };
+            auto store_quarter = [&](int q) {
+#pragma unroll
+                for (int i = 0; i < kTileRows / 4; ++i) {
+                    const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lane_rows + 4 * i * kTileStagePitch + q * 256);
+                    __builtin_amdgcn_raw_buffer_store_b128(w, rd_out, lane_dst + 4 * i * (kDv * 2) + q * 256, 0, 0);
+                }
+            };
+            auto store_rows = [&](auto whole_c) {
+                round_quarter(std::integral_constant<int, 0>(), whole_c);
+                round_quarter(std::integral_constant<int, 1>(), whole_c);
+                store_quarter(0);
+                round_quarter(std::integral_constant<int, 2>(), whole_c);
+                store_quarter(1);
+                round_quarter(std::integral_constant<int, 3>(), whole_c);
+                store_quarter(2);
+                store_quarter(3);
+            };
+            if (whole) store_rows(std::true_type());
+            else store_rows(std::false_type());
+            if (row < rows_total && h == 0) {
+                if (whole) {
+                    if (prm.lse) prm.lse[(long)b * rows_total + row] = l > 0.0f ? (st.m + __log2f(l)) * kLn2 : kNegInf;
+                } else {
+                    reinterpret_cast<float4*>(prm.part_ml)[slot * rows_total + row] = make_float4(st.m, l, lq, inv_scale);
+                }
+            }
+        }
+        __syncthreads();          // the next segment's first block goes to buffer 0, which staged output until here
+    }
+}
+
 
 // ----------------------------------------------------------------------- few query rows: 32 at most
 // With 16 rows (heads split over several GPUs) a cached byte meets 30 flop: bound by HBM, and what matters
@@ -1239,6 +1609,13 @@ hipError_t launch_mla_cfg(const MlaParams& prm, dim3 grid, hipStream_t stream) {
     return hipGetLastError();
 }
 
+hipError_t launch_mla_tile(const MlaParams& prm, dim3 grid, hipStream_t stream) {
+    if (prm.weight_mode == 1) hipLaunchKernelGGL((mla_tile_kernel<1>), grid, dim3(64 * kTileWaves), 0, stream, prm);
+    else if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_tile_kernel<2>), grid, dim3(64 * kTileWaves), 0, stream, prm);
+    else hipLaunchKernelGGL((mla_tile_kernel<0>), grid, dim3(64 * kTileWaves), 0, stream, prm);
+    return hipGetLastError();
+}
+
 template <int RT>
 hipError_t launch_mla_rows(const MlaParams& prm, dim3 grid, hipStream_t stream) {
     if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_rows_kernel<RT, false>), grid, dim3(256 * RT), 0, stream, prm);
@@ -1248,14 +1625,15 @@ hipError_t launch_mla_rows(const MlaParams& prm, dim3 grid, hipStream_t stream) 
 
 }  // namespace
 
-// Workgroup shape for rows_total = q_len * n_heads query rows per sequence: (waves, 16-row tiles per
-// wave).  Automatic: up to 32 rows mla_rows_kernel (one row group, as the shape given here); then one tile per
-// wave, 8 waves from 65 rows on (two waves per SIMD, 256 registers each).  layout 1: at most 4 waves of one tile
-// (64 rows per workgroup); layout 2: 4 waves of two tiles from 65 rows on (one wave per SIMD, 512 registers).
+// Workgroup shape for rows_total = q_len * n_heads query rows per sequence: (waves, 16-row tiles per wave).  Up to 32
+// rows mla_rows_kernel (one row group, as the shape given here), which has its line there; then mla_tile_kernel, 128
+// rows per workgroup: at 33 rows already 67.4 us against 76.9 with a wave per 16 rows.  layout 1: waves of 16 rows, 4
+// at most, for any number of rows; layout 2: as 1 up to 64 rows, then mla_tile_kernel.
 void mla_block_shape(int rows_total, int layout, int* waves, int* tiles_per_wave) {
     const int tiles = (rows_total + 15) / 16;
-    *tiles_per_wave = (tiles > 4 && layout == 2) ? 2 : 1;
-    *waves = (layout != 1 && layout != 2 && tiles > 4) ? 8 : tiles >= 3 ? 4 : tiles;
+    const bool tile32 = layout != 1 && tiles > (layout == 2 ? 4 : 2);
+    *tiles_per_wave = tile32 ? 2 : 1;
+    *waves = tile32 || tiles >= 3 ? 4 : tiles;
 }
 
 hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_t* events) {
@@ -1267,8 +1645,7 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     if (events && (e = hipEventRecord(events[0], stream)) != hipSuccess) return e;
     if (prm.layout == 0 && rows_total <= 16) e = launch_mla_rows<1>(prm, grid, stream);
     else if (prm.layout == 0 && rows_total <= 32) e = launch_mla_rows<2>(prm, grid, stream);
-    else if (rt == 2) e = launch_mla_cfg<4, 2>(prm, grid, stream);
-    else if (nw == 8) e = launch_mla_cfg<8, 1>(prm, grid, stream);
+    else if (rt == 2) e = launch_mla_tile(prm, grid, stream);
     else if (nw == 4) e = launch_mla_cfg<4, 1>(prm, grid, stream);
     else if (nw == 2) e = launch_mla_cfg<2, 1>(prm, grid, stream);
     else e = launch_mla_cfg<1, 1>(prm, grid, stream);

@@ -1,0 +1,65 @@
+"""The latent-KV kernel for more than 32 query rows (a wave per 32 rows) against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import bf16_to_f32
+from test_gpu_mla import DV, SCALE, _case, _default_partition, gpu_mla      # noqa: F401  (the fixture resets the knobs)
+
+pytestmark = pytest.mark.gpu
+
+# rows 33 (second wave with one row), 64, 65, 97, 127, 128 (one workgroup), 129, 261 (a row group with 1 and 5 rows);
+# lengths around the 32-key block, the four LDS buffers and the four blocks with lo parts of a segment, then long ones
+# that are split; keys that carry a row in late blocks (scores times 16: the second pass with the lo parts)
+LENS = (1, 31, 32, 33, 64, 65, 97, 127, 128, 129, 160, 161, 193, 700, 2049)
+
+
+@pytest.mark.parametrize("T,H", [(3, 11), (1, 64), (5, 13), (1, 97), (1, 127), (16, 8), (3, 43), (9, 29)])
+@pytest.mark.parametrize("pieces,pv_mode,scale_up", [(0, 0, 1.0), (8, 0, 16.0), (37, 2, 1.0), (1024, 1, 4.0)])
+def test_tiles_of_32_rows(T, H, pieces, pv_mode, scale_up):
+    import paper_2510_14686_amd as xa
+    from gpu_util import TOL_LSE, TOL_REL_L2, assert_parity, errors
+    xa.xattn_configure(xa.XATTN_CFG_PIECES, pieces)
+    xa.xattn_configure(xa.XATTN_CFG_PV_MODE, pv_mode)
+    if pieces > 256:
+        xa.xattn_configure(xa.XATTN_CFG_MIN_PIECE_TOKENS, 16)
+    # One-key rows put out single value elements: halved values (exact in bf16) keep every output below 4, from
+    # where on bf16 rounding of the result alone exceeds the absolute bar.
+    lens = [max(T, n) for n in LENS]
+    q, cs = _case(400 + T, lens, T, H)
+    cs = [(bf16_to_f32(c) * 0.5).astype(np.float32) for c in cs]
+    cs = [(c.view(np.uint32) >> 16).astype(np.uint16) for c in cs]
+    scale = float(np.float32(2.0 * SCALE * scale_up))
+    out_bits, lse = gpu_mla(q, cs, lens, scale)
+    ref_out, ref_lse = oracle.mla(q, cs, lens, DV, scale)
+    what = "T=%d H=%d pieces=%d" % (T, H, pieces)
+    if scale_up == 1.0:
+        assert_parity(out_bits, lse, ref_out, ref_lse, what)
+        return
+    # As in test_few_rows: one key can carry a row, so element by element: rounding to bf16 (half an ulp is at
+    # most 2^-8 of the value) and the fp16 partial rows (2^-11 of values up to 5, weights summing to 1).
+    _, rel_rows, _, lse_err = errors(out_bits, lse, ref_out, ref_lse)
+    diff = np.abs(bf16_to_f32(out_bits).astype(np.float64).reshape(ref_out.shape) - ref_out)
+    assert np.all(diff <= 2.0 ** -8 * np.abs(ref_out) + 5 * 2.0 ** -11), what
+    assert rel_rows <= TOL_REL_L2 and lse_err <= TOL_LSE, what
+
+
+def test_reference_maximum_that_moves_rescales_every_column():
+    """Keys whose scores grow along the sequence move the reference maximum of a row block after block, in some rows
+    of a tile and not in others."""
+    from gpu_util import TOL_LSE, TOL_REL_L2, errors
+    from workloads import f32_to_bf16
+    lens = [900, 330]
+    q, cs = _case(410, lens, 1, 96)
+    qf = bf16_to_f32(q).copy()
+    qf[..., 0] = np.where(np.arange(96) % 3 == 0, 6.0, 0.0)                 # every third head sees the ramp
+    ramped = []
+    for c in cs:
+        cf = bf16_to_f32(c).copy()
+        cf[:, 0] = np.arange(cf.shape[0]) * 0.125                           # up to 112: scores up to 670 * SCALE = 48
+        ramped.append(f32_to_bf16(cf).reshape(c.shape))
+    q2 = f32_to_bf16(qf).reshape(q.shape)
+    ref_out, ref_lse = oracle.mla(q2, ramped, lens, DV, SCALE)
+    out_bits, lse = gpu_mla(q2, ramped, lens, SCALE)
+    _, rel_rows, _, lse_err = errors(out_bits, lse, ref_out, ref_lse)
+    assert rel_rows <= TOL_REL_L2 and lse_err <= TOL_LSE
