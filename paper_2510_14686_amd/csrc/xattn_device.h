@@ -220,8 +220,7 @@ __device__ __forceinline__ int chunk_positions(__amdgpu_buffer_rsrc_t rl, int fi
 }
 
 // win (optional): with at most 64 sequences (one per lane) the window is filled here, in the plan's own
-// round trip.  (It pays in the latent-KV kernel, whose workgroups wait at a barrier for the first block
-// of a segment; the GQA kernel's independent waves hide those two loads and only lose registers to it.)
+// round trip.
 __device__ __forceinline__ WavePlan wave_plan(const int32_t* __restrict__ kv_lens, const void* const* k_ptrs,
                                               const void* const* v_ptrs, int batch, int n_pieces, int min_piece,
                                               int seg_cost, int xcd_skew, FewPieces few, int lane, SeqWindow* win) {

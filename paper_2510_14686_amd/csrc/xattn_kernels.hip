@@ -615,8 +615,17 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     const int part = prm.parts == 1 ? 0 : wave / heads;
     const int kvh = blockIdx.z * kMaxWavesPerBlock + wave - part * heads;
     if (kvh >= prm.n_kv_heads) return;
-    const WavePlan wp = wave_plan(prm.kv_lens, nullptr, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kGqaSegCost,
-                                  prm.xcd_skew, prm.few, lane, nullptr);
+    // A piece's first segment takes its length and pointers from the plan's own round trips, which saves a start two
+    // dependent loads (138468 tokens of 2 KV heads 31.7 -> 31.1 us, of 8 94.3 -> 93.2).  Only the first: kept longer the
+    // window's registers cost the large calls up to 1.7 %.  Not with two tiles: that kernel's registers are full, and
+    // those the window spills cost it 17 %.
+    constexpr bool kWindow = kTiles == 1;
+    SeqWindow win;
+    SeqWindow* const window = kWindow ? &win : nullptr;
+    const void* const* const win_k = kWindow ? prm.k_ptrs : nullptr;
+    const void* const* const win_v = kWindow ? prm.v_ptrs : nullptr;
+    const WavePlan wp = wave_plan(prm.kv_lens, win_k, win_v, prm.batch, prm.n_pieces, prm.min_piece_tokens, kGqaSegCost,
+                                  prm.xcd_skew, prm.few, lane, window);
     const Plan& pl = wp.pl;
 
     const int bid = blockIdx.x;
@@ -635,7 +644,7 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     if (!active) return;
 
     Walk walk;
-    wave_locate(wp, prm.kv_lens, nullptr, nullptr, prm.batch, s0, lane, nullptr, walk.b, walk.j);
+    wave_locate(wp, prm.kv_lens, win_k, win_v, prm.batch, s0, lane, window, walk.b, walk.j);
     walk.remaining = uniform(s1 - s0);
 
     Segment seg;
@@ -643,17 +652,20 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     seg.row0 = work.row0;
     seg.n_rows = rows_total - seg.row0 < rows ? rows_total - seg.row0 : rows;
     // Next (piece, sequence) intersection of this piece, in stream order; false when the piece is done.
-    auto next_seg = [&](Segment& out) {
+    auto next_seg = [&](Segment& out, auto first) {
+        constexpr bool kFirst = kWindow && decltype(first)::value;
         PieceSeg ps;
-        if (!next_segment(walk, prm.batch, pl.seg_cost,
-                          [&](int b) { return __builtin_amdgcn_readfirstlane(clamp_len(prm.kv_lens[b])); }, ps))
-            return false;
+        auto len_of = [&](int b) {
+            if constexpr (kFirst) return window_len(win, prm.kv_lens, b);
+            else return __builtin_amdgcn_readfirstlane(clamp_len(prm.kv_lens[b]));
+        };
+        if (!next_segment(walk, prm.batch, pl.seg_cost, len_of, ps)) return false;
         // Everything about a segment is wave-uniform; said so, it lives in scalar registers, and the loads
         // through its descriptors need no loop over the lanes' values.
         out = seg;
         out.b = uniform(ps.b);
-        out.kp = uniform(prm.k_ptrs[out.b]);
-        out.vp = uniform(prm.v_ptrs[out.b]);
+        out.kp = kFirst ? window_ptr(win, win.k, prm.k_ptrs, out.b) : uniform(prm.k_ptrs[out.b]);
+        out.vp = kFirst ? window_ptr(win, win.v, prm.v_ptrs, out.b) : uniform(prm.v_ptrs[out.b]);
         out.L = uniform(ps.L);
         out.j0 = uniform(ps.j0);
         out.j1 = uniform(ps.j1);
@@ -666,14 +678,14 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
         auto run_piece = [&](auto tiles) {
             constexpr int kT = decltype(tiles)::value;
             Segment cur_seg;
-            if (uniform(next_seg(cur_seg)) == 0) return;
+            if (uniform(next_seg(cur_seg, std::true_type())) == 0) return;
             MatrixCtx<kT> cur;
             matrix_begin(cur, prm, cur_seg, lane);
             for (;;) {
                 MatrixState st[kT];
                 matrix_run<kPv, kT>(st, cur, prm, lane, lds_wave);
                 Segment nxt_seg;
-                const bool more = uniform(next_seg(nxt_seg)) != 0;
+                const bool more = uniform(next_seg(nxt_seg, std::false_type())) != 0;
                 MatrixCtx<kT> nxt;
                 if (more) matrix_begin(nxt, prm, nxt_seg, lane);     // its loads go out before cur's stores
 #pragma unroll
@@ -689,7 +701,7 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
         else run_piece(std::integral_constant<int, kTiles>());
     } else {
         Segment s2;
-        while (next_seg(s2)) vector_segment<R>(prm, s2, lane);
+        for (bool more = next_seg(s2, std::true_type()); more; more = next_seg(s2, std::false_type())) vector_segment<R>(prm, s2, lane);
     }
 }
 
