@@ -172,7 +172,8 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *                               pieces) as far as the partial results fit XATTN_NOALLOC_SCRATCH_BYTES
  *   XATTN_CFG_MIN_PIECE_TOKENS  lower bound on a piece's tokens; 0 = default (64; 16 for up to as many
  *                               pieces as compute units and 8 MiB of partial results;
- *                               xattn_mla_decode: 64, and 32 for up to 32 pieces); values below 16
+ *                               xattn_mla_decode: 64, above 64 query rows per sequence 128 or, with up to
+ *                               8 sequences, 192, and 32 for up to 32 pieces); values below 16
  *                               count as 16
  *   XATTN_CFG_TIMING            1 = record per-kernel events (see xattn_timing_read); 0 = off
  *   XATTN_CFG_PATH              inner loop of the decode kernel: 0 = automatic (the matrix-core path),

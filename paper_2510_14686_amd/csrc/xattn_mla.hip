@@ -632,14 +632,12 @@ constexpr int kTileSteps = kDqk / 16;            // 36 MFMA steps of 16 columns
 constexpr int kTileQRegs = 33;                   // Q steps in registers, the rest parked in LDS
 constexpr int kTileQLds = (kTileSteps - kTileQRegs) * 1024;      // per wave
 constexpr int kTileCols = kDv / 32;              // 16 tiles of 32 value columns
-constexpr int kTileFrags = 2 * kTileCols;        // value fragments (16 keys x 32 columns) of a block
 constexpr int kTileStages = 4;
 constexpr int kTileHalf = 16 * kPitch + 16;      // rows 16..31
 constexpr int kTileTailOff = kTileHalf + 15 * kPitch + 1024;
 constexpr int kTileBlock = kTileTailOff + kMlaKeys * 128;
 constexpr int kTileLoads = kMlaKeys / kTileWaves + 1;            // loads per wave and block: 8 rows, and 8 rows' rope parts
 constexpr int kTileKAhead = 4, kTileVAhead = 4;  // fragments in flight ahead of their MFMAs
-constexpr int kTileLoadEvery = 7, kTileLoadsA = 5;       // a load every so many MFMAs, this many of them in phase A
 constexpr int kTileStagePitch = kDv * 2 + 16;    // epilogue: whole rows, padded
 
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
@@ -685,19 +683,26 @@ __device__ __forceinline__ void acc_mfma(TileAcc& o, bf16x8_t a, bf16x8_t b) {  
     XATTN_ACC_EACH(X)
 #undef X
 }
+// The first kN tiles.
+template <int kN>
 __device__ __forceinline__ void acc_zero(TileAcc& o) {
 #define Z(ct, i) "v_accvgpr_write_b32 " XATTN_ACC_REG(ct, i) ", 0\n\t"
 #define X(ct)                                                                                                              \
+    if constexpr (ct < kN)                                                                                                 \
     asm volatile(Z(ct, 0) Z(ct, 1) Z(ct, 2) Z(ct, 3) Z(ct, 4) Z(ct, 5) Z(ct, 6) Z(ct, 7) Z(ct, 8) Z(ct, 9) Z(ct, 10)        \
                  Z(ct, 11) Z(ct, 12) Z(ct, 13) Z(ct, 14) Z(ct, 15) : "=" XATTN_ACC_TILE(ct)(o.t[ct]));
     XATTN_ACC_EACH(X)
 #undef X
 #undef Z
 }
-// Before the first vector instruction that reads the accumulators; all but the last were written long ago.
+// Before the first vector instruction that reads the accumulators; all but the last two tiles were written long ago.
+template <int kN>
 __device__ __forceinline__ void acc_drain(TileAcc& o) {
-    asm volatile("s_nop 15\n\ts_nop 7" : "+" XATTN_ACC_TILE(14)(o.t[14]), "+" XATTN_ACC_TILE(15)(o.t[15]));
+    if constexpr (kN == 16) asm volatile("s_nop 15\n\ts_nop 7" : "+" XATTN_ACC_TILE(14)(o.t[14]), "+" XATTN_ACC_TILE(15)(o.t[15]));
+    else asm volatile("s_nop 15\n\ts_nop 7" : "+" XATTN_ACC_TILE(6)(o.t[6]), "+" XATTN_ACC_TILE(7)(o.t[7]));
+    static_assert(kN == 16 || kN == 8, "the last two tiles");
 }
+template <int kN>
 __device__ __forceinline__ void acc_scale(TileAcc& o, float f) {                           // behind acc_drain
     float t0, t1, t2, t3;
 #define R(ct, i, t) "v_accvgpr_read_b32 %" #t ", " XATTN_ACC_REG(ct, i) "\n\t"
@@ -705,6 +710,7 @@ __device__ __forceinline__ void acc_scale(TileAcc& o, float f) {                
 #define W(ct, i, t) "v_accvgpr_write_b32 " XATTN_ACC_REG(ct, i) ", %" #t "\n\t"
 #define Q(ct, a, b, c, d) R(ct, a, 1) R(ct, b, 2) R(ct, c, 3) R(ct, d, 4) M(1) M(2) M(3) M(4) W(ct, a, 1) W(ct, b, 2) W(ct, c, 3) W(ct, d, 4)
 #define X(ct)                                                                                          \
+    if constexpr (ct < kN)                                                                             \
     asm volatile(Q(ct, 0, 1, 2, 3) Q(ct, 4, 5, 6, 7) Q(ct, 8, 9, 10, 11) Q(ct, 12, 13, 14, 15)         \
                  : "+" XATTN_ACC_TILE(ct)(o.t[ct]), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3) : "v"(f));
     XATTN_ACC_EACH(X)
@@ -861,11 +867,15 @@ __device__ __forceinline__ float tile_max(float t) {
 
 // Block i: its scores s become weights while the scores s_next of the block at `next` are computed (not in a
 // segment's last block), then its values at `cur` are added to o.  issue(q): the caller's load q of a later block.
-template <int kLo, bool kLast, typename Issue>
+template <int kLo, bool kLast, int kN, typename Issue>
 __device__ __forceinline__ void tile_block(TileAcc& o, TileRow& st, const f32x16_t& s, f32x16_t& s_next,
                                            const bf16x8_t (&qop)[kTileQRegs], const char* q_lds, const TileReads& rd,
                                            const char* cur, const char* next, float scale_log2, int j_next, int lim, int h,
                                            bool exact, Issue issue) {
+    constexpr int kTileFrags = 2 * kN;               // value fragments (16 keys x 32 columns) of the wave's columns
+    // A load every so many MFMAs, this many of them in phase A.
+    constexpr int kTileLoadEvery = kN == 16 ? 7 : 5, kTileLoadsA = (kTileSteps + kTileLoadEvery - 4) / kTileLoadEvery;
+    static_assert(kTileLoadsA + (kTileFrags + kTileLoadEvery - 4) / kTileLoadEvery >= kTileLoads, "a slot for every load");
     bf16x8_t ka[kTileSteps], ql[kTileSteps - kTileQRegs], va[kTileFrags];
     auto load_k = [&](auto f_c) {
         constexpr int F = decltype(f_c)::value;
@@ -883,8 +893,8 @@ __device__ __forceinline__ void tile_block(TileAcc& o, TileRow& st, const f32x16
         st.l *= alpha;
         st.lq *= alpha;
         if (!first) {
-            acc_drain(o);
-            acc_scale(o, alpha);
+            acc_drain<kN>(o);
+            acc_scale<kN>(o, alpha);
         }
     }
     const float m_use = st.m == kNegInf ? 0.0f : st.m;
@@ -1004,12 +1014,17 @@ __device__ __forceinline__ void tile_block(TileAcc& o, TileRow& st, const f32x16
     }
 }
 
-// kMode: as mla_decode_kernel.
-template <int kMode>
+// kMode: as mla_decode_kernel.  kSmall: up to 64 rows, so that two of the four waves would have no rows.  In short pieces
+// two waves then share a tile: each computes the tile's scores and weights for itself and accumulates half of the columns.
+// A block takes 52 MFMAs of a wave instead of 68 and the output's rounding half as long, but the chip does 1.5 times the
+// MFMAs.  64 rows, tile per wave / per two waves, us: 29 sequences of 131 to 262 tokens 20.5 / 19.3, 32 of 30 to 100 18.5 /
+// 16.7, 4 of 500 to 3000 21.3 / 20.0, 64 of 1024 to 8192 73.8 / 78.8: about 2 us less per segment against 0.15 us more per
+// block, hence the line at 512 positions (segment cost included) per piece.
+constexpr int kTileShortLog2 = 9;
+template <int kMode, bool kSmall>
 __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm) {
     __shared__ __attribute__((aligned(16))) char lds_c[kTileStages * kTileBlock];
     __shared__ __attribute__((aligned(16))) char lds_q[kTileWaves * kTileQLds];      // each lane reads back what it wrote
-    static_assert(kTileWaves * kTileRows * kTileStagePitch <= kTileStages * kTileBlock, "output staging must fit the block buffers");
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     const int n = lane & 31, h = lane >> 5;
     const int T = prm.q_len, H = prm.n_heads, rows_total = T * H;
@@ -1017,249 +1032,267 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
     const WavePlan wp = wave_plan(prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kMlaSegCost,
                                   prm.xcd_skew, prm.few, lane, &win);
     const Plan& pl = wp.pl;
-    const int per_xcd = (pl.n_pieces + 7) >> 3;
-    // Workgroups as in mla_decode_kernel: the row groups of a piece side by side on one XCD.
-    const int bid = blockIdx.x;
-    const int n_groups = (rows_total + kTileWaves * kTileRows - 1) / (kTileWaves * kTileRows);
-    const int slot_in_xcd = bid >> 3;
-    const int row_group = slot_in_xcd % n_groups;
-    const int p = (bid & 7) * per_xcd + slot_in_xcd / n_groups;
-    const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
-    const bool active = slot_in_xcd / n_groups < per_xcd && p < pl.n_pieces && s0 < s1;
-    if (tid < 64)
-        for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
-    if (!active) return;       // the whole workgroup: every wave computed the same plan
+    auto work = [&](auto split_c) {
+        constexpr int kSplit = decltype(split_c)::value;             // waves per tile
+        constexpr int kN = kTileCols / kSplit, kTiles = kTileWaves / kSplit;     // column tiles per wave, row tiles per workgroup
+        static_assert(kTiles * kTileRows * kTileStagePitch <= (kSplit == 1 ? 4 : 3) * kTileBlock, "output staging must fit the block buffers");
+        const int per_xcd = (pl.n_pieces + 7) >> 3;
+        // Workgroups as in mla_decode_kernel: the row groups of a piece side by side on one XCD.
+        const int bid = blockIdx.x;
+        const int n_groups = (rows_total + kTiles * kTileRows - 1) / (kTiles * kTileRows);
+        const int slot_in_xcd = bid >> 3;
+        const int row_group = slot_in_xcd % n_groups;
+        const int p = (bid & 7) * per_xcd + slot_in_xcd / n_groups;
+        const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
+        const bool active = slot_in_xcd / n_groups < per_xcd && p < pl.n_pieces && s0 < s1;
+        if (tid < 64)
+            for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
+        if (!active) return;       // the whole workgroup: every wave computed the same plan
 
-    Walk walk;
-    wave_locate(wp, prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, s0, lane, &win, walk.b, walk.j);
-    walk.remaining = uniform(s1 - s0);
-    dma_wait_all();
+        Walk walk;
+        wave_locate(wp, prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, s0, lane, &win, walk.b, walk.j);
+        walk.remaining = uniform(s1 - s0);
+        dma_wait_all();
 
-    const int wave_row0 = (row_group * kTileWaves + wave) * kTileRows;
-    const bool busy = wave_row0 < rows_total;          // a wave without rows only loads
-    const int row = wave_row0 + n;
-    char* q_lds = lds_q + wave * kTileQLds + lane * 16;
-    char* stage = lds_c + wave * (kTileRows * kTileStagePitch);
-    const TileDma dma = tile_dma(wave, lane);
-    const TileReads rd = tile_reads(lane);
-    auto fence = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-
-    PieceSeg ps;
-    while (uniform(next_segment(walk, prm.batch, pl.seg_cost,
-                                [&](int bb) { return window_len(win, prm.kv_lens, bb); }, ps))) {
-        const int b = uniform(ps.b), L = uniform(ps.L), j0 = uniform(ps.j0), j1 = uniform(ps.j1);
-        const bool whole = uniform(ps.whole) != 0;
-        const long slot = (long)uniform(p) + b;
-        const unsigned long long cbytes = (unsigned long long)L * kRowB;
-        const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, prm.c_ptrs, b);
-        const u32x4_t rc = {(uint32_t)uniform((int)(uint32_t)caddr), (uint32_t)uniform((int)((uint32_t)(caddr >> 32) & 0xffffu)),
-                            cbytes > 0xffffffffull ? 0xffffffffu : (uint32_t)cbytes, 0x00020000u};
-        const int n_blocks = (j1 - j0 + kMlaKeys - 1) / kMlaKeys;
-        // The loads of block blk.  Past the segment's end they run against an empty descriptor (zeros land in a free
-        // buffer), so that every block has its loads and the waits need no case.
-        auto load_for = [&](int blk) {
-            u32x4_t r = rc;
-            if (blk >= n_blocks) r[2] = 0u;
-            return tile_load_for(lds_c + (blk & 3) * kTileBlock, r, j0 + blk * kMlaKeys, wave);
-        };
-        auto load_block = [&](int blk) {
-            const TileLoad b = load_for(blk);
-            static_for<kTileLoads>([&](auto q_c) { tile_load<decltype(q_c)::value>(b, dma); });
+        const int tile = wave / kSplit, part = wave - tile * kSplit;
+        const int wave_row0 = (row_group * kTiles + tile) * kTileRows;
+        const bool busy = wave_row0 < rows_total;          // a wave without rows only loads
+        const int row = wave_row0 + n;
+        char* q_lds = lds_q + wave * kTileQLds + lane * 16;
+        char* stage = lds_c + tile * (kTileRows * kTileStagePitch) + part * (kN * 64);
+        const TileDma dma = tile_dma(wave, lane);
+        TileReads rd = tile_reads(lane);
+        rd.value += part * (kN * 64);
+        auto fence = [] {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         };
 
-        // Q operand: lane (h, n) holds columns 16 step + 8 h .. + 7 of row n; rows past the last lie past the end of the
-        // descriptor and read as zero.
-        const uint64_t qaddr = (uint64_t)(uintptr_t)(prm.q + (long)b * rows_total * kDqk);
-        const u32x4_t rq = {(uint32_t)uniform((int)(uint32_t)qaddr), (uint32_t)uniform((int)((uint32_t)(qaddr >> 32) & 0xffffu)),
-                            (uint32_t)rows_total * kRowB, 0x00020000u};
-        bf16x8_t qop[kTileQRegs];
-        TileAcc o;
-        f32x16_t s_even, s_odd;
-        TileRow st{kNegInf, 0.0f, 0.0f, kNegInf};
-        const int causal = L - T + (row < rows_total ? row : 0) / H + 1;
-        const int lim = causal < j1 ? causal : j1;
-        acc_zero(o);
-        // Q goes through the buffers behind those of blocks 0 and 1, in the wave's own part of them.
-        static_assert(kTileWaves * kTileQStage <= 2 * kTileBlock && kTileQRegs == 33, "Q's stage; the steps that are parked");
-        char* q_stage = lds_c + 2 * kTileBlock + wave * kTileQStage;
-        int q_lane = lane;
-        pin(q_lane);              // the addresses are made here: kept from segment to segment they would be spilled
-        auto park = [&](int step) { *reinterpret_cast<bf16x8_t*>(q_lds + (step - kTileQRegs) * 1024) = tile_q_frag(q_stage, q_lane, step); };
-        if (busy) tile_q_load(q_stage, rq, wave_row0, q_lane, 0, bid >> 3);
-        load_block(0);
-        if (busy) {
-            dma_wait_for<kTileLoads>();
-#pragma unroll
-            for (int step = 0; step < 16; ++step) qop[step] = tile_q_frag(q_stage, q_lane, step);
-            qop[32] = tile_q_frag(q_stage, q_lane, 32);
-            park(33);
-#pragma unroll
-            for (int step = 0; step < 16; ++step) pin(qop[step]);      // read before the second round overwrites them
-            pin(qop[32]);
-            fence();
-            tile_q_load(q_stage, rq, wave_row0, q_lane, 1, bid >> 3);
-        }
-        load_block(1);
-        dma_wait_for<kTileLoads>();
-        if (busy) {
-#pragma unroll
-            for (int step = 16; step < 32; ++step) qop[step] = tile_q_frag(q_stage, q_lane, step);
-            park(34);
-            park(35);
-#pragma unroll
-            for (int step = 16; step < 32; ++step) pin(qop[step]);
-            fence();
-        }
-        __syncthreads();
-        load_block(2);
-        if (busy) {
-            // Scores of block 0.
-            bf16x8_t ka[kTileSteps], ql[kTileSteps - kTileQRegs];
-            auto load_k = [&](auto f_c) {
-                constexpr int F = decltype(f_c)::value;
-                ka[F] = tile_key_frag(lds_c, rd, F);
-                if constexpr (F >= kTileQRegs) ql[F - kTileQRegs] = *reinterpret_cast<const bf16x8_t*>(q_lds + (F - kTileQRegs) * 1024);
+        PieceSeg ps;
+        while (uniform(next_segment(walk, prm.batch, pl.seg_cost,
+                                    [&](int bb) { return window_len(win, prm.kv_lens, bb); }, ps))) {
+            const int b = uniform(ps.b), L = uniform(ps.L), j0 = uniform(ps.j0), j1 = uniform(ps.j1);
+            const bool whole = uniform(ps.whole) != 0;
+            const long slot = (long)uniform(p) + b;
+            const unsigned long long cbytes = (unsigned long long)L * kRowB;
+            const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, prm.c_ptrs, b);
+            const u32x4_t rc = {(uint32_t)uniform((int)(uint32_t)caddr), (uint32_t)uniform((int)((uint32_t)(caddr >> 32) & 0xffffu)),
+                                cbytes > 0xffffffffull ? 0xffffffffu : (uint32_t)cbytes, 0x00020000u};
+            const int n_blocks = (j1 - j0 + kMlaKeys - 1) / kMlaKeys;
+            // The loads of block blk.  Past the segment's end they run against an empty descriptor (zeros land in a free
+            // buffer), so that every block has its loads and the waits need no case.
+            auto load_for = [&](int blk) {
+                u32x4_t r = rc;
+                if (blk >= n_blocks) r[2] = 0u;
+                return tile_load_for(lds_c + (blk & 3) * kTileBlock, r, j0 + blk * kMlaKeys, wave);
             };
-            static_for<kTileKAhead>(load_k);
-            static_for<kTileSteps>([&](auto f_c) {
-                constexpr int F = decltype(f_c)::value;
-                if constexpr (F + kTileKAhead < kTileSteps) load_k(std::integral_constant<int, F + kTileKAhead>());
-                bf16x8_t qv;
-                if constexpr (F < kTileQRegs) qv = qop[F];
-                else qv = ql[F - kTileQRegs];
-                if constexpr (F == 0) mfma_first_v(s_even, ka[F], qv);
-                else mfma_v(s_even, ka[F], qv);
-            });
-            mfma_drain(s_even);
-            if (__builtin_amdgcn_ballot_w64(j0 + kMlaKeys > lim) != 0) tile_mask(s_even, j0, lim, h);
-            float mx = max3(s_even[0], s_even[1], s_even[2]);
+            auto load_block = [&](int blk) {
+                const TileLoad b = load_for(blk);
+                static_for<kTileLoads>([&](auto q_c) { tile_load<decltype(q_c)::value>(b, dma); });
+            };
+
+            // Q operand: lane (h, n) holds columns 16 step + 8 h .. + 7 of row n; rows past the last lie past the end of the
+            // descriptor and read as zero.
+            const uint64_t qaddr = (uint64_t)(uintptr_t)(prm.q + (long)b * rows_total * kDqk);
+            const u32x4_t rq = {(uint32_t)uniform((int)(uint32_t)qaddr), (uint32_t)uniform((int)((uint32_t)(qaddr >> 32) & 0xffffu)),
+                                (uint32_t)rows_total * kRowB, 0x00020000u};
+            bf16x8_t qop[kTileQRegs];
+            TileAcc o;
+            f32x16_t s_even, s_odd;
+            TileRow st{kNegInf, 0.0f, 0.0f, kNegInf};
+            const int causal = L - T + (row < rows_total ? row : 0) / H + 1;
+            const int lim = causal < j1 ? causal : j1;
+            acc_zero<kN>(o);
+            // Q goes through the buffers behind those of blocks 0 and 1, in the wave's own part of them.
+            static_assert(kTileWaves * kTileQStage <= 2 * kTileBlock && kTileQRegs == 33, "Q's stage; the steps that are parked");
+            char* q_stage = lds_c + 2 * kTileBlock + wave * kTileQStage;
+            int q_lane = lane;
+            pin(q_lane);              // the addresses are made here: kept from segment to segment they would be spilled
+            auto park = [&](int step) { *reinterpret_cast<bf16x8_t*>(q_lds + (step - kTileQRegs) * 1024) = tile_q_frag(q_stage, q_lane, step); };
+            if (busy) tile_q_load(q_stage, rq, wave_row0, q_lane, 0, bid >> 3);
+            load_block(0);
+            if (busy) {
+                dma_wait_for<kTileLoads>();
 #pragma unroll
-            for (int t = 3; t < 15; t += 2) mx = max3(mx, s_even[t], s_even[t + 1]);
-            st.mx = tile_max(max3(mx, s_even[15], s_even[15])) * prm.scale_log2;
-        }
-        // Block blk while block blk + 1 is scored.  Every wave waits for its own loads of block blk + 1 (those of block
-        // blk + 2 may stay in flight), then the barrier: block blk + 1 is in LDS and everyone is done with block blk - 1,
-        // whose buffer the loads of block blk + 3 overwrite.
-        auto step = [&](int blk, f32x16_t& s, f32x16_t& s_next, auto lo_mode) {
+                for (int step = 0; step < 16; ++step) qop[step] = tile_q_frag(q_stage, q_lane, step);
+                qop[32] = tile_q_frag(q_stage, q_lane, 32);
+                park(33);
+#pragma unroll
+                for (int step = 0; step < 16; ++step) pin(qop[step]);      // read before the second round overwrites them
+                pin(qop[32]);
+                fence();
+                tile_q_load(q_stage, rq, wave_row0, q_lane, 1, bid >> 3);
+            }
+            load_block(1);
             dma_wait_for<kTileLoads>();
+            if (busy) {
+#pragma unroll
+                for (int step = 16; step < 32; ++step) qop[step] = tile_q_frag(q_stage, q_lane, step);
+                park(34);
+                park(35);
+#pragma unroll
+                for (int step = 16; step < 32; ++step) pin(qop[step]);
+                fence();
+            }
             __syncthreads();
-            const TileLoad later = load_for(blk + 3);
-            tile_block<decltype(lo_mode)::value, false>(o, st, s, s_next, qop, q_lds, rd, lds_c + (blk & 3) * kTileBlock,
-                                                        lds_c + ((blk + 1) & 3) * kTileBlock, prm.scale_log2, j0 + (blk + 1) * kMlaKeys,
-                                                        lim, h, false, [&](auto q_c) { tile_load<decltype(q_c)::value>(later, dma); });
-        };
-        auto last = [&](f32x16_t& s, auto lo_mode) {
-            tile_block<decltype(lo_mode)::value, true>(o, st, s, s, qop, q_lds, rd, lds_c + ((n_blocks - 1) & 3) * kTileBlock, nullptr,
-                                                       prm.scale_log2, 0, lim, h, n_blocks <= kExactBlocks, [](auto) {});
-        };
-        // Default mode: the first blocks of a segment with hi + lo weights, the others with hi + lo only where a
-        // key dominates.
-        constexpr auto kFirstMode = std::integral_constant<int, kMode == 2 ? kLoNever : kLoAlways>();
-        constexpr auto kThenMode = std::integral_constant<int, kMode == 0 ? kLoDynamic : kMode == 1 ? kLoAlways : kLoNever>();
-        if (busy) {
-            int blk = 0;
-            for (; blk + 1 < n_blocks && blk < kExactBlocks; ++blk) {
-                step(blk, s_even, s_odd, kFirstMode);
-                s_even = s_odd;
+            load_block(2);
+            if (busy) {
+                // Scores of block 0.
+                bf16x8_t ka[kTileSteps], ql[kTileSteps - kTileQRegs];
+                auto load_k = [&](auto f_c) {
+                    constexpr int F = decltype(f_c)::value;
+                    ka[F] = tile_key_frag(lds_c, rd, F);
+                    if constexpr (F >= kTileQRegs) ql[F - kTileQRegs] = *reinterpret_cast<const bf16x8_t*>(q_lds + (F - kTileQRegs) * 1024);
+                };
+                static_for<kTileKAhead>(load_k);
+                static_for<kTileSteps>([&](auto f_c) {
+                    constexpr int F = decltype(f_c)::value;
+                    if constexpr (F + kTileKAhead < kTileSteps) load_k(std::integral_constant<int, F + kTileKAhead>());
+                    bf16x8_t qv;
+                    if constexpr (F < kTileQRegs) qv = qop[F];
+                    else qv = ql[F - kTileQRegs];
+                    if constexpr (F == 0) mfma_first_v(s_even, ka[F], qv);
+                    else mfma_v(s_even, ka[F], qv);
+                });
+                mfma_drain(s_even);
+                if (__builtin_amdgcn_ballot_w64(j0 + kMlaKeys > lim) != 0) tile_mask(s_even, j0, lim, h);
+                float mx = max3(s_even[0], s_even[1], s_even[2]);
+#pragma unroll
+                for (int t = 3; t < 15; t += 2) mx = max3(mx, s_even[t], s_even[t + 1]);
+                st.mx = tile_max(max3(mx, s_even[15], s_even[15])) * prm.scale_log2;
             }
-            for (; blk + 2 < n_blocks; blk += 2) {
-                step(blk, s_even, s_odd, kThenMode);
-                step(blk + 1, s_odd, s_even, kThenMode);
-            }
-            if (blk + 1 < n_blocks) {
-                step(blk, s_even, s_odd, kThenMode);
-                s_even = s_odd;
-                ++blk;
-            }
-            last(s_even, kThenMode);
-            acc_drain(o);
-        } else {
-            for (int blk = 0; blk + 1 < n_blocks; ++blk) {
+            // Block blk while block blk + 1 is scored.  Every wave waits for its own loads of block blk + 1 (those of block
+            // blk + 2 may stay in flight), then the barrier: block blk + 1 is in LDS and everyone is done with block blk - 1,
+            // whose buffer the loads of block blk + 3 overwrite.
+            auto step = [&](int blk, f32x16_t& s, f32x16_t& s_next, auto lo_mode) {
                 dma_wait_for<kTileLoads>();
                 __syncthreads();
-                load_block(blk + 3);
-            }
-        }
-        dma_wait_for<0>();        // the empty loads behind the last block: they write (zeros) to the buffers
-        __syncthreads();          // everyone is done with the block buffers: they stage the output now
-        if (busy) {
-            const float l = st.l;
-            float lq, lq_b;
-            swap32(st.lq, lq, lq_b);
-            lq += lq_b;
-            // Rounded as in mla_decode_kernel: bf16 results; partial rows fp16, scaled to the row's largest magnitude.
-            float sc, inv_scale = 0.0f;
-            if (whole) {
-                sc = lq > 0.0f ? 1.0f / lq : 0.0f;
+                const TileLoad later = load_for(blk + 3);
+                tile_block<decltype(lo_mode)::value, false, kN>(o, st, s, s_next, qop, q_lds, rd, lds_c + (blk & 3) * kTileBlock,
+                                                            lds_c + ((blk + 1) & 3) * kTileBlock, prm.scale_log2, j0 + (blk + 1) * kMlaKeys,
+                                                            lim, h, false, [&](auto q_c) { tile_load<decltype(q_c)::value>(later, dma); });
+            };
+            auto last = [&](f32x16_t& s, auto lo_mode) {
+                tile_block<decltype(lo_mode)::value, true, kN>(o, st, s, s, qop, q_lds, rd, lds_c + ((n_blocks - 1) & 3) * kTileBlock, nullptr,
+                                                           prm.scale_log2, 0, lim, h, n_blocks <= kExactBlocks, [](auto) {});
+            };
+            // Default mode: the first blocks of a segment with hi + lo weights, the others with hi + lo only where a
+            // key dominates.
+            constexpr auto kFirstMode = std::integral_constant<int, kMode == 2 ? kLoNever : kLoAlways>();
+            constexpr auto kThenMode = std::integral_constant<int, kMode == 0 ? kLoDynamic : kMode == 1 ? kLoAlways : kLoNever>();
+            if (busy) {
+                int blk = 0;
+                for (; blk + 1 < n_blocks && blk < kExactBlocks; ++blk) {
+                    step(blk, s_even, s_odd, kFirstMode);
+                    s_even = s_odd;
+                }
+                for (; blk + 2 < n_blocks; blk += 2) {
+                    step(blk, s_even, s_odd, kThenMode);
+                    step(blk + 1, s_odd, s_even, kThenMode);
+                }
+                if (blk + 1 < n_blocks) {
+                    step(blk, s_even, s_odd, kThenMode);
+                    s_even = s_odd;
+                    ++blk;
+                }
+                last(s_even, kThenMode);
+                acc_drain<kN>(o);
             } else {
-                float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                static_for<kTileCols>([&](auto ct_c) {
-                    float v[16];
-                    acc_read<decltype(ct_c)::value>(o, v);
-#pragma unroll
-                    for (int i = 0; i < 16; i += 2) max3_abs(part[(i / 2) & 3], v[i], v[i + 1]);
-                });
-                const float amax = tile_max(fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3])));
-                sc = amax > 0.0f ? fminf(32768.0f / amax, 0x1.0p100f) : 0.0f;
-                inv_scale = amax > 0.0f ? 1.0f / sc : 0.0f;
-            }
-            uint16_t* dst = whole ? prm.out + (long)b * rows_total * kDv : prm.part_o + slot * rows_total * kDv;
-            const __amdgpu_buffer_rsrc_t rd_out = make_rsrc(uniform(static_cast<void*>(dst)), (uint32_t)rows_total * (kDv * 2));
-            // A quarter of the columns at a time through the stage, its rows stored behind the rounding of the quarter
-            // after it; four rows of 256 bytes per store, rows past the last are dropped.
-            int lane_out = lane;
-            pin(lane_out);        // as q_lane
-            char* lane_stage = stage + (lane_out & 31) * kTileStagePitch + 8 * (lane_out >> 5);
-            const char* lane_rows = stage + (lane_out >> 4) * kTileStagePitch + (lane_out & 15) * 16;
-            const int lane_dst = (wave_row0 + (lane_out >> 4)) * (kDv * 2) + (lane_out & 15) * 16;
-            auto round_quarter = [&](auto q_c, auto whole_c) {
-                static_for<kTileCols / 4>([&](auto t_c) {
-                    constexpr int ct = decltype(q_c)::value * (kTileCols / 4) + decltype(t_c)::value;
-                    float v[16];
-                    acc_read<ct>(o, v);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) v[i] *= sc;
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)      // columns 32 ct + 8 g + 4 h .. + 3 of row n
-                        *reinterpret_cast<uint2*>(lane_stage + (32 * ct + 8 * g) * 2) =
-                            decltype(whole_c)::value ? make_uint2(cvt_bf16(v[4 * g], v[4 * g + 1]), cvt_bf16(v[4 * g + 2], v[4 * g + 3]))
-                                                     : make_uint2(pack_f16(v[4 * g], v[4 * g + 1]), pack_f16(v[4 * g + 2], v[4 * g + 3]));
-                });
-                fence();
-            };
-            auto store_quarter = [&](int q) {
-#pragma unroll
-                for (int i = 0; i < kTileRows / 4; ++i) {
-                    const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lane_rows + 4 * i * kTileStagePitch + q * 256);
-                    __builtin_amdgcn_raw_buffer_store_b128(w, rd_out, lane_dst + 4 * i * (kDv * 2) + q * 256, 0, 0);
+                for (int blk = 0; blk + 1 < n_blocks; ++blk) {
+                    dma_wait_for<kTileLoads>();
+                    __syncthreads();
+                    load_block(blk + 3);
                 }
-            };
-            auto store_rows = [&](auto whole_c) {
-                round_quarter(std::integral_constant<int, 0>(), whole_c);
-                round_quarter(std::integral_constant<int, 1>(), whole_c);
-                store_quarter(0);
-                round_quarter(std::integral_constant<int, 2>(), whole_c);
-                store_quarter(1);
-                round_quarter(std::integral_constant<int, 3>(), whole_c);
-                store_quarter(2);
-                store_quarter(3);
-            };
-            if (whole) store_rows(std::true_type());
-            else store_rows(std::false_type());
-            if (row < rows_total && h == 0) {
+            }
+            dma_wait_for<0>();        // the empty loads behind the last block: they write (zeros) to the buffers
+            __syncthreads();          // everyone is done with the block buffers: they stage the output now
+            // Rounded as in mla_decode_kernel: bf16 results; partial rows fp16, scaled to the row's largest magnitude, which
+            // the waves of a tile agree on in LDS.
+            float amax = 0.0f;
+            float* amax_of = reinterpret_cast<float*>(lds_c + 3 * kTileBlock);
+            if (!whole) {
+                if (busy) {
+                    float m4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                    static_for<kN>([&](auto ct_c) {
+                        float v[16];
+                        acc_read<decltype(ct_c)::value>(o, v);
+#pragma unroll
+                        for (int i = 0; i < 16; i += 2) max3_abs(m4[(i / 2) & 3], v[i], v[i + 1]);
+                    });
+                    amax = tile_max(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
+                    if (kSplit > 1 && h == 0) amax_of[wave * kTileRows + n] = amax;
+                }
+                if constexpr (kSplit > 1) __syncthreads();
+            }
+            if (busy) {
+                const float l = st.l;
+                float lq, lq_b;
+                swap32(st.lq, lq, lq_b);
+                lq += lq_b;
+                float sc, inv_scale = 0.0f;
                 if (whole) {
-                    if (prm.lse) prm.lse[(long)b * rows_total + row] = l > 0.0f ? (st.m + __log2f(l)) * kLn2 : kNegInf;
+                    sc = lq > 0.0f ? 1.0f / lq : 0.0f;
                 } else {
-                    reinterpret_cast<float4*>(prm.part_ml)[slot * rows_total + row] = make_float4(st.m, l, lq, inv_scale);
+                    if constexpr (kSplit == 2) amax = fmaxf(amax, amax_of[(wave ^ 1) * kTileRows + n]);
+                    sc = amax > 0.0f ? fminf(32768.0f / amax, 0x1.0p100f) : 0.0f;
+                    inv_scale = amax > 0.0f ? 1.0f / sc : 0.0f;
+                }
+                uint16_t* dst = whole ? prm.out + (long)b * rows_total * kDv : prm.part_o + slot * rows_total * kDv;
+                const __amdgpu_buffer_rsrc_t rd_out = make_rsrc(uniform(static_cast<void*>(dst)), (uint32_t)rows_total * (kDv * 2));
+                // 128 columns at a time through the stage, their rows stored behind the rounding of the next 128; four rows of
+                // 256 bytes per store, rows past the last are dropped.
+                int lane_out = lane;
+                pin(lane_out);        // as q_lane
+                char* lane_stage = stage + (lane_out & 31) * kTileStagePitch + 8 * (lane_out >> 5);
+                const char* lane_rows = stage + (lane_out >> 4) * kTileStagePitch + (lane_out & 15) * 16;
+                const int lane_dst = (wave_row0 + (lane_out >> 4)) * (kDv * 2) + part * (kN * 64) + (lane_out & 15) * 16;
+                auto round_quarter = [&](auto q_c, auto whole_c) {
+                    static_for<4>([&](auto t_c) {
+                        constexpr int ct = decltype(q_c)::value * 4 + decltype(t_c)::value;
+                        float v[16];
+                        acc_read<ct>(o, v);
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) v[i] *= sc;
+#pragma unroll
+                        for (int g = 0; g < 4; ++g)      // columns 32 ct + 8 g + 4 h .. + 3 of row n
+                            *reinterpret_cast<uint2*>(lane_stage + (32 * ct + 8 * g) * 2) =
+                                decltype(whole_c)::value ? make_uint2(cvt_bf16(v[4 * g], v[4 * g + 1]), cvt_bf16(v[4 * g + 2], v[4 * g + 3]))
+                                                         : make_uint2(pack_f16(v[4 * g], v[4 * g + 1]), pack_f16(v[4 * g + 2], v[4 * g + 3]));
+                    });
+                    fence();
+                };
+                auto store_quarter = [&](int q) {
+#pragma unroll
+                    for (int i = 0; i < kTileRows / 4; ++i) {
+                        const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lane_rows + 4 * i * kTileStagePitch + q * 256);
+                        __builtin_amdgcn_raw_buffer_store_b128(w, rd_out, lane_dst + 4 * i * (kDv * 2) + q * 256, 0, 0);
+                    }
+                };
+                auto store_rows = [&](auto whole_c) {
+                    static_for<kN / 4>([&](auto q_c) {
+                        round_quarter(q_c, whole_c);
+                        if constexpr (decltype(q_c)::value > 0) store_quarter(decltype(q_c)::value - 1);
+                    });
+                    store_quarter(kN / 4 - 1);
+                };
+                if (whole) store_rows(std::true_type());
+                else store_rows(std::false_type());
+                if (row < rows_total && h == 0 && part == 0) {
+                    if (whole) {
+                        if (prm.lse) prm.lse[(long)b * rows_total + row] = l > 0.0f ? (st.m + __log2f(l)) * kLn2 : kNegInf;
+                    } else {
+                        reinterpret_cast<float4*>(prm.part_ml)[slot * rows_total + row] = make_float4(st.m, l, lq, inv_scale);
+                    }
                 }
             }
+            __syncthreads();          // the next segment's first block goes to buffer 0, which staged output until here
         }
-        __syncthreads();          // the next segment's first block goes to buffer 0, which staged output until here
+    };
+    if constexpr (kSmall) {
+        if ((pl.total >> kTileShortLog2) < pl.n_pieces) return work(std::integral_constant<int, 2>());
     }
+    work(std::integral_constant<int, 1>());
 }
 
 
@@ -1609,10 +1642,11 @@ hipError_t launch_mla_cfg(const MlaParams& prm, dim3 grid, hipStream_t stream) {
     return hipGetLastError();
 }
 
+template <bool kSmall>
 hipError_t launch_mla_tile(const MlaParams& prm, dim3 grid, hipStream_t stream) {
-    if (prm.weight_mode == 1) hipLaunchKernelGGL((mla_tile_kernel<1>), grid, dim3(64 * kTileWaves), 0, stream, prm);
-    else if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_tile_kernel<2>), grid, dim3(64 * kTileWaves), 0, stream, prm);
-    else hipLaunchKernelGGL((mla_tile_kernel<0>), grid, dim3(64 * kTileWaves), 0, stream, prm);
+    if (prm.weight_mode == 1) hipLaunchKernelGGL((mla_tile_kernel<1, kSmall>), grid, dim3(64 * kTileWaves), 0, stream, prm);
+    else if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_tile_kernel<2, kSmall>), grid, dim3(64 * kTileWaves), 0, stream, prm);
+    else hipLaunchKernelGGL((mla_tile_kernel<0, kSmall>), grid, dim3(64 * kTileWaves), 0, stream, prm);
     return hipGetLastError();
 }
 
@@ -1645,7 +1679,8 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     if (events && (e = hipEventRecord(events[0], stream)) != hipSuccess) return e;
     if (prm.layout == 0 && rows_total <= 16) e = launch_mla_rows<1>(prm, grid, stream);
     else if (prm.layout == 0 && rows_total <= 32) e = launch_mla_rows<2>(prm, grid, stream);
-    else if (rt == 2) e = launch_mla_tile(prm, grid, stream);
+    else if (rt == 2 && rows_total <= 2 * kTileRows) e = launch_mla_tile<true>(prm, grid, stream);
+    else if (rt == 2) e = launch_mla_tile<false>(prm, grid, stream);
     else if (nw == 4) e = launch_mla_cfg<4, 1>(prm, grid, stream);
     else if (nw == 2) e = launch_mla_cfg<2, 1>(prm, grid, stream);
     else e = launch_mla_cfg<1, 1>(prm, grid, stream);
