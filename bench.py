@@ -296,7 +296,7 @@ def run_mla_workload(w, steps, warmup, cpu_seconds):
         dec_ms, mrg_ms, n = kernel_timing(step, min(steps, 1000))
         achieved = flops / (dec_ms * 1e-3) / 1e12
         traffic, traffic_info = measured_traffic(w.name)
-        res["roofline"] = {"kernel": "mla_decode_kernel", "bound": "mfma", "achieved": achieved,
+        res["roofline"] = {"kernel": "mla_tile_kernel", "bound": "mfma", "achieved": achieved,
                            "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / MFMA_BF16_PEAK_TFLOPS,
                            "traffic": traffic, "traffic_source": traffic_info,
                            "timing": "HIP events recorded by the library on the launch stream around the kernel",

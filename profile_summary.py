@@ -29,11 +29,11 @@ sys.path.insert(0, ROOT)
 
 SQ_COUNTERS = ("SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_INSTS_VALU_MFMA_MOPS_F32 "
                "SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE GRBM_GUI_ACTIVE")
-KERNELS = {"split_decode_kernel": "merge_kernel", "mla_decode_kernel": "mla_merge_kernel"}
+KERNELS = {"split_decode_kernel": "merge_kernel", "mla_tile_kernel": "mla_merge_kernel"}
 
 
 def short_name(kernel_name):
-    for k in ("split_decode_kernel", "mla_decode_kernel", "mla_merge_kernel", "merge_kernel", "copyBuffer"):
+    for k in ("split_decode_kernel", "mla_tile_kernel", "mla_merge_kernel", "merge_kernel", "copyBuffer"):
         if k in kernel_name:
             return k
     return None
@@ -95,7 +95,7 @@ python3 bench.py --calibrate-copy: ten 1 GiB device-to-device copies, each reads
     traffic["calibration"] = {"fetch_factor": f_fetch, "write_factor": f_write}
     for w in names:
         mla = w in workloads.MLA_CONFIGS
-        kern = "mla_decode_kernel" if mla else "split_decode_kernel"
+        kern = "mla_tile_kernel" if mla else "split_decode_kernel"
         merge = KERNELS[kern]
         cfg = workloads.MLA_CONFIGS[w] if mla else workloads.CONFIGS[w]
         st = kernel_stats(raw, "trace_" + w)
