@@ -85,6 +85,7 @@ constexpr int kLoNever = 0;                      // one bf16 per weight everywhe
 constexpr int kLoAlways = 1;                     // hi + lo bf16 parts everywhere
 constexpr int kLoDynamic = 2;                    // hi + lo parts only in blocks with a dominant key
 constexpr int kExactBlocks = 4;                  // default mode: the first blocks of a segment run as kLoAlways
+constexpr int kExactShortBlocks = 7;             // the same in mla_tile_kernel's pieces of minimal length, see there
 constexpr float kDominantShare = 4.0f;           // a key is dominant from 1 / 4 of the row's running sum
 constexpr int kStages = 3;                       // LDS block buffers: two blocks in flight behind the one in use
 
@@ -1060,6 +1061,9 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
         const int row = wave_row0 + n;
         char* q_lds = lds_q + wave * kTileQLds + lane * 16;
         char* stage = lds_c + tile * (kTileRows * kTileStagePitch) + part * (kN * 64);
+        // Where the minimal piece length (64 positions up to 64 rows, above 128 or 192) cuts the number of pieces, all
+        // blocks of a piece run with hi + lo weights, as they do in pieces of 64: a longer piece must not round more weights.
+        const int exact_blocks = !kSmall && pl.n_pieces < prm.n_pieces ? kExactShortBlocks : kExactBlocks;
         const TileDma dma = tile_dma(wave, lane);
         TileReads rd = tile_reads(lane);
         rd.value += part * (kN * 64);
@@ -1175,7 +1179,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
             };
             auto last = [&](f32x16_t& s, auto lo_mode) {
                 tile_block<decltype(lo_mode)::value, true, kN>(o, st, s, s, qop, q_lds, rd, lds_c + ((n_blocks - 1) & 3) * kTileBlock, nullptr,
-                                                           prm.scale_log2, 0, lim, h, n_blocks <= kExactBlocks, [](auto) {});
+                                                           prm.scale_log2, 0, lim, h, n_blocks <= exact_blocks, [](auto) {});
             };
             // Default mode: the first blocks of a segment with hi + lo weights, the others with hi + lo only where a
             // key dominates.
@@ -1183,7 +1187,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
             constexpr auto kThenMode = std::integral_constant<int, kMode == 0 ? kLoDynamic : kMode == 1 ? kLoAlways : kLoNever>();
             if (busy) {
                 int blk = 0;
-                for (; blk + 1 < n_blocks && blk < kExactBlocks; ++blk) {
+                for (; blk + 1 < n_blocks && blk < exact_blocks; ++blk) {
                     step(blk, s_even, s_odd, kFirstMode);
                     s_even = s_odd;
                 }
