@@ -62,7 +62,7 @@ const char* xattn_last_error(void);
  *                  tokens' K/V are already written).  Read on the device only.  A value < q_len
  *                  leaves the tokens without visible keys with out = 0 and lse = -inf.  The device
  *                  adds the lengths up in 32 bits: the sum over the batch of (kv_lens[b] + 16) must
- *                  stay below 2^31 (for xattn_mla_decode: kv_lens[b] + 256).  The host cannot check
+ *                  stay below 2^31 (for xattn_mla_decode: kv_lens[b] + 192).  The host cannot check
  *                  it and results are undefined beyond, but lengths whose caches fit one GPU's
  *                  memory cannot reach it (2^31 rows of the smallest K/V row pair are 1 TiB).
  * batch    1..4096;  q_len 1..16;  head_dim must be 128;  n_q_heads a multiple of n_kv_heads;

@@ -89,6 +89,18 @@ int xattn_test_decode_work(int total, int n_pieces, int min_piece, int seg_cost,
     return rows;
 }
 
+// How a latent-KV call above 32 query rows is cut: smallest piece, segment cost, few pieces and their smallest, keys per block.
+int xattn_test_mla_cut(int rows_total, int batch, int32_t* out) {
+    const int32_t cut[] = {mla_min_piece(rows_total, batch), kMlaSegCost, kMlaFew.pieces, kMlaFew.min_piece, kMlaKeys};
+    for (int i = 0; i < 5; ++i) out[i] = cut[i];
+    return 0;
+}
+
+// The blocks of a segment that run with hi + lo weights, in that call with `used` of n_pieces pieces in use.
+int xattn_test_mla_exact_blocks(int used, int rows_total, int n_pieces) {
+    return mla_exact_blocks(Plan{0, used, kMlaSegCost, 0}, rows_total, n_pieces);
+}
+
 // meta_out[2 b], meta_out[2 b + 1]: (first partial slot, number of segments) of sequence b.
 int xattn_test_meta(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int32_t* meta_out) {
     const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew, few_pieces, few_min);

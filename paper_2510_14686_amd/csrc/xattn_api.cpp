@@ -441,19 +441,14 @@ int xattn_mla_decode(const void* q, const void* const* c_ptrs, const int32_t* kv
     prm.part_ml = reinterpret_cast<float*>(ws + w.ml_off);
     prm.part_o = reinterpret_cast<uint16_t*>(ws + w.o_off);
     prm.n_pieces = n_pieces;
-    // Above 64 rows a segment's fixed work is worth more tokens, and with few sequences every piece is one more partial
-    // row to merge.  At least 64 / 128 / 192 / 256 positions per piece, us: 30 sequences of 100 to 700 tokens, 72 rows 25.8 /
-    // 25.3 / 27.0 / 29.0; 12 of 60 to 900, 144 rows 27.7 / 25.9 / 27.0 / 29.3; 20 of 300 to 1200, 128 rows 30.3 / 29.6 / 30.8 /
-    // 31.9; 8 of 2000 to 9000 38.8 / 38.8 / 34.9 / 35.9; one of 30000 39.8 / 38.4 / 35.5 / 35.7.
-    const int min_piece = q_len * n_heads <= 64 ? kDefaultMinPieceTokens : batch > 8 ? 128 : 192;
-    prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : min_piece;
+    prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : mla_min_piece(q_len * n_heads, batch);
     if (prm.min_piece_tokens < 16) prm.min_piece_tokens = 16;
     // A block is 32 keys and a segment's fixed work larger here.  Up to 0 / 16 / 32 / 64 / 128 / 256 short pieces,
     // us: 171 tokens, 72 rows 18.8 / 16.9 / 15.0 / 15.0 / 15.0 / 15.0; 113 tokens, 128 rows 20.4 / 16.3 from 16 on; 469
     // tokens, 16 rows 10.9 / 10.9 / 10.8 / 10.7 / 10.7 / 10.7.  Longer streams gain up to 8 % from 128 (2194 tokens,
     // 16 rows 13.4 / 13.4 / 13.4 / 12.7 / 12.3 / 12.3) or lose from 64 (1298 tokens, 128 rows 20.4 / 20.4 / 20.4 /
     // 21.4 / 19.9 / 19.9); 32 changes none of them.
-    prm.few = g_cfg_min_piece > 0 ? FewPieces{0, 1} : FewPieces{32, 32};
+    prm.few = g_cfg_min_piece > 0 ? FewPieces{0, 1} : kMlaFew;
     prm.xcd_skew = g_cfg_xcd_skew > 0 ? g_cfg_xcd_skew - 1 : kDefaultXcdSkewMla;
     prm.layout = g_cfg_mla_layout;
     prm.weight_mode = g_cfg_pv_mode;

@@ -29,7 +29,7 @@
 //   * O^T += C[:, 0:512]^T P^T: bf16 MFMA over the 32 keys, the A operand (value columns x
 //     8 keys per lane) fetched with LDS transposing reads.  A weight enters the product as one bf16
 //     where it is small against the row's sum, and as hi + lo bf16 parts (two MFMAs, 16 significant
-//     bits) where it is not: in the first kExactBlocks blocks of every segment, whose keys' share of
+//     bits) where it is not: in the first mla_exact_blocks() blocks of every segment, whose keys' share of
 //     the final sum is not yet known, and in any later block that holds a key with at least 1/4 of
 //     the row's running sum (of any row of the tile).  The output is normalised by the sum of the weights as they
 //     entered the product.  (Rounding every weight to one bf16 costs nothing on diffuse rows, where the
@@ -51,7 +51,6 @@ namespace {
 constexpr int kDqk = 576;                        // key width: latent + rope
 constexpr int kDv = 512;                         // value width: the latent part
 constexpr int kRowB = kDqk * 2;                  // 1152 bytes per cached token
-constexpr int kMlaKeys = 32;                     // keys per LDS block
 // LDS image of a block: the first 1024 bytes of each row (the latent part, 64 chunks of 16 bytes) at
 // pitch kPitch, the last 128 bytes (the rope part) in a tail area at pitch kTailPitch.  Both pitches are
 // 2 * odd chunks modulo 16: measured, that serves the operand reads below without bank conflicts (an
@@ -74,18 +73,12 @@ constexpr int kVAhead = 2;                       // value fragments in flight ah
 constexpr int kColTiles = kDv / 16;              // 32 tiles of 16 value columns
 constexpr int kStagePitch = (kDv / 2) * 2 + 16;  // epilogue: 16 rows x 256 16-bit columns at a time per wave, padded rows
 constexpr int kStageWave = 16 * kStagePitch;     // 8448 bytes
-// A segment's fixed work (Q, the first block's latency and scores, the rounding and stores of the output) in units of
-// one token's share of the block loop.  Calls with 192 / 224 / 256 / 320, us: 64 sequences of 1024 to 8192 tokens, 128
-// rows 98.9 / 98.0 / 97.1 / -, 256 rows 165.9 / 165.0 / 163.5 / -, 64 rows 74.6 / 73.9 / 73.3 / -; 64 of 64 to 256, 128
-// rows 28.8 / 29.4 / 29.6 / -; 320 was level with 256.
-constexpr int kMlaSegCost = 256;
 constexpr float kLazyLog2 = 8.0f;                // slack of the softmax reference maximum, in powers of two
 // Precision of the softmax weights in the value product (see the header comment).
 constexpr int kLoNever = 0;                      // one bf16 per weight everywhere
 constexpr int kLoAlways = 1;                     // hi + lo bf16 parts everywhere
-constexpr int kLoDynamic = 2;                    // hi + lo parts only in blocks with a dominant key
-constexpr int kExactBlocks = 4;                  // default mode: the first blocks of a segment run as kLoAlways
-constexpr int kExactShortBlocks = 7;             // the same in mla_tile_kernel's pieces of minimal length, see there
+constexpr int kLoDynamic = 2;                    // default mode: hi + lo parts in a segment's first blocks (mla_exact_blocks),
+                                                 // then only in blocks with a dominant key
 constexpr float kDominantShare = 4.0f;           // a key is dominant from 1 / 4 of the row's running sum
 constexpr int kStages = 3;                       // LDS block buffers: two blocks in flight behind the one in use
 
@@ -405,7 +398,7 @@ __device__ __forceinline__ void mla_block(MlaTile (&st)[RT], const char* qk_base
     }
 }
 
-// kMode: 0 = default (hi + lo weights in the first kExactBlocks blocks of a segment and wherever a key
+// kMode: 0 = default (hi + lo weights in the first mla_exact_blocks() blocks of a segment and wherever a key
 // dominates its row), 1 = hi + lo weights everywhere, 2 = one bf16 per weight everywhere.
 template <int NW, int RT, int kMode>
 __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
@@ -447,6 +440,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     const int wave_row0 = row_group * (16 * RT * NW) + wave * (16 * RT);
     char* q_lds = lds_q + wave * (RT * kQLdsWave) + lane * 16;
     char* stage = lds_c + wave * kStageWave;
+    const int exact_blocks = mla_exact_blocks(pl, rows_total, prm.n_pieces);
     const DmaLane dma = dma_lane(lane);
     const int my_loads = (kDmaPerBlock - wave + NW - 1) / NW;      // block loads this wave issues per block
     const int qk_off = n * kPitch + kb * 16;
@@ -525,7 +519,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
         };
         // Default mode: the first blocks of a segment with hi + lo weights, the others with hi + lo
         // only where a key dominates.
-        const int n_exact = kMode == 1 ? n_blocks : kMode == 2 ? 0 : (n_blocks < kExactBlocks ? n_blocks : kExactBlocks);
+        const int n_exact = kMode == 1 ? n_blocks : kMode == 2 ? 0 : (n_blocks < exact_blocks ? n_blocks : exact_blocks);
         int blk = 0;
         for (; blk < n_exact; ++blk) step(blk, std::integral_constant<int, kLoAlways>());
         for (; blk < n_blocks; ++blk)
@@ -1061,9 +1055,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
         const int row = wave_row0 + n;
         char* q_lds = lds_q + wave * kTileQLds + lane * 16;
         char* stage = lds_c + tile * (kTileRows * kTileStagePitch) + part * (kN * 64);
-        // Where the minimal piece length (64 positions up to 64 rows, above 128 or 192) cuts the number of pieces, all
-        // blocks of a piece run with hi + lo weights, as they do in pieces of 64: a longer piece must not round more weights.
-        const int exact_blocks = !kSmall && pl.n_pieces < prm.n_pieces ? kExactShortBlocks : kExactBlocks;
+        const int exact_blocks = mla_exact_blocks(pl, rows_total, prm.n_pieces);
         const TileDma dma = tile_dma(wave, lane);
         TileReads rd = tile_reads(lane);
         rd.value += part * (kN * 64);

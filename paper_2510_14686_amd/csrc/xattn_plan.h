@@ -198,5 +198,31 @@ XATTN_HD bool next_segment(Walk& w, int batch, int seg_cost, LenFn len_of, Piece
     return false;
 }
 
+// ---------------------------------------------------------------- latent-KV calls above 32 query rows
+// How their stream is cut, and which softmax weights go into the value product as hi + lo bf16 parts whatever their size
+// (see xattn_mla.hip): those of a segment's first mla_exact_blocks() blocks.  The two belong together: a longer piece with
+// the same number of such blocks rounds more weights to one bf16.
+constexpr int kMlaKeys = 32;                     // keys per block
+// A segment's fixed work (Q, the first block's latency and scores, the rounding and stores of the output) in units of
+// one token's share of the block loop.  256 would take 2 % off long calls (64 sequences of 1024 to 8192 tokens, 128 rows
+// 103.0 -> 100.7 us, 256 rows 173.8 -> 170.6), but makes every piece of an uncut plan longer: more keys behind the first
+// kExactBlocks, error against 64 bits 1.69e-3 -> 1.72e-3 (30 sequences of 64 to 256 tokens, 384 rows) and 1.73e-3 ->
+// 1.75e-3 (63 of 172 to 688, 48 rows).
+constexpr int kMlaSegCost = 192;
+constexpr int kExactBlocks = 4;
+constexpr int kExactShortBlocks = 7;
+constexpr FewPieces kMlaFew = {32, 32};
+// Fewest positions per piece.  Above 64 rows a segment's fixed work is worth more tokens, and with few sequences every
+// piece is one more partial row to merge.  At least 64 / 128 / 192 / 256 positions per piece, us: 30 sequences of 100 to
+// 700 tokens, 72 rows 25.8 / 25.3 / 27.0 / 29.0; 12 of 60 to 900, 144 rows 27.7 / 25.9 / 27.0 / 29.3; 20 of 300 to 1200,
+// 128 rows 30.3 / 29.6 / 30.8 / 31.9; 8 of 2000 to 9000 38.8 / 38.8 / 34.9 / 35.9; one of 30000 39.8 / 38.4 / 35.5 / 35.7.
+XATTN_HD int mla_min_piece(int rows_total, int batch) { return rows_total <= 64 ? 64 : batch > 8 ? 128 : 192; }
+// Where that minimum cuts the number of pieces below the n_pieces that the call may use, all blocks of a piece run with
+// hi + lo weights, as they do in pieces of 64: with the minima above and kMlaFew such a piece holds at most 7 blocks.
+// (A caller's own minimum, XATTN_CFG_MIN_PIECE_TOKENS, has no such bound.)
+XATTN_HD int mla_exact_blocks(const Plan& pl, int rows_total, int n_pieces) {
+    return rows_total > 64 && pl.n_pieces < n_pieces ? kExactShortBlocks : kExactBlocks;
+}
+
 }  // namespace xattn
 #endif

@@ -31,6 +31,8 @@ def load(path=None):
                        ("xattn_test_piece_of", [vp, i32] + cut + [i32]),
                        ("xattn_test_piece_segments", [vp, i32] + cut + [i32, vp, i32]),
                        ("xattn_test_decode_work", [i32] + cut + [i32, i32, i32, vp]),
+                       ("xattn_test_mla_cut", [i32, i32, vp]),
+                       ("xattn_test_mla_exact_blocks", [i32, i32, i32]),
                        ("xattn_test_meta", [vp, i32] + cut + [vp])):
         fn = getattr(lib, name)
         fn.restype = i32
@@ -116,3 +118,14 @@ def meta(kv_lens, n_pieces, min_piece, seg_cost, skew=0, few=NO_FEW):
     out = np.zeros((len(kv), 2), np.int32)
     assert load().xattn_test_meta(kv.ctypes.data, len(kv), n_pieces, min_piece, seg_cost, skew, *few, out.ctypes.data) == 0
     return out
+
+
+def mla_cut(rows_total, batch):
+    """(smallest piece, segment cost, few pieces and their smallest, keys per block) of a latent-KV call above 32 query rows."""
+    out = np.zeros(5, np.int32)
+    load().xattn_test_mla_cut(rows_total, batch, out.ctypes.data)
+    return int(out[0]), int(out[1]), (int(out[2]), int(out[3])), int(out[4])
+
+
+def mla_exact_blocks(used, rows_total, n_pieces):
+    return load().xattn_test_mla_exact_blocks(used, rows_total, n_pieces)

@@ -239,3 +239,41 @@ def test_every_piece_and_row_has_one_workgroup_part(n_pieces, parts):
                     narrow += got_rows == 16
                     wide += got_rows == 32
     assert n_pieces < 128 or (narrow and wide)          # both ways were taken
+
+
+# ----------------------------------------------------------------------------- latent-KV weights
+def _mla_streams():
+    rng = np.random.RandomState(13)
+    for n, lo, hi in ((78, 85, 342), (63, 172, 688), (128, 51, 410), (64, 1024, 8192), (30, 64, 256), (100, 64, 256), (16, 300, 1200),
+                      (8, 2000, 9000), (5, 16, 8000), (300, 1, 40), (40, 500, 700)):
+        yield "%d of %d to %d" % (n, lo, hi), rng.randint(lo, hi + 1, size=n)
+    for n in (1, 129, 385, 1024, 2000, 5900, 6200, 24576, 30000, 50000):
+        yield "one of %d" % n, [n]
+
+
+MLA_STREAMS = list(_mla_streams())
+
+
+def _segment_blocks(lens, n_pieces, min_piece, cost, few, keys):
+    """Pieces in use, and the keys of every segment."""
+    used = host_lib.plan(lens, n_pieces, min_piece, cost, 0, few)[1]
+    segs = [host_lib.piece_segments(lens, n_pieces, min_piece, cost, p, few=few) for p in range(used)]
+    return used, np.concatenate([s[:, 2] - s[:, 1] for s in segs]).astype(np.int64)
+
+
+@pytest.mark.parametrize("rows", [33, 48, 64, 72, 128, 256, 384])
+@pytest.mark.parametrize("name,lens", MLA_STREAMS, ids=[c[0] for c in MLA_STREAMS])
+def test_mla_partition_keeps_the_share_of_exact_weights(name, lens, rows):
+    """Keys past a segment's first exact blocks may enter the value product as one bf16 weight.  However the stream is
+    cut, they are no more than with pieces of at least 64 positions, a segment cost of 192 and four such blocks, for
+    which the error against the oracle was measured."""
+    groups = (rows + 127) // 128
+    n_pieces = 256 // groups // 8 * 8
+    min_piece, cost, few, keys = host_lib.mla_cut(rows, len(lens))
+    used, tokens = _segment_blocks(lens, n_pieces, min_piece, cost, few, keys)
+    exact = host_lib.mla_exact_blocks(used, rows, n_pieces)
+    _, bar_tokens = _segment_blocks(lens, n_pieces, 64, 192, (32, 32), keys)
+    assert int(tokens.sum()) == int(bar_tokens.sum())
+    assert np.maximum(tokens - exact * keys, 0).sum() <= np.maximum(bar_tokens - 4 * keys, 0).sum()
+    if rows > 64 and used < n_pieces:           # the minimum cut the count: all blocks are exact
+        assert tokens.max() <= exact * keys
