@@ -101,6 +101,26 @@ int xattn_test_mla_exact_blocks(int used, int rows_total, int n_pieces) {
     return mla_exact_blocks(Plan{0, used, kMlaSegCost, 0}, rows_total, n_pieces);
 }
 
+// Waves per tile of mla_tile_kernel in that call, for a plan of `total` positions in `used` pieces.
+int xattn_test_mla_tile_split(int total, int used, int n_pieces, int rows_total) {
+    return mla_tile_split(Plan{total, used, kMlaSegCost, 0}, n_pieces, rows_total);
+}
+
+// How its workgroups share the pieces and tiles out: count_out[piece in use * tiles + tile of 32 rows] = the number of
+// workgroups that compute it.  Returns the waves per tile; -1 where a workgroup works on a piece that is not in use, or
+// on no row.
+int xattn_test_mla_tile_work(int total, int used, int n_pieces, int rows_total, int32_t* count_out) {
+    const Plan pl{total, used, kMlaSegCost, 0};
+    const int split = mla_tile_split(pl, n_pieces, rows_total), tiles = (rows_total + kTileRows - 1) / kTileRows;
+    for (int bid = 0; bid < mla_tile_grid(n_pieces, rows_total); ++bid) {
+        const MlaTileWork w = mla_tile_work(pl, split, rows_total, bid);
+        if (!w.any) continue;
+        if (w.piece < 0 || w.piece >= used || w.row0 < 0 || w.row0 >= rows_total || w.row0 % kTileRows != 0) return -1;
+        for (int t = w.row0 / kTileRows; t < tiles && t < w.row0 / kTileRows + kTileWaves / split; ++t) ++count_out[(size_t)w.piece * tiles + t];
+    }
+    return split;
+}
+
 // meta_out[2 b], meta_out[2 b + 1]: (first partial slot, number of segments) of sequence b.
 int xattn_test_meta(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min, int32_t* meta_out) {
     const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew, few_pieces, few_min);

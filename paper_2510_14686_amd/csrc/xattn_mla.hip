@@ -621,8 +621,6 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
 // What the compiler cannot see of an MFMA inside a statement: a vector instruction may read a result register only
 // once the MFMA has left the pipe (mfma_drain where no later MFMAs stand in between), and an MFMA may read a
 // register two instructions after a vector instruction wrote it (mfma_operands).
-constexpr int kTileRows = 32;
-constexpr int kTileWaves = 4;
 constexpr int kTileSteps = kDqk / 16;            // 36 MFMA steps of 16 columns
 constexpr int kTileQRegs = 33;                   // Q steps in registers, the rest parked in LDS
 constexpr int kTileQLds = (kTileSteps - kTileQRegs) * 1024;      // per wave
@@ -1009,14 +1007,9 @@ __device__ __forceinline__ void tile_block(TileAcc& o, TileRow& st, const f32x16
     }
 }
 
-// kMode: as mla_decode_kernel.  kSmall: up to 64 rows, so that two of the four waves would have no rows.  In short pieces
-// two waves then share a tile: each computes the tile's scores and weights for itself and accumulates half of the columns.
-// A block takes 52 MFMAs of a wave instead of 68 and the output's rounding half as long, but the chip does 1.5 times the
-// MFMAs.  64 rows, tile per wave / per two waves, us: 29 sequences of 131 to 262 tokens 20.5 / 19.3, 32 of 30 to 100 18.5 /
-// 16.7, 4 of 500 to 3000 21.3 / 20.0, 64 of 1024 to 8192 73.8 / 78.8: about 2 us less per segment against 0.15 us more per
-// block, hence the line at 512 positions (segment cost included) per piece.
-constexpr int kTileShortLog2 = 9;
-template <int kMode, bool kSmall>
+// kMode: as mla_decode_kernel.  The form with two waves per tile: see mla_tile_split.  There each of the two computes the
+// tile's scores and weights for itself and accumulates half of the columns.
+template <int kMode>
 __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm) {
     __shared__ __attribute__((aligned(16))) char lds_c[kTileStages * kTileBlock];
     __shared__ __attribute__((aligned(16))) char lds_q[kTileWaves * kTileQLds];      // each lane reads back what it wrote
@@ -1031,15 +1024,10 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
         constexpr int kSplit = decltype(split_c)::value;             // waves per tile
         constexpr int kN = kTileCols / kSplit, kTiles = kTileWaves / kSplit;     // column tiles per wave, row tiles per workgroup
         static_assert(kTiles * kTileRows * kTileStagePitch <= (kSplit == 1 ? 4 : 3) * kTileBlock, "output staging must fit the block buffers");
-        const int per_xcd = (pl.n_pieces + 7) >> 3;
-        // Workgroups as in mla_decode_kernel: the row groups of a piece side by side on one XCD.
         const int bid = blockIdx.x;
-        const int n_groups = (rows_total + kTiles * kTileRows - 1) / (kTiles * kTileRows);
-        const int slot_in_xcd = bid >> 3;
-        const int row_group = slot_in_xcd % n_groups;
-        const int p = (bid & 7) * per_xcd + slot_in_xcd / n_groups;
-        const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
-        const bool active = slot_in_xcd / n_groups < per_xcd && p < pl.n_pieces && s0 < s1;
+        const MlaTileWork mine = mla_tile_work(pl, kSplit, rows_total, bid);
+        const int p = mine.piece, s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
+        const bool active = mine.any && s0 < s1;
         if (tid < 64)
             for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
         if (!active) return;       // the whole workgroup: every wave computed the same plan
@@ -1050,7 +1038,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
         dma_wait_all();
 
         const int tile = wave / kSplit, part = wave - tile * kSplit;
-        const int wave_row0 = (row_group * kTiles + tile) * kTileRows;
+        const int wave_row0 = mine.row0 + tile * kTileRows;
         const bool busy = wave_row0 < rows_total;          // a wave without rows only loads
         const int row = wave_row0 + n;
         char* q_lds = lds_q + wave * kTileQLds + lane * 16;
@@ -1285,10 +1273,8 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
             __syncthreads();          // the next segment's first block goes to buffer 0, which staged output until here
         }
     };
-    if constexpr (kSmall) {
-        if ((pl.total >> kTileShortLog2) < pl.n_pieces) return work(std::integral_constant<int, 2>());
-    }
-    work(std::integral_constant<int, 1>());
+    if (mla_tile_split(pl, prm.n_pieces, rows_total) == 2) work(std::integral_constant<int, 2>());
+    else work(std::integral_constant<int, 1>());
 }
 
 
@@ -1638,11 +1624,11 @@ hipError_t launch_mla_cfg(const MlaParams& prm, dim3 grid, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <bool kSmall>
-hipError_t launch_mla_tile(const MlaParams& prm, dim3 grid, hipStream_t stream) {
-    if (prm.weight_mode == 1) hipLaunchKernelGGL((mla_tile_kernel<1, kSmall>), grid, dim3(64 * kTileWaves), 0, stream, prm);
-    else if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_tile_kernel<2, kSmall>), grid, dim3(64 * kTileWaves), 0, stream, prm);
-    else hipLaunchKernelGGL((mla_tile_kernel<0, kSmall>), grid, dim3(64 * kTileWaves), 0, stream, prm);
+hipError_t launch_mla_tile(const MlaParams& prm, hipStream_t stream) {
+    const dim3 grid((unsigned)mla_tile_grid(prm.n_pieces, prm.q_len * prm.n_heads));
+    if (prm.weight_mode == 1) hipLaunchKernelGGL(mla_tile_kernel<1>, grid, dim3(64 * kTileWaves), 0, stream, prm);
+    else if (prm.weight_mode == 2) hipLaunchKernelGGL(mla_tile_kernel<2>, grid, dim3(64 * kTileWaves), 0, stream, prm);
+    else hipLaunchKernelGGL(mla_tile_kernel<0>, grid, dim3(64 * kTileWaves), 0, stream, prm);
     return hipGetLastError();
 }
 
@@ -1675,8 +1661,7 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     if (events && (e = hipEventRecord(events[0], stream)) != hipSuccess) return e;
     if (prm.layout == 0 && rows_total <= 16) e = launch_mla_rows<1>(prm, grid, stream);
     else if (prm.layout == 0 && rows_total <= 32) e = launch_mla_rows<2>(prm, grid, stream);
-    else if (rt == 2 && rows_total <= 2 * kTileRows) e = launch_mla_tile<true>(prm, grid, stream);
-    else if (rt == 2) e = launch_mla_tile<false>(prm, grid, stream);
+    else if (rt == 2) e = launch_mla_tile(prm, stream);
     else if (nw == 4) e = launch_mla_cfg<4, 1>(prm, grid, stream);
     else if (nw == 2) e = launch_mla_cfg<2, 1>(prm, grid, stream);
     else e = launch_mla_cfg<1, 1>(prm, grid, stream);

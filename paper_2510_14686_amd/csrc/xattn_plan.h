@@ -224,5 +224,41 @@ XATTN_HD int mla_exact_blocks(const Plan& pl, int rows_total, int n_pieces) {
     return rows_total > 64 && pl.n_pieces < n_pieces ? kExactShortBlocks : kExactBlocks;
 }
 
+// mla_tile_kernel's workgroups: four waves, one tile of 32 rows each, or, split, two waves per tile that accumulate half of
+// the columns each.  A split block takes 52 MFMAs of a wave instead of 68 and the output's rounding half as long, but the
+// chip does 1.5 times the MFMAs and twice the block loads: about 2 us less per segment against 0.15 us more per block,
+// hence only where a piece has under 512 positions (segment cost included), and where workgroups would be idle otherwise:
+// the rows of a piece take twice as many.  Four waves with a tile each / split, us: 64 rows, 29 sequences of 131 to 262
+// tokens 20.5 / 19.3, 32 of 30 to 100 18.5 / 16.7, 4 of 500 to 3000 21.3 / 20.0, 64 of 1024 to 8192 73.8 / 78.8; 72 rows, 16 of
+// 20 to 256 21.4 / 18.4; 128 rows, 40 of 64 to 256 28.1 / 24.8, 4 of 500 to 3000 28.9 / 24.5; 256 rows, 16 of 64 to 256 26.1 /
+// 22.9.
+constexpr int kTileRows = 32;
+constexpr int kTileWaves = 4;
+constexpr int kTileShortLog2 = 9;
+XATTN_HD int mla_tile_grid(int n_pieces, int rows_total) {
+    return (n_pieces + 7) / 8 * 8 * ((rows_total + kTileWaves * kTileRows - 1) / (kTileWaves * kTileRows));
+}
+// Waves per tile of 32 rows: the same in the whole launch.
+XATTN_HD int mla_tile_split(const Plan& pl, int n_pieces, int rows_total) {
+    const int groups = (rows_total + kTileWaves / 2 * kTileRows - 1) / (kTileWaves / 2 * kTileRows);
+    return (pl.total >> kTileShortLog2) < pl.n_pieces && mla_tile_grid(n_pieces, rows_total) >> 3 >= ((pl.n_pieces + 7) >> 3) * groups ? 2 : 1;
+}
+struct MlaTileWork {
+    int piece, row0;      // the workgroup's rows: row0 .. row0 + kTileWaves / split * kTileRows - 1, as far as there are so many
+    bool any;             // false: nothing to do
+};
+// Workgroup ids go round-robin over the 8 XCDs.  Of an XCD's workgroups, consecutive ones are the row groups of one piece:
+// they run at the same time on the same XCD and share its L2, so the piece's cache rows come from HBM once.
+XATTN_HD MlaTileWork mla_tile_work(const Plan& pl, int split, int rows_total, int bid) {
+    const int per_xcd = (pl.n_pieces + 7) >> 3, rows = kTileWaves / split * kTileRows;
+    const int groups = (rows_total + rows - 1) / rows, slot = bid >> 3;
+    const int local = groups == 1 ? slot : slot / groups;
+    MlaTileWork w;
+    w.row0 = (slot - local * groups) * rows;
+    w.piece = (bid & 7) * per_xcd + local;
+    w.any = local < per_xcd && w.piece < pl.n_pieces;
+    return w;
+}
+
 }  // namespace xattn
 #endif

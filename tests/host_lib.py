@@ -33,6 +33,8 @@ def load(path=None):
                        ("xattn_test_decode_work", [i32] + cut + [i32, i32, i32, vp]),
                        ("xattn_test_mla_cut", [i32, i32, vp]),
                        ("xattn_test_mla_exact_blocks", [i32, i32, i32]),
+                       ("xattn_test_mla_tile_split", [i32] * 4),
+                       ("xattn_test_mla_tile_work", [i32] * 4 + [vp]),
                        ("xattn_test_meta", [vp, i32] + cut + [vp])):
         fn = getattr(lib, name)
         fn.restype = i32
@@ -129,3 +131,14 @@ def mla_cut(rows_total, batch):
 
 def mla_exact_blocks(used, rows_total, n_pieces):
     return load().xattn_test_mla_exact_blocks(used, rows_total, n_pieces)
+
+
+def mla_tile_split(total, used, n_pieces, rows_total):
+    """Waves per tile of 32 rows in a latent-KV call above 32 query rows."""
+    return load().xattn_test_mla_tile_split(total, used, n_pieces, rows_total)
+
+
+def mla_tile_work(total, used, n_pieces, rows_total):
+    """(waves per tile, int32 [pieces in use, tiles of 32 rows]: how many workgroups compute each)."""
+    out = np.zeros((used, (rows_total + 31) // 32), np.int32)
+    return load().xattn_test_mla_tile_work(total, used, n_pieces, rows_total, out.ctypes.data), out

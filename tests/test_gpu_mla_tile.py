@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+import host_lib
 import oracle
 from workloads import bf16_to_f32
 from test_gpu_mla import DV, SCALE, _case, _default_partition, gpu_mla      # noqa: F401  (the fixture resets the knobs)
@@ -18,21 +19,23 @@ LENS = (1, 31, 32, 33, 64, 65, 97, 127, 128, 129, 160, 161, 193, 700, 2049)
 @pytest.mark.parametrize("pieces,pv_mode,scale_up", [(0, 0, 1.0), (8, 0, 16.0), (37, 2, 1.0), (1024, 1, 4.0)])
 def test_tiles_of_32_rows(T, H, pieces, pv_mode, scale_up):
     import paper_2510_14686_amd as xa
-    from gpu_util import TOL_LSE, TOL_REL_L2, assert_parity, errors
     xa.xattn_configure(xa.XATTN_CFG_PIECES, pieces)
     xa.xattn_configure(xa.XATTN_CFG_PV_MODE, pv_mode)
     if pieces > 256:
         xa.xattn_configure(xa.XATTN_CFG_MIN_PIECE_TOKENS, 16)
+    _check(400 + T, [max(T, n) for n in LENS], T, H, scale_up, "T=%d H=%d pieces=%d" % (T, H, pieces))
+
+
+def _check(seed, lens, T, H, scale_up, what):
+    from gpu_util import TOL_LSE, TOL_REL_L2, assert_parity, errors
     # One-key rows put out single value elements: halved values (exact in bf16) keep every output below 4, from
     # where on bf16 rounding of the result alone exceeds the absolute bar.
-    lens = [max(T, n) for n in LENS]
-    q, cs = _case(400 + T, lens, T, H)
+    q, cs = _case(seed, lens, T, H)
     cs = [(bf16_to_f32(c) * 0.5).astype(np.float32) for c in cs]
     cs = [(c.view(np.uint32) >> 16).astype(np.uint16) for c in cs]
     scale = float(np.float32(2.0 * SCALE * scale_up))
     out_bits, lse = gpu_mla(q, cs, lens, scale)
     ref_out, ref_lse = oracle.mla(q, cs, lens, DV, scale)
-    what = "T=%d H=%d pieces=%d" % (T, H, pieces)
     if scale_up == 1.0:
         assert_parity(out_bits, lse, ref_out, ref_lse, what)
         return
@@ -63,3 +66,27 @@ def test_reference_maximum_that_moves_rescales_every_column():
     out_bits, lse = gpu_mla(q2, ramped, lens, SCALE)
     _, rel_rows, _, lse_err = errors(out_bits, lse, ref_out, ref_lse)
     assert rel_rows <= TOL_REL_L2 and lse_err <= TOL_LSE
+
+
+def _form(lens, rows, pieces, min_piece):
+    """How the kernel runs this partition: waves per tile, blocks of its longest segment, and a segment's exact blocks."""
+    least, cost, few, keys = host_lib.mla_cut(rows, len(lens))
+    cut = (pieces, min_piece, cost, 0, (0, 1)) if min_piece else (pieces, least, cost, 0, few)
+    total, used = host_lib.plan(lens, *cut)
+    longest = max(j1 - j0 for p in range(used) for _, j0, j1, _, _ in host_lib.piece_segments(lens, *cut[:3], p, few=cut[4]))
+    return host_lib.mla_tile_split(total, used, pieces, rows), -(-int(longest) // keys), host_lib.mla_exact_blocks(used, rows, pieces)
+
+
+# rows 65 and 97 (the last tile of one row), 128, 129 and 261 (two and three more row groups than without the split);
+# pieces of 1 to 5 blocks, all exact, and of up to 14, half of which add the lo parts only where a key dominates
+@pytest.mark.parametrize("T,H", [(5, 13), (1, 97), (16, 8), (3, 43), (9, 29)])
+@pytest.mark.parametrize("min_piece,pv_mode,scale_up", [(0, 0, 1.0), (0, 1, 1.0), (0, 2, 1.0), (448, 0, 1.0), (448, 0, 16.0), (448, 1, 16.0), (448, 2, 1.0)])
+def test_two_waves_per_tile_above_64_rows(T, H, min_piece, pv_mode, scale_up):
+    import paper_2510_14686_amd as xa
+    lens = [max(T, n) for n in LENS]
+    split, blocks, exact = _form(lens, T * H, 128, min_piece)
+    assert split == 2 and (blocks > exact + 3 if min_piece else blocks <= exact)
+    xa.xattn_configure(xa.XATTN_CFG_PIECES, 128)
+    xa.xattn_configure(xa.XATTN_CFG_MIN_PIECE_TOKENS, min_piece)
+    xa.xattn_configure(xa.XATTN_CFG_PV_MODE, pv_mode)
+    _check(430 + T, lens, T, H, scale_up, "T=%d H=%d pv_mode=%d min_piece=%d" % (T, H, pv_mode, min_piece))

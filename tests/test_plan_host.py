@@ -277,3 +277,35 @@ def test_mla_partition_keeps_the_share_of_exact_weights(name, lens, rows):
     assert np.maximum(tokens - exact * keys, 0).sum() <= np.maximum(bar_tokens - 4 * keys, 0).sum()
     if rows > 64 and used < n_pieces:           # the minimum cut the count: all blocks are exact
         assert tokens.max() <= exact * keys
+
+
+@pytest.mark.parametrize("n_pieces", [1, 8, 37, 80, 128, 256, 1000])
+def test_every_piece_and_tile_has_one_mla_workgroup(n_pieces):
+    """The map from workgroups to pieces and tiles of 32 query rows, with short and with long pieces, for every number of
+    pieces that a stream may bring into use: each tile of each piece in use is computed once."""
+    seen = set()
+    for used in sorted({1, 2, 7, 8, 9, 16, 17, n_pieces // 4, n_pieces // 2, n_pieces // 2 + 1, n_pieces - 1, n_pieces}):
+        if not 1 <= used <= n_pieces:
+            continue
+        for rows in (33, 64, 65, 72, 96, 97, 128, 129, 192, 193, 261, 384, 4096):
+            for positions in (64, 511, 512, 5000):           # per piece
+                split, count = host_lib.mla_tile_work(positions * used, used, n_pieces, rows)
+                assert np.all(count == 1), (used, rows, positions)
+                seen.add((split, positions < 512))
+                if split == 2:
+                    assert positions < 512 and (used + 7) // 8 * ((rows + 63) // 64) <= (n_pieces + 7) // 8 * ((rows + 127) // 128)
+    assert seen == {(1, True), (1, False), (2, True)}
+
+
+@pytest.mark.parametrize("n,lo,hi,rows,split", [(8, 64, 256, 128, 2), (16, 20, 256, 72, 2), (30, 64, 256, 128, 2), (40, 64, 256, 128, 2),
+                                                (40, 20, 256, 128, 2), (16, 64, 256, 256, 2), (4, 500, 3000, 128, 2), (29, 131, 262, 64, 2),
+                                                (64, 1024, 8192, 128, 1), (64, 1024, 8192, 64, 1), (64, 64, 256, 256, 1)])
+def test_short_mla_streams_halve_the_columns(n, lo, hi, rows, split):
+    """Short sequences that leave workgroups idle: two waves per tile, above 64 query rows as well (with a tile per wave,
+    calls of 16 to 40 sequences of 20 to 256 tokens spent most of their time at the start and end of a segment)."""
+    rng = np.random.RandomState(14)
+    lens = rng.randint(lo, hi + 1, size=n)
+    n_pieces = 256 // ((rows + 127) // 128) // 8 * 8
+    min_piece, cost, few, _ = host_lib.mla_cut(rows, n)
+    total, used = host_lib.plan(lens, n_pieces, min_piece, cost, 0, few)
+    assert host_lib.mla_tile_split(total, used, n_pieces, rows) == split
