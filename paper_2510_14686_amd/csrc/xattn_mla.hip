@@ -619,8 +619,10 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
 // pass through an empty statement of the same kind (pin): a slice cannot start before the pin its inputs came
 // through nor end after its own.
 // What the compiler cannot see of an MFMA inside a statement: a vector instruction may read a result register only
-// once the MFMA has left the pipe (mfma_drain where no later MFMAs stand in between), and an MFMA may read a
-// register two instructions after a vector instruction wrote it (mfma_operands).
+// once the MFMA has left the pipe (12 wait states), and an MFMA may read a register two instructions after a vector
+// instruction wrote it (mfma_operands).  The compiler may copy scores from the end of the statement that made them on,
+// not only where the source reads them, so the statement with a block's last score MFMA ends behind the wait
+// (mfma_last_v) or behind two value MFMAs (mfma_last_acc).
 constexpr int kTileSteps = kDqk / 16;            // 36 MFMA steps of 16 columns
 constexpr int kTileQRegs = 33;                   // Q steps in registers, the rest parked in LDS
 constexpr int kTileQLds = (kTileSteps - kTileQRegs) * 1024;      // per wave
@@ -641,9 +643,9 @@ __device__ __forceinline__ void mfma_first_v(f32x16_t& acc, bf16x8_t a, bf16x8_t
 __device__ __forceinline__ void mfma_v(f32x16_t& acc, bf16x8_t a, bf16x8_t b) {            // acc += a b
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
-// 24 wait states between an MFMA (8 passes) and vector instructions that read its result; the result passes
-// through the statement, so its readers stay behind it.
-__device__ __forceinline__ void mfma_drain(f32x16_t& s) { asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s)); }
+__device__ __forceinline__ void mfma_last_v(f32x16_t& acc, bf16x8_t a, bf16x8_t b) {       // acc += a b, done
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0\n\ts_nop 15\n\ts_nop 7" : "+v"(acc) : "v"(a), "v"(b));
+}
 
 // The output accumulators: column tile ct is a[16 ct : 16 ct + 15] wherever it is used, all 256 accumulation
 // registers together.  Every access is a statement that names those registers: left to choose, the compiler moves
@@ -675,6 +677,13 @@ __device__ __forceinline__ void acc_mfma(TileAcc& o, bf16x8_t a, bf16x8_t b) {  
 #define X(ct) if constexpr (kCt == ct) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+" XATTN_ACC_TILE(ct)(o.t[ct]) : "v"(a), "v"(b));
     XATTN_ACC_EACH(X)
 #undef X
+}
+// s += a b, done; then tile 0 += a0 b0 + a1 b1, whose first MFMA waits for the one of s and takes 8 passes itself.
+__device__ __forceinline__ void mfma_last_acc(f32x16_t& s, bf16x8_t a, bf16x8_t b, TileAcc& o, bf16x8_t a0, bf16x8_t b0, bf16x8_t a1, bf16x8_t b1) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %2, %3, %0\n\t"
+                 "v_mfma_f32_32x32x16_bf16 %1, %4, %5, %1\n\t"
+                 "v_mfma_f32_32x32x16_bf16 %1, %6, %7, %1"
+                 : "+v"(s), "+" XATTN_ACC_TILE(0)(o.t[0]) : "v"(a), "v"(b), "v"(a0), "v"(b0), "v"(a1), "v"(b1));
 }
 // The first kN tiles.
 template <int kN>
@@ -945,7 +954,7 @@ __device__ __forceinline__ void tile_block(TileAcc& o, TileRow& st, const f32x16
             if constexpr (F < kTileQRegs) qv = qop[F];
             else qv = ql[F - kTileQRegs];
             if constexpr (F == 0) mfma_first_v(s_next, ka[F], qv);
-            else mfma_v(s_next, ka[F], qv);
+            else if constexpr (F + 1 < kTileSteps) mfma_v(s_next, ka[F], qv);      // the last one below
             if constexpr (F % kTileLoadEvery == 3 && F / kTileLoadEvery < kTileLoadsA) issue(std::integral_constant<int, F / kTileLoadEvery>());
         }
         weights(f_c);
@@ -958,23 +967,25 @@ __device__ __forceinline__ void tile_block(TileAcc& o, TileRow& st, const f32x16
         ph[k] = __builtin_bit_cast(bf16x8_t, u32x4_t{hi[4 * k], hi[4 * k + 1], hi[4 * k + 2], hi[4 * k + 3]});
         if (kLo == kLoAlways) pl[k] = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[4 * k], lo[4 * k + 1], lo[4 * k + 2], lo[4 * k + 3]});
     }
-    if constexpr (!kLast) {
-        if (__builtin_amdgcn_ballot_w64(j_next + kMlaKeys > lim) != 0) {         // only blocks that reach a limit
-            mfma_drain(s_next);
-            tile_mask(s_next, j_next, lim, h);
-        }
-    }
-    // Phase B.
     mfma_operands(ph[0], ph[1]);
     if (kLo == kLoAlways) mfma_operands(pl[0], pl[1]);
+    if constexpr (!kLast) {
+        constexpr int kEnd = kTileSteps - 1;
+        mfma_last_acc(s_next, ka[kEnd], ql[kEnd - kTileQRegs], o, va[0], ph[0], kLo == kLoAlways ? va[0] : va[1], kLo == kLoAlways ? pl[0] : ph[1]);
+        if (__builtin_amdgcn_ballot_w64(j_next + kMlaKeys > lim) != 0) tile_mask(s_next, j_next, lim, h);   // blocks that reach a limit
+    }
+    // Phase B.
+    constexpr int kDone = kLast ? 0 : kLo == kLoAlways ? 1 : 2;      // fragments whose MFMAs went with the last scores
     float t0, t1;
     static_for<kTileFrags>([&](auto c_c) {
         constexpr int C = decltype(c_c)::value;
         if constexpr (C + kTileVAhead < kTileFrags) va[C + kTileVAhead] = tile_value_frag(cur, rd, C + kTileVAhead);
-        acc_mfma<(C >> 1)>(o, va[C], ph[C & 1]);
-        if constexpr (kLo == kLoAlways) acc_mfma<(C >> 1)>(o, va[C], pl[C & 1]);
+        if constexpr (C >= kDone) {
+            acc_mfma<(C >> 1)>(o, va[C], ph[C & 1]);
+            if constexpr (kLo == kLoAlways) acc_mfma<(C >> 1)>(o, va[C], pl[C & 1]);
+        }
         if constexpr (!kLast) {
-            // The maximum of the next block's scores, whose last MFMA left the pipe behind the second of these.
+            // The maximum of the next block's scores.
             if constexpr (C == 3) pin(s_next);
             if constexpr (C == 4) {
                 t0 = max3(s_next[0], s_next[1], s_next[2]);
@@ -1137,9 +1148,9 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
                     if constexpr (F < kTileQRegs) qv = qop[F];
                     else qv = ql[F - kTileQRegs];
                     if constexpr (F == 0) mfma_first_v(s_even, ka[F], qv);
-                    else mfma_v(s_even, ka[F], qv);
+                    else if constexpr (F + 1 < kTileSteps) mfma_v(s_even, ka[F], qv);
+                    else mfma_last_v(s_even, ka[F], qv);
                 });
-                mfma_drain(s_even);
                 if (__builtin_amdgcn_ballot_w64(j0 + kMlaKeys > lim) != 0) tile_mask(s_even, j0, lim, h);
                 float mx = max3(s_even[0], s_even[1], s_even[2]);
 #pragma unroll
