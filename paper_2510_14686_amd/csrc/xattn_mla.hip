@@ -102,11 +102,10 @@ __device__ __forceinline__ void static_for(F&& f) { static_for(f, std::make_inte
 // cannot tell the two halves of the double buffer apart and would wait for every outstanding load
 // before each read.  dma_wait() before the workgroup barrier is what makes a block visible.
 __device__ __forceinline__ void dma16(u32x4_t rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
-    // m0 carries the LDS address of the load.  It is not saved: the compiler uses it for indexed register moves,
-    // messages and LDS loads of its own, of which these kernels have none (and it takes no m0 in a clobber list).
-    // Saving and restoring it costs as much as the load: a wave issues an instruction every four cycles or so.
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                 : : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    // m0 carries the LDS address of the load.  As an operand of the statement it is written by the compiler, which
+    // so knows of it (and often makes the address in it).  The load needs a wait state behind that write.
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 : : "{m0}"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 // Waits until at most n of this wave's loads are outstanding (they complete in order): n = the number
 // of loads of the newest block leaves the block before it complete.

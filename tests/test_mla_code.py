@@ -1,8 +1,8 @@
 """The latent-KV kernels as compiled: what their assembly statements rely on and the compiler does not check.
 
 The MFMAs of mla_tile_kernel are assembly statements, so no wait states are inserted between an MFMA and the instructions
-that touch its registers.  They are checked here in the device code of the built library (its own disassembly), over every
-path through a kernel."""
+that touch its registers, and its loads into LDS take their LDS address from m0.  Both are read here from the device code of
+the built library (its own disassembly), over every path through a kernel."""
 import glob
 import os
 import re
@@ -178,3 +178,33 @@ def test_the_hazard_check_sees_hazards():
     assert [ins[1] for ins in _hazards(around)] == ["v_mov_b32_e32"]
     loop = code(("v_add_f32_e32", "v30, v31, v3", None), mfma, ("s_cbranch_scc1", "0", 0), end)
     assert [ins[1] for ins in _hazards(loop)] == ["v_add_f32_e32"]
+
+
+def test_loads_into_lds_take_their_address_from_an_m0_the_compiler_knows_of(kernels):
+    """m0 is an operand of the load's statement: a statement that wrote m0 behind the compiler's back would break any use
+    that the compiler makes of it.  In the code every such load has its own write of m0 ahead, a wait state between."""
+    for path in glob.glob(os.path.join(xbuild.CSRC, "*.hip")) + glob.glob(os.path.join(xbuild.CSRC, "*.h")):
+        with open(path) as f:
+            assert not re.search(r'"[^"\n]*\bm0\s*,', f.read()), path
+    loads = 0
+    for name, code in kernels.items():
+        write = None
+        starts = {s for s, _ in _blocks(code)[0]}
+        for i, (_, op, operands, _) in enumerate(code):
+            if i in starts:
+                write = None
+            if re.match(r"m0\b", operands):
+                write = i
+            elif operands.endswith(" lds"):
+                loads += 1
+                assert write is not None and i - write >= 2, (name, i)
+                write = None
+    assert loads > 500
+
+
+def test_loads_into_lds_wait_for_their_scalar_operands(kernels):
+    """Their statements read scalar registers (descriptor, offset), which the compiler may have just written from a lane."""
+    names = [name for name, code in kernels.items() if any(ins[2].endswith(" lds") for ins in code)]
+    assert len(names) >= 16
+    for name in names:
+        assert [ins for ins in _hazards(kernels[name]) if ins[2].endswith(" lds")] == [], name
