@@ -53,8 +53,8 @@ def _default_partition():
 
 @pytest.mark.parametrize("T,H", [(1, 128), (2, 128), (1, 16), (1, 32), (3, 64), (1, 8), (2, 24), (1, 144)])
 def test_mla_shapes(T, H):
-    """Head counts from 8 to 144 (1 to 8 waves per workgroup, partial 16-row tiles, more than 128 rows:
-    two row groups) and 1 to 3 query tokens, ragged lengths around the 16-key block."""
+    """Head counts from 8 to 144 (four waves per 16-row tile, one or two waves per 32-row tile, partial tiles, more than
+    128 rows: several row groups) and 1 to 3 query tokens, ragged lengths around multiples of 16 keys."""
     from gpu_util import assert_parity
     lens = [T, T + 1, 15 + T, 16 + T, 17 + T, 64, 65, 200, 333, 1500]
     q, cs = _case(200 + T, lens, T, H)
@@ -92,8 +92,8 @@ def test_mla_xtensor_equals_plain_and_rows_past_kv_len_are_not_read():
 
 @pytest.mark.parametrize("pv_mode,layout", [(1, 0), (0, 1), (1, 1), (0, 2)])
 def test_mla_weight_precision_modes_and_workgroup_shapes(pv_mode, layout):
-    """hi + lo weights (PV mode 1) and the other workgroup shapes against the oracle; 144 heads: two row
-    groups, the second one partial."""
+    """hi + lo weights (PV mode 1) and the kernel of 16-row tiles (layout 1; layout 2 above 64 rows is the default one)
+    against the oracle; 144 heads: several row groups, the last one partial."""
     import paper_2510_14686_amd as xa
     from gpu_util import assert_parity
     lens = [1, 3, 31, 32, 33, 100, 777, 2100]
@@ -105,12 +105,13 @@ def test_mla_weight_precision_modes_and_workgroup_shapes(pv_mode, layout):
     assert_parity(out_bits, lse, ref_out, ref_lse, "mla pv_mode=%d layout=%d" % (pv_mode, layout))
 
 
+@pytest.mark.parametrize("layout", [1, 2])
 @pytest.mark.parametrize("T,H,pv_mode,pieces", [(1, 128, 0, 0), (2, 128, 0, 0), (3, 80, 0, 37), (2, 72, 1, 0), (1, 128, 2, 8),
                                                (4, 40, 0, 1024)])
-def test_mla_two_tiles_per_wave(T, H, pv_mode, pieces):
-    """The workgroup shape of four waves with two 16-row tiles each (from 65 query rows per sequence
-    on): whole and partial row groups, causal limits inside and across 32-key blocks (the masked and
-    the unmasked form of its block), every weight mode, ragged lengths, several partitions."""
+def test_mla_chosen_layouts(T, H, pv_mode, pieces, layout):
+    """The kernel of 16-row tiles (layout 1) and the one of 32-row tiles (layout 2, from 65 query rows per sequence on):
+    whole and partial row groups, causal limits inside and across 32-key blocks, every weight mode, ragged lengths,
+    several partitions."""
     import paper_2510_14686_amd as xa
     from gpu_util import assert_parity
     lens = [T, T + 1, 31 + T, 32 + T, 33 + T, 64, 129, 200, 640, 1500, 2100]
@@ -120,13 +121,13 @@ def test_mla_two_tiles_per_wave(T, H, pv_mode, pieces):
     # 4, from where on rounding the reference itself to bf16 is off by more than the bar (checked here).
     ref = np.asarray(ref_out, dtype=np.float64)
     assert np.abs(bf16_to_f32(f32_to_bf16(ref.astype(np.float32))) - ref).max() < 8e-3
-    xa.xattn_configure(xa.XATTN_CFG_MLA_LAYOUT, 2)
+    xa.xattn_configure(xa.XATTN_CFG_MLA_LAYOUT, layout)
     xa.xattn_configure(xa.XATTN_CFG_PV_MODE, pv_mode)
     xa.xattn_configure(xa.XATTN_CFG_PIECES, pieces)
     if pieces:
         xa.xattn_configure(xa.XATTN_CFG_MIN_PIECE_TOKENS, 16)
     out_bits, lse = gpu_mla(q, cs, lens, SCALE)
-    assert_parity(out_bits, lse, ref_out, ref_lse, "mla two tiles T=%d H=%d pv_mode=%d pieces=%d" % (T, H, pv_mode, pieces))
+    assert_parity(out_bits, lse, ref_out, ref_lse, "mla layout=%d T=%d H=%d pv_mode=%d pieces=%d" % (layout, T, H, pv_mode, pieces))
 
 
 @pytest.mark.parametrize("scale_up", [4.0, 16.0])

@@ -183,7 +183,8 @@ SHORT = list(_short_streams())
 
 
 @pytest.mark.parametrize("cost,few,n_pieces,min_piece", [(GQA_COST, FEW_GQA, 256, 64), (GQA_COST, FEW_GQA, 1024, 64), (GQA_COST, FEW_GQA, 128, 64),
-                                                         (GQA_COST, (37, 16), 256, 64), (MLA_COST, FEW_MLA, 256, 64), (96, FEW_MLA, 128, 64)])
+                                                         (GQA_COST, (37, 16), 256, 64), (MLA_COST, FEW_MLA, 256, 64), (96, FEW_MLA, 128, 64),
+                                                         (MLA_COST, FEW_MLA, 256, 128), (MLA_COST, FEW_MLA, 128, 192)])
 @pytest.mark.parametrize("name,lens", SHORT, ids=[c[0] for c in SHORT])
 def test_short_streams_are_cut_finer(name, lens, cost, few, n_pieces, min_piece):
     lens = np.asarray(lens, np.int64)
