@@ -529,7 +529,7 @@ def main():
     ap.add_argument("--min-piece-tokens", type=int, default=0, help="override the minimum piece size (0 = default)")
     ap.add_argument("--path", type=int, default=0, help="inner loop: 0 automatic, 1 vector, 2 matrix cores")
     ap.add_argument("--beam", action="store_true", help="host-only: time the beam-search selection step (heap with early exit vs sorting everything)")
-    ap.add_argument("--mla-layout", type=int, default=0, help="latent-KV kernel: 0 automatic, 1 one 16-row tile per wave, 2 two tiles per wave")
+    ap.add_argument("--mla-layout", type=int, default=0, help="latent-KV kernel: 0 automatic, 1 one 16-row tile per wave, 2 as 1 up to 64 rows, then 32-row tiles")
     ap.add_argument("--pv-mode", type=int, default=0, help="precision of the softmax weights in the value product, see XATTN_CFG_PV_MODE")
     ap.add_argument("--xcd-skew", type=int, default=0, help="XATTN_CFG_XCD_SKEW: 0 default, n = (n - 1) per mille moved from the odd XCDs' parts to the even ones'")
     ap.add_argument("--calibrate-copy", action="store_true",

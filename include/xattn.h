@@ -185,12 +185,13 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *                               with XATTN_CFG_PATH = 2
  *                               (xattn_mla_decode: 0 = default, hi + lo bf16 parts throughout with up to 32
  *                               query rows per sequence, else for the first 128 keys
- *                               of every segment and wherever a key carries 1/4 or more of its row's
- *                               running sum, one bf16 elsewhere; 1 = hi + lo parts everywhere;
+ *                               of every segment (224 above 64 rows where the lower bound on a piece
+ *                               cuts the number of pieces) and wherever a key carries 1/4 or more of its
+ *                               row's running sum, one bf16 elsewhere; 1 = hi + lo parts everywhere;
  *                               2 = one bf16 per weight everywhere, less exact on peaked rows)
  *   XATTN_CFG_MLA_LAYOUT        xattn_mla_decode workgroup shape: 0 = automatic (up to 32 query rows per
- *                               sequence four waves share a 16-row tile; then one 32-row tile per wave,
- *                               4 waves), 1 = one 16-row tile per wave, up to 4 waves, for any number of
+ *                               sequence four waves share a 16-row tile; then 32-row tiles, 4 waves,
+ *                               one or, in short pieces, two per tile), 1 = one 16-row tile per wave, up to 4 waves, for any number of
  *                               rows, 2 = as 1 up to 64 rows, then 32-row tiles; for experiments,
  *                               results agree within their rounding
  *   XATTN_CFG_XCD_SKEW          the chip's eight XCDs do not stream at the same rate (the odd-numbered ones

@@ -86,7 +86,7 @@ struct MlaParams {
     int n_pieces, min_piece_tokens;
     FewPieces few;
     int xcd_skew;                    // as in DecodeParams
-    int layout;                      // 0 automatic, 1 one 16-row tile per wave, 2 one 32-row tile per wave from 65 rows on
+    int layout;                      // 0 automatic, 1 one 16-row tile per wave, 2 32-row tiles from 65 rows on
     int weight_mode;                 // softmax weights in the value product: 0 default (hi + lo bf16 parts where a key
                                      // dominates, one bf16 elsewhere), 1 hi + lo everywhere, 2 one bf16 everywhere
 };

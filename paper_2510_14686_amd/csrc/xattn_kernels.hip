@@ -715,8 +715,8 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
 // per row took 21.4 us for one sequence of 30001 tokens (32 rows of 256 slots); sixteen waves that each sum a share of
 // the slots and meet once in LDS take 5.2 us.  For the same reason a lane fetches one slot's record and takes its
 // weight while the first 8 partial rows are on their way, weights pass by lane reads, and the row's sequence comes
-// from a 32-bit division (the whole call, with a shuffle per weight and a 64-bit division before: 695 tokens of 2 KV
-// heads 8.8 -> 8.5 us; 138468 tokens 32.3 -> 31.8).
+// from a 32-bit division (the whole call, with a shuffle per weight and a 64-bit division before: 138468 tokens of 2 KV
+// heads 32.3 -> 31.8 us; 695 tokens level, 8.9).
 template <int kWaves>
 __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(DecodeParams prm) {
     const int lane = threadIdx.x & 63;

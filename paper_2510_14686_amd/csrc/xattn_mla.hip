@@ -11,7 +11,7 @@
 // up to 128 query rows (row = token * n_heads + head), and walks the piece in 32-key blocks that all its waves share
 // through LDS.  Three kernels by the number of rows per sequence:
 //   * up to 32: mla_rows_kernel, four waves per tile of 16 rows;
-//   * more: mla_tile_kernel, one wave per tile of 32 rows;
+//   * more: mla_tile_kernel, one wave per tile of 32 rows, in short pieces two;
 //   * mla_decode_kernel, one wave per tile of 16 rows, four tiles at most (XATTN_CFG_MLA_LAYOUT = 1): a second computation
 //     of the same function that shares neither the layouts nor the MFMA shape of the others, for cross-checks.
 // Common to them (the figures are mla_decode_kernel's):
@@ -209,40 +209,38 @@ __device__ __forceinline__ uint32_t pack_f16(float a, float b) {
 // Scheduling groups (the group sizes must be compile-time constants, hence the templates).
 template <int N> __device__ __forceinline__ void sched_ds() { __builtin_amdgcn_sched_group_barrier(0x100, N, 0); }
 template <int N> __device__ __forceinline__ void sched_mfma() { __builtin_amdgcn_sched_group_barrier(0x008, N, 0); }
-constexpr int qk_reads_of(int step, int rt) { return 2 + (step >= kQRegSteps ? rt : 0); }
-constexpr int qk_reads_before(int steps, int rt) {
+constexpr int qk_reads_of(int step) { return 2 + (step >= kQRegSteps ? 1 : 0); }
+constexpr int qk_reads_before(int steps) {
     int n = 0;
-    for (int i = 0; i < steps; ++i) n += qk_reads_of(i, rt);
+    for (int i = 0; i < steps; ++i) n += qk_reads_of(i);
     return n;
 }
-template <int STEP, int RT>
+template <int STEP>
 struct QkSched {
     static __device__ __forceinline__ void run() {
-        sched_mfma<2 * RT>();
-        if constexpr (STEP + kQAhead < kQSteps) sched_ds<qk_reads_of(STEP + kQAhead, RT)>();
-        if constexpr (STEP + 1 < kQSteps) QkSched<STEP + 1, RT>::run();
+        sched_mfma<2>();
+        if constexpr (STEP + kQAhead < kQSteps) sched_ds<qk_reads_of(STEP + kQAhead)>();
+        if constexpr (STEP + 1 < kQSteps) QkSched<STEP + 1>::run();
     }
 };
 
-// One 32-key block from LDS against this wave's RT tiles of 16 rows.  Every operand read from LDS is
-// used for all RT tiles.  kLo: how the softmax weights go into the value product (kLoNever, kLoAlways,
-// kLoDynamic).
+// One 32-key block from LDS against this wave's tile of 16 rows.  kLo: how the softmax weights go into the value
+// product (kLoNever, kLoAlways, kLoDynamic).
 //   qk_base = block + n * kPitch + kb * 16                     (key row n of a tile, chunk kb)
 //   qt_base = block + kTailOff + n * kTailPitch + kb * 16      (the same for the rope part)
 //   pv_base = block + (4 kb + n / 4) * kPitch + (n % 4) * 8    (transposing read, see below)
-template <int RT, int kLo>
-__device__ __forceinline__ void mla_block(MlaTile (&st)[RT], const char* qk_base, const char* qt_base, const char* pv_base,
-                                          const bf16x8_t (&qop)[RT][kQRegSteps], const char* q_lds, float scale_log2,
-                                          int j_block, const int (&lim)[RT], int kb) {
+template <int kLo>
+__device__ __forceinline__ void mla_block(MlaTile& st, const char* qk_base, const char* qt_base, const char* pv_base,
+                                          const bf16x8_t (&qop)[kQRegSteps], const char* q_lds, float scale_log2,
+                                          int j_block, int lim, int kb) {
     // S^T tile kt: A = keys 16 kt .. 16 kt + 15 of the block (lane (kb, n): key n, columns 32 step +
     // 8 kb .. + 7), B = Q; the result at lane (kb, n) is key 16 kt + 4 kb + i against row n.
-    f32x4_t s[RT][2];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) s[rt][0] = s[rt][1] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4_t s[2];
+    s[0] = s[1] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     // The key fragments (and, from step kQRegSteps on, the lane's Q chunks, which it parked in LDS at
-    // q_lds + tile * kQLdsWave + (step - kQRegSteps) * 1024) are fetched kQAhead steps before the MFMAs
+    // q_lds + (step - kQRegSteps) * 1024) are fetched kQAhead steps before the MFMAs
     // that use them.
-    bf16x8_t ka[kQSteps][2], ql[RT][kQSteps - kQRegSteps];
+    bf16x8_t ka[kQSteps][2], ql[kQSteps - kQRegSteps];
     auto load_step = [&](int step) {
         if (step < kMainSteps) {
             ka[step][0] = *reinterpret_cast<const bf16x8_t*>(qk_base + step * 64);
@@ -251,27 +249,20 @@ __device__ __forceinline__ void mla_block(MlaTile (&st)[RT], const char* qk_base
             ka[step][0] = *reinterpret_cast<const bf16x8_t*>(qt_base + (step - kMainSteps) * 64);
             ka[step][1] = *reinterpret_cast<const bf16x8_t*>(qt_base + kTailTileB + (step - kMainSteps) * 64);
         }
-        if (step >= kQRegSteps) {
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-                ql[rt][step - kQRegSteps] = *reinterpret_cast<const bf16x8_t*>(q_lds + rt * kQLdsWave + (step - kQRegSteps) * 1024);
-        }
+        if (step >= kQRegSteps) ql[step - kQRegSteps] = *reinterpret_cast<const bf16x8_t*>(q_lds + (step - kQRegSteps) * 1024);
     };
 #pragma unroll
     for (int step = 0; step < kQAhead; ++step) load_step(step);
 #pragma unroll
     for (int step = 0; step < kQSteps; ++step) {
         if (step + kQAhead < kQSteps) load_step(step + kQAhead);
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const bf16x8_t qv = step < kQRegSteps ? qop[rt][step < kQRegSteps ? step : 0] : ql[rt][step < kQRegSteps ? 0 : step - kQRegSteps];
-            s[rt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[step][0], qv, s[rt][0], 0, 0, 0);
-            s[rt][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[step][1], qv, s[rt][1], 0, 0, 0);
-        }
+        const bf16x8_t qv = step < kQRegSteps ? qop[step < kQRegSteps ? step : 0] : ql[step < kQRegSteps ? 0 : step - kQRegSteps];
+        s[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[step][0], qv, s[0], 0, 0, 0);
+        s[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[step][1], qv, s[1], 0, 0, 0);
     }
     // Pin that order for the instruction scheduler: the first reads, then MFMAs and reads in turn.
-    sched_ds<qk_reads_before(kQAhead, RT)>();
-    QkSched<0, RT>::run();
+    sched_ds<qk_reads_before(kQAhead)>();
+    QkSched<0>::run();
     // O^T tile ct: A = value columns 16 ct .. + 15 (lane (kb, n): column n, keys as in the softmax
     // below), B = P^T.  A transposing read hands lane n of a 16-lane group, from the 64 values that
     // the group's lanes point at taken in lane order, the values n, n + 16, n + 32, n + 48: lanes 4 j ..
@@ -290,77 +281,72 @@ __device__ __forceinline__ void mla_block(MlaTile (&st)[RT], const char* qk_base
     for (int ct = 0; ct < 2 * kVAhead; ++ct) va[ct] = load_v(ct);
     // Softmax.  The lane's 8 weights of a row, ordered (kt, i), are the B operand of the value product
     // when contraction index 8 kb + 4 kt + i stands for key 16 kt + 4 kb + i.
-    bf16x8_t ph[RT], pl[RT];
-    bool with_lo[RT];                // the tile's weights go in as hi + lo parts in this block
+    // Keys at or past lim (the end of the segment, or the causal limit of the row) count as
+    // -inf; only the blocks that reach that far pay for the comparison.  scale_log2 > 0, so the
+    // maximum is taken before scaling, and one fused multiply-add scales and shifts.
+    float p[8];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        // Keys at or past lim[rt] (the end of the segment, or the causal limit of the row) count as
-        // -inf; only the blocks that reach that far pay for the comparison.  scale_log2 > 0, so the
-        // maximum is taken before scaling, and one fused multiply-add scales and shifts.
-        float p[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) p[t] = s[rt][t >> 2][t & 3];
-        if (__builtin_amdgcn_ballot_w64(j_block + kMlaKeys > lim[rt]) != 0) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int key = j_block + 16 * (t >> 2) + 4 * kb + (t & 3);
-                p[t] = key < lim[rt] ? p[t] : kNegInf;
-            }
-        }
-        float mx = fmaxf(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])), fmaxf(fmaxf(p[4], p[5]), fmaxf(p[6], p[7])));
-        mx = kb_max(mx) * scale_log2;
-        // The reference maximum follows the row's maximum lazily: it moves only when a block exceeds
-        // it by more than kLazyLog2, so weights reach 2^kLazyLog2 at most (harmless in fp32 sums and in
-        // bf16's relative precision) and the rescaling of the 128 accumulators below, which would
-        // otherwise run in most blocks (some row of the tile sees a new maximum), runs about once.
-        const float m_new = mx > st[rt].m + kLazyLog2 ? mx : st[rt].m;
-        const float m_use = (m_new == kNegInf) ? 0.0f : m_new;
-        const float alpha = fast_exp2(st[rt].m - m_use);
-        float sum = 0.0f;
+    for (int t = 0; t < 8; ++t) p[t] = s[t >> 2][t & 3];
+    if (__builtin_amdgcn_ballot_w64(j_block + kMlaKeys > lim) != 0) {
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            p[t] = fast_exp2(__builtin_fmaf(p[t], scale_log2, -m_use));
-            sum += p[t];
+            const int key = j_block + 16 * (t >> 2) + 4 * kb + (t & 3);
+            p[t] = key < lim ? p[t] : kNegInf;
         }
-        st[rt].l = st[rt].l * alpha + kb_sum(sum);
-        st[rt].m = m_new;
-        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+    }
+    float mx = fmaxf(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])), fmaxf(fmaxf(p[4], p[5]), fmaxf(p[6], p[7])));
+    mx = kb_max(mx) * scale_log2;
+    // The reference maximum follows the row's maximum lazily: it moves only when a block exceeds
+    // it by more than kLazyLog2, so weights reach 2^kLazyLog2 at most (harmless in fp32 sums and in
+    // bf16's relative precision) and the rescaling of the 128 accumulators below, which would
+    // otherwise run in most blocks (some row of the tile sees a new maximum), runs about once.
+    const float m_new = mx > st.m + kLazyLog2 ? mx : st.m;
+    const float m_use = (m_new == kNegInf) ? 0.0f : m_new;
+    const float alpha = fast_exp2(st.m - m_use);
+    float sum = 0.0f;
 #pragma unroll
-            for (int ct = 0; ct < kColTiles; ++ct) st[rt].o[ct] *= alpha;
-        }
-        // Dominant key: the block's largest weight of a row against the row's sum so far (this block
-        // included), which is at most the sum the output is divided by in the end.  The tile adds the
-        // lo parts if any of its rows has one.
-        with_lo[rt] = kLo == kLoAlways ||
-                      (kLo == kLoDynamic && __builtin_amdgcn_ballot_w64(fast_exp2(mx - m_use) * kDominantShare >= st[rt].l) != 0);
-        // Where a weight goes in as one bf16 the output is normalised by the sum of the ROUNDED weights:
-        // a softmax over slightly perturbed scores (relative weight error 2^-9, the same for equal
-        // weights, none for a lone key) instead of rounded weights over an exact sum.
-        uint32_t h[4], lo[4] = {0u, 0u, 0u, 0u};
-        float sum_q = 0.0f;
+    for (int t = 0; t < 8; ++t) {
+        p[t] = fast_exp2(__builtin_fmaf(p[t], scale_log2, -m_use));
+        sum += p[t];
+    }
+    st.l = st.l * alpha + kb_sum(sum);
+    st.m = m_new;
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+        for (int ct = 0; ct < kColTiles; ++ct) st.o[ct] *= alpha;
+    }
+    // Dominant key: the block's largest weight of a row against the row's sum so far (this block
+    // included), which is at most the sum the output is divided by in the end.  The tile adds the
+    // lo parts if any of its rows has one.
+    const bool with_lo = kLo == kLoAlways ||
+                         (kLo == kLoDynamic && __builtin_amdgcn_ballot_w64(fast_exp2(mx - m_use) * kDominantShare >= st.l) != 0);
+    // Where a weight goes in as one bf16 the output is normalised by the sum of the ROUNDED weights:
+    // a softmax over slightly perturbed scores (relative weight error 2^-9, the same for equal
+    // weights, none for a lone key) instead of rounded weights over an exact sum.
+    uint32_t h[4], lo[4] = {0u, 0u, 0u, 0u};
+    float sum_q = 0.0f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const f32x2_t pp = {p[2 * u], p[2 * u + 1]};
+        const bf16x2_t hh = __builtin_convertvector(pp, bf16x2_t);
+        const f32x2_t back = __builtin_convertvector(hh, f32x2_t);
+        h[u] = __builtin_bit_cast(uint32_t, hh);
+        sum_q += back[0] + back[1];
+        p[2 * u] -= back[0];
+        p[2 * u + 1] -= back[1];
+    }
+    if (with_lo) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const f32x2_t pp = {p[2 * u], p[2 * u + 1]};
-            const bf16x2_t hh = __builtin_convertvector(pp, bf16x2_t);
-            const f32x2_t back = __builtin_convertvector(hh, f32x2_t);
-            h[u] = __builtin_bit_cast(uint32_t, hh);
-            sum_q += back[0] + back[1];
-            p[2 * u] -= back[0];
-            p[2 * u + 1] -= back[1];
+            const f32x2_t rest = {p[2 * u], p[2 * u + 1]};
+            lo[u] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2_t));
         }
-        if (with_lo[rt]) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const f32x2_t rest = {p[2 * u], p[2 * u + 1]};
-                lo[u] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2_t));
-            }
-        }
-        st[rt].lq = st[rt].lq * alpha + (with_lo[rt] ? sum : sum_q);
-        ph[rt] = __builtin_bit_cast(bf16x8_t, u32x4_t{h[0], h[1], h[2], h[3]});
-        pl[rt] = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[0], lo[1], lo[2], lo[3]});
     }
-    // Value product, fragments kVAhead tile pairs ahead; per pair the hi parts of both tiles (and row
-    // tiles) first, then the lo parts, so that no MFMA waits for the one just before it.
+    st.lq = st.lq * alpha + (with_lo ? sum : sum_q);
+    const bf16x8_t ph = __builtin_bit_cast(bf16x8_t, u32x4_t{h[0], h[1], h[2], h[3]});
+    const bf16x8_t pl = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[0], lo[1], lo[2], lo[3]});
+    // Value product, fragments kVAhead tile pairs ahead; per pair the hi parts of both tiles
+    // first, then the lo parts, so that no MFMA waits for the one just before it.
 #pragma unroll
     for (int c2 = 0; c2 < kColTiles; c2 += 2) {
         if (c2 + 2 * kVAhead < kColTiles) {
@@ -368,42 +354,32 @@ __device__ __forceinline__ void mla_block(MlaTile (&st)[RT], const char* qk_base
             va[c2 + 2 * kVAhead + 1] = load_v(c2 + 2 * kVAhead + 1);
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-                st[rt].o[c2 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c2 + u], ph[rt], st[rt].o[c2 + u], 0, 0, 0);
+        for (int u = 0; u < 2; ++u) st.o[c2 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c2 + u], ph, st.o[c2 + u], 0, 0, 0);
         if (kLo == kLoAlways) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-                    st[rt].o[c2 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c2 + u], pl[rt], st[rt].o[c2 + u], 0, 0, 0);
+            for (int u = 0; u < 2; ++u) st.o[c2 + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[c2 + u], pl, st.o[c2 + u], 0, 0, 0);
         }
     }
 #pragma unroll
     for (int c2 = 0; c2 < kColTiles; c2 += 2) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 2 * RT * (kLo == kLoAlways ? 2 : 1), 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 2 * (kLo == kLoAlways ? 2 : 1), 0);
         if (c2 + 2 * kVAhead < kColTiles) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
     }
-    if (kLo == kLoDynamic) {
+    if (kLo == kLoDynamic && with_lo) {
         // The rare block with a dominant key: a second pass over the value fragments with the lo parts.
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            if (!with_lo[rt]) continue;
-#pragma unroll
-            for (int ct = 0; ct < kColTiles; ++ct)      // fully unrolled: the accumulators are registers
-                st[rt].o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(load_v(ct), pl[rt], st[rt].o[ct], 0, 0, 0);
-        }
+        for (int ct = 0; ct < kColTiles; ++ct)          // fully unrolled: the accumulators are registers
+            st.o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(load_v(ct), pl, st.o[ct], 0, 0, 0);
     }
 }
 
 // kMode: 0 = default (hi + lo weights in the first mla_exact_blocks() blocks of a segment and wherever a key
 // dominates its row), 1 = hi + lo weights everywhere, 2 = one bf16 per weight everywhere.
-template <int NW, int RT, int kMode>
+template <int NW, int kMode>
 __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     __shared__ __attribute__((aligned(16))) char lds_c[kStages * kLdsBlock];
-    // Per wave and tile: the Q chunks of steps kQRegSteps.. (each lane reads back what it wrote).
-    __shared__ __attribute__((aligned(16))) char lds_q[NW * RT * kQLdsWave];
+    // Per wave: the Q chunks of steps kQRegSteps.. (each lane reads back what it wrote).
+    __shared__ __attribute__((aligned(16))) char lds_q[NW * kQLdsWave];
     static_assert(NW * kStageWave <= kStages * kLdsBlock, "output staging must fit the block buffers");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = lane >> 4, n = lane & 15;
@@ -417,7 +393,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     // row groups of one piece: they run at the same time on the same XCD and share its L2, so the
     // piece's cache rows come from HBM once.
     const int bid = blockIdx.x;
-    const int n_groups = (rows_total + 16 * RT * NW - 1) / (16 * RT * NW);
+    const int n_groups = (rows_total + 16 * NW - 1) / (16 * NW);
     const int slot_in_xcd = bid >> 3;
     const int row_group = slot_in_xcd % n_groups;
     const int p = (bid & 7) * per_xcd + slot_in_xcd / n_groups;
@@ -435,9 +411,9 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     wave_locate(wp, prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, s0, lane, &win, walk.b, walk.j);
     walk.remaining = uniform(s1 - s0);
 
-    // Row n of tile rt of this wave: row index within the sequence's T * H rows.
-    const int wave_row0 = row_group * (16 * RT * NW) + wave * (16 * RT);
-    char* q_lds = lds_q + wave * (RT * kQLdsWave) + lane * 16;
+    // Lane n's row: index within the sequence's T * H rows.
+    const int wave_row0 = (row_group * NW + wave) * 16, row = wave_row0 + n;
+    char* q_lds = lds_q + wave * kQLdsWave + lane * 16;
     char* stage = lds_c + wave * kStageWave;
     const int exact_blocks = mla_exact_blocks(pl, rows_total, prm.n_pieces);
     const DmaLane dma = dma_lane(lane);
@@ -464,30 +440,24 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
                             (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(caddr >> 32) & 0xffffu)),
                             cbytes > 0xffffffffull ? 0xffffffffu : (uint32_t)cbytes, 0x00020000u};
 
-        // Q operand: lane (kb, n) holds columns 32 step + 8 kb .. + 7 of row n of each tile; rows past the last
+        // Q operand: lane (kb, n) holds columns 32 step + 8 kb .. + 7 of row n; rows past the last
         // lie past the end of the descriptor and read as zero.
         const __amdgpu_buffer_rsrc_t rq = make_rsrc(prm.q + (long)b * rows_total * kDqk, (uint32_t)rows_total * kRowB);
-        bf16x8_t qop[RT][kQRegSteps];
-        int lim[RT];
-        MlaTile st[RT];
+        bf16x8_t qop[kQRegSteps];
+        MlaTile st;
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int row = wave_row0 + 16 * rt + n;
-            const bool row_ok = row < rows_total;
-#pragma unroll
-            for (int step = 0; step < kQSteps; ++step) {
-                const u32x4_t qv = __builtin_amdgcn_raw_buffer_load_b128(rq, row * kRowB + kb * 16 + 64 * step, 0, 0);
-                if (step < kQRegSteps) qop[rt][step < kQRegSteps ? step : 0] = __builtin_bit_cast(bf16x8_t, qv);
-                else *reinterpret_cast<u32x4_t*>(q_lds + rt * kQLdsWave + (step - kQRegSteps) * 1024) = qv;
-            }
-            const int causal = L - T + (row_ok ? row : 0) / H + 1;
-            lim[rt] = causal < j1 ? causal : j1;
-#pragma unroll
-            for (int ct = 0; ct < kColTiles; ++ct) st[rt].o[ct] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            st[rt].m = kNegInf;
-            st[rt].l = 0.0f;
-            st[rt].lq = 0.0f;
+        for (int step = 0; step < kQSteps; ++step) {
+            const u32x4_t qv = __builtin_amdgcn_raw_buffer_load_b128(rq, row * kRowB + kb * 16 + 64 * step, 0, 0);
+            if (step < kQRegSteps) qop[step < kQRegSteps ? step : 0] = __builtin_bit_cast(bf16x8_t, qv);
+            else *reinterpret_cast<u32x4_t*>(q_lds + (step - kQRegSteps) * 1024) = qv;
         }
+        const int causal = L - T + (row < rows_total ? row : 0) / H + 1;
+        const int lim = causal < j1 ? causal : j1;
+#pragma unroll
+        for (int ct = 0; ct < kColTiles; ++ct) st.o[ct] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        st.m = kNegInf;
+        st.l = 0.0f;
+        st.lq = 0.0f;
 
         // Block 0 -> buffer 0, behind the Q loads: those do not need the sequence's base address, whose
         // own load they now cover.
@@ -495,9 +465,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
         // Q is used here, before the loop, so that the wait for its loads sits here as well: a wait
         // inside the loop would also wait for the block loads that were just issued.
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int step = 0; step < kQRegSteps; ++step) asm volatile("" : "+v"(qop[rt][step]));
+        for (int step = 0; step < kQRegSteps; ++step) asm volatile("" : "+v"(qop[step]));
         fence();                  // the Q chunks in LDS are read back by the lane that wrote them
 
         const int n_blocks = (j1 - j0 + kMlaKeys - 1) / kMlaKeys;
@@ -511,8 +479,8 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
             dma_wait(blk + 1 < n_blocks ? my_loads : 0);
             __syncthreads();
             if (blk + 2 < n_blocks) block_to_lds<NW>(lds_c + next_buf * kLdsBlock, rc, j0 + (blk + 2) * kMlaKeys, wave, dma);
-            mla_block<RT, decltype(lo_mode)::value>(st, cur + qk_off, cur + qt_off, cur + pv_off, qop, q_lds, prm.scale_log2,
-                                                    j0 + blk * kMlaKeys, lim, kb);
+            mla_block<decltype(lo_mode)::value>(st, cur + qk_off, cur + qt_off, cur + pv_off, qop, q_lds, prm.scale_log2,
+                                                j0 + blk * kMlaKeys, lim, kb);
             cur_buf = cur_buf == kStages - 1 ? 0 : cur_buf + 1;
             next_buf = next_buf == kStages - 1 ? 0 : next_buf + 1;
         };
@@ -525,63 +493,58 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
             step(blk, std::integral_constant<int, kMode == 0 ? kLoDynamic : (kMode == 1 ? kLoAlways : kLoNever)>());
         __syncthreads();          // everyone is done with the block buffers: they stage the output now
 
+        const float l = st.l;
+        const float lq = kb_sum(st.lq);
+        // A partial row goes out as fp16 after scaling its largest magnitude to 2^15 (the scale's
+        // inverse is kept in fp32 beside the row's m and l): half the bytes of fp32 to write here
+        // and to read back in the merge.  Every element keeps 11 significant bits of its own
+        // (down to 2^-29 of the row's maximum), so a few large columns cost the others nothing.
+        // The scale is capped so that rows of denormal size do not overflow it.
+        float sc, inv_scale = 0.0f;
+        if (whole) {
+            sc = lq > 0.0f ? 1.0f / lq : 0.0f;
+        } else {
+            float amax = 0.0f;
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const float l = st[rt].l;
-            const float lq = kb_sum(st[rt].lq);
-            // A partial row goes out as fp16 after scaling its largest magnitude to 2^15 (the scale's
-            // inverse is kept in fp32 beside the row's m and l): half the bytes of fp32 to write here
-            // and to read back in the merge.  Every element keeps 11 significant bits of its own
-            // (down to 2^-29 of the row's maximum), so a few large columns cost the others nothing.
-            // The scale is capped so that rows of denormal size do not overflow it.
-            float sc, inv_scale = 0.0f;
+            for (int ct = 0; ct < kColTiles; ++ct)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) amax = fmaxf(amax, __builtin_fabsf(st.o[ct][i]));
+            amax = kb_max(amax);
+            sc = amax > 0.0f ? fminf(32768.0f / amax, 0x1.0p100f) : 0.0f;
+            inv_scale = amax > 0.0f ? 1.0f / sc : 0.0f;
+        }
+        // Rounded to 16 bits (bf16 results, fp16 partial rows), half a row at a time through the
+        // block buffers, which are free between the segment's last block and the next segment's
+        // first: two rounds, each store instruction writing two whole 512-byte half rows.
+        // The stores go through a buffer descriptor over the sequence's (or slot's) rows: 32-bit
+        // offsets, and rows past rows_total fall outside and are dropped, so the loop has no branch.
+        uint16_t* dst = whole ? prm.out + (long)b * rows_total * kDv : prm.part_o + slot * rows_total * kDv;
+        const __amdgpu_buffer_rsrc_t rd = make_rsrc(uniform(static_cast<void*>(dst)), (uint32_t)rows_total * (kDv * 2));
+        const uint32_t lane_dst = (uint32_t)((wave_row0 + (lane >> 5)) * (kDv * 2) + (lane & 31) * 16);
+        const char* lane_stage = stage + (lane >> 5) * kStagePitch + (lane & 31) * 16;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int c = 0; c < kColTiles / 2; ++c) {
+                const f32x4_t o = st.o[(kColTiles / 2) * h + c] * sc;
+                uint2 w;
+                w.x = whole ? cvt_bf16(o[0], o[1]) : pack_f16(o[0], o[1]);
+                w.y = whole ? cvt_bf16(o[2], o[3]) : pack_f16(o[2], o[3]);
+                *reinterpret_cast<uint2*>(stage + n * kStagePitch + (16 * c + 4 * kb) * 2) = w;
+            }
+            fence();
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {          // rows 2 i and 2 i + 1, 256 columns each, per instruction
+                const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lane_stage + 2 * i * kStagePitch);
+                __builtin_amdgcn_raw_buffer_store_b128(w, rd, (int)(lane_dst + 2 * i * (kDv * 2) + h * kDv), 0, 0);
+            }
+            fence();
+        }
+        if (row < rows_total && kb == 0) {
             if (whole) {
-                sc = lq > 0.0f ? 1.0f / lq : 0.0f;
+                if (prm.lse) prm.lse[(long)b * rows_total + row] = l > 0.0f ? (st.m + __log2f(l)) * kLn2 : kNegInf;
             } else {
-                float amax = 0.0f;
-#pragma unroll
-                for (int ct = 0; ct < kColTiles; ++ct)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) amax = fmaxf(amax, __builtin_fabsf(st[rt].o[ct][i]));
-                amax = kb_max(amax);
-                sc = amax > 0.0f ? fminf(32768.0f / amax, 0x1.0p100f) : 0.0f;
-                inv_scale = amax > 0.0f ? 1.0f / sc : 0.0f;
-            }
-            const int tile_row0 = wave_row0 + 16 * rt;
-            // Rounded to 16 bits (bf16 results, fp16 partial rows), half a row at a time through the
-            // block buffers, which are free between the segment's last block and the next segment's
-            // first: two rounds per tile, each store instruction writing two whole 512-byte half rows.
-            // The stores go through a buffer descriptor over the sequence's (or slot's) rows: 32-bit
-            // offsets, and rows past rows_total fall outside and are dropped, so the loop has no branch.
-            uint16_t* dst = whole ? prm.out + (long)b * rows_total * kDv : prm.part_o + slot * rows_total * kDv;
-            const __amdgpu_buffer_rsrc_t rd = make_rsrc(uniform(static_cast<void*>(dst)), (uint32_t)rows_total * (kDv * 2));
-            const uint32_t lane_dst = (uint32_t)((tile_row0 + (lane >> 5)) * (kDv * 2) + (lane & 31) * 16);
-            const char* lane_stage = stage + (lane >> 5) * kStagePitch + (lane & 31) * 16;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                for (int c = 0; c < kColTiles / 2; ++c) {
-                    const f32x4_t o = st[rt].o[(kColTiles / 2) * h + c] * sc;
-                    uint2 w;
-                    w.x = whole ? cvt_bf16(o[0], o[1]) : pack_f16(o[0], o[1]);
-                    w.y = whole ? cvt_bf16(o[2], o[3]) : pack_f16(o[2], o[3]);
-                    *reinterpret_cast<uint2*>(stage + n * kStagePitch + (16 * c + 4 * kb) * 2) = w;
-                }
-                fence();
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {          // rows 2 i and 2 i + 1, 256 columns each, per instruction
-                    const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lane_stage + 2 * i * kStagePitch);
-                    __builtin_amdgcn_raw_buffer_store_b128(w, rd, (int)(lane_dst + 2 * i * (kDv * 2) + h * kDv), 0, 0);
-                }
-                fence();
-            }
-            const int row = tile_row0 + n;
-            if (row < rows_total && kb == 0) {
-                if (whole) {
-                    if (prm.lse) prm.lse[(long)b * rows_total + row] = l > 0.0f ? (st[rt].m + __log2f(l)) * kLn2 : kNegInf;
-                } else {
-                    reinterpret_cast<float4*>(prm.part_ml)[slot * rows_total + row] = make_float4(st[rt].m, l, lq, inv_scale);
-                }
+                reinterpret_cast<float4*>(prm.part_ml)[slot * rows_total + row] = make_float4(st.m, l, lq, inv_scale);
             }
         }
         __syncthreads();          // the next segment's first block goes to buffer 0, which staged output until here
@@ -593,7 +556,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
 // accumulators in the 256 accumulation registers, Q (33 of its 36 MFMA steps) and two blocks' scores in the
 // ordinary ones.  With 32x32x16 MFMAs an operand fragment read from LDS (1 KiB) feeds 32 cycles of the matrix
 // pipe; with 16x16x32 it is 16, as fast as the LDS delivers fragments, and a loop with a wave per 16 rows (eight of
-// them) was bound by both in turn, 4600 cycles per block against 2900 here.
+// them) was bound by both in turn, 4600 cycles per block against 3100 here.
 // A block's 32 keys run through two phases, the work of two blocks interleaved so that the matrix pipe has
 // work while the vector unit does the softmax:
 //   A: scores of block i + 1 (36 MFMAs), and between them the weights of block i from its scores;
@@ -602,14 +565,16 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
 // most of the others but not all: against MFMAs alone the loads into LDS cost 290 cycles of a block, the softmax 300, the
 // operand reads 120.  And power: on random data the clock falls from 2.4 to 1.8 GHz (all-zero data: 256 rows 130 us
 // instead of 164).  Whole calls, eight waves of 16 rows -> here, 64 sequences of 1024 to 8192 tokens: 128 rows
-// 106.4 -> 97.1 us, 256 rows 179.6 -> 163.5, 72 rows 97.0 -> 81.7, 33 rows 76.9 -> 67.4 (four waves of 16 before).
+// 109.4 -> 100.3 us, 256 rows 184.4 -> 168.4, 72 rows 100.1 -> 84.3, 33 rows 77.7 -> 69.3 (four waves of 16 before); short
+// ones (see mla_tile_split): 40 of 64 to 256, 128 rows 27.7 -> 24.5; 64 of 64 to 256, 256 rows level at 37.1.
 // Tried without gain: operands 3, 5 or 6 fragments ahead; one wait for two fragments (2 % slower); a block's last
 // MFMAs behind the next barrier; its first weights ahead of its first MFMA (1 % slower).
 // Four LDS buffers: block i (values), i + 1 (scores), i + 2 and i + 3 on their way; one barrier per block.
 // A block's image in LDS: row r's latent part at r * kPitch, 16 bytes further from row 16 on, and the rope parts
 // as 128-byte rows whose 16-byte chunks are permuted by row (through the global address each lane fetches).
 // Key row x of the score MFMA is row tile_key(x) of the block.  With that, the lanes that one pass of an
-// LDS read serves (0-3, 12-15, 20-27 and so on for 128 bits; 0-31 for the transposing read) hit different banks.
+// LDS read serves (0-3, 12-15, 20-27 and so on for 128 bits; 0-31 for the transposing read) hit different banks; what
+// conflicts remain take 3 to 4 % of the LDS-active cycles.
 // The MFMAs are assembly statements: their accumulators can then be named (scores in ordinary registers, outputs
 // in accumulation registers; through the builtin the compiler puts every MFMA result into the accumulation
 // registers, which the outputs fill alone), and such statements keep their order among themselves and against
@@ -1626,11 +1591,11 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_ker
     if (prm.lse && lane == 0) prm.lse[row] = l > 0.0f ? (M + __log2f(l)) * kLn2 : kNegInf;
 }
 
-template <int NW, int RT>
-hipError_t launch_mla_cfg(const MlaParams& prm, dim3 grid, hipStream_t stream) {
-    if (prm.weight_mode == 1) hipLaunchKernelGGL((mla_decode_kernel<NW, RT, 1>), grid, dim3(64 * NW), 0, stream, prm);
-    else if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_decode_kernel<NW, RT, 2>), grid, dim3(64 * NW), 0, stream, prm);
-    else hipLaunchKernelGGL((mla_decode_kernel<NW, RT, 0>), grid, dim3(64 * NW), 0, stream, prm);
+template <int NW>
+hipError_t launch_mla_16(const MlaParams& prm, dim3 grid, hipStream_t stream) {
+    if (prm.weight_mode == 1) hipLaunchKernelGGL((mla_decode_kernel<NW, 1>), grid, dim3(64 * NW), 0, stream, prm);
+    else if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_decode_kernel<NW, 2>), grid, dim3(64 * NW), 0, stream, prm);
+    else hipLaunchKernelGGL((mla_decode_kernel<NW, 0>), grid, dim3(64 * NW), 0, stream, prm);
     return hipGetLastError();
 }
 
@@ -1653,7 +1618,7 @@ hipError_t launch_mla_rows(const MlaParams& prm, dim3 grid, hipStream_t stream) 
 
 // Workgroup shape for rows_total = q_len * n_heads query rows per sequence: (waves, 16-row tiles per wave).  Up to 32
 // rows mla_rows_kernel (one row group, as the shape given here), which has its line there; then mla_tile_kernel, 128
-// rows per workgroup: at 33 rows already 67.4 us against 76.9 with a wave per 16 rows.  layout 1: waves of 16 rows, 4
+// rows per workgroup: at 33 rows already 69.3 us against 77.7 with a wave per 16 rows.  layout 1: waves of 16 rows, 4
 // at most, for any number of rows; layout 2: as 1 up to 64 rows, then mla_tile_kernel.
 void mla_block_shape(int rows_total, int layout, int* waves, int* tiles_per_wave) {
     const int tiles = (rows_total + 15) / 16;
@@ -1672,9 +1637,9 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     if (prm.layout == 0 && rows_total <= 16) e = launch_mla_rows<1>(prm, grid, stream);
     else if (prm.layout == 0 && rows_total <= 32) e = launch_mla_rows<2>(prm, grid, stream);
     else if (rt == 2) e = launch_mla_tile(prm, stream);
-    else if (nw == 4) e = launch_mla_cfg<4, 1>(prm, grid, stream);
-    else if (nw == 2) e = launch_mla_cfg<2, 1>(prm, grid, stream);
-    else e = launch_mla_cfg<1, 1>(prm, grid, stream);
+    else if (nw == 4) e = launch_mla_16<4>(prm, grid, stream);
+    else if (nw == 2) e = launch_mla_16<2>(prm, grid, stream);
+    else e = launch_mla_16<1>(prm, grid, stream);
     if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[1], stream)) != hipSuccess) return e;
     const long rows = (long)prm.batch * rows_total;
