@@ -71,6 +71,11 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
 constexpr int kMergeAlone = 8;
 inline int merge_waves(long rows) { return rows <= 512 ? 16 : rows <= 2048 ? 4 : 1; }
 
+// Workgroups of a merge kernel whose work is `n` of them in the order of the output rows: a multiple of the eight XCDs,
+// with 8 or more sequences XCD x taking the x-th eighth of that order (merge_workgroup in xattn_device.h), as the decode kernels give it the x-th
+// eighth of the token stream.  Most partial rows are then read through the L2 that they were written through.
+inline unsigned merge_grid(long n) { return (unsigned)((n + 7) / 8 * 8); }
+
 // Latent-KV (MLA-shaped) decode: every head reads the same cached row of 576 bf16 per token.
 struct MlaParams {
     const uint16_t* q;               // bf16 [batch, q_len, n_heads, 576]

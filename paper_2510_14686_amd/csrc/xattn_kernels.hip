@@ -722,7 +722,7 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
     const uint32_t seq_rows = (uint32_t)(prm.q_len * prm.n_q_heads);
-    const uint32_t row = kWaves == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
+    const uint32_t row = kWaves == 1 ? merge_workgroup(prm.batch) * 4 + wave : merge_workgroup(prm.batch);
     const uint32_t b = row / seq_rows;
     if (b >= (uint32_t)prm.batch) return;
     const int2 fs = reinterpret_cast<const int2*>(prm.meta)[b];
@@ -747,7 +747,10 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(
         if (sh.first + lane < sh.end) mine = ml[(sh.first + lane) * stride_rows];
         float2 o[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) o[u] = po[(sh.first + u < sh.end ? sh.first + u : sh.end - 1) * stride_rows * (kHeadDim / 2)];
+        for (int u = 0; u < 8; ++u) {                     // (the last row again past the end: 2 to 5 % of short calls)
+            o[u] = make_float2(0.0f, 0.0f);
+            if (sh.first + u < sh.end) o[u] = po[(sh.first + u) * stride_rows * (kHeadDim / 2)];
+        }
         M = mine.x;
         for (int base = sh.first + 64; base < sh.end; base += 64)
             if (base + lane < sh.end) M = fmaxf(M, ml[(base + lane) * stride_rows].x);
@@ -891,9 +894,9 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
     if (events && (e = hipEventRecord(events[1], stream)) != hipSuccess) return e;
     const long rows = (long)prm.batch * prm.q_len * prm.n_q_heads;
     switch (merge_waves(rows)) {
-        case 16: hipLaunchKernelGGL(merge_kernel<16>, dim3((unsigned)rows), dim3(1024), 0, stream, prm); break;
-        case 4: hipLaunchKernelGGL(merge_kernel<4>, dim3((unsigned)rows), dim3(256), 0, stream, prm); break;
-        default: hipLaunchKernelGGL(merge_kernel<1>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, prm); break;
+        case 16: hipLaunchKernelGGL(merge_kernel<16>, dim3(merge_grid(rows)), dim3(1024), 0, stream, prm); break;
+        case 4: hipLaunchKernelGGL(merge_kernel<4>, dim3(merge_grid(rows)), dim3(256), 0, stream, prm); break;
+        default: hipLaunchKernelGGL(merge_kernel<1>, dim3(merge_grid((rows + 3) / 4)), dim3(256), 0, stream, prm); break;
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[2], stream)) != hipSuccess) return e;
