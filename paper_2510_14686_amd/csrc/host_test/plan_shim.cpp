@@ -70,6 +70,44 @@ int xattn_test_piece_segments(const int32_t* kv_lens, int batch, int n_pieces, i
     return n;
 }
 
+// The segments of all parts of all pieces as the matrix path walks them, with their joins: rows of (piece, part, b, j0, j1,
+// prev, next, ends) in out (up to max_rows); returns their number.
+int xattn_test_part_runs(const int32_t* kv_lens, int batch, int n_pieces, int min_piece, int seg_cost, int xcd_skew, int few_pieces, int few_min,
+                         int parts, int32_t* out, int max_rows) {
+    const Plan pl = plan_of(kv_lens, batch, n_pieces, min_piece, seg_cost, xcd_skew, few_pieces, few_min);
+    if (pl.total < 0) return -1;
+    int n = 0;
+    for (int p = 0; p < pl.n_pieces; ++p) {
+        const int piece0 = piece_bound(pl, p), piece1 = piece_bound(pl, p + 1), sub = part_positions(piece1 - piece0, parts);
+        for (int part = 0; part < parts; ++part) {
+            const int s0 = piece0 + part * sub, s1 = s0 + sub < piece1 ? s0 + sub : piece1;
+            if (s0 >= s1) continue;
+            Walk w = {0, 0, s1 - s0};
+            int before = 0;
+            for (w.b = 0; w.b < batch; ++w.b) {
+                const int v = stream_len(kv_lens[w.b], seg_cost);
+                if (s0 < before + v) break;
+                before += v;
+            }
+            w.j = s0 - before;
+            PieceSeg ps;
+            while (next_segment(w, batch, seg_cost, [&](int b) { return clamp_len(kv_lens[b]); }, ps)) {
+                const PartRun r = part_run(part, ps.j0, ps.j1, ps.L, piece1 - s1, sub);
+                const int32_t row[8] = {p, part, ps.b, ps.j0, ps.j1, r.prev, r.next, r.ends};
+                for (int i = 0; i < 8 && n < max_rows; ++i) out[8 * n + i] = row[i];
+                ++n;
+            }
+        }
+    }
+    return n;
+}
+
+// KV heads per workgroup and waves per head of the matrix path: heads * 16 + waves.
+int xattn_test_piece_share(int n_kv_heads, int max_waves) {
+    const PieceShare s = piece_share(n_kv_heads, max_waves);
+    return s.heads * 16 + s.parts;
+}
+
 // How xattn_decode's workgroups share a plan of `total` positions out: count_out[piece in use * rows_total + row] =
 // the number of workgroup parts that compute it.  Returns the rows a wave holds in this launch; -1 where a part
 // works on a piece that is not in use, or on no row.

@@ -93,6 +93,14 @@ DecodeSplit decode_split(int n_cu, int batch, int q_len, int n_q_heads, int n_kv
     return DecodeSplit{pieces * parts, parts};
 }
 
+// Pieces of a GQA call on the matrix path, whose row groups of `rows` query rows each work on a piece: one workgroup per
+// compute unit, those of other KV heads and other query rows of a piece counted.
+int shared_pieces(int n_cu, int rows_total, int rows, int n_kv_heads, PieceShare share) {
+    const int on_a_piece = (rows_total + rows - 1) / rows * ((n_kv_heads + share.heads - 1) / share.heads);
+    const int pieces = on_a_piece == 1 ? n_cu : n_cu / on_a_piece / 8 * 8;
+    return pieces < 8 ? 8 : pieces;
+}
+
 // Pieces of a latent-KV call: as many as give one workgroup per compute unit when a piece is worked
 // on by several workgroups (one per group of query rows; they sit side by side on one XCD and share
 // the piece's cache rows in its L2).  More pieces than that only add partial rows: measured with 256
@@ -288,7 +296,13 @@ int decode_call(const char* who, FixedWorkspaceFn fixed_workspace, const void* q
     prm.part_o = reinterpret_cast<float*>(ws + w.o_off);
     prm.n_pieces = split.pieces;
     prm.parts = split.parts;
-    prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : kDefaultMinPieceTokens;
+    prm.share = piece_share(n_kv_heads, kMaxWavesPerBlock);
+    const int rows_total = prm.group * q_len;
+    const bool shared = use_matrix_path(g_cfg_path);
+    prm.shared_pieces = g_cfg_pieces > 0 ? g_cfg_pieces
+                                         : shared_pieces(d->n_cu, rows_total, rows_per_wave(rows_total, g_cfg_path), n_kv_heads, prm.share);
+    const int waves = shared ? prm.share.parts : 1;                // waves per piece and KV head
+    prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : kDefaultMinPieceTokens * waves;
     if (prm.min_piece_tokens < 16) prm.min_piece_tokens = 16;      // one 16-key block at least
     // One block per piece up to one piece per compute unit (with more than 8 KV heads, per group of 8 heads): 695
     // tokens 11.4 -> 8.9 us, 207 tokens of 16 KV heads 13.7 -> 11.8; 64-token pieces beyond that (smaller ones only
@@ -298,7 +312,10 @@ int decode_call(const char* who, FixedWorkspaceFn fixed_workspace, const void* q
     // 15.2 / 15.2 / 15.5 / 17.9 / 17.9, 8 rows 13.1 / 13.3 / 11.7 / 11.7 / 11.7 / 11.7; on seven more shapes 8 is
     // within 3 % of the best but for 20 sequences of 60 to 120 with 8 rows of 16 KV heads (7 %).
     const int few_slots = (int)(kFewBytes / ((size_t)q_len * n_q_heads * (kHeadDim + 2) * sizeof(float))) - batch;
-    prm.few = g_cfg_min_piece > 0 || few_slots < 1 ? FewPieces{0, 1} : FewPieces{few_slots < d->n_cu ? few_slots : d->n_cu, 16};
+    // On the matrix path as many as leave every tile of 16 query rows a workgroup of its own (decode_work): 59 sequences of 32
+    // to 512, 48 rows of 2 KV heads 18.2 us with a piece per workgroup, 14.8 so; 2 of 12080 to 24160, 35 rows of one 21.6 / 17.1.
+    const int few_max = shared ? shared_pieces(d->n_cu, rows_total, 16, n_kv_heads, prm.share) : d->n_cu;
+    prm.few = g_cfg_min_piece > 0 || few_slots < 1 ? FewPieces{0, 1} : FewPieces{few_slots < few_max ? few_slots : few_max, 16};
     prm.xcd_skew = g_cfg_xcd_skew > 0 ? g_cfg_xcd_skew - 1 : kDefaultXcdSkewGqa;
     prm.path = g_cfg_path;
     prm.pv_mode = g_cfg_pv_mode;

@@ -15,9 +15,11 @@ namespace {
 constexpr int kU = 4;                 // key rows per 16-lane group per block
 constexpr int kBlockKeys = 4 * kU;    // key rows per wave per block
 constexpr int kRowBytes = kHeadDim * 2;
-// Wave-private LDS of the matrix path: a 16-key K block (4.5 KiB) during the key loop, a 16-row fp32
-// output tile with padded rows (16 x 528 bytes) when a segment is stored.
-constexpr int kLdsPerWave = 16 * (kHeadDim * 4 + 16);
+// Wave-private LDS of the matrix path: a 16-key K block (rows padded to 288 bytes) during the key loop, 256 bytes of 16 output
+// rows when a segment is stored.
+constexpr int kLdsPerWave = 16 * (kRowBytes + 32);
+// A tile's running state in LDS as the lanes hold it: 8 x 16 bytes of sums, (m, l).
+constexpr int kLdsPerState = 64 * (8 * 16 + 8);
 constexpr float kNegInf = -__builtin_inff();
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -223,7 +225,7 @@ __device__ __forceinline__ int chunk_positions(__amdgpu_buffer_rsrc_t rl, int fi
 // round trip.
 __device__ __forceinline__ WavePlan wave_plan(const int32_t* __restrict__ kv_lens, const void* const* k_ptrs,
                                               const void* const* v_ptrs, int batch, int n_pieces, int min_piece,
-                                              int seg_cost, int xcd_skew, FewPieces few, int lane, SeqWindow* win) {
+                                              int seg_cost, int xcd_skew, FewPieces few, int lane, SeqWindow* win, int parts = 1) {
     WavePlan wp;
     int lg = 0;
     while ((64 << lg) < batch) ++lg;                       // wave-uniform: batch is a kernel argument
@@ -252,7 +254,7 @@ __device__ __forceinline__ WavePlan wave_plan(const int32_t* __restrict__ kv_len
     const int incl = wave_incl_scan_i(mine);
     wp.mine = mine;
     wp.excl = incl - mine;
-    wp.pl = plan_for_total(__builtin_amdgcn_readlane(incl, 63), n_pieces, min_piece, seg_cost, xcd_skew, few);
+    wp.pl = plan_for_total(__builtin_amdgcn_readlane(incl, 63), n_pieces, min_piece, seg_cost, xcd_skew, few, parts);
     return wp;
 }
 

@@ -34,9 +34,11 @@ struct DecodeParams {
     float* part_o;                   // fp32 [slots, q_len * n_q_heads, 128]
     float* part_ml;                  // fp32 [slots, q_len * n_q_heads, 2]  (max, sum)
     int32_t* meta;                   // int32 [batch, 2]
-    int n_pieces;                    // pieces the token stream is cut into (upper bound on active ones)
-    int parts;                       // pieces per workgroup: waves per workgroup / KV heads per workgroup
-    int min_piece_tokens;
+    int n_pieces;                    // vector path: pieces the token stream is cut into (upper bound on active ones)
+    int parts;                       // and pieces per workgroup: waves per workgroup / KV heads per workgroup
+    int shared_pieces;               // matrix path: pieces, n_pieces at most; share.parts waves per KV head work on each
+    PieceShare share;
+    int min_piece_tokens;            // of the path's pieces, as `few`
     FewPieces few;                   // see plan_for_total
     int xcd_skew;                    // per mille: share taken from the odd XCDs' parts of the stream and given to the even ones
     int path;                        // kPathAuto, kPathVector or kPathMatrix

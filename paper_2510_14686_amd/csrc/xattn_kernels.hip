@@ -3,12 +3,15 @@
 // Work decomposition (paper section 4.4.3, "Layer 3": balance compute units by token count, split
 // long sequences, let short ones share a unit).  The keys of the whole batch form one stream of
 // N = sum_b kv_lens[b] tokens, cut into P pieces of N / P tokens (to within one 16-key block); a workgroup
-// owns one piece of that stream, whatever sequences it falls in (several with fewer than 8 KV heads).  Inside
-// a workgroup wave w owns KV head w, so a workgroup streams one contiguous byte range of K and one of V (no
-// block table: section 4.3, "Operator Adaptation").  Each (piece, sequence) intersection is a segment.  A segment
-// that covers its whole sequence writes the final result; any other writes an un-normalised partial
-// (o, m, l) to slot piece + sequence_index, and the merge kernel combines a sequence's slots (the
-// aggregation step of section 4.4.3, "Layer 2").  Combining inside the decode kernel by the last wave
+// owns one piece of that stream, whatever sequences it falls in, for up to four KV heads, side by side in
+// memory: a wave streams one head's K and V of a run of the piece's tokens (no block table: section 4.3,
+// "Operator Adaptation").  Each (piece, sequence) intersection is a segment; the waves that hold runs of it put
+// their sums together in LDS.  A segment that covers its whole sequence writes the final result; any other writes an
+// un-normalised partial (o, m, l) to slot piece + sequence_index, and the merge kernel combines a sequence's
+// slots (the aggregation step of section 4.4.3, "Layer 2").  (A wave per head with a piece and a partial result of
+// its own, 8 heads of a piece in a workgroup, before: 64 sequences of 512 to 4096 tokens, 2 KV heads 30.4 us, now
+// 29.5; 8 KV heads 92.5 / 91.9; 32 of 1024 to 8192, 32 rows per KV head 130.5 / 119.6, where the partial results were
+// 38 MB; one of 30001 27.9 / 26.7.)  Combining inside the decode kernel by the last wave
 // to finish a sequence was tried and is slower: that wave alone reads all of a long sequence's
 // partials with dependent device-scope loads, while the merge kernel spreads them over the chip.
 //
@@ -572,22 +575,28 @@ __device__ __forceinline__ void matrix_finish(const MatrixState& st, const Segme
         if (n < n_rows && prm.lse && kb == 0)
             prm.lse[(long)seg.b * seq_rows + seq_row(prm, seg, 16 * tile + n)] = l > 0.0f ? (st.m + __log2f(l)) * kLn2 : kNegInf;
     } else {
-        constexpr int kPitch = kHeadDim * 4 + 16;                // fp32 rows, padded
+        constexpr int kPitch = kRowBytes + 16;                   // half a row in fp32, padded: lanes kb < 2 hold the first halves
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float4* w = reinterpret_cast<float4*>(lds_wave + n * kPitch + (4 * kb + j) * 32);
-            w[0] = make_float4(st.o[0][j], st.o[1][j], st.o[2][j], st.o[3][j]);
-            w[1] = make_float4(st.o[4][j], st.o[5][j], st.o[6][j], st.o[7][j]);
-        }
-        fence();
+        for (int half = 0; half < 2; ++half) {
+            if ((kb >> 1) == half) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {                             // 2 rows of 512 bytes per store instruction
-            if (2 * i >= n_rows) break;
-            const int r = 2 * i + (lane >> 5);
-            const uint32_t off = (uint32_t)seq_row(prm, seg, 16 * tile + r) * (kHeadDim * 4) + (lane & 31) * 16;
-            const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lds_wave + r * kPitch + (lane & 31) * 16);
-            store_b128<kWriteThrough>(prm.part_o + (long)seg.slot * seq_rows * kHeadDim, (uint32_t)(seq_rows * kHeadDim * 4),
-                          off | (r < n_rows ? 0u : kPastTheEnd), w);
+                for (int j = 0; j < 4; ++j) {
+                    float4* w = reinterpret_cast<float4*>(lds_wave + n * kPitch + (4 * (kb & 1) + j) * 32);
+                    w[0] = make_float4(st.o[0][j], st.o[1][j], st.o[2][j], st.o[3][j]);
+                    w[1] = make_float4(st.o[4][j], st.o[5][j], st.o[6][j], st.o[7][j]);
+                }
+            }
+            fence();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {                         // 256 bytes of 4 rows per store instruction
+                if (4 * i >= n_rows) break;
+                const int r = 4 * i + (lane >> 4);
+                const uint32_t off = (uint32_t)seq_row(prm, seg, 16 * tile + r) * (kHeadDim * 4) + half * kRowBytes + (lane & 15) * 16;
+                const u32x4_t w = *reinterpret_cast<const u32x4_t*>(lds_wave + r * kPitch + (lane & 15) * 16);
+                store_b128<kWriteThrough>(prm.part_o + (long)seg.slot * seq_rows * kHeadDim, (uint32_t)(seq_rows * kHeadDim * 4),
+                                          off | (r < n_rows ? 0u : kPastTheEnd), w);
+            }
+            if (half == 0) fence();
         }
         if (n < n_rows && kb == 0) {
             const long prow = (long)seg.slot * seq_rows + seq_row(prm, seg, 16 * tile + n);
@@ -597,9 +606,31 @@ __device__ __forceinline__ void matrix_finish(const MatrixState& st, const Segme
     fence();      // the next tile, or the next segment's K blocks, reuse this LDS
 }
 
+// The state of a tile, left in LDS by the wave that holds a later run of the sequence's keys, and added to the own one by the
+// wave that holds the first.
+__device__ __forceinline__ void state_put(const MatrixState& st, char* area, int lane) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) *reinterpret_cast<f32x4_t*>(area + e * 1024 + lane * 16) = st.o[e];
+    *reinterpret_cast<float2*>(area + 8192 + lane * 8) = make_float2(st.m, st.l);
+}
+__device__ __forceinline__ void state_add(MatrixState& st, const char* area, int lane) {
+    const float2 ml = *reinterpret_cast<const float2*>(area + 8192 + lane * 8);
+    const float m = fmaxf(st.m, ml.x), m_use = m == kNegInf ? 0.0f : m;
+    const float mine = fast_exp2(st.m - m_use), other = fast_exp2(ml.x - m_use);
+    st.m = m;
+    st.l = st.l * mine + ml.y * other;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const f32x4_t o = *reinterpret_cast<const f32x4_t*>(area + e * 1024 + lane * 16);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) st.o[e][j] = __builtin_fmaf(o[j], other, st.o[e][j] * mine);
+    }
+}
+
 // ---------------------------------------------------------------------------------- decode kernel
-// grid.x = workgroups of pieces times groups of R query rows, grid.z = groups of up to 8 KV heads;
-// block = 64 * heads * parts: a workgroup holds `parts` pieces, one wave per KV head and piece.
+// grid.x = workgroups of pieces times groups of R query rows, grid.z = groups of KV heads.  Matrix path: a workgroup works on
+// one piece, share.heads KV heads in share.parts waves each (see piece_share).  Vector path: up to 8 KV heads and `parts`
+// pieces, one wave per KV head and piece.
 // kMatrix selects the matrix path (R must be 16 * kTiles then).
 // Fixed work of a (piece, sequence) segment in token units for the partition (0 = pieces of equal token
 // count; 16 measured best of 0 / 16 / 48: 0.2 to 1 % on the four large workloads).
@@ -608,13 +639,16 @@ constexpr int kGqaSegCost = 16;
 template <int R, bool kMatrix, int kPv>
 __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     constexpr int kTiles = kMatrix ? R / 16 : 1;
-    __shared__ __attribute__((aligned(16))) char lds[kMatrix ? kMaxWavesPerBlock * kLdsPerWave : 16];
+    // Behind the waves' own parts: the states of all waves of a workgroup but the first of every KV head.
+    constexpr int kStates = (kMaxWavesPerBlock - 1) * kTiles;
+    __shared__ __attribute__((aligned(16))) char lds[kMatrix ? kMaxWavesPerBlock * kLdsPerWave + kStates * kLdsPerState : 16];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int heads = prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;      // per workgroup
-    const int part = prm.parts == 1 ? 0 : wave / heads;
-    const int kvh = blockIdx.z * kMaxWavesPerBlock + wave - part * heads;
-    if (kvh >= prm.n_kv_heads) return;
+    const int heads = kMatrix ? prm.share.heads : prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;
+    const int parts = kMatrix ? prm.share.parts : prm.parts;
+    const int part = parts == 1 ? 0 : wave / heads;
+    const int kvh = blockIdx.z * heads + wave - part * heads;
+    if (!kMatrix && kvh >= prm.n_kv_heads) return;
     // A piece's first segment takes its length and pointers from the plan's own round trips, which saves a start two
     // dependent loads (138468 tokens of 2 KV heads 31.7 -> 31.1 us, of 8 94.3 -> 93.2).  Only the first: kept longer the
     // window's registers cost the large calls up to 1.7 %.  Not with two tiles: that kernel's registers are full, and
@@ -624,16 +658,17 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     SeqWindow* const window = kWindow ? &win : nullptr;
     const void* const* const win_k = kWindow ? prm.k_ptrs : nullptr;
     const void* const* const win_v = kWindow ? prm.v_ptrs : nullptr;
-    const WavePlan wp = wave_plan(prm.kv_lens, win_k, win_v, prm.batch, prm.n_pieces, prm.min_piece_tokens, kGqaSegCost,
-                                  prm.xcd_skew, prm.few, lane, window);
+    const WavePlan wp = wave_plan(prm.kv_lens, win_k, win_v, prm.batch, kMatrix ? prm.shared_pieces : prm.n_pieces, prm.min_piece_tokens,
+                                  kGqaSegCost, prm.xcd_skew, prm.few, lane, window, kMatrix ? parts : 1);
     const Plan& pl = wp.pl;
 
     const int bid = blockIdx.x;
     const int rows_total = prm.group * prm.q_len;
-    const DecodeWork work = decode_work(pl, gridDim.x, prm.parts, rows_total, R, bid, part);
+    const DecodeWork work = decode_work(pl, gridDim.x, kMatrix ? 1 : parts, rows_total, R, bid, kMatrix ? 0 : part);
     const int p = work.piece, rows = work.rows;
-    const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
-    const bool active = work.any && s0 < s1;
+    const int piece0 = piece_bound(pl, p), piece1 = piece_bound(pl, p + 1);
+    const int sub = kMatrix ? part_positions(piece1 - piece0, parts) : piece1 - piece0;
+    const int s0 = kMatrix ? piece0 + part * sub : piece0, s1 = s0 + sub < piece1 ? s0 + sub : piece1;
 
     if (blockIdx.z == 0 && threadIdx.x < 64) {
         // For the merge kernel: first partial slot and number of segments of every sequence, 64
@@ -641,10 +676,12 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
         // has no piece of its own when the stream is short.
         for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
     }
-    if (!active) return;
+    if (!work.any || piece0 >= piece1) return;      // the whole workgroup on the matrix path
+    if (!kMatrix && s0 >= s1) return;
+    const bool active = s0 < s1 && kvh < prm.n_kv_heads;
 
     Walk walk;
-    wave_locate(wp, prm.kv_lens, win_k, win_v, prm.batch, s0, lane, window, walk.b, walk.j);
+    if (active) wave_locate(wp, prm.kv_lens, win_k, win_v, prm.batch, s0, lane, window, walk.b, walk.j);
     walk.remaining = uniform(s1 - s0);
 
     Segment seg;
@@ -677,25 +714,48 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
         char* lds_wave = lds + wave * kLdsPerWave;
         auto run_piece = [&](auto tiles) {
             constexpr int kT = decltype(tiles)::value;
-            Segment cur_seg;
-            if (uniform(next_seg(cur_seg, std::true_type())) == 0) return;
+            char* const lds_head = lds + kMaxWavesPerBlock * kLdsPerWave + (wave - part * heads) * (kT * kLdsPerState);
+            auto state_of = [&](int of_part, int t) { return lds_head + (of_part - 1) * heads * (kT * kLdsPerState) + t * kLdsPerState; };
+            MatrixState st[kT];
             MatrixCtx<kT> cur;
-            matrix_begin(cur, prm, cur_seg, lane);
-            for (;;) {
-                MatrixState st[kT];
-                matrix_run<kPv, kT>(st, cur, prm, lane, lds_wave);
-                Segment nxt_seg;
-                const bool more = uniform(next_seg(nxt_seg, std::false_type())) != 0;
-                MatrixCtx<kT> nxt;
-                if (more) matrix_begin(nxt, prm, nxt_seg, lane);     // its loads go out before cur's stores
+            auto put = [&] {
 #pragma unroll
-                for (int t = 0; t < kT; ++t) {
-                    if (more) matrix_finish<true>(st[t], cur.seg, t, prm, lane, lds_wave);
-                    else matrix_finish<false>(st[t], cur.seg, t, prm, lane, lds_wave);
-                }
-                if (!more) break;
-                cur = nxt;
+                for (int t = 0; t < kT; ++t) state_put(st[t], state_of(part, t), lane);
+            };
+            bool have = false;
+            if (active) {
+                Segment first;
+                have = uniform(next_seg(first, std::true_type())) != 0;
+                if (have) matrix_begin(cur, prm, first, lane);
             }
+            if (have) {
+                for (;;) {
+                    matrix_run<kPv, kT>(st, cur, prm, lane, lds_wave);
+                    Segment nxt_seg;
+                    if (uniform(next_seg(nxt_seg, std::false_type())) == 0) break;
+                    MatrixCtx<kT> nxt;
+                    matrix_begin(nxt, prm, nxt_seg, lane);     // its loads go out before cur's stores
+                    if (part > 0 && cur.seg.j0 > 0) {
+                        put();
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < kT; ++t) matrix_finish<true>(st[t], cur.seg, t, prm, lane, lds_wave);
+                    }
+                    cur = nxt;
+                }
+            }
+            // The last segment: what the wave before began goes to LDS, what this wave begins is put together there.
+            PartRun run = {false, 0, false};
+            if (have) run = part_run(part, cur.seg.j0, cur.seg.j1, cur.seg.L, piece1 - s1, sub);
+            if (have && run.prev) put();
+            if (parts > 1) __syncthreads();
+            if (!have || run.prev) return;
+            for (int q = part + 1; q <= part + run.next; ++q)
+#pragma unroll
+                for (int t = 0; t < kT; ++t) state_add(st[t], state_of(q, t), lane);
+            cur.seg.whole = cur.seg.j0 == 0 && run.ends;
+#pragma unroll
+            for (int t = 0; t < kT; ++t) matrix_finish<false>(st[t], cur.seg, t, prm, lane, lds_wave);
         };
         if (kTiles == 2 && rows == 16) run_piece(std::integral_constant<int, 1>());
         else run_piece(std::integral_constant<int, kTiles>());
@@ -859,9 +919,9 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
     const int rows_total = prm.group * prm.q_len;
     const bool matrix = use_matrix_path(prm.path);
     const int R = rows_per_wave(rows_total, prm.path);
-    const int heads_per_block = prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;
-    dim3 grid(decode_grid_x(prm.n_pieces, prm.parts, rows_total, R), 1, (prm.n_kv_heads + kMaxWavesPerBlock - 1) / kMaxWavesPerBlock);
-    dim3 block(64 * heads_per_block * prm.parts);
+    const int heads = matrix ? prm.share.heads : prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;
+    const int grid_x = matrix ? decode_grid_x(prm.shared_pieces, 1, rows_total, R) : decode_grid_x(prm.n_pieces, prm.parts, rows_total, R);
+    const dim3 grid(grid_x, 1, (prm.n_kv_heads + heads - 1) / heads), block(64 * heads * (matrix ? prm.share.parts : prm.parts));
     hipError_t e;
     if (events && (e = hipEventRecord(events[0], stream)) != hipSuccess) return e;
     if (matrix && R == 32) {

@@ -47,7 +47,7 @@ XATTN_HD int stream_len(int len, int seg_cost) { return len > 0 ? len + seg_cost
 struct FewPieces {
     int pieces, min_piece;
 };
-XATTN_HD Plan plan_for_total(int total, int n_pieces, int min_piece, int seg_cost, int xcd_skew = 0, FewPieces few = {0, 1}) {
+XATTN_HD Plan plan_for_total(int total, int n_pieces, int min_piece, int seg_cost, int xcd_skew = 0, FewPieces few = {0, 1}, int parts = 1) {
     int n = total / (min_piece > 0 ? min_piece : 1);
     int n_few = total / few.min_piece;
     n_few = n_few < few.pieces ? n_few : few.pieces;
@@ -58,9 +58,8 @@ XATTN_HD Plan plan_for_total(int total, int n_pieces, int min_piece, int seg_cos
     pl.n_pieces = n < n_pieces ? n : n_pieces;
     pl.seg_cost = seg_cost;
     // the skew needs the eight XCD parts to hold the same number of pieces, and pieces long enough for a
-    // few per cent of them to be a block or more (pieces, not workgroups: calls with several pieces per
-    // workgroup reach it at that many times the tokens; the skew was not measured for them)
-    const bool can_skew = xcd_skew > 0 && pl.n_pieces % 8 == 0 && total / pl.n_pieces >= kMinSkewPiece;
+    // few per cent of them to be a block or more (where the `parts` waves of a workgroup share a piece, a wave's share of it)
+    const bool can_skew = xcd_skew > 0 && pl.n_pieces % 8 == 0 && total / pl.n_pieces >= kMinSkewPiece * parts;
     pl.xcd_skew = can_skew ? (xcd_skew < kMaxXcdSkew ? xcd_skew : kMaxXcdSkew) : 0;
     return pl;
 }
@@ -146,6 +145,36 @@ XATTN_HD DecodeWork decode_work(const Plan& pl, int grid_x, int parts, int rows_
     w.piece = (bid & 7) * per_xcd + local;
     w.any = set < sets && local < per_xcd && w.piece < pl.n_pieces;
     return w;
+}
+
+// The matrix path's workgroups: `heads` KV heads, and `parts` waves per head that share a piece, a run of positions each.  A
+// sequence that the waves cut among themselves is put together in LDS; only what the piece's own ends cut leaves a
+// partial result.  Four heads of 256 bytes side by side stream as fast as eight; two cost 2.7 % of a large call, one 6 to 9.
+struct PieceShare {
+    int heads, parts;
+};
+XATTN_HD PieceShare piece_share(int n_kv_heads, int max_waves) {
+    int h = n_kv_heads;
+    if (h > 4) h = h % 4 == 0 ? 4 : h % 3 == 0 ? 3 : h < max_waves ? h : max_waves;
+    return PieceShare{h, max_waves / h};
+}
+// Positions per part of a piece of `len` positions, all but the last one's: whole 16-key blocks, so parts without any
+// positions come last.
+XATTN_HD int part_positions(int len, int parts) { return ((len + parts - 1) / parts + kPlanRound - 1) / kPlanRound * kPlanRound; }
+// How a part's segment [j0, j1) of a sequence of L tokens joins with its neighbours'.  `left`: positions of the piece behind
+// this part's own, `sub`: part_positions.
+struct PartRun {
+    bool prev;     // its tokens join those of the part before
+    int next;      // the parts behind that hold more of the sequence
+    bool ends;     // the sequence's last token is in the piece
+};
+XATTN_HD PartRun part_run(int part, int j0, int j1, int L, int left, int sub) {
+    const int rest = L - j1;
+    PartRun r;
+    r.prev = part > 0 && j0 > 0;
+    r.next = ((rest < left ? rest : left) + sub - 1) / sub;
+    r.ends = rest <= left;
+    return r;
 }
 
 // What the merge kernel needs to know of a sequence that starts at stream position `start` and has
