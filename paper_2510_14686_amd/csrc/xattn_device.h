@@ -305,13 +305,12 @@ __device__ __forceinline__ void wave_write_meta(const WavePlan& wp, const int32_
     }
 }
 
-// This workgroup's place in the order of the output rows: see merge_grid.  (31 sequences of 41 to 666 tokens, 8 KV heads,
-// the call 16.3 -> 15.2 us; latent-KV, 128 of 244 to 1958, 128 rows 72.3 -> 69.2, 64 of 1024 to 8192, 16 rows 60.8 -> 60.0;
-// large GQA calls level.)  With fewer sequences than XCDs a long one's rows would all meet on one of them (7 of 2216 to
-// 17728, 72 rows 37.0 -> 37.8): round robin then.
-__device__ __forceinline__ uint32_t merge_workgroup(int batch) {
-    return batch < 8 ? blockIdx.x : (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-}
+// This workgroup's place in the order of the output rows, and a lane's share of a partial row.  (Which form as a branch of one
+// kernel costs 2 % of the short calls.)
+template <int kRead>
+__device__ __forceinline__ uint32_t merge_workgroup() { return kRead == kReadOwn ? (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x; }
+template <int kRead, typename T>
+__device__ __forceinline__ T load_partial(const T* p) { return kRead == kReadFarOnce ? __builtin_nontemporal_load(p) : *p; }
 
 // The share of a row's n partial results that one of the kWaves waves of a merge workgroup sums.  With few
 // of them (`alone`) the first wave takes all: a second round trip costs less than meeting in LDS.

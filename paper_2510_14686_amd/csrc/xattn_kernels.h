@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "xattn_plan.h"
 
 namespace xattn {
@@ -73,10 +75,29 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
 constexpr int kMergeAlone = 8;
 inline int merge_waves(long rows) { return rows <= 512 ? 16 : rows <= 2048 ? 4 : 1; }
 
-// Workgroups of a merge kernel whose work is `n` of them in the order of the output rows: a multiple of the eight XCDs,
-// with 8 or more sequences XCD x taking the x-th eighth of that order (merge_workgroup in xattn_device.h), as the decode kernels give it the x-th
-// eighth of the token stream.  Most partial rows are then read through the L2 that they were written through.
+// Whose partial rows an XCD reads.  From 8 sequences on it merges the x-th eighth of the output rows, as the decode kernels
+// give it the x-th eighth of the token stream (kReadOwn): most partial rows are then read through the L2 that they were
+// written through.  (Round robin: 31 sequences of 41 to 666 tokens, 8 KV heads, the call 15.2 -> 16.3 us; latent-KV, 128
+// of 244 to 1958, 128 rows 69.2 -> 72.3, 64 of 1024 to 8192, 16 rows 60.0 -> 60.8; large GQA calls level.)  With fewer
+// sequences than XCDs a long one's rows would all meet on one of them (latent-KV, 7 of 2216 to 17728, 72 rows 37.0 ->
+// 37.8): round robin then.  The rows come from all XCDs, through the L2 (kReadFar) or past it (kReadFarOnce).
+constexpr int kReadOwn = 0, kReadFar = 1, kReadFarOnce = 2;
+// Workgroups of a merge kernel whose work is `n` of them in the order of the output rows: a multiple of the eight XCDs.
 inline unsigned merge_grid(long n) { return (unsigned)((n + 7) / 8 * 8); }
+// launch(waves per row, kRead..., workgroups), the first two as types.
+template <typename Launch>
+inline void launch_merge(long rows, int batch, bool far_cached, Launch launch) {
+    auto with_waves = [&](auto read) {
+        switch (merge_waves(rows)) {
+            case 16: launch(std::integral_constant<int, 16>(), read, merge_grid(rows)); break;
+            case 4: launch(std::integral_constant<int, 4>(), read, merge_grid(rows)); break;
+            default: launch(std::integral_constant<int, 1>(), read, merge_grid((rows + 3) / 4)); break;
+        }
+    };
+    if (batch >= 8) with_waves(std::integral_constant<int, kReadOwn>());
+    else if (far_cached) with_waves(std::integral_constant<int, kReadFar>());
+    else with_waves(std::integral_constant<int, kReadFarOnce>());
+}
 
 // Latent-KV (MLA-shaped) decode: every head reads the same cached row of 576 bf16 per token.
 struct MlaParams {

@@ -1480,12 +1480,14 @@ __global__ __launch_bounds__(256 * RT) void mla_rows_kernel(MlaParams prm) {
 // bytes in large calls and by its dependent steps in small ones: as merge_kernel, and 8 partial rows on their way
 // instead of 4 (the whole call: 29 sequences of 131 to 262 tokens, 64 rows 20.2 -> 19.4 us; 64 of 1024 to 8192, 16
 // rows 61.9 -> 60.9; 128 rows 109.6 -> 108.9).
-template <int kWaves>
+// kRead = kReadOwn: non-temporal there, 1.5 to 2 us more of a large call.  kReadFarOnce, through the L2s before: 3 of 817 to 13076
+// tokens, 64 rows 31.6 -> 30.4 us; 7 of 2216 to 17728, 72 rows 41.1 -> 39.9; one of 30000, 128 rows 37.6 -> 36.7.
+template <int kWaves, int kRead>
 __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_kernel(MlaParams prm) {
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
     const uint32_t seq_rows = (uint32_t)(prm.q_len * prm.n_heads);
-    const uint32_t row = kWaves == 1 ? merge_workgroup(prm.batch) * 4 + wave : merge_workgroup(prm.batch);
+    const uint32_t row = kWaves == 1 ? merge_workgroup<kRead>() * 4 + wave : merge_workgroup<kRead>();
     const uint32_t b = row / seq_rows;
     if (b >= (uint32_t)prm.batch) return;
     const int2 fs = reinterpret_cast<const int2*>(prm.meta)[b];
@@ -1513,9 +1515,9 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_ker
     if (sh.first < sh.end) {
         float4 mine = record(sh.first + lane);
         u32x4_t o[8];
-        auto load = [&](int s0) {                         // (non-temporal, past the L2 that holds them: 1.5 to 2 us of a large call)
+        auto load = [&](int s0) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) o[u] = po[(s0 + u < sh.end ? s0 + u : sh.end - 1) * po_stride];
+            for (int u = 0; u < 8; ++u) o[u] = load_partial<kRead>(&po[(s0 + u < sh.end ? s0 + u : sh.end - 1) * po_stride]);
         };
         load(sh.first);
         M = mine.x;
@@ -1643,11 +1645,10 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[1], stream)) != hipSuccess) return e;
     const long rows = (long)prm.batch * rows_total;
-    switch (merge_waves(rows)) {
-        case 16: hipLaunchKernelGGL(mla_merge_kernel<16>, dim3(merge_grid(rows)), dim3(1024), 0, stream, prm); break;
-        case 4: hipLaunchKernelGGL(mla_merge_kernel<4>, dim3(merge_grid(rows)), dim3(256), 0, stream, prm); break;
-        default: hipLaunchKernelGGL(mla_merge_kernel<1>, dim3(merge_grid((rows + 3) / 4)), dim3(256), 0, stream, prm); break;
-    }
+    launch_merge(rows, prm.batch, false, [&](auto waves, auto read, unsigned grid) {
+        constexpr int kWaves = decltype(waves)::value;
+        hipLaunchKernelGGL((mla_merge_kernel<kWaves, decltype(read)::value>), dim3(grid), dim3(kWaves == 1 ? 256 : 64 * kWaves), 0, stream, prm);
+    });
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[2], stream)) != hipSuccess) return e;
     return hipSuccess;
