@@ -151,8 +151,8 @@ __device__ __forceinline__ void store_b128(void* base, uint32_t bytes, uint32_t 
 // kv_lens (the host never reads the lengths: section 4.2, "Integrating Custom Operators"), in two
 // memory round trips and two wave scans whatever the batch: lane l owns the `chunk` consecutive
 // sequences l * chunk .. l * chunk + chunk - 1 (chunk = the power of two >= batch / 64, so at most 64
-// for the largest batch) and adds up their stream positions from 128-bit loads that are all in
-// flight together; one scan over the 64 lane sums gives the total and every chunk's first position;
+// for the largest batch) and adds up their stream positions from 128-bit loads, up to 20 lengths of them in
+// flight together (above 1024 sequences another round trip for 16 more); one scan over the 64 lane sums gives the total and every chunk's first position;
 // a stream position is then located by one ballot (its chunk) and one scan over that chunk's
 // sequences.  The loads go through a buffer descriptor over kv_lens, so indices past the batch read 0.
 struct WavePlan {
@@ -208,14 +208,14 @@ __device__ __forceinline__ const void* window_ptr(const SeqWindow& win, const u3
     return reinterpret_cast<const void*>((uintptr_t)a);
 }
 
-template <int kQuads>
-__device__ __forceinline__ int chunk_positions(__amdgpu_buffer_rsrc_t rl, int first, int seg_cost) {
-    u32x4_t v[kQuads];
+// Stream positions of up to 16 sequences, `count` of them (a multiple of four) from `first` on.
+__device__ __forceinline__ int chunk_positions(__amdgpu_buffer_rsrc_t rl, int first, int count, int seg_cost) {
+    u32x4_t v[4];
 #pragma unroll
-    for (int k = 0; k < kQuads; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(rl, (first + 4 * k) * 4, 0, 0);
+    for (int k = 0; k < 4; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(rl, 4 * k < count ? (first + 4 * k) * 4 : 0x7ffffff0, 0, 0);
     int sum = 0;
 #pragma unroll
-    for (int k = 0; k < kQuads; ++k)
+    for (int k = 0; k < 4; ++k)
         sum += stream_len((int)v[k].x, seg_cost) + stream_len((int)v[k].y, seg_cost) +
                stream_len((int)v[k].z, seg_cost) + stream_len((int)v[k].w, seg_cost);
     return sum;
@@ -227,34 +227,33 @@ __device__ __forceinline__ WavePlan wave_plan(const int32_t* __restrict__ kv_len
                                               const void* const* v_ptrs, int batch, int n_pieces, int min_piece,
                                               int seg_cost, int xcd_skew, FewPieces few, int lane, SeqWindow* win, int parts = 1) {
     WavePlan wp;
-    int lg = 0;
-    while ((64 << lg) < batch) ++lg;                       // wave-uniform: batch is a kernel argument
+    const int lg = batch <= 64 ? 0 : 26 - __builtin_clz((unsigned)(batch - 1));      // least with 64 << lg >= batch
     wp.chunk_log2 = lg;
     wp.chunk = 1 << lg;
     const __amdgpu_buffer_rsrc_t rl = make_rsrc(kv_lens, (uint32_t)batch * 4u);
     const int first = lane << lg;
+    const PlanRule rule = plan_rule(n_pieces, min_piece, seg_cost, xcd_skew, few, parts);
     int mine;
     if (win) {
         win->base = 0;
         win->count = 0;
     }
-    switch (lg) {
-        case 0:
-            if (win) window_load(*win, kv_lens, k_ptrs, v_ptrs, batch, 0, batch, lane, seg_cost, mine);
-            else mine = stream_len(__builtin_amdgcn_raw_buffer_load_b32(rl, first * 4, 0, 0), seg_cost);
-            break;
-        case 1: mine = stream_len(__builtin_amdgcn_raw_buffer_load_b32(rl, first * 4, 0, 0), seg_cost) +
-                       stream_len(__builtin_amdgcn_raw_buffer_load_b32(rl, first * 4 + 4, 0, 0), seg_cost); break;
-        case 2: mine = chunk_positions<1>(rl, first, seg_cost); break;
-        case 3: mine = chunk_positions<2>(rl, first, seg_cost); break;
-        case 4: mine = chunk_positions<4>(rl, first, seg_cost); break;
-        case 5: mine = chunk_positions<8>(rl, first, seg_cost); break;
-        default: mine = chunk_positions<16>(rl, first, seg_cost); break;   // batch <= 4096 (checked by the host)
+    if (lg == 0) {
+        if (win) window_load(*win, kv_lens, k_ptrs, v_ptrs, batch, 0, batch, lane, seg_cost, mine);
+        else mine = stream_len(__builtin_amdgcn_raw_buffer_load_b32(rl, first * 4, 0, 0), seg_cost);
+    } else {
+        // Four lengths, at chunk 2 the last two are the next lane's; of longer chunks sixteen more at a time, the first of
+        // them in the same round trip.  (A form for every chunk size is code that all calls jump across.)
+        const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rl, first * 4, 0, 0);
+        mine = 0;
+        for (int k = 4; k < wp.chunk; k += 16) mine += chunk_positions(rl, first + k, wp.chunk - k, seg_cost);
+        mine += stream_len((int)v.x, seg_cost) + stream_len((int)v.y, seg_cost);
+        if (lg > 1) mine += stream_len((int)v.z, seg_cost) + stream_len((int)v.w, seg_cost);
     }
     const int incl = wave_incl_scan_i(mine);
     wp.mine = mine;
     wp.excl = incl - mine;
-    wp.pl = plan_for_total(__builtin_amdgcn_readlane(incl, 63), n_pieces, min_piece, seg_cost, xcd_skew, few, parts);
+    wp.pl = plan_for_total(__builtin_amdgcn_readlane(incl, 63), rule);
     return wp;
 }
 

@@ -646,7 +646,7 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int heads = kMatrix ? prm.share.heads : prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;
     const int parts = kMatrix ? prm.share.parts : prm.parts;
-    const int part = parts == 1 ? 0 : wave / heads;
+    const int part = parts == 1 ? 0 : kMatrix ? wave * prm.share.inv_heads >> 5 : wave / heads;
     const int kvh = blockIdx.z * heads + wave - part * heads;
     if (!kMatrix && kvh >= prm.n_kv_heads) return;
     // A piece's first segment takes its length and pointers from the plan's own round trips, which saves a start two

@@ -34,6 +34,7 @@ struct Plan {
     int n_pieces;   // pieces in use: see plan_for_total
     int seg_cost;
     int xcd_skew;   // per mille; see piece_bound
+    double inv;     // 1 / (pieces that share a part of the stream: an XCD part with skew, else all of it)
 };
 constexpr int kMaxXcdSkew = 200;
 constexpr int kMinSkewPiece = 32 * kPlanRound;      // positions per piece from which the XCD skew applies
@@ -47,26 +48,57 @@ XATTN_HD int stream_len(int len, int seg_cost) { return len > 0 ? len + seg_cost
 struct FewPieces {
     int pieces, min_piece;
 };
-XATTN_HD Plan plan_for_total(int total, int n_pieces, int min_piece, int seg_cost, int xcd_skew = 0, FewPieces few = {0, 1}, int parts = 1) {
-    int n = total / (min_piece > 0 ? min_piece : 1);
-    int n_few = total / few.min_piece;
-    n_few = n_few < few.pieces ? n_few : few.pieces;
+// Every wave works the plan out ahead of its first load, so its quotients are products with an inverse: an integer division
+// is some forty dependent instructions, of which a start had a dozen in a row.  floor(a / m) = floor((a + 1/4) / m): the
+// product is within 2^-51 of that, relative, and so closer than the 1 / (4 m) that lie between it and the next integer on
+// either side, for a < 2^47, a / m < 2^31 and m <= kMaxPieces, or for a < 2^31 and any m.  (That, and less code ahead of the
+// first loads: 12 sequences of 100 to 800 tokens, 24 rows of 2 KV heads 12.3 -> 11.8 us; 300 of 30 to 200, 8 rows of 2 17.2 ->
+// 16.7; one of 30001 27.7 -> 27.5; 64 of 512 to 4096 level.)
+XATTN_HD double plan_inverse(int m) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    double r = __builtin_amdgcn_rcp((double)m);      // 1 / m to 2^-20 or better, twice as many bits with each step
+    r = __builtin_fma(__builtin_fma(-(double)m, r, 1.0), r, r);
+    return __builtin_fma(__builtin_fma(-(double)m, r, 1.0), r, r);
+#else
+    return 1.0 / (double)m;
+#endif
+}
+XATTN_HD int plan_quotient(int a, double inv) { return (int)(((double)a + 0.25) * inv); }
+
+// What the plan of a call follows from beside the lengths, and the inverses of the two minima.
+struct PlanRule {
+    int n_pieces, min_piece, seg_cost, xcd_skew;
+    FewPieces few;
+    int parts;
+    double inv_min, inv_few;
+};
+XATTN_HD PlanRule plan_rule(int n_pieces, int min_piece, int seg_cost, int xcd_skew, FewPieces few, int parts) {
+    const int least = min_piece > 0 ? min_piece : 1;
+    return PlanRule{n_pieces, least, seg_cost, xcd_skew, few, parts, plan_inverse(least), plan_inverse(few.min_piece)};
+}
+XATTN_HD Plan plan_for_total(int total, const PlanRule& rule) {
+    int n = plan_quotient(total, rule.inv_min);
+    int n_few = plan_quotient(total, rule.inv_few);
+    n_few = n_few < rule.few.pieces ? n_few : rule.few.pieces;
     n = n < n_few ? n_few : n;
     n = n < 1 ? 1 : n;
     Plan pl;
     pl.total = total;
-    pl.n_pieces = n < n_pieces ? n : n_pieces;
-    pl.seg_cost = seg_cost;
+    pl.n_pieces = n < rule.n_pieces ? n : rule.n_pieces;
+    pl.seg_cost = rule.seg_cost;
     // the skew needs the eight XCD parts to hold the same number of pieces, and pieces long enough for a
     // few per cent of them to be a block or more (where the `parts` waves of a workgroup share a piece, a wave's share of it)
-    const bool can_skew = xcd_skew > 0 && pl.n_pieces % 8 == 0 && total / pl.n_pieces >= kMinSkewPiece * parts;
-    pl.xcd_skew = can_skew ? (xcd_skew < kMaxXcdSkew ? xcd_skew : kMaxXcdSkew) : 0;
+    const bool can_skew = rule.xcd_skew > 0 && pl.n_pieces % 8 == 0 && total >= (long long)kMinSkewPiece * rule.parts * pl.n_pieces;
+    pl.xcd_skew = can_skew ? (rule.xcd_skew < kMaxXcdSkew ? rule.xcd_skew : kMaxXcdSkew) : 0;
+    pl.inv = plan_inverse(can_skew ? pl.n_pieces >> 3 : pl.n_pieces);
     return pl;
 }
+XATTN_HD Plan plan_for_total(int total, int n_pieces, int min_piece, int seg_cost, int xcd_skew = 0, FewPieces few = {0, 1}, int parts = 1) {
+    return plan_for_total(total, plan_rule(n_pieces, min_piece, seg_cost, xcd_skew, few, parts));
+}
 
-// floor(i * span / m) in 32-bit arithmetic: i * (span / m) + i * (span % m) / m, with i <= m <= 65536
-// so that i * (span % m) < m^2 <= 2^32.
-XATTN_HD uint32_t scaled_index(uint32_t i, uint32_t span, uint32_t m) { return i * (span / m) + i * (span % m) / m; }
+// floor(i * span / m), i <= m <= 65536 (see plan_inverse).
+XATTN_HD uint32_t scaled_index(uint32_t i, uint32_t span, double inv_m) { return (uint32_t)(((double)i * (double)span + 0.25) * inv_m); }
 
 // The chip's eight XCDs do not stream at the same rate: measured on MI355X, the odd-numbered ones
 // take about 7 % longer than the even-numbered ones for the same bytes, whatever data they are given.
@@ -88,11 +120,11 @@ XATTN_HD int piece_bound(const Plan& pl, int p) {
     if (p >= pl.n_pieces) return pl.total;
     uint32_t x;
     if (pl.xcd_skew == 0) {
-        x = scaled_index((uint32_t)p, (uint32_t)pl.total, (uint32_t)pl.n_pieces);
+        x = scaled_index((uint32_t)p, (uint32_t)pl.total, pl.inv);
     } else {
-        const uint32_t m = (uint32_t)pl.n_pieces / 8u, part = (uint32_t)p / m;
+        const uint32_t m = (uint32_t)pl.n_pieces / 8u, part = (uint32_t)plan_quotient(p, pl.inv);
         const uint32_t a = xcd_part_start(pl, (int)part), b = xcd_part_start(pl, (int)part + 1);
-        x = a + scaled_index((uint32_t)p - part * m, b - a, m);
+        x = a + scaled_index((uint32_t)p - part * m, b - a, pl.inv);
     }
     const uint32_t rounded = (x + kPlanRound / 2) / kPlanRound * kPlanRound;
     return rounded < (uint32_t)pl.total ? (int)rounded : pl.total;
@@ -137,13 +169,14 @@ XATTN_HD DecodeWork decode_work(const Plan& pl, int grid_x, int parts, int rows_
     w.rows = rows_max;
     // When the pieces in use leave enough workgroups idle, every tile of 16 rows gets one of its own (35 rows, 53
     // sequences of 6 to 100 tokens: 17.5 us in pairs, 10.0 us apart).
-    if (rows_max == 32 && parts * (slots_per_xcd / ((rows_total + 15) / 16)) >= per_xcd) w.rows = 16;
-    const int n_groups = (rows_total + w.rows - 1) / w.rows, slot = bid >> 3;
+    const int sets_needed = (per_xcd + parts - 1) / parts;
+    if (rows_max == 32 && (rows_total + 15) / 16 * sets_needed <= slots_per_xcd) w.rows = 16;
+    const int n_groups = w.rows == rows_max ? (rows_total + rows_max - 1) / rows_max : (rows_total + 15) / 16, slot = bid >> 3;
     const int set = n_groups == 1 ? slot : slot / n_groups;
-    const int sets = slots_per_xcd / n_groups, local = part * sets + set;
+    const int local = part == 0 ? set : part * (slots_per_xcd / n_groups) + set;
     w.row0 = (slot - set * n_groups) * w.rows;
     w.piece = (bid & 7) * per_xcd + local;
-    w.any = set < sets && local < per_xcd && w.piece < pl.n_pieces;
+    w.any = (set + 1) * n_groups <= slots_per_xcd && local < per_xcd && w.piece < pl.n_pieces;
     return w;
 }
 
@@ -152,15 +185,18 @@ XATTN_HD DecodeWork decode_work(const Plan& pl, int grid_x, int parts, int rows_
 // partial result.  Four heads of 256 bytes side by side stream as fast as eight; two cost 2.7 % of a large call, one 6 to 9.
 struct PieceShare {
     int heads, parts;
+    int inv_heads;      // wave w < 32 is of part w * inv_heads / 32
 };
 XATTN_HD PieceShare piece_share(int n_kv_heads, int max_waves) {
     int h = n_kv_heads;
     if (h > 4) h = h % 4 == 0 ? 4 : h % 3 == 0 ? 3 : h < max_waves ? h : max_waves;
-    return PieceShare{h, max_waves / h};
+    return PieceShare{h, max_waves / h, (31 + h) / h};
 }
 // Positions per part of a piece of `len` positions, all but the last one's: whole 16-key blocks, so parts without any
-// positions come last.
-XATTN_HD int part_positions(int len, int parts) { return ((len + parts - 1) / parts + kPlanRound - 1) / kPlanRound * kPlanRound; }
+// positions come last.  (parts: a power of two.)
+XATTN_HD int part_positions(int len, int parts) {
+    return ((int)((uint32_t)(len + parts - 1) >> __builtin_ctz((unsigned)parts)) + kPlanRound - 1) / kPlanRound * kPlanRound;
+}
 // How a part's segment [j0, j1) of a sequence of L tokens joins with its neighbours'.  `left`: positions of the piece behind
 // this part's own, `sub`: part_positions.
 struct PartRun {
@@ -169,10 +205,11 @@ struct PartRun {
     bool ends;     // the sequence's last token is in the piece
 };
 XATTN_HD PartRun part_run(int part, int j0, int j1, int L, int left, int sub) {
-    const int rest = L - j1;
+    const int rest = L - j1, held = rest < left ? rest : left;
     PartRun r;
     r.prev = part > 0 && j0 > 0;
-    r.next = ((rest < left ? rest : left) + sub - 1) / sub;
+    r.next = 0;
+    while (r.next * sub < held) ++r.next;      // seven at most
     r.ends = rest <= left;
     return r;
 }
