@@ -26,6 +26,8 @@ HOSTTEST_SOURCES = ["xattn_error.cpp", "xtensor_pool.cpp", "xbeam.cpp", os.path.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
                # packed-fp32 VALU forms are switched off for all device code of this library
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+               # a kernel's first scalar arguments, up to 14 words of them, are in registers when its waves start
+               "-mllvm", "-amdgpu-kernarg-preload-count=14",
                "-Wall", "-Wno-unused-command-line-argument", "-pthread"]
 GXX_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra", "-pthread"]
 

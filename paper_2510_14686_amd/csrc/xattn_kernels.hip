@@ -636,17 +636,23 @@ __device__ __forceinline__ void state_add(MatrixState& st, const char* area, int
 // count; 16 measured best of 0 / 16 / 48: 0.2 to 1 % on the four large workloads).
 constexpr int kGqaSegCost = 16;
 
+// What the plan needs are arguments of their own, not members of prm: the first 14 words of scalar arguments are in registers
+// when a wave starts (see build.py), so the loads of the lengths, or a merge kernel's of its table, do not wait for one of
+// their addresses.  All kernels so, 0.4 to 0.5 us per launch: 695 tokens 9.5 -> 8.7 us, one sequence of 3000 12.4 -> 11.5, 300 of 30 to
+// 200 16.5 -> 15.4, one of 30001 27.4 -> 26.6, 64 of 512 to 4096 92.5 -> 92.0, latent-KV 40 of 50 to 200, 16 rows 11.3 -> 10.5.
 template <int R, bool kMatrix, int kPv>
-__global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
+__global__ __launch_bounds__(512) void split_decode_kernel(const int32_t* __restrict__ kv_lens, const void* const* k_ptrs, const void* const* v_ptrs,
+                                                           int batch, int n_pieces, int min_piece, int few_pieces, int few_min,
+                                                           int xcd_skew, uint32_t share, DecodeParams prm) {
     constexpr int kTiles = kMatrix ? R / 16 : 1;
     // Behind the waves' own parts: the states of all waves of a workgroup but the first of every KV head.
     constexpr int kStates = (kMaxWavesPerBlock - 1) * kTiles;
     __shared__ __attribute__((aligned(16))) char lds[kMatrix ? kMaxWavesPerBlock * kLdsPerWave + kStates * kLdsPerState : 16];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int heads = kMatrix ? prm.share.heads : prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;
-    const int parts = kMatrix ? prm.share.parts : prm.parts;
-    const int part = parts == 1 ? 0 : kMatrix ? wave * prm.share.inv_heads >> 5 : wave / heads;
+    const int heads = kMatrix ? (int)(share & 255u) : prm.n_kv_heads < kMaxWavesPerBlock ? prm.n_kv_heads : kMaxWavesPerBlock;
+    const int parts = kMatrix ? (int)(share >> 8 & 255u) : prm.parts;
+    const int part = parts == 1 ? 0 : kMatrix ? wave * (int)(share >> 16) >> 5 : wave / heads;
     const int kvh = blockIdx.z * heads + wave - part * heads;
     if (!kMatrix && kvh >= prm.n_kv_heads) return;
     // A piece's first segment takes its length and pointers from the plan's own round trips, which saves a start two
@@ -656,10 +662,10 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
     constexpr bool kWindow = kTiles == 1;
     SeqWindow win;
     SeqWindow* const window = kWindow ? &win : nullptr;
-    const void* const* const win_k = kWindow ? prm.k_ptrs : nullptr;
-    const void* const* const win_v = kWindow ? prm.v_ptrs : nullptr;
-    const WavePlan wp = wave_plan(prm.kv_lens, win_k, win_v, prm.batch, kMatrix ? prm.shared_pieces : prm.n_pieces, prm.min_piece_tokens,
-                                  kGqaSegCost, prm.xcd_skew, prm.few, lane, window, kMatrix ? parts : 1);
+    const void* const* const win_k = kWindow ? k_ptrs : nullptr;
+    const void* const* const win_v = kWindow ? v_ptrs : nullptr;
+    const WavePlan wp = wave_plan(kv_lens, win_k, win_v, batch, n_pieces, min_piece, kGqaSegCost, xcd_skew, FewPieces{few_pieces, few_min},
+                                  lane, window, kMatrix ? parts : 1);
     const Plan& pl = wp.pl;
 
     const int bid = blockIdx.x;
@@ -675,14 +681,14 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
         // sequences per wave, the groups of 64 dealt out over the workgroups from the last one, which
         // has no piece of its own when the stream is short.  Of such a workgroup the last wave, which a short piece leaves
         // without keys (30 sequences of 100 to 900 tokens of one KV head by the first wave 11.4 us, by the last 10.9).
-        for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
+        for (int g = gridDim.x - 1 - bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, g, lane, prm.meta);
     }
     if (!work.any || piece0 >= piece1) return;      // the whole workgroup on the matrix path
     if (!kMatrix && s0 >= s1) return;
     const bool active = s0 < s1 && kvh < prm.n_kv_heads;
 
     Walk walk;
-    if (active) wave_locate(wp, prm.kv_lens, win_k, win_v, prm.batch, s0, lane, window, walk.b, walk.j);
+    if (active) wave_locate(wp, kv_lens, win_k, win_v, batch, s0, lane, window, walk.b, walk.j);
     walk.remaining = uniform(s1 - s0);
 
     Segment seg;
@@ -694,16 +700,16 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
         constexpr bool kFirst = kWindow && decltype(first)::value;
         PieceSeg ps;
         auto len_of = [&](int b) {
-            if constexpr (kFirst) return window_len(win, prm.kv_lens, b);
-            else return __builtin_amdgcn_readfirstlane(clamp_len(prm.kv_lens[b]));
+            if constexpr (kFirst) return window_len(win, kv_lens, b);
+            else return __builtin_amdgcn_readfirstlane(clamp_len(kv_lens[b]));
         };
-        if (!next_segment(walk, prm.batch, pl.seg_cost, len_of, ps)) return false;
+        if (!next_segment(walk, batch, pl.seg_cost, len_of, ps)) return false;
         // Everything about a segment is wave-uniform; said so, it lives in scalar registers, and the loads
         // through its descriptors need no loop over the lanes' values.
         out = seg;
         out.b = uniform(ps.b);
-        out.kp = kFirst ? window_ptr(win, win.k, prm.k_ptrs, out.b) : uniform(prm.k_ptrs[out.b]);
-        out.vp = kFirst ? window_ptr(win, win.v, prm.v_ptrs, out.b) : uniform(prm.v_ptrs[out.b]);
+        out.kp = kFirst ? window_ptr(win, win.k, k_ptrs, out.b) : uniform(k_ptrs[out.b]);
+        out.vp = kFirst ? window_ptr(win, win.v, v_ptrs, out.b) : uniform(v_ptrs[out.b]);
         out.L = uniform(ps.L);
         out.j0 = uniform(ps.j0);
         out.j1 = uniform(ps.j1);
@@ -780,27 +786,28 @@ __global__ __launch_bounds__(512) void split_decode_kernel(DecodeParams prm) {
 // heads 32.3 -> 31.8 us; 695 tokens level, 8.9).
 // kRead = kReadFarOnce: one of 30000 tokens, 32 rows of 8 KV heads 39.3 -> 37.0 us; 4 of 2000 to 16000, 16 rows 28.3 -> 27.3.
 template <int kWaves, int kRead>
-__global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(DecodeParams prm) {
+__global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(const int32_t* __restrict__ meta, const float* __restrict__ part_ml,
+                                                                                const float* __restrict__ part_o, uint16_t* __restrict__ out,
+                                                                                float* __restrict__ lse, int batch, uint32_t seq_rows) {
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
-    const uint32_t seq_rows = (uint32_t)(prm.q_len * prm.n_q_heads);
     const uint32_t row = kWaves == 1 ? merge_workgroup<kRead>() * 4 + wave : merge_workgroup<kRead>();
     const uint32_t b = row / seq_rows;
-    if (b >= (uint32_t)prm.batch) return;
-    const int2 fs = reinterpret_cast<const int2*>(prm.meta)[b];
+    if (b >= (uint32_t)batch) return;
+    const int2 fs = reinterpret_cast<const int2*>(meta)[b];
     const int n = fs.y;
     if (n == 1) return;
     const MergeShare sh = merge_share<kWaves>(n, wave);
     if (sh.alone && kWaves > 1 && wave > 0) return;       // few slots: the first wave does the row
-    uint32_t* outp = reinterpret_cast<uint32_t*>(prm.out + (long)row * kHeadDim) + lane;
+    uint32_t* outp = reinterpret_cast<uint32_t*>(out + (long)row * kHeadDim) + lane;
     if (n == 0) {
         *outp = 0u;
-        if (prm.lse && lane == 0) prm.lse[row] = kNegInf;
+        if (lse && lane == 0) lse[row] = kNegInf;
         return;
     }
     const long stride_rows = seq_rows, first_row = (long)fs.x * stride_rows + (row - b * seq_rows);
-    const float2* ml = reinterpret_cast<const float2*>(prm.part_ml) + first_row;
-    const f32x2_t* po = reinterpret_cast<const f32x2_t*>(prm.part_o + first_row * kHeadDim) + lane;
+    const float2* ml = reinterpret_cast<const float2*>(part_ml) + first_row;
+    const f32x2_t* po = reinterpret_cast<const f32x2_t*>(part_o + first_row * kHeadDim) + lane;
     // Lane i holds (m, l) of slot first + i of the current group of 64 slots; the first 8 slots' partial
     // rows are requested in the same breath, so a typical row (up to 8 segments) costs one round trip.
     float M = kNegInf, l = 0.0f, o0 = 0.0f, o1 = 0.0f;
@@ -843,19 +850,19 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(
     }
     if constexpr (kWaves > 1) {
         if (!sh.alone) {                                  // the waves' sums, each against its own maximum, meet in LDS
-            __shared__ float2 part[kWaves][64], part_ml[kWaves];
+            __shared__ float2 part[kWaves][64], wave_ml[kWaves];
             part[wave][lane] = make_float2(o0, o1);
-            if (lane == 0) part_ml[wave] = make_float2(M, l);
+            if (lane == 0) wave_ml[wave] = make_float2(M, l);
             __syncthreads();
             if (wave > 0) return;
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) M = fmaxf(M, part_ml[w].x);
+            for (int w = 1; w < kWaves; ++w) M = fmaxf(M, wave_ml[w].x);
             const float m_use = (M == kNegInf) ? 0.0f : M;
             l = o0 = o1 = 0.0f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
-                const float f = fast_exp2(part_ml[w].x - m_use);
-                l = __builtin_fmaf(part_ml[w].y, f, l);
+                const float f = fast_exp2(wave_ml[w].x - m_use);
+                l = __builtin_fmaf(wave_ml[w].y, f, l);
                 o0 = __builtin_fmaf(part[w][lane].x, f, o0);
                 o1 = __builtin_fmaf(part[w][lane].y, f, o1);
             }
@@ -863,7 +870,7 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(
     }
     const float inv = l > 0.0f ? 1.0f / l : 0.0f;
     *outp = cvt_bf16(o0 * inv, o1 * inv);
-    if (prm.lse && lane == 0) prm.lse[row] = l > 0.0f ? (M + __log2f(l)) * kLn2 : kNegInf;
+    if (lse && lane == 0) lse[row] = l > 0.0f ? (M + __log2f(l)) * kLn2 : kNegInf;
 }
 
 // ---------------------------------------------------------------------------------- write_kvcache
@@ -871,17 +878,18 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void merge_kernel(
 // each) to row kv_len - q_len + t of the sequence's ranges, 16 bytes per lane, one half of the workgroup the
 // K row and the other the V row.  Bound by its round trips: the rows are read while the length and the
 // addresses are fetched (256 sequences of 2 KB rows, the call behind an append: 57.9 -> 57.3 us).
-__global__ __launch_bounds__(256) void write_kvcache_kernel(WriteParams prm) {
-    const int b = blockIdx.x / prm.q_len, t = blockIdx.x - b * prm.q_len;
+__global__ __launch_bounds__(256) void write_kvcache_kernel(const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, void* const* k_ptrs,
+                                                            void* const* v_ptrs, const int32_t* __restrict__ kv_lens, int q_len, int row_bytes) {
+    const int b = blockIdx.x / q_len, t = blockIdx.x - b * q_len;
     const bool is_v = threadIdx.x >= 128;
-    const char* src = reinterpret_cast<const char*>(is_v ? prm.v_new : prm.k_new) + (long)blockIdx.x * prm.row_bytes;
+    const char* src = reinterpret_cast<const char*>(is_v ? v_new : k_new) + (long)blockIdx.x * row_bytes;
     const int first = (threadIdx.x & 127) * 16;
     uint4 x = make_uint4(0u, 0u, 0u, 0u);
-    if (first < prm.row_bytes) x = *reinterpret_cast<const uint4*>(src + first);
-    const long pos = (long)prm.kv_lens[b] - prm.q_len + t;
-    char* dst = static_cast<char*>(is_v ? prm.v_ptrs[b] : prm.k_ptrs[b]) + pos * prm.row_bytes;
+    if (first < row_bytes) x = *reinterpret_cast<const uint4*>(src + first);
+    const long pos = (long)kv_lens[b] - q_len + t;
+    char* dst = static_cast<char*>(is_v ? v_ptrs[b] : k_ptrs[b]) + pos * row_bytes;
     if (pos < 0) return;
-    for (int i = first; i < prm.row_bytes; i += 128 * 16) {
+    for (int i = first; i < row_bytes; i += 128 * 16) {
         if (i != first) x = *reinterpret_cast<const uint4*>(src + i);
         *reinterpret_cast<uint4*>(dst + i) = x;
     }
@@ -889,14 +897,18 @@ __global__ __launch_bounds__(256) void write_kvcache_kernel(WriteParams prm) {
 
 template <int R, bool kMatrix, int kPv = kPvBf16x3>
 hipError_t launch_decode_r(const DecodeParams& prm, dim3 grid, dim3 block, hipStream_t stream) {
-    hipLaunchKernelGGL((split_decode_kernel<R, kMatrix, kPv>), grid, block, 0, stream, prm);
+    const uint32_t share = (uint32_t)prm.share.heads | (uint32_t)prm.share.parts << 8 | (uint32_t)prm.share.inv_heads << 16;
+    hipLaunchKernelGGL((split_decode_kernel<R, kMatrix, kPv>), grid, block, 0, stream, prm.kv_lens, prm.k_ptrs, prm.v_ptrs, prm.batch,
+                       kMatrix ? prm.shared_pieces : prm.n_pieces, prm.min_piece_tokens, prm.few.pieces, prm.few.min_piece, prm.xcd_skew,
+                       share, prm);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_write_kvcache(const WriteParams& prm, hipStream_t stream) {
-    hipLaunchKernelGGL(write_kvcache_kernel, dim3((unsigned)(prm.batch * prm.q_len)), dim3(256), 0, stream, prm);
+    hipLaunchKernelGGL(write_kvcache_kernel, dim3((unsigned)(prm.batch * prm.q_len)), dim3(256), 0, stream, prm.k_new, prm.v_new,
+                       prm.k_ptrs, prm.v_ptrs, prm.kv_lens, prm.q_len, prm.row_bytes);
     return hipGetLastError();
 }
 
@@ -958,7 +970,8 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
     // Fewer rows are read as fast either way, or 0.2 us faster through the L2s.
     launch_merge(rows, prm.batch, rows < 256, [&](auto waves, auto read, unsigned grid) {
         constexpr int kWaves = decltype(waves)::value;
-        hipLaunchKernelGGL((merge_kernel<kWaves, decltype(read)::value>), dim3(grid), dim3(kWaves == 1 ? 256 : 64 * kWaves), 0, stream, prm);
+        hipLaunchKernelGGL((merge_kernel<kWaves, decltype(read)::value>), dim3(grid), dim3(kWaves == 1 ? 256 : 64 * kWaves), 0, stream, prm.meta,
+                           prm.part_ml, prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)(prm.q_len * prm.n_q_heads));
     });
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[2], stream)) != hipSuccess) return e;

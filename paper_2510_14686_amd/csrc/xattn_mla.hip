@@ -376,17 +376,19 @@ __device__ __forceinline__ void mla_block(MlaTile& st, const char* qk_base, cons
 // kMode: 0 = default (hi + lo weights in the first mla_exact_blocks() blocks of a segment and wherever a key
 // dominates its row), 1 = hi + lo weights everywhere, 2 = one bf16 per weight everywhere.
 template <int NW, int kMode>
-__global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
+__global__ __launch_bounds__(64 * NW) void mla_decode_kernel(
+        const int32_t* __restrict__ kv_lens, const void* const* c_ptrs, int batch, int n_pieces, int min_piece,
+        int few_pieces, int few_min, int xcd_skew, int q_len, int n_heads, MlaParams prm) {
     __shared__ __attribute__((aligned(16))) char lds_c[kStages * kLdsBlock];
     // Per wave: the Q chunks of steps kQRegSteps.. (each lane reads back what it wrote).
     __shared__ __attribute__((aligned(16))) char lds_q[NW * kQLdsWave];
     static_assert(NW * kStageWave <= kStages * kLdsBlock, "output staging must fit the block buffers");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = lane >> 4, n = lane & 15;
-    const int T = prm.q_len, H = prm.n_heads, rows_total = T * H;
+    const int T = q_len, H = n_heads, rows_total = T * H;
     SeqWindow win;
-    const WavePlan wp = wave_plan(prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kMlaSegCost,
-                                  prm.xcd_skew, prm.few, lane, &win);
+    const WavePlan wp = wave_plan(kv_lens, c_ptrs, nullptr, batch, n_pieces, min_piece, kMlaSegCost,
+                                  xcd_skew, FewPieces{few_pieces, few_min}, lane, &win);
     const Plan& pl = wp.pl;
     const int per_xcd = (pl.n_pieces + 7) >> 3;
     // Workgroup ids go round-robin over the 8 XCDs.  Of an XCD's workgroups, consecutive ones are the
@@ -403,19 +405,19 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     if (tid < 64) {
         // For the merge kernel: first partial slot and number of segments of every sequence, 64
         // sequences per wave, the groups of 64 dealt out over the workgroups.
-        for (int g = bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
+        for (int g = bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, g, lane, prm.meta);
     }
     if (!active) return;       // the whole workgroup: every wave computed the same plan
 
     Walk walk;
-    wave_locate(wp, prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, s0, lane, &win, walk.b, walk.j);
+    wave_locate(wp, kv_lens, c_ptrs, nullptr, batch, s0, lane, &win, walk.b, walk.j);
     walk.remaining = uniform(s1 - s0);
 
     // Lane n's row: index within the sequence's T * H rows.
     const int wave_row0 = (row_group * NW + wave) * 16, row = wave_row0 + n;
     char* q_lds = lds_q + wave * kQLdsWave + lane * 16;
     char* stage = lds_c + wave * kStageWave;
-    const int exact_blocks = mla_exact_blocks(pl, rows_total, prm.n_pieces);
+    const int exact_blocks = mla_exact_blocks(pl, rows_total, n_pieces);
     const DmaLane dma = dma_lane(lane);
     const int my_loads = (kDmaPerBlock - wave + NW - 1) / NW;      // block loads this wave issues per block
     const int qk_off = n * kPitch + kb * 16;
@@ -428,13 +430,13 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(MlaParams prm) {
     };
 
     PieceSeg ps;
-    while (uniform(next_segment(walk, prm.batch, pl.seg_cost,
-                                [&](int bb) { return window_len(win, prm.kv_lens, bb); }, ps))) {
+    while (uniform(next_segment(walk, batch, pl.seg_cost,
+                                [&](int bb) { return window_len(win, kv_lens, bb); }, ps))) {
         const int b = uniform(ps.b), L = uniform(ps.L), j0 = uniform(ps.j0), j1 = uniform(ps.j1);
         const bool whole = uniform(ps.whole) != 0;
         const long slot = (long)uniform(p) + b;
         const unsigned long long cbytes = (unsigned long long)L * kRowB;
-        const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, prm.c_ptrs, b);
+        const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, c_ptrs, b);
         // raw buffer descriptor: base, no stride, bytes, 32-bit raw format
         const u32x4_t rc = {(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)caddr),
                             (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(caddr >> 32) & 0xffffu)),
@@ -985,15 +987,17 @@ __device__ __forceinline__ void tile_block(TileAcc& o, TileRow& st, const f32x16
 // kMode: as mla_decode_kernel.  The form with two waves per tile: see mla_tile_split.  There each of the two computes the
 // tile's scores and weights for itself and accumulates half of the columns.
 template <int kMode>
-__global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm) {
+__global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(
+        const int32_t* __restrict__ kv_lens, const void* const* c_ptrs, int batch, int n_pieces, int min_piece,
+        int few_pieces, int few_min, int xcd_skew, int q_len, int n_heads, MlaParams prm) {
     __shared__ __attribute__((aligned(16))) char lds_c[kTileStages * kTileBlock];
     __shared__ __attribute__((aligned(16))) char lds_q[kTileWaves * kTileQLds];      // each lane reads back what it wrote
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     const int n = lane & 31, h = lane >> 5;
-    const int T = prm.q_len, H = prm.n_heads, rows_total = T * H;
+    const int T = q_len, H = n_heads, rows_total = T * H;
     SeqWindow win;
-    const WavePlan wp = wave_plan(prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kMlaSegCost,
-                                  prm.xcd_skew, prm.few, lane, &win);
+    const WavePlan wp = wave_plan(kv_lens, c_ptrs, nullptr, batch, n_pieces, min_piece, kMlaSegCost,
+                                  xcd_skew, FewPieces{few_pieces, few_min}, lane, &win);
     const Plan& pl = wp.pl;
     auto work = [&](auto split_c) {
         constexpr int kSplit = decltype(split_c)::value;             // waves per tile
@@ -1004,11 +1008,11 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
         const int p = mine.piece, s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
         const bool active = mine.any && s0 < s1;
         if (tid < 64)
-            for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
+            for (int g = gridDim.x - 1 - bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, g, lane, prm.meta);
         if (!active) return;       // the whole workgroup: every wave computed the same plan
 
         Walk walk;
-        wave_locate(wp, prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, s0, lane, &win, walk.b, walk.j);
+        wave_locate(wp, kv_lens, c_ptrs, nullptr, batch, s0, lane, &win, walk.b, walk.j);
         walk.remaining = uniform(s1 - s0);
         dma_wait_all();
 
@@ -1018,7 +1022,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
         const int row = wave_row0 + n;
         char* q_lds = lds_q + wave * kTileQLds + lane * 16;
         char* stage = lds_c + tile * (kTileRows * kTileStagePitch) + part * (kN * 64);
-        const int exact_blocks = mla_exact_blocks(pl, rows_total, prm.n_pieces);
+        const int exact_blocks = mla_exact_blocks(pl, rows_total, n_pieces);
         const TileDma dma = tile_dma(wave, lane);
         TileReads rd = tile_reads(lane);
         rd.value += part * (kN * 64);
@@ -1029,13 +1033,13 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
         };
 
         PieceSeg ps;
-        while (uniform(next_segment(walk, prm.batch, pl.seg_cost,
-                                    [&](int bb) { return window_len(win, prm.kv_lens, bb); }, ps))) {
+        while (uniform(next_segment(walk, batch, pl.seg_cost,
+                                    [&](int bb) { return window_len(win, kv_lens, bb); }, ps))) {
             const int b = uniform(ps.b), L = uniform(ps.L), j0 = uniform(ps.j0), j1 = uniform(ps.j1);
             const bool whole = uniform(ps.whole) != 0;
             const long slot = (long)uniform(p) + b;
             const unsigned long long cbytes = (unsigned long long)L * kRowB;
-            const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, prm.c_ptrs, b);
+            const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, c_ptrs, b);
             const u32x4_t rc = {(uint32_t)uniform((int)(uint32_t)caddr), (uint32_t)uniform((int)((uint32_t)(caddr >> 32) & 0xffffu)),
                                 cbytes > 0xffffffffull ? 0xffffffffu : (uint32_t)cbytes, 0x00020000u};
             const int n_blocks = (j1 - j0 + kMlaKeys - 1) / kMlaKeys;
@@ -1248,7 +1252,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(MlaParams prm
             __syncthreads();          // the next segment's first block goes to buffer 0, which staged output until here
         }
     };
-    if (mla_tile_split(pl, prm.n_pieces, rows_total) == 2) work(std::integral_constant<int, 2>());
+    if (mla_tile_split(pl, n_pieces, rows_total) == 2) work(std::integral_constant<int, 2>());
     else work(std::integral_constant<int, 1>());
 }
 
@@ -1273,7 +1277,9 @@ constexpr int kRowsCols = kColTiles / 4;         // value column tiles per wave
 constexpr int kRowsStagePitch = kRowsCols * 32 + 16;
 
 template <int RT, bool kLo>
-__global__ __launch_bounds__(256 * RT) void mla_rows_kernel(MlaParams prm) {
+__global__ __launch_bounds__(256 * RT) void mla_rows_kernel(
+        const int32_t* __restrict__ kv_lens, const void* const* c_ptrs, int batch, int n_pieces, int min_piece,
+        int few_pieces, int few_min, int xcd_skew, int q_len, int n_heads, MlaParams prm) {
     constexpr int NW = 4 * RT;
     __shared__ __attribute__((aligned(16))) char lds_c[kStages * kLdsBlock];
     __shared__ f32x4_t lds_x[RT][4][64];    // partial scores: [rt][key tile + 2 * half][lane]
@@ -1282,10 +1288,10 @@ __global__ __launch_bounds__(256 * RT) void mla_rows_kernel(MlaParams prm) {
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     const int kb = lane >> 4, n = lane & 15;
     const int rt = wave >> 2, quarter = wave & 3, kt = quarter & 1, half = quarter >> 1;
-    const int T = prm.q_len, H = prm.n_heads, rows_total = T * H;
+    const int T = q_len, H = n_heads, rows_total = T * H;
     SeqWindow win;
-    const WavePlan wp = wave_plan(prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, prm.n_pieces, prm.min_piece_tokens, kRowsSegCost,
-                                  prm.xcd_skew, prm.few, lane, &win);
+    const WavePlan wp = wave_plan(kv_lens, c_ptrs, nullptr, batch, n_pieces, min_piece, kRowsSegCost,
+                                  xcd_skew, FewPieces{few_pieces, few_min}, lane, &win);
     const Plan& pl = wp.pl;
     const int per_xcd = (pl.n_pieces + 7) >> 3;
     const int bid = blockIdx.x;
@@ -1293,11 +1299,11 @@ __global__ __launch_bounds__(256 * RT) void mla_rows_kernel(MlaParams prm) {
     const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
     const bool active = (bid >> 3) < per_xcd && p < pl.n_pieces && s0 < s1;
     if (tid < 64)
-        for (int g = gridDim.x - 1 - bid; 64 * g < prm.batch; g += gridDim.x) wave_write_meta(wp, prm.kv_lens, prm.batch, g, lane, prm.meta);
+        for (int g = gridDim.x - 1 - bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, g, lane, prm.meta);
     if (!active) return;       // the whole workgroup: every wave computed the same plan
 
     Walk walk;
-    wave_locate(wp, prm.kv_lens, prm.c_ptrs, nullptr, prm.batch, s0, lane, &win, walk.b, walk.j);
+    wave_locate(wp, kv_lens, c_ptrs, nullptr, batch, s0, lane, &win, walk.b, walk.j);
     walk.remaining = uniform(s1 - s0);
 
     const DmaLane dma = dma_lane(lane);
@@ -1314,13 +1320,13 @@ __global__ __launch_bounds__(256 * RT) void mla_rows_kernel(MlaParams prm) {
     };
 
     PieceSeg ps;
-    while (uniform(next_segment(walk, prm.batch, pl.seg_cost,
-                                [&](int bb) { return window_len(win, prm.kv_lens, bb); }, ps))) {
+    while (uniform(next_segment(walk, batch, pl.seg_cost,
+                                [&](int bb) { return window_len(win, kv_lens, bb); }, ps))) {
         const int b = uniform(ps.b), L = uniform(ps.L), j0 = uniform(ps.j0), j1 = uniform(ps.j1);
         const bool whole = uniform(ps.whole) != 0;
         const long slot = (long)uniform(p) + b;
         const unsigned long long cbytes = (unsigned long long)L * kRowB;
-        const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, prm.c_ptrs, b);
+        const uint64_t caddr = (uint64_t)(uintptr_t)window_ptr(win, win.k, c_ptrs, b);
         const u32x4_t rc = {(uint32_t)uniform((int)(uint32_t)caddr), (uint32_t)uniform((int)((uint32_t)(caddr >> 32) & 0xffffu)),
                             cbytes > 0xffffffffull ? 0xffffffffu : (uint32_t)cbytes, 0x00020000u};
         const int n_blocks = (j1 - j0 + kMlaKeys - 1) / kMlaKeys;
@@ -1483,27 +1489,28 @@ __global__ __launch_bounds__(256 * RT) void mla_rows_kernel(MlaParams prm) {
 // kRead = kReadOwn: non-temporal there, 1.5 to 2 us more of a large call.  kReadFarOnce, through the L2s before: 3 of 817 to 13076
 // tokens, 64 rows 31.6 -> 30.4 us; 7 of 2216 to 17728, 72 rows 41.1 -> 39.9; one of 30000, 128 rows 37.6 -> 36.7.
 template <int kWaves, int kRead>
-__global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_kernel(MlaParams prm) {
+__global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_kernel(
+        const int32_t* __restrict__ meta, const float* __restrict__ part_ml, const uint16_t* __restrict__ part_o, uint16_t* __restrict__ out,
+        float* __restrict__ lse, int batch, uint32_t seq_rows) {
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
-    const uint32_t seq_rows = (uint32_t)(prm.q_len * prm.n_heads);
     const uint32_t row = kWaves == 1 ? merge_workgroup<kRead>() * 4 + wave : merge_workgroup<kRead>();
     const uint32_t b = row / seq_rows;
-    if (b >= (uint32_t)prm.batch) return;
-    const int2 fs = reinterpret_cast<const int2*>(prm.meta)[b];
+    if (b >= (uint32_t)batch) return;
+    const int2 fs = reinterpret_cast<const int2*>(meta)[b];
     const int n = fs.y;
     if (n == 1) return;
     const MergeShare sh = merge_share<kWaves>(n, wave);
     if (sh.alone && kWaves > 1 && wave > 0) return;       // few slots: the first wave does the row
-    uint4* outp = reinterpret_cast<uint4*>(prm.out + (long)row * kDv) + lane;
+    uint4* outp = reinterpret_cast<uint4*>(out + (long)row * kDv) + lane;
     if (n == 0) {
         *outp = make_uint4(0u, 0u, 0u, 0u);
-        if (prm.lse && lane == 0) prm.lse[row] = kNegInf;
+        if (lse && lane == 0) lse[row] = kNegInf;
         return;
     }
     const long stride_rows = seq_rows, first_row = (long)fs.x * stride_rows + (row - b * seq_rows);
-    const float4* ml = reinterpret_cast<const float4*>(prm.part_ml) + first_row;   // (m, l, lq, 1 / scale)
-    const u32x4_t* po = reinterpret_cast<const u32x4_t*>(prm.part_o + first_row * kDv) + lane;
+    const float4* ml = reinterpret_cast<const float4*>(part_ml) + first_row;   // (m, l, lq, 1 / scale)
+    const u32x4_t* po = reinterpret_cast<const u32x4_t*>(part_o + first_row * kDv) + lane;
     const long po_stride = stride_rows * (kDv / 8);
     auto record = [&](int s) {
         float4 r = make_float4(kNegInf, 0.0f, 0.0f, 0.0f);
@@ -1561,23 +1568,23 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_ker
     if constexpr (kWaves > 1) {
         if (!sh.alone) {                                  // the waves' sums, each against its own maximum, meet in LDS
             __shared__ f32x4_t part[kWaves][2][64];
-            __shared__ f32x4_t part_ml[kWaves];
+            __shared__ f32x4_t wave_ml[kWaves];
             part[wave][0][lane] = f32x4_t{acc[0], acc[1], acc[2], acc[3]};
             part[wave][1][lane] = f32x4_t{acc[4], acc[5], acc[6], acc[7]};
-            if (lane == 0) part_ml[wave] = f32x4_t{M, l, lq, 0.0f};
+            if (lane == 0) wave_ml[wave] = f32x4_t{M, l, lq, 0.0f};
             __syncthreads();
             if (wave > 0) return;
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) M = fmaxf(M, part_ml[w][0]);
+            for (int w = 1; w < kWaves; ++w) M = fmaxf(M, wave_ml[w][0]);
             const float m_all = (M == kNegInf) ? 0.0f : M;
             l = lq = 0.0f;
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc[c] = 0.0f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
-                const float f = fast_exp2(part_ml[w][0] - m_all);
-                l = __builtin_fmaf(part_ml[w][1], f, l);
-                lq = __builtin_fmaf(part_ml[w][2], f, lq);
+                const float f = fast_exp2(wave_ml[w][0] - m_all);
+                l = __builtin_fmaf(wave_ml[w][1], f, l);
+                lq = __builtin_fmaf(wave_ml[w][2], f, lq);
 #pragma unroll
                 for (int c = 0; c < 8; ++c) acc[c] = __builtin_fmaf(part[w][c >> 2][lane][c & 3], f, acc[c]);
             }
@@ -1590,30 +1597,35 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_ker
     w.z = cvt_bf16(acc[4] * inv, acc[5] * inv);
     w.w = cvt_bf16(acc[6] * inv, acc[7] * inv);
     *outp = w;
-    if (prm.lse && lane == 0) prm.lse[row] = l > 0.0f ? (M + __log2f(l)) * kLn2 : kNegInf;
+    if (lse && lane == 0) lse[row] = l > 0.0f ? (M + __log2f(l)) * kLn2 : kNegInf;
+}
+
+// A decode kernel on its arguments: those of the plan ahead of prm, see split_decode_kernel.
+template <typename Kernel>
+hipError_t launch_mla(Kernel kernel, const MlaParams& prm, dim3 grid, int threads, hipStream_t stream) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, prm.kv_lens, prm.c_ptrs, prm.batch, prm.n_pieces, prm.min_piece_tokens,
+                       prm.few.pieces, prm.few.min_piece, prm.xcd_skew, prm.q_len, prm.n_heads, prm);
+    return hipGetLastError();
 }
 
 template <int NW>
 hipError_t launch_mla_16(const MlaParams& prm, dim3 grid, hipStream_t stream) {
-    if (prm.weight_mode == 1) hipLaunchKernelGGL((mla_decode_kernel<NW, 1>), grid, dim3(64 * NW), 0, stream, prm);
-    else if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_decode_kernel<NW, 2>), grid, dim3(64 * NW), 0, stream, prm);
-    else hipLaunchKernelGGL((mla_decode_kernel<NW, 0>), grid, dim3(64 * NW), 0, stream, prm);
-    return hipGetLastError();
+    if (prm.weight_mode == 1) return launch_mla(mla_decode_kernel<NW, 1>, prm, grid, 64 * NW, stream);
+    if (prm.weight_mode == 2) return launch_mla(mla_decode_kernel<NW, 2>, prm, grid, 64 * NW, stream);
+    return launch_mla(mla_decode_kernel<NW, 0>, prm, grid, 64 * NW, stream);
 }
 
 hipError_t launch_mla_tile(const MlaParams& prm, hipStream_t stream) {
     const dim3 grid((unsigned)mla_tile_grid(prm.n_pieces, prm.q_len * prm.n_heads));
-    if (prm.weight_mode == 1) hipLaunchKernelGGL(mla_tile_kernel<1>, grid, dim3(64 * kTileWaves), 0, stream, prm);
-    else if (prm.weight_mode == 2) hipLaunchKernelGGL(mla_tile_kernel<2>, grid, dim3(64 * kTileWaves), 0, stream, prm);
-    else hipLaunchKernelGGL(mla_tile_kernel<0>, grid, dim3(64 * kTileWaves), 0, stream, prm);
-    return hipGetLastError();
+    if (prm.weight_mode == 1) return launch_mla(mla_tile_kernel<1>, prm, grid, 64 * kTileWaves, stream);
+    if (prm.weight_mode == 2) return launch_mla(mla_tile_kernel<2>, prm, grid, 64 * kTileWaves, stream);
+    return launch_mla(mla_tile_kernel<0>, prm, grid, 64 * kTileWaves, stream);
 }
 
 template <int RT>
 hipError_t launch_mla_rows(const MlaParams& prm, dim3 grid, hipStream_t stream) {
-    if (prm.weight_mode == 2) hipLaunchKernelGGL((mla_rows_kernel<RT, false>), grid, dim3(256 * RT), 0, stream, prm);
-    else hipLaunchKernelGGL((mla_rows_kernel<RT, true>), grid, dim3(256 * RT), 0, stream, prm);
-    return hipGetLastError();
+    if (prm.weight_mode == 2) return launch_mla(mla_rows_kernel<RT, false>, prm, grid, 256 * RT, stream);
+    return launch_mla(mla_rows_kernel<RT, true>, prm, grid, 256 * RT, stream);
 }
 
 }  // namespace
@@ -1647,7 +1659,8 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     const long rows = (long)prm.batch * rows_total;
     launch_merge(rows, prm.batch, false, [&](auto waves, auto read, unsigned grid) {
         constexpr int kWaves = decltype(waves)::value;
-        hipLaunchKernelGGL((mla_merge_kernel<kWaves, decltype(read)::value>), dim3(grid), dim3(kWaves == 1 ? 256 : 64 * kWaves), 0, stream, prm);
+        hipLaunchKernelGGL((mla_merge_kernel<kWaves, decltype(read)::value>), dim3(grid), dim3(kWaves == 1 ? 256 : 64 * kWaves), 0, stream, prm.meta,
+                           prm.part_ml, prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)rows_total);
     });
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[2], stream)) != hipSuccess) return e;
