@@ -84,19 +84,19 @@ inline int merge_waves(long rows) { return rows <= 512 ? 16 : rows <= 2048 ? 4 :
 constexpr int kReadOwn = 0, kReadFar = 1, kReadFarOnce = 2;
 // Workgroups of a merge kernel whose work is `n` of them in the order of the output rows: a multiple of the eight XCDs.
 inline unsigned merge_grid(long n) { return (unsigned)((n + 7) / 8 * 8); }
-// launch(waves per row, kRead..., workgroups), the first two as types.
+// Returns launch(waves per row, kRead..., workgroups), the first two as types.
 template <typename Launch>
-inline void launch_merge(long rows, int batch, bool far_cached, Launch launch) {
+inline hipError_t launch_merge(long rows, int batch, bool far_cached, Launch launch) {
     auto with_waves = [&](auto read) {
         switch (merge_waves(rows)) {
-            case 16: launch(std::integral_constant<int, 16>(), read, merge_grid(rows)); break;
-            case 4: launch(std::integral_constant<int, 4>(), read, merge_grid(rows)); break;
-            default: launch(std::integral_constant<int, 1>(), read, merge_grid((rows + 3) / 4)); break;
+            case 16: return launch(std::integral_constant<int, 16>(), read, merge_grid(rows));
+            case 4: return launch(std::integral_constant<int, 4>(), read, merge_grid(rows));
+            default: return launch(std::integral_constant<int, 1>(), read, merge_grid((rows + 3) / 4));
         }
     };
-    if (batch >= 8) with_waves(std::integral_constant<int, kReadOwn>());
-    else if (far_cached) with_waves(std::integral_constant<int, kReadFar>());
-    else with_waves(std::integral_constant<int, kReadFarOnce>());
+    if (batch >= 8) return with_waves(std::integral_constant<int, kReadOwn>());
+    if (far_cached) return with_waves(std::integral_constant<int, kReadFar>());
+    return with_waves(std::integral_constant<int, kReadFarOnce>());
 }
 
 // Latent-KV (MLA-shaped) decode: every head reads the same cached row of 576 bf16 per token.

@@ -37,6 +37,7 @@
 
 #include "xattn_device.h"
 #include "xattn_kernels.h"
+#include "xattn_launch.h"
 
 namespace xattn {
 namespace {
@@ -901,18 +902,16 @@ __global__ __launch_bounds__(256) void write_kvcache_kernel(const uint16_t* __re
 template <int R, bool kMatrix, int kPv = kPvBf16x3>
 hipError_t launch_decode_r(const DecodeParams& prm, dim3 grid, dim3 block, hipStream_t stream) {
     const uint32_t share = (uint32_t)prm.share.heads | (uint32_t)prm.share.parts << 8 | (uint32_t)prm.share.inv_heads << 16;
-    hipLaunchKernelGGL((split_decode_kernel<R, kMatrix, kPv>), grid, block, 0, stream, prm.kv_lens, prm.k_ptrs, prm.v_ptrs, prm.batch,
-                       kMatrix ? prm.shared_pieces : prm.n_pieces, prm.min_piece_tokens, prm.few.pieces, prm.few.min_piece, prm.xcd_skew,
-                       share, (int)grid.x, prm);
-    return hipGetLastError();
+    return launch(split_decode_kernel<R, kMatrix, kPv>, grid, (int)block.x, stream, prm.kv_lens, prm.k_ptrs, prm.v_ptrs, prm.batch,
+                  kMatrix ? prm.shared_pieces : prm.n_pieces, prm.min_piece_tokens, prm.few.pieces, prm.few.min_piece, prm.xcd_skew,
+                  share, (int)grid.x, prm);
 }
 
 }  // namespace
 
 hipError_t launch_write_kvcache(const WriteParams& prm, hipStream_t stream) {
-    hipLaunchKernelGGL(write_kvcache_kernel, dim3((unsigned)(prm.batch * prm.q_len)), dim3(256), 0, stream, prm.k_new, prm.v_new,
-                       prm.k_ptrs, prm.v_ptrs, prm.kv_lens, prm.q_len, prm.row_bytes);
-    return hipGetLastError();
+    return launch(write_kvcache_kernel, dim3((unsigned)(prm.batch * prm.q_len)), 256, stream, prm.k_new, prm.v_new, prm.k_ptrs, prm.v_ptrs,
+                  prm.kv_lens, prm.q_len, prm.row_bytes);
 }
 
 // Measured on MI355X, the matrix path is the faster one from a single query row per KV head up, although most
@@ -971,12 +970,12 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
     if (events && (e = hipEventRecord(events[1], stream)) != hipSuccess) return e;
     const long rows = (long)prm.batch * prm.q_len * prm.n_q_heads;
     // Fewer rows are read as fast either way, or 0.2 us faster through the L2s.
-    launch_merge(rows, prm.batch, rows < 256, [&](auto waves, auto read, unsigned grid) {
+    e = launch_merge(rows, prm.batch, rows < 256, [&](auto waves, auto read, unsigned grid) {
         constexpr int kWaves = decltype(waves)::value;
-        hipLaunchKernelGGL((merge_kernel<kWaves, decltype(read)::value>), dim3(grid), dim3(kWaves == 1 ? 256 : 64 * kWaves), 0, stream, prm.meta,
-                           prm.part_ml, prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)(prm.q_len * prm.n_q_heads));
+        return launch(merge_kernel<kWaves, decltype(read)::value>, dim3(grid), kWaves == 1 ? 256 : 64 * kWaves, stream, prm.meta, prm.part_ml,
+                      prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)(prm.q_len * prm.n_q_heads));
     });
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[2], stream)) != hipSuccess) return e;
     return hipSuccess;
 }

@@ -44,6 +44,7 @@
 
 #include "xattn_device.h"
 #include "xattn_kernels.h"
+#include "xattn_launch.h"
 
 namespace xattn {
 namespace {
@@ -1603,9 +1604,8 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_ker
 // A decode kernel on its arguments: those of the plan ahead of prm, see split_decode_kernel.
 template <typename Kernel>
 hipError_t launch_mla(Kernel kernel, const MlaParams& prm, dim3 grid, int threads, hipStream_t stream) {
-    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, prm.kv_lens, prm.c_ptrs, prm.batch, prm.n_pieces, prm.min_piece_tokens,
-                       prm.few.pieces, prm.few.min_piece, prm.xcd_skew, prm.q_len, prm.n_heads, prm);
-    return hipGetLastError();
+    return launch(kernel, grid, threads, stream, prm.kv_lens, prm.c_ptrs, prm.batch, prm.n_pieces, prm.min_piece_tokens, prm.few.pieces,
+                  prm.few.min_piece, prm.xcd_skew, prm.q_len, prm.n_heads, prm);
 }
 
 template <int NW>
@@ -1657,12 +1657,12 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[1], stream)) != hipSuccess) return e;
     const long rows = (long)prm.batch * rows_total;
-    launch_merge(rows, prm.batch, false, [&](auto waves, auto read, unsigned grid) {
+    e = launch_merge(rows, prm.batch, false, [&](auto waves, auto read, unsigned grid) {
         constexpr int kWaves = decltype(waves)::value;
-        hipLaunchKernelGGL((mla_merge_kernel<kWaves, decltype(read)::value>), dim3(grid), dim3(kWaves == 1 ? 256 : 64 * kWaves), 0, stream, prm.meta,
-                           prm.part_ml, prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)rows_total);
+        return launch(mla_merge_kernel<kWaves, decltype(read)::value>, dim3(grid), kWaves == 1 ? 256 : 64 * kWaves, stream, prm.meta, prm.part_ml,
+                      prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)rows_total);
     });
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[2], stream)) != hipSuccess) return e;
     return hipSuccess;
 }
