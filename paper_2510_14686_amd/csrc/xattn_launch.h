@@ -33,12 +33,18 @@ inline hipError_t function_for(const void* kernel, hipFunction_t* f) {
     return hipSuccess;
 }
 
+// An error that the call returns is taken back from the runtime: the thread's next check of other work must not find it.
+inline hipError_t taken_back(hipError_t e) {
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 template <typename... P, typename... A>
 hipError_t launch(void (*kernel)(P...), dim3 grid, int threads, hipStream_t stream, const A&... args) {
     static_assert(sizeof...(P) == sizeof...(A), "one value per parameter");
     hipFunction_t f;
     const hipError_t e = function_for(reinterpret_cast<const void*>(kernel), &f);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) return taken_back(e);
     alignas(16) char buffer[(0 + ... + (sizeof(P) + alignof(P)))];
     size_t bytes = 0;
     auto put = [&](const auto& value) {
@@ -49,7 +55,7 @@ hipError_t launch(void (*kernel)(P...), dim3 grid, int threads, hipStream_t stre
     };
     (put(static_cast<P>(args)), ...);
     void* extra[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, buffer, HIP_LAUNCH_PARAM_BUFFER_SIZE, &bytes, HIP_LAUNCH_PARAM_END};
-    return hipModuleLaunchKernel(f, grid.x, grid.y, grid.z, (unsigned)threads, 1, 1, 0, stream, nullptr, extra);
+    return taken_back(hipModuleLaunchKernel(f, grid.x, grid.y, grid.z, (unsigned)threads, 1, 1, 0, stream, nullptr, extra));
 }
 
 }  // namespace xattn
