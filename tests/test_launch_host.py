@@ -1,5 +1,5 @@
 """Kernel launches on the CPU: csrc/xattn_launch.h built with g++ against a stand-in for the HIP runtime
-(tests/host/launch_main.cpp), with failing lookups and launches."""
+(tests/host/launch_main.cpp), with failing lookups and launches, and streams of a device that is not the current one."""
 import os
 import subprocess
 
