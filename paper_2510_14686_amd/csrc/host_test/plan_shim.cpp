@@ -102,6 +102,17 @@ int xattn_test_part_runs(const int32_t* kv_lens, int batch, int n_pieces, int mi
     return n;
 }
 
+// Whether a merge kernel's rows are dealt out round robin; before a sequence as a wave's lanes of `chunk` sequences know it.
+int xattn_test_spread_rows(const int32_t* kv_lens, int batch, int seg_cost, int chunk) {
+    int total = 0;
+    for (int b = 0; b < batch; ++b) total += stream_len(kv_lens[b], seg_cost);
+    return spread_rows(batch, total, [&](int until) {
+        int n = 0;
+        for (int b = 0; b < until / chunk * chunk; ++b) n += stream_len(kv_lens[b], seg_cost);
+        return n;
+    });
+}
+
 // KV heads per workgroup and waves per head of the matrix path: heads * 16 + waves.
 int xattn_test_piece_share(int n_kv_heads, int max_waves) {
     const PieceShare s = piece_share(n_kv_heads, max_waves);

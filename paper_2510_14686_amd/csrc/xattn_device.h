@@ -293,21 +293,44 @@ __device__ __forceinline__ void wave_write_meta(const WavePlan& wp, const int32_
                                                 int lane, int32_t* __restrict__ meta) {
     const int seq = 64 * g + lane;
     const __amdgpu_buffer_rsrc_t rl = make_rsrc(kv_lens, (uint32_t)batch * 4u);
-    const int len = clamp_len(__builtin_amdgcn_raw_buffer_load_b32(rl, seq * 4, 0, 0));
+    const int raw = __builtin_amdgcn_raw_buffer_load_b32(rl, seq * 4, 0, 0);
+    // the parts of the batch to the next lane's first sequence
+    const bool spread = spread_rows(batch, wp.pl.total, [&](int b) { return __builtin_amdgcn_readlane(wp.excl, b >> wp.chunk_log2); });
+    const int len = clamp_len(raw);
     const int v = stream_len(len, wp.pl.seg_cost);
     const int before = wave_incl_scan_i(v) - v;                       // within the group
     const int chunk_first = __shfl(wp.excl, (seq >> wp.chunk_log2) & 63, 64);
     const int start = chunk_first + before - __shfl(before, lane & ~(wp.chunk - 1), 64);
     if (seq < batch) {
         const SeqMeta m = seq_meta(wp.pl, seq, start, len);
-        reinterpret_cast<int2*>(meta)[seq] = make_int2(m.first_slot, m.n_seg);
+        reinterpret_cast<int2*>(meta)[seq] = make_int2(m.first_slot, m.n_seg | (spread ? kSpreadRows : 0));
     }
 }
 
-// This workgroup's place in the order of the output rows, and a lane's share of a partial row.  (Which form as a branch of one
-// kernel costs 2 % of the short calls.)
-template <int kRead>
-__device__ __forceinline__ uint32_t merge_workgroup() { return kRead == kReadOwn ? (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x; }
+// The output row of a merge kernel's workgroup or (kWaves == 1) wave, its sequence and that one's table entry.
+struct MergeRow {
+    uint32_t row, b;
+    int first_slot, n;
+};
+template <int kWaves, int kRead>
+__device__ __forceinline__ MergeRow merge_row(const int32_t* __restrict__ meta, uint32_t batch, uint32_t seq_rows, uint32_t per_xcd, int wave) {
+    const int2* table = reinterpret_cast<const int2*>(meta);
+    auto row_of = [&](uint32_t workgroup) { return kWaves == 1 ? workgroup * 4 + wave : workgroup; };
+    auto entry = [&](uint32_t b) { return table[b < batch ? b : 0]; };
+    MergeRow r;
+    r.row = row_of(kRead == kReadOwn ? (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3) : blockIdx.x);
+    r.b = r.row / seq_rows;
+    int2 e = entry(r.b);
+    if (kRead == kReadOwn && __builtin_expect(e.y & kSpreadRows, 0)) {
+        r.row = row_of(blockIdx.x);
+        r.b = r.row / seq_rows;
+        e = entry(r.b);
+    }
+    r.first_slot = e.x;
+    r.n = r.b < batch ? e.y & (kSpreadRows - 1) : 1;       // no such row: nothing to do, as for a finished one
+    return r;
+}
+// A lane's share of a partial row.  (Which form as a branch of one kernel costs 2 % of the short calls.)
 template <int kRead, typename T>
 __device__ __forceinline__ T load_partial(const T* p) { return kRead == kReadFarOnce ? __builtin_nontemporal_load(p) : *p; }
 

@@ -76,11 +76,12 @@ constexpr int kMergeAlone = 8;
 inline int merge_waves(long rows) { return rows <= 512 ? 16 : rows <= 2048 ? 4 : 1; }
 
 // Whose partial rows an XCD reads.  From 8 sequences on it merges the x-th eighth of the output rows, as the decode kernels
-// give it the x-th eighth of the token stream (kReadOwn): most partial rows are then read through the L2 that they were
-// written through.  (Round robin: 31 sequences of 41 to 666 tokens, 8 KV heads, the call 15.2 -> 16.3 us; latent-KV, 128
-// of 244 to 1958, 128 rows 69.2 -> 72.3, 64 of 1024 to 8192, 16 rows 60.0 -> 60.8; large GQA calls level.)  With fewer
-// sequences than XCDs a long one's rows would all meet on one of them (latent-KV, 7 of 2216 to 17728, 72 rows 37.0 ->
-// 37.8): round robin then.  The rows come from all XCDs, through the L2 (kReadFar) or past it (kReadFarOnce).
+// give it the x-th eighth of the token stream (kReadOwn): where the lengths are about even, most partial rows are then read through
+// the L2 that they were written through.  (Round robin: 31 sequences of 41 to 666 tokens, 8 KV heads, 32 rows 26.2 -> 27.7 us;
+// latent-KV, 128 rows 27.8 -> 29.5, 128 of 244 to 1958 71.3 -> 73.4; large GQA calls level.)  Where they are not, an XCD would be left
+// with most of the work: the workgroups then turn to the rows round robin themselves (see spread_rows).  With fewer sequences than
+// XCDs a long one's rows would all meet on one of them (latent-KV, 7 of 2216 to 17728, 72 rows 37.0 -> 37.8): always round robin.
+// Those rows come from all XCDs, through the L2 (kReadFar) or past it (kReadFarOnce).
 constexpr int kReadOwn = 0, kReadFar = 1, kReadFarOnce = 2;
 // Workgroups of a merge kernel whose work is `n` of them in the order of the output rows: a multiple of the eight XCDs.
 inline unsigned merge_grid(long n) { return (unsigned)((n + 7) / 8 * 8); }

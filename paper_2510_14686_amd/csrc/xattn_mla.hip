@@ -1492,14 +1492,12 @@ __global__ __launch_bounds__(256 * RT) void mla_rows_kernel(
 template <int kWaves, int kRead>
 __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_kernel(
         const int32_t* __restrict__ meta, const float* __restrict__ part_ml, const uint16_t* __restrict__ part_o, uint16_t* __restrict__ out,
-        float* __restrict__ lse, int batch, uint32_t seq_rows) {
+        float* __restrict__ lse, int batch, uint32_t seq_rows, uint32_t per_xcd) {
     const int lane = threadIdx.x & 63;
     const int wave = uniform(threadIdx.x >> 6);
-    const uint32_t row = kWaves == 1 ? merge_workgroup<kRead>() * 4 + wave : merge_workgroup<kRead>();
-    const uint32_t b = row / seq_rows;
-    if (b >= (uint32_t)batch) return;
-    const int2 fs = reinterpret_cast<const int2*>(meta)[b];
-    const int n = fs.y;
+    const MergeRow mr = merge_row<kWaves, kRead>(meta, (uint32_t)batch, seq_rows, per_xcd, wave);
+    const uint32_t row = mr.row, b = mr.b;
+    const int n = mr.n;
     if (n == 1) return;
     const MergeShare sh = merge_share<kWaves>(n, wave);
     if (sh.alone && kWaves > 1 && wave > 0) return;       // few slots: the first wave does the row
@@ -1509,7 +1507,7 @@ __global__ __launch_bounds__(kWaves == 1 ? 256 : 64 * kWaves) void mla_merge_ker
         if (lse && lane == 0) lse[row] = kNegInf;
         return;
     }
-    const long stride_rows = seq_rows, first_row = (long)fs.x * stride_rows + (row - b * seq_rows);
+    const long stride_rows = seq_rows, first_row = (long)mr.first_slot * stride_rows + (row - b * seq_rows);
     const float4* ml = reinterpret_cast<const float4*>(part_ml) + first_row;   // (m, l, lq, 1 / scale)
     const u32x4_t* po = reinterpret_cast<const u32x4_t*>(part_o + first_row * kDv) + lane;
     const long po_stride = stride_rows * (kDv / 8);
@@ -1660,7 +1658,7 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     e = launch_merge(rows, prm.batch, false, [&](auto waves, auto read, unsigned grid) {
         constexpr int kWaves = decltype(waves)::value;
         return launch(mla_merge_kernel<kWaves, decltype(read)::value>, dim3(grid), kWaves == 1 ? 256 : 64 * kWaves, stream, prm.meta, prm.part_ml,
-                      prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)rows_total);
+                      prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)rows_total, grid >> 3);
     });
     if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[2], stream)) != hipSuccess) return e;
