@@ -294,8 +294,11 @@ __device__ __forceinline__ void wave_write_meta(const WavePlan& wp, const int32_
     const int seq = 64 * g + lane;
     const __amdgpu_buffer_rsrc_t rl = make_rsrc(kv_lens, (uint32_t)batch * 4u);
     const int raw = __builtin_amdgcn_raw_buffer_load_b32(rl, seq * 4, 0, 0);
-    // the parts of the batch to the next lane's first sequence
-    const bool spread = spread_rows(batch, wp.pl.total, [&](int b) { return __builtin_amdgcn_readlane(wp.excl, b >> wp.chunk_log2); });
+    // lane x: what part x of the batch holds, cut at a lane's first sequence
+    const int first = __shfl(wp.excl, batch_part(lane & 7, batch) >> wp.chunk_log2, 64), from = lane < 8 ? first : wp.pl.total;
+    const int until = __builtin_amdgcn_update_dpp(0, from, 0x101, 0xf, 0xf, false);      // lane + 1's
+    const bool spread = batch >= 8 && __ballot(lane < 8 && large_part(until - from, wp.pl.total)) != 0;
+    __builtin_amdgcn_sched_barrier(0);      // while the lengths are on their way
     const int len = clamp_len(raw);
     const int v = stream_len(len, wp.pl.seg_cost);
     const int before = wave_incl_scan_i(v) - v;                       // within the group
@@ -314,20 +317,36 @@ struct MergeRow {
 };
 template <int kWaves, int kRead>
 __device__ __forceinline__ MergeRow merge_row(const int32_t* __restrict__ meta, uint32_t batch, uint32_t seq_rows, uint32_t per_xcd, int wave) {
-    const int2* table = reinterpret_cast<const int2*>(meta);
     auto row_of = [&](uint32_t workgroup) { return kWaves == 1 ? workgroup * 4 + wave : workgroup; };
-    auto entry = [&](uint32_t b) { return table[b < batch ? b : 0]; };
+    auto entry = [&](uint32_t b) { return reinterpret_cast<const int2*>(meta)[b]; };
     MergeRow r;
     r.row = row_of(kRead == kReadOwn ? (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3) : blockIdx.x);
     r.b = r.row / seq_rows;
-    int2 e = entry(r.b);
-    if (kRead == kReadOwn && __builtin_expect(e.y & kSpreadRows, 0)) {
-        r.row = row_of(blockIdx.x);
-        r.b = r.row / seq_rows;
-        e = entry(r.b);
+    if constexpr (kRead == kReadOwn) {
+        constexpr int kPast = 2 * kSpreadRows;
+        const int past = r.b < batch ? 0 : kPast;
+        const int2 e = entry(past ? 0 : r.b);
+        int slot = e.x, n = e.y | past;
+        asm("" : "+s"(slot), "+s"(n));      // both words in one load: the compiler would fetch the slot behind the test
+        if (__builtin_expect(n >= kSpreadRows, 0)) {
+            r.n = 1;                        // no such row: nothing to do, as for a finished one
+            if ((n & kSpreadRows) == 0) return r;
+            r.row = row_of(blockIdx.x);
+            r.b = r.row / seq_rows;
+            if (r.b >= batch) return r;
+            const int2 mine = entry(r.b);
+            slot = mine.x;
+            n = mine.y & (kSpreadRows - 1);
+        }
+        r.first_slot = slot;
+        r.n = n;
+    } else {
+        r.n = 1;
+        if (r.b >= batch) return r;
+        const int2 e = entry(r.b);
+        r.first_slot = e.x;
+        r.n = e.y;
     }
-    r.first_slot = e.x;
-    r.n = r.b < batch ? e.y & (kSpreadRows - 1) : 1;       // no such row: nothing to do, as for a finished one
     return r;
 }
 // A lane's share of a partial row.  (Which form as a branch of one kernel costs 2 % of the short calls.)

@@ -235,17 +235,11 @@ XATTN_HD SeqMeta seq_meta(const Plan& pl, int b, int start, int len) {
 // parts, 41.4 round robin, GQA 32 rows of 8 KV heads 50.8 / 46.5; 8 of 4000 ahead of 56 of 100: 51.0 / 38.7 and 55.1 / 46.5; 32 of
 // 4000 ahead of 32 of 100: 73.2 / 70.3 and 115.1 / 113.8; 4000 among 15 of 20: 24.0 / 21.6 and 21.5 / 19.2.  The other way
 // round 12 sequences of 100 to 800, the largest part a quarter of 6000 positions: 20.4 by parts, 21.0 round robin and 10.8 / 11.0.
-// before(b): the positions of the sequences ahead of sequence b.
 constexpr int kSpreadRows = 1 << 20;
-template <typename Before>
-XATTN_HD bool spread_rows(int batch, int total, Before before) {
-    int most = 0, at = 0;
-    for (int x = 1; x <= 8; ++x) {
-        const int next = x == 8 ? total : before(x * batch >> 3);
-        most = most > next - at ? most : next - at;
-        at = next;
-    }
-    return most > (total >> 3) * 3 || (most >= 8192 && most > (total >> 5) * 7);
+// First sequence of part x (0 to 8) of a batch; whether a part of `positions` calls for round robin.
+XATTN_HD int batch_part(int x, int batch) { return x * batch >> 3; }
+XATTN_HD bool large_part(int positions, int total) {
+    return positions > (total >> 3) * 3 || (positions >= 8192 && positions > (total >> 5) * 7);
 }
 
 // A piece's walk over the sequences it intersects, in stream order.
