@@ -123,6 +123,15 @@ int xattn_test_piece_share(int n_kv_heads, int max_waves) {
     return s.heads * 16 + s.parts;
 }
 
+// The same of a call on n_cu compute units, whose query rows make row_groups groups; runs_out: share_runs of it and, then, of
+// 1 to max_waves heads.
+int xattn_test_call_share(int n_cu, int row_groups, int n_kv_heads, int max_waves, int32_t* runs_out) {
+    const PieceShare s = call_share(n_cu, row_groups, n_kv_heads, max_waves);
+    runs_out[0] = share_runs(n_cu, row_groups, n_kv_heads, s);
+    for (int h = 1; h <= max_waves; ++h) runs_out[h] = share_runs(n_cu, row_groups, n_kv_heads, share_of(h, max_waves));
+    return s.heads * 16 + s.parts;
+}
+
 // How xattn_decode's workgroups share a plan of `total` positions out: count_out[piece in use * rows_total + row] =
 // the number of workgroup parts that compute it.  Returns the rows a wave holds in this launch; -1 where a part
 // works on a piece that is not in use, or on no row.

@@ -93,12 +93,9 @@ DecodeSplit decode_split(int n_cu, int batch, int q_len, int n_q_heads, int n_kv
     return DecodeSplit{pieces * parts, parts};
 }
 
-// Pieces of a GQA call on the matrix path, whose row groups of `rows` query rows each work on a piece: one workgroup per
-// compute unit, those of other KV heads and other query rows of a piece counted.
+// Pieces of a GQA call on the matrix path, whose row groups of `rows` query rows each work on a piece.
 int shared_pieces(int n_cu, int rows_total, int rows, int n_kv_heads, PieceShare share) {
-    const int on_a_piece = (rows_total + rows - 1) / rows * ((n_kv_heads + share.heads - 1) / share.heads);
-    const int pieces = on_a_piece == 1 ? n_cu : n_cu / on_a_piece / 8 * 8;
-    return pieces < 8 ? 8 : pieces;
+    return pieces_of(n_cu, (rows_total + rows - 1) / rows * ((n_kv_heads + share.heads - 1) / share.heads));
 }
 
 // Pieces of a latent-KV call: as many as give one workgroup per compute unit when a piece is worked
@@ -296,11 +293,10 @@ int decode_call(const char* who, FixedWorkspaceFn fixed_workspace, const void* q
     prm.part_o = reinterpret_cast<float*>(ws + w.o_off);
     prm.n_pieces = split.pieces;
     prm.parts = split.parts;
-    prm.share = piece_share(n_kv_heads, kMaxWavesPerBlock);
-    const int rows_total = prm.group * q_len;
+    const int rows_total = prm.group * q_len, rows = rows_per_wave(rows_total, g_cfg_path);
     const bool shared = use_matrix_path(g_cfg_path);
-    prm.shared_pieces = g_cfg_pieces > 0 ? g_cfg_pieces
-                                         : shared_pieces(d->n_cu, rows_total, rows_per_wave(rows_total, g_cfg_path), n_kv_heads, prm.share);
+    prm.share = call_share(d->n_cu, (rows_total + rows - 1) / rows, n_kv_heads, kMaxWavesPerBlock);
+    prm.shared_pieces = g_cfg_pieces > 0 ? g_cfg_pieces : shared_pieces(d->n_cu, rows_total, rows, n_kv_heads, prm.share);
     const int waves = shared ? prm.share.parts : 1;                // waves per piece and KV head
     prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : kDefaultMinPieceTokens * waves;
     if (prm.min_piece_tokens < 16) prm.min_piece_tokens = 16;      // one 16-key block at least

@@ -182,15 +182,53 @@ XATTN_HD DecodeWork decode_work(const Plan& pl, int grid_x, int parts, int rows_
 
 // The matrix path's workgroups: `heads` KV heads, and `parts` waves per head that share a piece, a run of positions each.  A
 // sequence that the waves cut among themselves is put together in LDS; only what the piece's own ends cut leaves a
-// partial result.  Four heads of 256 bytes side by side stream as fast as eight; two cost 2.7 % of a large call, one 6 to 9.
+// partial result.
 struct PieceShare {
     int heads, parts;
     int inv_heads;      // wave w < 32 is of part w * inv_heads / 32
 };
+XATTN_HD PieceShare share_of(int heads, int max_waves) { return PieceShare{heads, max_waves / heads, (31 + heads) / heads}; }
+// Whether groups of four heads, or else of three, come out even.
+XATTN_HD bool even_shares(int n_kv_heads) { return n_kv_heads <= 4 || n_kv_heads % 4 == 0 || n_kv_heads % 3 == 0; }
+// Four heads of 256 bytes side by side stream as fast as eight; two cost 2.7 % of a large call, one 6 to 9.
 XATTN_HD PieceShare piece_share(int n_kv_heads, int max_waves) {
-    int h = n_kv_heads;
-    if (h > 4) h = h % 4 == 0 ? 4 : h % 3 == 0 ? 3 : h < max_waves ? h : max_waves;
-    return PieceShare{h, max_waves / h, (31 + h) / h};
+    return share_of(n_kv_heads < 4 ? n_kv_heads : n_kv_heads % 4 != 0 && n_kv_heads % 3 == 0 ? 3 : 4, max_waves);
+}
+// Pieces where `on_a_piece` workgroups, those of other KV heads and other query rows counted, work on each: one workgroup per
+// compute unit.
+XATTN_HD int pieces_of(int n_cu, int on_a_piece) {
+    const int pieces = on_a_piece == 1 ? n_cu : n_cu / on_a_piece / 8 * 8;
+    return pieces < 8 ? 8 : pieces;
+}
+// 64 times the number of runs that the waves of a call cut a head's keys into, per round of workgroups: what it has of the chip.  A
+// wave per head and piece leaves more partial results and a second round starts anew: an eighth off for each.
+XATTN_HD int share_runs(int n_cu, int row_groups, int n_kv_heads, PieceShare s) {
+    const int on_a_piece = row_groups * ((n_kv_heads + s.heads - 1) / s.heads), pieces = pieces_of(n_cu, on_a_piece);
+    const int rounds = (pieces * on_a_piece + n_cu - 1) / n_cu;
+    return 64 * pieces * s.parts / rounds / 8 * (s.parts == 1 ? 7 : 8) / 8 * (rounds > 1 ? 7 : 8);
+}
+// The share of a call.  Piece counts are multiples of 8 and groups of heads may not come out even, which can leave much of the chip
+// idle: then heads are grouped otherwise, where that gives more runs.  (Where up to 32 query rows let a call be bound by memory,
+// even groups stay unless the gain is large.)  32 sequences of 512 to 4096 tokens, 40 query rows per KV head, us, with groups of
+// four, three or eight heads and so: 5 KV heads 81.7 / 63.3, 10 159.6 / 114.8, 11 162.2 / 134.6, 17 250.5 / 213.5; 24 of them, 18
+// 193.6 / 150.0, 27 359.3 / 222.0, 30 373.1 / 235.8, 36 398.9 / 322.2, 40 423.3 / 356.5, 44 410.3 / 381.4; 4 rows, 5 KV heads 39.0 / 37.0, 10
+// 57.2 / 50.6, 22 102.6 / 101.6, 33 158.3 / 150.9.  (A wave per piece and KV head: 18, 27 and 36 KV heads 187.0, 272.9, 345.5.)
+XATTN_HD PieceShare call_share(int n_cu, int row_groups, int n_kv_heads, int max_waves) {
+    PieceShare best = piece_share(n_kv_heads, max_waves);
+    int most = share_runs(n_cu, row_groups, n_kv_heads, best);
+    if (most * row_groups * n_kv_heads == 64 * n_cu * max_waves) return best;      // all of the chip (and no time spent on a short call)
+    const bool stays = row_groups == 1 && even_shares(n_kv_heads);
+    const int first = row_groups == 1 ? 4 : 2;
+    const int others[] = {first, 6 - first, max_waves, 1};
+    for (int h : others) {
+        if (h >= n_kv_heads) continue;
+        const PieceShare s = share_of(h, max_waves);
+        const int runs = share_runs(n_cu, row_groups, n_kv_heads, s);
+        if (stays ? runs * 5 <= most * 7 : runs <= most) continue;
+        best = s;
+        most = runs;
+    }
+    return best;
 }
 // Positions per part of a piece of `len` positions, all but the last one's: whole 16-key blocks, so parts without any
 // positions come last.  (parts: a power of two.)
