@@ -73,7 +73,7 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
 // (256 compute units of 32 waves).  Few rows mean few sequences, whose keys may be split into hundreds of
 // slots; rows of up to kMergeAlone slots are summed by their first wave alone whatever this says.
 constexpr int kMergeAlone = 8;
-inline int merge_waves(long rows) { return rows <= 512 ? 16 : rows <= 2048 ? 4 : 1; }
+constexpr int merge_waves(long rows) { return rows <= 512 ? 16 : rows <= 2048 ? 4 : 1; }
 
 // Whose partial rows an XCD reads.  From 8 sequences on it merges the x-th eighth of the output rows, as the decode kernels
 // give it the x-th eighth of the token stream (kReadOwn): where the lengths are about even, most partial rows are then read through
@@ -85,9 +85,10 @@ inline int merge_waves(long rows) { return rows <= 512 ? 16 : rows <= 2048 ? 4 :
 constexpr int kReadOwn = 0, kReadFar = 1, kReadFarOnce = 2;
 // Workgroups of a merge kernel whose work is `n` of them in the order of the output rows: a multiple of the eight XCDs.
 inline unsigned merge_grid(long n) { return (unsigned)((n + 7) / 8 * 8); }
-// Returns launch(waves per row, kRead..., workgroups), the first two as types.
-template <typename Launch>
-inline hipError_t launch_merge(long rows, int batch, bool far_cached, Launch launch) {
+// Returns launch(waves per row, kRead..., workgroups), the first two as types.  Of few sequences' rows, fewer than kCachedBelow are
+// read through the L2s.
+template <int kCachedBelow, typename Launch>
+inline hipError_t launch_merge(long rows, int batch, Launch launch) {
     auto with_waves = [&](auto read) {
         switch (merge_waves(rows)) {
             case 16: return launch(std::integral_constant<int, 16>(), read, merge_grid(rows));
@@ -96,7 +97,10 @@ inline hipError_t launch_merge(long rows, int batch, bool far_cached, Launch lau
         }
     };
     if (batch >= 8) return with_waves(std::integral_constant<int, kReadOwn>());
-    if (far_cached) return with_waves(std::integral_constant<int, kReadFar>());
+    if constexpr (kCachedBelow > 0) {
+        static_assert(merge_waves(kCachedBelow) == 16, "one form of the kernel");
+        if (rows < kCachedBelow) return launch(std::integral_constant<int, 16>(), std::integral_constant<int, kReadFar>(), merge_grid(rows));
+    }
     return with_waves(std::integral_constant<int, kReadFarOnce>());
 }
 

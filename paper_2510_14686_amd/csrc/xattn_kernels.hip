@@ -967,8 +967,8 @@ hipError_t launch_decode(const DecodeParams& prm, hipStream_t stream, hipEvent_t
     if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[1], stream)) != hipSuccess) return e;
     const long rows = (long)prm.batch * prm.q_len * prm.n_q_heads;
-    // Fewer rows are read as fast either way, or 0.2 us faster through the L2s.
-    e = launch_merge(rows, prm.batch, rows < 256, [&](auto waves, auto read, unsigned grid) {
+    // Fewer than 256 rows are read as fast either way, or 0.2 us faster through the L2s.
+    e = launch_merge<256>(rows, prm.batch, [&](auto waves, auto read, unsigned grid) {
         constexpr int kWaves = decltype(waves)::value;
         return launch(merge_kernel<kWaves, decltype(read)::value>, dim3(grid), kWaves == 1 ? 256 : 64 * kWaves, stream, prm.meta, prm.part_ml,
                       prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)(prm.q_len * prm.n_q_heads), grid >> 3);

@@ -1655,7 +1655,7 @@ hipError_t launch_mla_decode(const MlaParams& prm, hipStream_t stream, hipEvent_
     if (e != hipSuccess) return e;
     if (events && (e = hipEventRecord(events[1], stream)) != hipSuccess) return e;
     const long rows = (long)prm.batch * rows_total;
-    e = launch_merge(rows, prm.batch, false, [&](auto waves, auto read, unsigned grid) {
+    e = launch_merge<0>(rows, prm.batch, [&](auto waves, auto read, unsigned grid) {
         constexpr int kWaves = decltype(waves)::value;
         return launch(mla_merge_kernel<kWaves, decltype(read)::value>, dim3(grid), kWaves == 1 ? 256 : 64 * kWaves, stream, prm.meta, prm.part_ml,
                       prm.part_o, prm.out, prm.lse, prm.batch, (uint32_t)rows_total, grid >> 3);
