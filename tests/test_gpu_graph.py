@@ -126,13 +126,16 @@ def test_capture_refuses_to_grow_the_workspace():
         assert float(marker[0]) == 1.0                             # the capture recorded the rest and replays
 
 
-def test_capture_after_a_smaller_call_gives_the_eager_bits():
-    """With fewer than 8 KV heads the partition takes several pieces per workgroup: the same ones in a graph, on a
-    stream whose workspace a smaller call of another shape made, as eagerly and in the fixed scratch array."""
+@pytest.mark.parametrize("path", [0, 1])
+def test_capture_after_a_smaller_call_gives_the_eager_bits(path, request):
+    """With fewer than 8 KV heads several waves share a piece or (vector path) a workgroup takes several: the same ones in a
+    graph, on a stream whose workspace a smaller call of another shape made, as eagerly and in the fixed scratch array."""
     import torch
 
     import paper_2510_14686_amd as xa
     xa.xattn_configure(xa.XATTN_CFG_PIECES, 0)
+    xa.xattn_configure(xa.XATTN_CFG_PATH, path)
+    request.addfinalizer(lambda: xa.xattn_configure(xa.XATTN_CFG_PATH, 0))
     B, T, Hq, Hkv = 8, 1, 8, 2
     lens = np.array([3000, 2000, 50, 4000, 9000, 1, 700, 5000], np.int32)
     q = normal_bf16(99, 0, B * T * Hq * D).reshape(B, T, Hq, D)

@@ -42,3 +42,37 @@ def test_latent_kv(lens, T, H):
     out_bits, lse = gpu_mla(q, cs, lens, scale)
     ref_out, ref_lse = oracle.mla(q, cs, lens, 512, scale)
     assert_parity(out_bits, lse, ref_out, ref_lse, what="%s T=%d" % (name, T))
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (32, 8)])
+def test_a_replayed_graph_takes_the_order_of_its_lengths(Hq, Hkv):
+    """Recorded with even lengths, replayed with very unequal ones and back: the bits of an eager call each time."""
+    import torch
+
+    import paper_2510_14686_amd as xa
+    B, D, scale = 16, 128, float(np.float32(1.0 / math.sqrt(128)))
+    kv = [torch.from_numpy(normal_bf16(53, s, B * 4000 * Hkv * D).view(np.int16)).cuda() for s in (1, 2)]
+    q = torch.from_numpy(normal_bf16(53, 0, B * Hq * D).view(np.int16)).cuda()
+    ptrs = [torch.tensor([t.data_ptr() + b * 4000 * Hkv * D * 2 for b in range(B)], dtype=torch.int64, device="cuda") for t in kv]
+    lens = torch.full((B,), 500, dtype=torch.int32, device="cuda")
+    outs = [torch.zeros((B, 1, Hq, D), dtype=torch.int16, device="cuda") for _ in range(2)]
+    lses = [torch.zeros((B, 1, Hq), dtype=torch.float32, device="cuda") for _ in range(2)]
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+
+    def call(i, stream):
+        xa.xattn_decode(q, ptrs[0], ptrs[1], lens, B, 1, Hq, Hkv, D, scale, outs[i], lses[i], stream)
+    call(0, side)
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call(0, side)
+    for given in ([500] * B, [4000] + [50] * (B - 1), [500] * B, [20] * (B - 1) + [3999]):
+        lens.copy_(torch.tensor(given, dtype=torch.int32))
+        outs[0].fill_(0x7FC0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        call(1, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1]) and torch.equal(lses[0], lses[1]), given

@@ -1,5 +1,5 @@
-"""Grouped-query decode where a workgroup holds several pieces (few KV heads) and where a wave or several
-workgroups share a KV head's query rows, against the oracle."""
+"""Grouped-query decode where a workgroup holds several pieces (the vector path with few KV heads) or its waves share one, and
+where a wave or several workgroups share a KV head's query rows, against the oracle."""
 import math
 
 import numpy as np
@@ -38,8 +38,9 @@ def _case(lens, T, Hq, Hkv):
 @pytest.mark.parametrize("Hkv", [1, 2, 3, 8])
 @pytest.mark.parametrize("lens", [(5000, 16, 37, 3333), (700, 16, 37, 300), (17,)])
 def test_pieces_and_rows_per_workgroup(T, group, Hkv, lens, path):
-    """More pieces than workgroups with few KV heads, so that several waves of one have a piece of their own; and short
-    streams in the default partition: pieces of 16 keys, a workgroup for every 16 query rows."""
+    """With few KV heads more pieces than workgroups on the vector path, so that several waves of one have a piece of their own,
+    and several waves on a piece on the matrix path; and short streams in the default partition: pieces of 16 keys, a workgroup
+    for every 16 query rows."""
     import paper_2510_14686_amd as xa
     from gpu_util import check_against_oracle
     xa.xattn_configure(xa.XATTN_CFG_PATH, path)
@@ -49,23 +50,29 @@ def test_pieces_and_rows_per_workgroup(T, group, Hkv, lens, path):
     check_against_oracle(q, ks, vs, lens, SCALE, what="T=%d group=%d Hkv=%d" % (T, group, Hkv))
 
 
+@pytest.mark.parametrize("path", [0, 1])
 @pytest.mark.parametrize("T,group", [(1, 3), (1, 8), (4, 8), (3, 11)])
 @pytest.mark.parametrize("Hkv", [1, 2, 3])
-def test_every_part_of_every_workgroup_has_a_piece(T, group, Hkv):
-    """256 workgroups of 8, 4 and 2 parts, half as many where two share a piece: 2048 pieces of 16 keys at most, which
-    the stream fills."""
+def test_every_part_of_every_workgroup_has_a_piece(T, group, Hkv, path):
+    """256 workgroups of 8, 4 and 2 parts, fewer where several share a piece.  Vector path: a piece each, 2048 of 16 keys at
+    most, which the stream fills; matrix path: a run of a piece each."""
+    import paper_2510_14686_amd as xa
     from gpu_util import check_against_oracle
+    xa.xattn_configure(xa.XATTN_CFG_PATH, path)
     lens = (33000, 5, 1000)
     q, ks, vs = _case(lens, T, group * Hkv, Hkv)
     check_against_oracle(q, ks, vs, lens, SCALE, what="T=%d group=%d Hkv=%d" % (T, group, Hkv))
 
 
-def test_a_workspace_for_one_piece_per_compute_unit_is_enough():
+@pytest.mark.parametrize("path", [0, 1])
+def test_a_workspace_for_one_piece_per_compute_unit_is_enough(path):
+    """The vector path then takes fewer pieces per workgroup; the matrix path never takes more."""
     import torch
 
     import paper_2510_14686_amd as xa
     from gpu_util import check_against_oracle
     lens, Hq, Hkv = [5000, 1, 37, 3333], 8, 2
+    xa.xattn_configure(xa.XATTN_CFG_PATH, path)
     xa.xattn_configure(xa.XATTN_CFG_PIECES, torch.cuda.get_device_properties(0).multi_processor_count)
     small = xa.xattn_workspace_bytes(len(lens), 1, Hq, Hkv, D)
     xa.xattn_configure(xa.XATTN_CFG_PIECES, 0)

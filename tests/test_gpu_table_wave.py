@@ -9,9 +9,9 @@ from workloads import normal_bf16
 pytestmark = pytest.mark.gpu
 
 
-# one KV head: 8 waves share a piece; 8: 2; 5 and 12: workgroups with fewer waves, and several of them per piece.  65 and 130
+# one KV head: 8 waves share a piece; 8: 2; 3: a workgroup with fewer waves; 5 and 12: several workgroups per piece.  65 and 130
 # sequences: a second and third group of 64 in the table.  Both inner loops.
-@pytest.mark.parametrize("Hkv", [1, 5, 8, 12])
+@pytest.mark.parametrize("Hkv", [1, 3, 5, 8, 12])
 @pytest.mark.parametrize("B,lo,hi", [(3, 200, 900), (65, 60, 150), (130, 1, 90)])
 @pytest.mark.parametrize("path", [0, 1])
 def test_segments_of_every_sequence_reach_the_merge(Hkv, B, lo, hi, path):
