@@ -147,9 +147,10 @@ int xattn_mla_decode(const void* q, const void* const* c_ptrs, const int32_t* kv
  *                            device, used by calls on every stream; the caller keeps ownership and
  *                            keeps it alive while calls are in flight or graphs that recorded them
  *                            exist.  xattn_decode with fewer than 8 KV heads also takes a buffer that
- *                            is smaller than xattn_workspace_bytes but holds one piece per compute unit,
- *                            and then cuts the keys into fewer pieces (slower; the result differs by
- *                            the order of the fp32 sums).  (NULL, 0) returns to the library-owned workspaces: one per
+ *                            is smaller than xattn_workspace_bytes but holds one piece per compute unit.
+ *                            The matrix-core path needs no more than that; the vector path
+ *                            (XATTN_CFG_PATH = 1) then cuts the keys into fewer pieces (slower; the result
+ *                            differs by the order of the fp32 sums).  (NULL, 0) returns to the library-owned workspaces: one per
  *                            stream (up to 64 streams per device), allocated with hipMalloc by the
  *                            first call on the stream that needs more than it has, 32 MiB at least
  *                            (or, where that much cannot be had, what the call needs).  An outgrown
@@ -165,13 +166,18 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  * Tuning knobs of the partition (section 4.4.3 Layer 3), for sweeps and for tests that show the
  * result does not depend on the partition.  key:
  *   XATTN_CFG_PIECES            number of equal-token pieces the batch's keys are cut into;
- *                               0 = automatic: the CU count; divided by the number of workgroups that
- *                               work on a piece (xattn_decode: one per 32 query rows of a KV head;
- *                               xattn_mla_decode: one per 128 query rows of a sequence); and, with fewer
- *                               than 8 KV heads, times 8 / n_kv_heads (a workgroup then holds that many
- *                               pieces) as far as the partial results fit XATTN_NOALLOC_SCRATCH_BYTES
- *   XATTN_CFG_MIN_PIECE_TOKENS  lower bound on a piece's tokens; 0 = default (64; 16 for up to as many
- *                               pieces as compute units and 8 MiB of partial results;
+ *                               0 = automatic: the CU count, divided by the number of workgroups that
+ *                               work on a piece (xattn_decode: one per 32 query rows of a group of KV heads,
+ *                               of which there are one to eight so that most compute units have work;
+ *                               xattn_mla_decode: one per 128 query rows of a sequence) and rounded down to a
+ *                               multiple of 8.  On the vector path one workgroup per 8 query rows works on a
+ *                               piece, and with fewer than 8 KV heads the count is times 8 / n_kv_heads (a
+ *                               workgroup then holds that many pieces) as far as the partial results fit
+ *                               XATTN_NOALLOC_SCRATCH_BYTES
+ *   XATTN_CFG_MIN_PIECE_TOKENS  lower bound on a piece's tokens; 0 = default (64 times the waves per KV head
+ *                               that share a piece, 512 with one KV head per group, and 64 on the vector
+ *                               path; 16 for up to as many pieces as give every compute unit a workgroup
+ *                               (vector path: as compute units) and 8 MiB of partial results;
  *                               xattn_mla_decode: 64, above 64 query rows per sequence 128 or, with up to
  *                               8 sequences, 192, and 32 for up to 32 pieces); values below 16
  *                               count as 16
@@ -199,7 +205,8 @@ int xattn_set_workspace(void* dev_ptr, size_t bytes);
  *                               before each part is cut into equal pieces: 0 = the kernel's default,
  *                               n = 1..201: the even XCDs' parts are longer and the odd ones' shorter by
  *                               (n - 1) per mille (1 = equal parts).  Applies when the pieces in use are a
- *                               multiple of 8 and hold 512 positions or more; results do not depend on it.
+ *                               multiple of 8 and hold 512 positions or more for every wave that shares one;
+ *                               results do not depend on it.
  * Values outside [0, 65536] give XATTN_EINVAL.  Process-wide.
  */
 enum { XATTN_CFG_PIECES = 0, XATTN_CFG_MIN_PIECE_TOKENS = 1, XATTN_CFG_TIMING = 2, XATTN_CFG_PATH = 3,

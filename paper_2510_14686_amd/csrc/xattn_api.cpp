@@ -66,7 +66,7 @@ struct WorkspaceLayout {
 };
 WorkspaceLayout layout_for(int batch, int q_len, int n_q_heads, int n_pieces);
 
-// How a GQA call's keys are cut: the number of pieces, and how many of them a workgroup holds.
+// How a GQA call's keys are cut on the vector path: the number of pieces, and how many of them a workgroup holds.
 struct DecodeSplit {
     int pieces, parts;
 };
@@ -74,12 +74,13 @@ struct DecodeSplit {
 size_t decode_least_bytes(int n_cu, int batch, int q_len, int n_q_heads) {
     return layout_for(batch, q_len, n_q_heads, g_cfg_pieces > 0 ? g_cfg_pieces : n_cu).total;
 }
-// One workgroup per compute unit.  A wave streams one KV head, so with fewer than eight KV heads a
+// One workgroup per compute unit.  A wave of the vector path streams one KV head, so with fewer than eight KV heads a
 // workgroup takes several pieces to keep eight waves' loads in flight (two KV heads, 138468 tokens: 46.6 us
 // with one piece per workgroup, 32.0 us with four), as long as the partial results stay within the workspace
 // and within the size of the fixed scratch array, which also bounds what the merge has to read back.  Several
 // workgroups share a piece when a wave cannot hold all query rows of its KV head: fewer pieces then, as in
-// mla_pieces_for.  `have` bytes of workspace: decode_least_bytes at least.
+// mla_pieces_for.  `have` bytes of workspace: decode_least_bytes at least.  The matrix path, whose waves share a piece, cuts
+// the keys into no more pieces than that (shared_pieces) and runs in the same layout.
 DecodeSplit decode_split(int n_cu, int batch, int q_len, int n_q_heads, int n_kv_heads, size_t have) {
     const int rows = n_q_heads / n_kv_heads * q_len;
     const int most = n_kv_heads < kMaxWavesPerBlock ? kMaxWavesPerBlock / n_kv_heads : 1;
@@ -300,7 +301,7 @@ int decode_call(const char* who, FixedWorkspaceFn fixed_workspace, const void* q
     const int waves = shared ? prm.share.parts : 1;                // waves per piece and KV head
     prm.min_piece_tokens = g_cfg_min_piece > 0 ? g_cfg_min_piece : kDefaultMinPieceTokens * waves;
     if (prm.min_piece_tokens < 16) prm.min_piece_tokens = 16;      // one 16-key block at least
-    // One block per piece up to one piece per compute unit (with more than 8 KV heads, per group of 8 heads): 695
+    // One block per piece up to one workgroup per compute unit (vector path: one piece, per group of 8 KV heads): 695
     // tokens 11.4 -> 8.9 us, 207 tokens of 16 KV heads 13.7 -> 11.8; 64-token pieces beyond that (smaller ones only
     // add merge work), and where the partial results of many query rows would come to more than kFewBytes.
     // 0 / 2 / 4 / 8 / 16 / 32 MiB of them, us: 62 sequences of 42 to 84 tokens, 8 KV heads, 24 rows 21.5 / 21.6 /

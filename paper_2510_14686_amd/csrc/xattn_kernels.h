@@ -18,9 +18,9 @@ constexpr int kHeadDim = 128;
 // equal parts leave the even XCDs idle at the end of the kernel.
 constexpr int kDefaultXcdSkewGqa = 32;
 constexpr int kDefaultXcdSkewMla = 0;
-constexpr int kMaxWavesPerBlock = 8;   // one wave per KV head, up to 8 KV heads per workgroup
+constexpr int kMaxWavesPerBlock = 8;   // KV heads times the waves that share a piece (matrix path) or the pieces (vector path)
 
-// Workspace header: per sequence two int32 words, (first partial slot, number of segments), written
+// Workspace header: per sequence two int32 words, (first partial slot, number of segments and kSpreadRows), written
 // by the decode kernel for the merge kernel.  0 segments = no keys; 1 = finished by the decode kernel.
 
 struct DecodeParams {
@@ -36,7 +36,8 @@ struct DecodeParams {
     float* part_o;                   // fp32 [slots, q_len * n_q_heads, 128]
     float* part_ml;                  // fp32 [slots, q_len * n_q_heads, 2]  (max, sum)
     int32_t* meta;                   // int32 [batch, 2]
-    int n_pieces;                    // vector path: pieces the token stream is cut into (upper bound on active ones)
+    int n_pieces;                    // vector path: pieces the token stream is cut into (upper bound on active ones); both: what the
+                                     // workspace has slots for
     int parts;                       // and pieces per workgroup: waves per workgroup / KV heads per workgroup
     int shared_pieces;               // matrix path: pieces, n_pieces at most; share.parts waves per KV head work on each
     PieceShare share;
