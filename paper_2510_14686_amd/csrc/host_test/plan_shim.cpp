@@ -102,16 +102,18 @@ int xattn_test_part_runs(const int32_t* kv_lens, int batch, int n_pieces, int mi
     return n;
 }
 
-// Whether a merge kernel's rows are dealt out round robin; before a sequence as a wave's lanes of `chunk` sequences know it.
-int xattn_test_spread_rows(const int32_t* kv_lens, int batch, int seg_cost, int chunk) {
+// Whether a merge kernel's rows, seq_rows per sequence, are dealt out round robin; the positions before a sequence as a wave's lanes
+// of `chunk` sequences know them.
+int xattn_test_spread_rows(const int32_t* kv_lens, int batch, int seg_cost, int chunk, int n_pieces, int seq_rows) {
     int total = 0;
     for (int b = 0; b < batch; ++b) total += stream_len(kv_lens[b], seg_cost);
+    const Plan pl = plan_for_total(total, n_pieces, 16, seg_cost);
     int at = 0, found = 0;
     for (int x = 1; x <= 8; ++x) {
         const int until = x == 8 ? batch : batch_part(x, batch) / chunk * chunk;
         int next = 0;
         for (int b = 0; b < until; ++b) next += stream_len(kv_lens[b], seg_cost);
-        found |= large_part(next - at, total);
+        found |= large_part(pl, next - at, seq_rows);
         at = next;
     }
     return found;

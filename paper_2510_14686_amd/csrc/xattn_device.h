@@ -291,16 +291,20 @@ __device__ __forceinline__ void wave_locate(const WavePlan& wp, const int32_t* _
 // For the merge kernel: (first partial slot, number of segments) of sequences 64 g .. 64 g + 63, one
 // per lane.  A group of 64 sequences holds 64 / chunk whole chunks; a sequence's first position is its
 // chunk's first position plus the positions of the chunk's earlier sequences.
-__device__ __forceinline__ void wave_write_meta(const WavePlan& wp, const int32_t* __restrict__ kv_lens, int batch, int g,
+__device__ __forceinline__ void wave_write_meta(const WavePlan& wp, const int32_t* __restrict__ kv_lens, int batch, int seq_rows, int g,
                                                 int lane, int32_t* __restrict__ meta) {
     const int seq = 64 * g + lane;
     const __amdgpu_buffer_rsrc_t rl = make_rsrc(kv_lens, (uint32_t)batch * 4u);
     const int raw = __builtin_amdgcn_raw_buffer_load_b32(rl, seq * 4, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);      // until the next: while the lengths are on their way
+    int x = lane, n = batch, rows = seq_rows;
+    Plan pl = wp.pl;
+    asm volatile("" : "+v"(x), "+s"(n), "+s"(rows), "+s"(pl.total));      // nothing of it ahead of the loop over g, or kept across it
     // lane x: what part x of the batch holds, cut at a lane's first sequence
-    const int first = __shfl(wp.excl, batch_part(lane & 7, batch) >> wp.chunk_log2, 64), from = lane < 8 ? first : wp.pl.total;
-    const int until = __builtin_amdgcn_update_dpp(0, from, 0x101, 0xf, 0xf, false);      // lane + 1's
-    const bool spread = batch >= 8 && __ballot(lane < 8 && large_part(until - from, wp.pl.total)) != 0;
-    __builtin_amdgcn_sched_barrier(0);      // while the lengths are on their way
+    const int first = __shfl(wp.excl, batch_part(x & 7, n) >> wp.chunk_log2, 64), from = x < 8 ? first : pl.total;
+    const int until = __builtin_amdgcn_update_dpp(0, from, 0x101, 0xf, 0xf, false);      // lane x + 1's
+    const bool spread = n >= 8 && __ballot(x < 8 && large_part(pl, until - from, rows)) != 0;
+    __builtin_amdgcn_sched_barrier(0);
     const int len = clamp_len(raw);
     const int v = stream_len(len, wp.pl.seg_cost);
     const int before = wave_incl_scan_i(v) - v;                       // within the group

@@ -685,7 +685,7 @@ __global__ __launch_bounds__(512) void split_decode_kernel(const int32_t* __rest
         // sequences per wave, the groups of 64 dealt out over the workgroups from the last one, which
         // has no piece of its own when the stream is short.  Of such a workgroup the last wave, which a short piece leaves
         // without keys (30 sequences of 100 to 900 tokens of one KV head by the first wave 11.4 us, by the last 10.9).
-        for (int g = grid_x - 1 - bid; 64 * g < batch; g += grid_x) wave_write_meta(wp, kv_lens, batch, g, lane, prm.meta);
+        for (int g = grid_x - 1 - bid; 64 * g < batch; g += grid_x) wave_write_meta(wp, kv_lens, batch, prm.q_len * prm.n_q_heads, g, lane, prm.meta);
     }
     if (!work.any || piece0 >= piece1) return;      // the whole workgroup on the matrix path
     if (!kMatrix && s0 >= s1) return;

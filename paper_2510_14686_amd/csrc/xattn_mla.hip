@@ -406,7 +406,7 @@ __global__ __launch_bounds__(64 * NW) void mla_decode_kernel(
     if (tid < 64) {
         // For the merge kernel: first partial slot and number of segments of every sequence, 64
         // sequences per wave, the groups of 64 dealt out over the workgroups.
-        for (int g = bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, g, lane, prm.meta);
+        for (int g = bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, rows_total, g, lane, prm.meta);
     }
     if (!active) return;       // the whole workgroup: every wave computed the same plan
 
@@ -1009,7 +1009,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void mla_tile_kernel(
         const int p = mine.piece, s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
         const bool active = mine.any && s0 < s1;
         if (tid < 64)
-            for (int g = gridDim.x - 1 - bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, g, lane, prm.meta);
+            for (int g = gridDim.x - 1 - bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, rows_total, g, lane, prm.meta);
         if (!active) return;       // the whole workgroup: every wave computed the same plan
 
         Walk walk;
@@ -1300,7 +1300,7 @@ __global__ __launch_bounds__(256 * RT) void mla_rows_kernel(
     const int s0 = piece_bound(pl, p), s1 = piece_bound(pl, p + 1);
     const bool active = (bid >> 3) < per_xcd && p < pl.n_pieces && s0 < s1;
     if (tid < 64)
-        for (int g = gridDim.x - 1 - bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, g, lane, prm.meta);
+        for (int g = gridDim.x - 1 - bid; 64 * g < batch; g += gridDim.x) wave_write_meta(wp, kv_lens, batch, rows_total, g, lane, prm.meta);
     if (!active) return;       // the whole workgroup: every wave computed the same plan
 
     Walk walk;

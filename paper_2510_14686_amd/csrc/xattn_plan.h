@@ -268,16 +268,18 @@ XATTN_HD SeqMeta seq_meta(const Plan& pl, int b, int start, int len) {
 
 // Table entry of a sequence for the merge kernel: its first slot, and its segments (kMaxPieces at most) with, in all entries of
 // a call alike, the bit kSpreadRows.  Set: of the eight parts of the batch, whose rows an XCD each would merge (kReadOwn), one holds
-// so much more than an eighth of the keys that its XCD would be the last by far, 7/32 of them and 8192 positions or more, or 3/8
-// of them; the rows are then dealt out round robin.  One sequence of 30000 tokens among 15 of 100: latent-KV 128 rows 54.6 us by
-// parts, 41.4 round robin, GQA 32 rows of 8 KV heads 50.8 / 46.5; 8 of 4000 ahead of 56 of 100: 51.0 / 38.7 and 55.1 / 46.5; 32 of
-// 4000 ahead of 32 of 100: 73.2 / 70.3 and 115.1 / 113.8; 4000 among 15 of 20: 24.0 / 21.6 and 21.5 / 19.2.  The other way
-// round 12 sequences of 100 to 800, the largest part a quarter of 6000 positions: 20.4 by parts, 21.0 round robin and 10.8 / 11.0.
+// so many of the keys that its XCD would be the last by far, 3/8 of them, or 7/32 where the partial rows are many; the rows are then
+// dealt out round robin.  One sequence of 30000 tokens among 15 of 100: latent-KV 128 rows 54.6 us by parts, 41.4 round robin, GQA 32
+// rows of 8 KV heads 50.8 / 46.5; 8 of 4000 ahead of 56 of 100: 51.0 / 38.7 and 55.1 / 46.5; 4000 among 15 of 20: 24.0 / 21.6 and
+// 21.5 / 19.2; 32 of 4000 ahead of 32 of 100, a quarter of the keys in a part: 73.2 / 70.3 and 115.1 / 113.8.  The other way round with
+// about a quarter in the largest part and fewer partial rows: 23 sequences around 1600, lognormal, 8 rows of one KV head 12.5 by parts,
+// 12.9 round robin; 12 of 100 to 800, latent-KV 128 rows 20.4 / 21.0, GQA 24 rows of 2 KV heads 10.8 / 11.0.
 constexpr int kSpreadRows = 1 << 20;
+constexpr int kManyPartialRows = 16384;
 // First sequence of part x (0 to 8) of a batch; whether a part of `positions` calls for round robin.
 XATTN_HD int batch_part(int x, int batch) { return x * batch >> 3; }
-XATTN_HD bool large_part(int positions, int total) {
-    return positions > (total >> 3) * 3 || (positions >= 8192 && positions > (total >> 5) * 7);
+XATTN_HD bool large_part(const Plan& pl, int positions, int seq_rows) {
+    return positions > (pl.total >> 5) * ((long long)pl.n_pieces * seq_rows >= kManyPartialRows ? 7 : 12);
 }
 
 // A piece's walk over the sequences it intersects, in stream order.
