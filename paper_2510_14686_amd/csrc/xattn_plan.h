@@ -216,8 +216,9 @@ XATTN_HD int share_runs(int n_cu, int row_groups, int n_kv_heads, PieceShare s) 
 XATTN_HD PieceShare call_share(int n_cu, int row_groups, int n_kv_heads, int max_waves) {
     PieceShare best = piece_share(n_kv_heads, max_waves);
     int most = share_runs(n_cu, row_groups, n_kv_heads, best);
-    if (most * row_groups * n_kv_heads == 64 * n_cu * max_waves) return best;      // all of the chip (and no time spent on a short call)
     const bool stays = row_groups == 1 && even_shares(n_kv_heads);
+    // all of the chip, or so much that nothing will change it: no time is spent on a short call
+    if (64LL * n_cu * max_waves * (stays ? 5 : 7) <= 7LL * most * row_groups * n_kv_heads) return best;
     const int first = row_groups == 1 ? 4 : 2;
     const int others[] = {first, 6 - first, max_waves, 1};
     for (int h : others) {
@@ -268,18 +269,20 @@ XATTN_HD SeqMeta seq_meta(const Plan& pl, int b, int start, int len) {
 
 // Table entry of a sequence for the merge kernel: its first slot, and its segments (kMaxPieces at most) with, in all entries of
 // a call alike, the bit kSpreadRows.  Set: of the eight parts of the batch, whose rows an XCD each would merge (kReadOwn), one holds
-// so many of the keys that its XCD would be the last by far, 3/8 of them, or 7/32 where the partial rows are many; the rows are then
+// so many of the keys that its XCD would be the last by far, half of them, or 7/32 where the partial rows are many; the rows are then
 // dealt out round robin.  One sequence of 30000 tokens among 15 of 100: latent-KV 128 rows 54.6 us by parts, 41.4 round robin, GQA 32
 // rows of 8 KV heads 50.8 / 46.5; 8 of 4000 ahead of 56 of 100: 51.0 / 38.7 and 55.1 / 46.5; 4000 among 15 of 20: 24.0 / 21.6 and
-// 21.5 / 19.2; 32 of 4000 ahead of 32 of 100, a quarter of the keys in a part: 73.2 / 70.3 and 115.1 / 113.8.  The other way round with
-// about a quarter in the largest part and fewer partial rows: 23 sequences around 1600, lognormal, 8 rows of one KV head 12.5 by parts,
-// 12.9 round robin; 12 of 100 to 800, latent-KV 128 rows 20.4 / 21.0, GQA 24 rows of 2 KV heads 10.8 / 11.0.
+// 21.5 / 19.2; 32 of 4000 ahead of 32 of 100, a quarter of the keys in a part: 73.2 / 70.3 and 115.1 / 113.8.  The other way round,
+// with less in the largest part or fewer partial rows, a row's second entry is what counts: 23 sequences around 1600, lognormal, 8 rows of
+// one KV head 12.5 by parts, 12.9 round robin; 12 of 100 to 800, latent-KV 128 rows 20.4 / 21.0; 1000 among 31 of 50, 4 rows of 8 KV
+// heads 10.5 / 10.8; 1000 among 15 of 20, latent-KV 16 rows 11.7 / 12.3.
 constexpr int kSpreadRows = 1 << 20;
-constexpr int kManyPartialRows = 16384;
+constexpr int kFewPartialRows = 2048, kManyPartialRows = 16384;
 // First sequence of part x (0 to 8) of a batch; whether a part of `positions` calls for round robin.
 XATTN_HD int batch_part(int x, int batch) { return x * batch >> 3; }
 XATTN_HD bool large_part(const Plan& pl, int positions, int seq_rows) {
-    return positions > (pl.total >> 5) * ((long long)pl.n_pieces * seq_rows >= kManyPartialRows ? 7 : 12);
+    const long long rows = (long long)pl.n_pieces * seq_rows;
+    return positions > (pl.total >> 5) * (rows >= kManyPartialRows ? 7 : rows >= kFewPartialRows ? 16 : 32) + 31;
 }
 
 // A piece's walk over the sequences it intersects, in stream order.
