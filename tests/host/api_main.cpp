@@ -84,12 +84,12 @@ static int mla_decode(intptr_t stream, int batch, int q_len, int heads) {
     return xattn_mla_decode(&dummy, reinterpret_cast<void**>(&dummy), &dummy, batch, q_len, heads, 512, 64, 0.125f, &dummy, nullptr,
                             reinterpret_cast<void*>(stream));
 }
-// The last launch's slots lie within `bytes` bytes from its table on.
+// The last launch's slots, of either path, lie within `bytes` bytes from its table on.
 static bool fits(size_t bytes) {
     const xattn::DecodeParams& p = xattn::g_prm;
     const size_t slots = (size_t)p.n_pieces + p.batch, rows = (size_t)p.q_len * p.n_q_heads;
     const char* base = reinterpret_cast<const char*>(p.meta);
-    return reinterpret_cast<const char*>(p.part_ml) >= base + 8 * (size_t)p.batch &&
+    return p.shared_pieces <= p.n_pieces && reinterpret_cast<const char*>(p.part_ml) >= base + 8 * (size_t)p.batch &&
            reinterpret_cast<const char*>(p.part_o) >= reinterpret_cast<const char*>(p.part_ml) + slots * rows * 8 &&
            reinterpret_cast<const char*>(p.part_o) + slots * rows * 512 <= base + bytes;
 }
